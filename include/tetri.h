@@ -227,6 +227,47 @@ TETRI_API tetri_status tetri_chunk_prefill_attn_append(tetri_ctx *ctx, const voi
                                                        void *out, void *stream);
 
 /*
+ * The same for a caller whose host also holds the chunk's two small metadata arrays (it built them: tetri_chunk_metadata):
+ * host_cu [num_segs + 1] and host_ctx_lens [num_segs] repeat cu_chunk_q_lens and ctx_lens.  With them the launch is
+ * shaped for the work that is really there instead of for what the handle's bounds allow.
+ *   append: 1 = as tetri_chunk_prefill_attn_append, 0 = as tetri_chunk_prefill_attn.
+ *   fp8: 1 = kv_pages is a pool of E4M3 codes (tetri_chunk_prefill_attn_fp8 below) under k_scale and v_scale, which are
+ *   otherwise ignored.
+ * Errors as for those entry points; host arrays that are no chunk of this handle (cu not ascending from 0 to at
+ * most chunk_size, a negative context, more tokens than max_blocks_per_seq pages hold): TETRI_ERR_INVALID_ARG.
+ */
+TETRI_API tetri_status tetri_chunk_prefill_planned(tetri_ctx *ctx, const void *q, const void *k_new, const void *v_new,
+                                                   void *kv_pages, const int32_t *block_table, const int32_t *cu_chunk_q_lens,
+                                                   const int32_t *ctx_lens, int32_t num_segs, float scale, int32_t append,
+                                                   int32_t fp8, float k_scale, float v_scale, const int32_t *host_cu,
+                                                   const int32_t *host_ctx_lens, void *out, void *stream);
+
+/*
+ * A scheduled batch as a repeatable step (Sec. 3.3.3): metadata staged in pinned host memory, uploaded, then one chunk
+ * after the other.  tetri_batch_create allocates a ring of staging buffers of meta_len int32 each (pinned); meta_dev is
+ * the caller's device buffer of as many int32.  A batch belongs to its handle and is used by one thread at a time.
+ *   tetri_batch_slot: the host address of staging buffer i in 0..tetri_batch_slots() - 1.
+ *   tetri_batch_upload: packs the prompts and writes every chunk's metadata (tetri_plan_metadata: same arguments, same
+ *   layout_out) into the next staging buffer and copies it to meta_dev on `stream`.  Waits only if the copy that used
+ *   this buffer a whole ring ago is not done yet.  The plan has to have n_chunks chunks (TETRI_ERR_INVALID_ARG if not).
+ *   tetri_batch_launch: chunks first_chunk .. first_chunk + n - 1 of the plan uploaded last (before the first upload: of
+ *   the plan that staging buffer 0 holds and the caller has copied to meta_dev), in order, each as tetri_chunk_prefill_planned
+ *   does it: mode 1 with append = 1, mode 2 attention only, mode 0 attention followed by tetri_kv_append.
+ *   q, k_new, v_new, out: host arrays of a device pointer per chunk.
+ */
+typedef struct tetri_batch tetri_batch;
+TETRI_API tetri_status tetri_batch_create(tetri_ctx *ctx, int64_t meta_len, int32_t *meta_dev, tetri_batch **out);
+TETRI_API void tetri_batch_destroy(tetri_batch *batch);
+TETRI_API int32_t tetri_batch_slots(void);
+TETRI_API int32_t *tetri_batch_slot(tetri_batch *batch, int32_t i);
+TETRI_API tetri_status tetri_batch_upload(tetri_batch *batch, const int32_t *prompt_lens, int32_t n_prompts,
+                                          const int32_t *order, int32_t n_order, const int32_t *req_block_tables,
+                                          int32_t *layout_out, int32_t n_chunks, void *stream);
+TETRI_API tetri_status tetri_batch_launch(tetri_batch *batch, const int32_t *layout, int32_t first_chunk, int32_t n,
+                                          const void *const *q, const void *const *k_new, const void *const *v_new,
+                                          void *kv_pages, void *const *out, float scale, int32_t mode, void *stream);
+
+/*
  * KV export and import: the data plane of the dispatcher (Sec. 3.3.4 "Dispatcher": a prefilled
  * request's KV cache is sent from the prefill instance's accelerator memory to the chosen decode
  * instance, either request-level, i.e. the whole request after its last chunk, or chunk-level, i.e.

@@ -1,12 +1,14 @@
-"""Build libtetri.so (HIP, gfx950 only) in-tree with hipcc."""
+"""Build libtetri.so (HIP, gfx950 only) in-tree with hipcc, and the CPython module _native.so that calls it."""
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libtetri.so")
+NATIVE = os.path.join(HERE, "_native.so")
 SOURCES = ["tetri_host.cpp", "tetri_plan.cpp", "tetri_append.hip", "tetri_kv_transfer.hip", "tetri_decode.hip", "tetri_attn.hip"]
 HEADERS = [os.path.join(CSRC, "tetri_internal.h"), os.path.join(CSRC, "tetri_plan.h"), os.path.join(CSRC, "attn_common.h"), os.path.join(ROOT, "include", "tetri.h")]
 
@@ -49,7 +51,20 @@ def build(force=True, verbose=False, extra_flags=()):
     res = subprocess.run(cmd, capture_output=True, text=True)
     if res.returncode != 0:
         raise RuntimeError("link failed:\n" + res.stderr)
+    build_native(verbose)
     return LIB
+
+
+def build_native(verbose=False):
+    """Compile the CPython module of fast calls (host code only).  Returns its path."""
+    cmd = [os.environ.get("CXX", "g++"), "-std=c++17", "-O2", "-shared", "-fPIC", "-fvisibility=hidden", "-Wno-cast-function-type",
+           "-I", sysconfig.get_paths()["include"], "-I", os.path.join(ROOT, "include"), os.path.join(CSRC, "tetri_py.cpp"), "-o", NATIVE, "-ldl"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("compiling tetri_py.cpp failed:\n" + res.stderr)
+    return NATIVE
 
 
 if __name__ == "__main__":

@@ -1,6 +1,7 @@
 // Host layer of libtetri: handle, argument checks, launch shapes and the debug validator.
 // (The chunk packer and the scheduler are in tetri_plan.cpp, which needs no HIP.)
 #include <algorithm>
+#include <climits>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -376,7 +377,8 @@ tetri_status tetri_decode_attn_append(tetri_ctx *h, const void *q, const void *k
 static tetri_status attn_common(const char *fn, tetri_ctx *h, const void *q, const void *k_new, const void *v_new,
                                 const void *kv_pages, void *kv_pages_w, const int32_t *block_table, const int32_t *cu,
                                 const int32_t *ctx_lens, int32_t num_segs, float scale, void *out, void *stream,
-                                bool fp8 = false, float k_scale = 1.f, float v_scale = 1.f)
+                                bool fp8 = false, float k_scale = 1.f, float v_scale = 1.f,
+                                const int32_t *host_cu = nullptr, const int32_t *host_ctx = nullptr)
 {
     const void *ptrs[] = {q, k_new, v_new, kv_pages, out};
     const char *names[] = {"q", "k_new", "v_new", "kv_pages", "out"};
@@ -532,6 +534,161 @@ tetri_status tetri_chunk_prefill_attn_fp8(tetri_ctx *h, const void *q, const voi
     if (append != 0 && append != 1) return fail(h, TETRI_ERR_INVALID_ARG, "tetri_chunk_prefill_attn_fp8: append must be 0 or 1");
     return attn_common("tetri_chunk_prefill_attn_fp8", h, q, k_new, v_new, kv_pages_fp8, append ? kv_pages_fp8 : nullptr,
                        block_table, cu, ctx_lens, num_segs, scale, out, stream, true, k_scale, v_scale);
+}
+
+// Host copies of a chunk's metadata: are they a chunk of this handle?
+static tetri_status check_host_chunk(tetri_ctx *h, const char *fn, const int32_t *cu, const int32_t *ctx_lens, int32_t num_segs)
+{
+    if (!cu || !ctx_lens) return fail(h, TETRI_ERR_INVALID_ARG, "%s: null host metadata", fn);
+    const int64_t most = (int64_t)h->cfg.max_blocks_per_seq * h->cfg.page_size;
+    bool ok = cu[0] == 0 && cu[num_segs] <= h->cfg.chunk_size;
+    for (int32_t s = 0; s < num_segs && ok; ++s)
+        ok = cu[s + 1] > cu[s] && ctx_lens[s] >= 0 && (int64_t)ctx_lens[s] + (cu[s + 1] - cu[s]) <= most;
+    if (!ok) return fail(h, TETRI_ERR_INVALID_ARG, "%s: the host metadata is not a chunk of this handle", fn);
+    return TETRI_OK;
+}
+
+tetri_status tetri_chunk_prefill_planned(tetri_ctx *h, const void *q, const void *k_new, const void *v_new, void *kv_pages,
+                                         const int32_t *block_table, const int32_t *cu, const int32_t *ctx_lens, int32_t num_segs,
+                                         float scale, int32_t append, int32_t fp8, float k_scale, float v_scale,
+                                         const int32_t *host_cu, const int32_t *host_ctx, void *out, void *stream)
+{
+    const char *fn = "tetri_chunk_prefill_planned";
+    if (!h) return fail(nullptr, TETRI_ERR_INVALID_ARG, "%s: null handle", fn);
+    if ((append != 0 && append != 1) || (fp8 != 0 && fp8 != 1)) return fail(h, TETRI_ERR_INVALID_ARG, "%s: append and fp8 must be 0 or 1", fn);
+    if (num_segs < 1 || num_segs > h->cfg.max_segs_per_chunk)
+        return fail(h, TETRI_ERR_INVALID_ARG, "%s: num_segs=%d outside 1..%d", fn, num_segs, h->cfg.max_segs_per_chunk);
+    tetri_status st = check_host_chunk(h, fn, host_cu, host_ctx, num_segs);
+    if (st != TETRI_OK) return st;
+    return attn_common(fn, h, q, k_new, v_new, kv_pages, append ? kv_pages : nullptr, block_table, cu, ctx_lens, num_segs, scale,
+                       out, stream, fp8 != 0, fp8 ? k_scale : 1.f, fp8 ? v_scale : 1.f, host_cu, host_ctx);
+}
+
+}  // extern "C"
+
+// A ring of pinned staging buffers.  A buffer may be written again when the upload that read it is done.  An event behind
+// every upload would say so, but costs its own packet in the queue (1.3 us of a step of 20): one event covers
+// the uploads of half a ring, because work on a stream is done in order.
+struct tetri_batch {
+    static constexpr int kSlots = 8, kGroup = kSlots / 2;
+    tetri_ctx *h = nullptr;
+    int32_t *host = nullptr, *dev = nullptr;
+    int64_t len = 0;                  // int32 per buffer, a multiple of 4
+    hipEvent_t ev[kSlots] = {};
+    int cover[kSlots];                // the event behind a buffer's last upload; -1: none was made, kOpen: not recorded yet
+    static constexpr int kOpen = -2;
+    uint64_t turn = 0;
+    int slot = 0;                     // the buffer of the last upload
+    hipStream_t last = nullptr;       // ... and its stream
+
+    hipError_t close_group()          // an event on the last stream covers every upload that has none yet
+    {
+        hipError_t e = hipEventRecord(ev[slot], last);
+        if (e != hipSuccess) return e;
+        for (int &c : cover)
+            if (c == kOpen) c = slot;
+        return hipSuccess;
+    }
+};
+
+extern "C" {
+
+int32_t tetri_batch_slots(void) { return tetri_batch::kSlots; }
+
+int32_t *tetri_batch_slot(tetri_batch *b, int32_t i)
+{
+    return b && i >= 0 && i < tetri_batch::kSlots ? b->host + (size_t)i * b->len : nullptr;
+}
+
+void tetri_batch_destroy(tetri_batch *b)
+{
+    if (!b) return;
+    for (int i = 0; i < tetri_batch::kSlots; ++i)
+        if (b->ev[i]) (void)hipEventDestroy(b->ev[i]);
+    if (b->host) (void)hipHostFree(b->host);          // (waits for the device: no upload reads it any more)
+    delete b;
+}
+
+tetri_status tetri_batch_create(tetri_ctx *h, int64_t meta_len, int32_t *meta_dev, tetri_batch **out)
+{
+    if (!h || !out) return fail(h, TETRI_ERR_INVALID_ARG, "tetri_batch_create: null argument");
+    *out = nullptr;
+    if (!meta_dev || !aligned16(meta_dev)) return fail(h, TETRI_ERR_INVALID_ARG, "tetri_batch_create: meta_dev is null or not 16-byte aligned");
+    if (meta_len < 4 || meta_len % 4 != 0 || meta_len > INT32_MAX - 3)
+        return fail(h, TETRI_ERR_INVALID_ARG, "tetri_batch_create: meta_len=%lld (a positive multiple of 4)", (long long)meta_len);
+    tetri_batch *b = new (std::nothrow) tetri_batch;
+    if (!b) return fail(h, TETRI_ERR_NOMEM, "tetri_batch_create: out of host memory");
+    b->h = h; b->len = meta_len; b->dev = meta_dev;
+    for (int &c : b->cover) c = -1;
+    hipError_t e = hipHostMalloc(reinterpret_cast<void **>(&b->host), (size_t)tetri_batch::kSlots * meta_len * sizeof(int32_t), hipHostMallocDefault);
+    for (int i = 0; i < tetri_batch::kSlots && e == hipSuccess; ++i) e = hipEventCreateWithFlags(&b->ev[i], hipEventDisableTiming);
+    if (e != hipSuccess) {
+        tetri_batch_destroy(b);
+        return fail(h, TETRI_ERR_HIP, "tetri_batch_create: %s", hipGetErrorString(e));
+    }
+    std::memset(b->host, 0, (size_t)tetri_batch::kSlots * meta_len * sizeof(int32_t));
+    *out = b;
+    return TETRI_OK;
+}
+
+tetri_status tetri_batch_upload(tetri_batch *b, const int32_t *prompt_lens, int32_t n_prompts, const int32_t *order, int32_t n_order,
+                                const int32_t *req_block_tables, int32_t *layout_out, int32_t n_chunks, void *stream)
+{
+    const char *fn = "tetri_batch_upload";
+    if (!b) return fail(nullptr, TETRI_ERR_INVALID_ARG, "%s: null batch", fn);
+    tetri_ctx *h = b->h;
+    if (!layout_out || n_chunks < 0) return fail(h, TETRI_ERR_INVALID_ARG, "%s: null layout_out or negative n_chunks", fn);
+    hipStream_t hs = static_cast<hipStream_t>(stream);
+    hipError_t e = hipSuccess;
+    if (b->turn != 0 && hs != b->last && b->cover[b->slot] == tetri_batch::kOpen) e = b->close_group();
+    const int slot = (int)(b->turn % tetri_batch::kSlots);
+    if (e == hipSuccess && b->cover[slot] >= 0 && hipEventQuery(b->ev[b->cover[slot]]) == hipErrorNotReady)
+        e = hipEventSynchronize(b->ev[b->cover[slot]]);
+    if (e != hipSuccess) return fail(h, TETRI_ERR_HIP, "%s: %s", fn, hipGetErrorString(e));
+    int32_t *host = b->host + (size_t)slot * b->len;
+    int64_t len = 0;
+    const int32_t got = tetri_plan_metadata(prompt_lens, n_prompts, order, n_order, h->cfg.chunk_size, req_block_tables,
+                                            h->cfg.max_blocks_per_seq, host, b->len, layout_out, n_chunks, &len);
+    if (got < 0) return fail(h, (tetri_status)got, "%s: %s", fn, tetri_thread_error());
+    if (got != n_chunks) return fail(h, TETRI_ERR_INVALID_ARG, "%s: the plan has %d chunks, expected %d", fn, got, n_chunks);
+    if (len > 0) {
+        e = tetri_launch_upload(host, b->dev, len, hs);
+        if (e != hipSuccess) return fail(h, TETRI_ERR_HIP, "%s: launch failed: %s", fn, hipGetErrorString(e));
+    }
+    b->slot = slot;
+    b->last = hs;
+    b->cover[slot] = tetri_batch::kOpen;
+    ++b->turn;
+    if (b->turn % tetri_batch::kGroup == 0 && (e = b->close_group()) != hipSuccess)
+        return fail(h, TETRI_ERR_HIP, "%s: %s", fn, hipGetErrorString(e));
+    return TETRI_OK;
+}
+
+tetri_status tetri_batch_launch(tetri_batch *b, const int32_t *layout, int32_t first_chunk, int32_t n, const void *const *q,
+                                const void *const *k_new, const void *const *v_new, void *kv_pages, void *const *out, float scale,
+                                int32_t mode, void *stream)
+{
+    const char *fn = "tetri_batch_launch";
+    if (!b) return fail(nullptr, TETRI_ERR_INVALID_ARG, "%s: null batch", fn);
+    tetri_ctx *h = b->h;
+    if (mode < 0 || mode > 2) return fail(h, TETRI_ERR_INVALID_ARG, "%s: mode=%d (0, 1 or 2)", fn, mode);
+    if (!layout || !q || !k_new || !v_new || !out || first_chunk < 0 || n < 0)
+        return fail(h, TETRI_ERR_INVALID_ARG, "%s: null argument or negative count", fn);
+    const int32_t *host = b->host + (size_t)b->slot * b->len;
+    for (int32_t c = first_chunk; c < first_chunk + n; ++c) {
+        const int32_t o_cu = layout[4 * c], o_ctx = layout[4 * c + 1], o_bt = layout[4 * c + 2], S = layout[4 * c + 3];
+        if (S < 1 || S > h->cfg.max_segs_per_chunk || o_cu < 0 || o_ctx < o_cu + S + 1 || o_bt < o_ctx + S ||
+            o_bt + (int64_t)S * h->cfg.max_blocks_per_seq > b->len)
+            return fail(h, TETRI_ERR_INVALID_ARG, "%s: the layout of chunk %d does not fit the batch", fn, c);
+        tetri_status st = check_host_chunk(h, fn, host + o_cu, host + o_ctx, S);
+        if (st != TETRI_OK) return st;
+        st = attn_common(fn, h, q[c], k_new[c], v_new[c], kv_pages, mode == 1 ? kv_pages : nullptr, b->dev + o_bt, b->dev + o_cu,
+                         b->dev + o_ctx, S, scale, out[c], stream, false, 1.f, 1.f, host + o_cu, host + o_ctx);
+        if (st == TETRI_OK && mode == 0)
+            st = tetri_kv_append(h, k_new[c], v_new[c], kv_pages, b->dev + o_bt, b->dev + o_cu, b->dev + o_ctx, S, stream);
+        if (st != TETRI_OK) return st;
+    }
+    return TETRI_OK;
 }
 
 tetri_status tetri_validate_chunk(tetri_ctx *h, const int32_t *block_table, const int32_t *cu, const int32_t *ctx_lens,

@@ -109,3 +109,6 @@ hipError_t tetri_launch_decode(const tetri_ctx *h, const DecodeParams &p, hipStr
 // Device address (on the current device) and size of the static scratch array of the decode kernels.
 hipError_t tetri_decode_static_scratch(float **ptr, size_t *bytes);
 hipError_t tetri_launch_append(const tetri_ctx *h, const AppendParams &p, int32_t chunk_rows, hipStream_t stream);
+
+// Copies len int32 (rounded up to a multiple of 4) from pinned host memory to the device, both 16-byte aligned.
+hipError_t tetri_launch_upload(const int32_t *pinned, int32_t *dev, int64_t len, hipStream_t stream);

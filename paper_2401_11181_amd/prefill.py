@@ -57,6 +57,11 @@ class ChunkedPrefill:
                 off, ln = layout[k * n + c]
                 views.append(self.meta_dev[off:off + ln])
             self.meta.append((views[0], views[1], views[2], len(ctxs[c])))
+        # the host's copies: addresses of cu and ctx_lens per chunk (the arrays are kept beside them)
+        self._host_arrays = (cus, ctxs)
+        self._host_meta = [(cu.ctypes.data, ctx.ctypes.data) for cu, ctx in zip(cus, ctxs)]
+        # ... and the device arrays' addresses
+        self._meta_ptr = [(cu.data_ptr(), ctx.data_ptr(), bt.data_ptr(), S) for cu, ctx, bt, S in self.meta]
 
     def chunk_segments(self, c):
         return [tuple(int(v) for v in s) for s in self.segs[self.offsets[c]:self.offsets[c + 1]]]
@@ -71,22 +76,24 @@ class ChunkedPrefill:
             at += n
         return rows
 
+    def _launch(self, c, q, k_new, v_new, kv_pages, scale, append, fp8, k_scale, v_scale, out, stream):
+        cu, ctx, bt, S = self._meta_ptr[c]
+        host_cu, host_ctx = self._host_meta[c]
+        self.handle.tetri_chunk_prefill_planned(q, k_new, v_new, kv_pages, bt, cu, ctx, S, scale, append, fp8, k_scale, v_scale,
+                                                host_cu, host_ctx, out, stream)
+
     def attn(self, c, q, k_new, v_new, kv_pages, scale, out, stream=None):
-        cu, ctx, bt, S = self.meta[c]
-        self.handle.tetri_chunk_prefill_attn(q, k_new, v_new, kv_pages, bt, cu, ctx, S, scale, out, stream)
+        self._launch(c, q, k_new, v_new, kv_pages, scale, 0, 0, 1.0, 1.0, out, stream)
 
     def append(self, c, k_new, v_new, kv_pages, stream=None):
-        cu, ctx, bt, S = self.meta[c]
+        cu, ctx, bt, S = self._meta_ptr[c]
         self.handle.tetri_kv_append(k_new, v_new, kv_pages, bt, cu, ctx, S, stream)
 
     def attn_append(self, c, q, k_new, v_new, kv_pages, scale, out, stream=None):
-        cu, ctx, bt, S = self.meta[c]
-        self.handle.tetri_chunk_prefill_attn_append(q, k_new, v_new, kv_pages, bt, cu, ctx, S, scale, out, stream)
+        self._launch(c, q, k_new, v_new, kv_pages, scale, 1, 0, 1.0, 1.0, out, stream)
 
     def attn_fp8(self, c, q, k_new, v_new, kv_pages_fp8, scale, k_scale, v_scale, append, out, stream=None):
-        cu, ctx, bt, S = self.meta[c]
-        self.handle.tetri_chunk_prefill_attn_fp8(q, k_new, v_new, kv_pages_fp8, bt, cu, ctx, S, scale, k_scale, v_scale,
-                                                 append, out, stream)
+        self._launch(c, q, k_new, v_new, kv_pages_fp8, scale, append, 1, k_scale, v_scale, out, stream)
 
     def validate(self, c):
         cu, ctx, bt, S = self.meta[c]
@@ -105,8 +112,6 @@ class PrefillPipeline:
     With use_graph the launches of a step are replayed from a HIP graph; packing, metadata and the
     upload still run every step.
     """
-
-    RING = 4    # pinned staging buffers in flight
 
     def __init__(self, prompt_lens, order, chunk_size, num_q_heads, num_kv_heads, head_dim, num_pages,
                  req_block_tables, scale, device="cuda:0", page_size=16, use_graph=False, fused=True, export=None, handle=None):
@@ -130,21 +135,23 @@ class PrefillPipeline:
             self.req_bt[r, :len(t)] = t
         self.plan_segs, self.plan_offsets = tetri.tetri_pack_chunks(self.lens, self.order, chunk_size)
         self.n_chunks, self.meta_len = tetri.tetri_plan_metadata(self.lens, self.order, chunk_size, self.req_bt)
-        self.meta_len = max(int(self.meta_len), 4)
-        self.stage = [torch.zeros(self.meta_len, dtype=torch.int32, pin_memory=True) for _ in range(self.RING)]
+        self.meta_len = max((int(self.meta_len) + 3) // 4 * 4, 4)
         self.layout_np = np.zeros((max(self.n_chunks, 1), 4), dtype=np.int32)
         self.meta_dev = torch.zeros(self.meta_len, dtype=torch.int32, device=self.device)
-        self.host_plan(0)
-        self.layout = [tuple(int(x) for x in row) for row in self.layout_np[:self.n_chunks]]
-        max_segs = max([1] + [l[3] for l in self.layout])
+        max_segs = max([1] + [int(n) for n in np.diff(self.plan_offsets)])
         # (several pipelines of one shape may share a handle, as long as their launches do not overlap)
         self.handle = handle or tetri.Tetri(num_q_heads, num_kv_heads, head_dim, chunk_size, num_pages, self.max_blocks,
                                             max_segs, page_size=page_size)
-        self.events = [torch.cuda.Event() for _ in range(self.RING)]
-        self.used = [False] * self.RING
+        # the pinned staging buffers, a ring: a step plans into the next one and uploads it
+        self.batch = tetri.Batch(self.handle, self.meta_len, self.meta_dev)
+        self.stage = self.batch.slots
+        self.host_plan(0)
+        self.layout = [tuple(int(x) for x in row) for row in self.layout_np[:self.n_chunks]]
+        self._plan_args = (self.lens.ctypes.data, len(self.lens), None if self.order is None else self.order.ctypes.data,
+                           len(self.lens) if self.order is None else len(self.order), self.req_bt.ctypes.data,
+                           self.layout_np.ctypes.data, self.n_chunks)
         self.graph = None
         self.use_graph = use_graph
-        self.turn = 0
 
     # --- inputs -------------------------------------------------------------------------------
     def bind(self, q_chunks, k_chunks, v_chunks, kv_pages, out_chunks):
@@ -199,66 +206,58 @@ class PrefillPipeline:
             self._attn_args.append((self.handle.h, q, k, v, pool, bt, cu, ctx, i32(S), f32(self.scale), o))
             self._app_args.append((self.handle.h, k, v, pool, bt, cu, ctx, i32(S)))
         self._lib = tetri.lib()
+        # the same as arrays of one address per chunk, for the calls that launch many chunks at once
+        self._chunk_ptrs = [np.array([t[c].data_ptr() for c in range(self.n_chunks)], dtype=np.uint64) for t in (self.q, self.k, self.v, self.out)]
+        q, k, v, o = (a.ctypes.data for a in self._chunk_ptrs)
+        self._layout_ptr = self.layout_np.ctypes.data
+        self._batch_args = (q, k, v, self.pool.data_ptr(), o, self.scale)
 
     def launch_attn(self, c, stream=None):
         """One attention launch of chunk c with the metadata currently on the device."""
-        rc = self._lib.tetri_chunk_prefill_attn(*self._attn_args[c], stream or tetri._stream(None))
-        if rc != tetri.TETRI_OK:
-            raise tetri.TetriError(rc, tetri.tetri_last_error(self.handle))
+        self.batch.launch(self._layout_ptr, c, 1, *self._batch_args, tetri.BATCH_ATTENTION, stream)
 
     def launch_fused(self, c, stream=None):
         """Attention and append of chunk c in one launch."""
-        rc = self._lib.tetri_chunk_prefill_attn_append(*self._attn_args[c], stream or tetri._stream(None))
-        if rc != tetri.TETRI_OK:
-            raise tetri.TetriError(rc, tetri.tetri_last_error(self.handle))
+        self.batch.launch(self._layout_ptr, c, 1, *self._batch_args, tetri.BATCH_FUSED, stream)
 
     def launch_fused_fp8(self, c, kv_pages_fp8, k_scale, v_scale, append=1, stream=None):
         """Chunk c over a pool of FP8 codes: attention and, with append, the quantising append, in one launch."""
         import ctypes
         h, q, k, v, _pool, bt, cu, ctx, S, scale, o = self._attn_args[c]
-        rc = self._lib.tetri_chunk_prefill_attn_fp8(h, q, k, v, ctypes.c_void_p(kv_pages_fp8.data_ptr()), bt, cu, ctx, S, scale,
-                                                    ctypes.c_float(k_scale), ctypes.c_float(v_scale), ctypes.c_int32(append), o,
-                                                    stream or tetri._stream(None))
-        if rc != tetri.TETRI_OK:
-            raise tetri.TetriError(rc, tetri.tetri_last_error(self.handle))
+        self._check(self._lib.tetri_chunk_prefill_attn_fp8(h, q, k, v, ctypes.c_void_p(kv_pages_fp8.data_ptr()), bt, cu, ctx, S, scale,
+                                                           ctypes.c_float(k_scale), ctypes.c_float(v_scale), ctypes.c_int32(append), o,
+                                                           self._stream_arg(stream)))
 
     def launch_append(self, c, stream=None):
-        rc = self._lib.tetri_kv_append(*self._app_args[c], stream or tetri._stream(None))
+        self._check(self._lib.tetri_kv_append(*self._app_args[c], self._stream_arg(stream)))
+
+    @staticmethod
+    def _stream_arg(stream):
+        # (the default stream is a null pointer, which is not "no stream given")
+        return tetri._stream(None) if stream is None else stream
+
+    def _check(self, rc):
         if rc != tetri.TETRI_OK:
             raise tetri.TetriError(rc, tetri.tetri_last_error(self.handle))
 
     def _launch_all(self):
-        stream = tetri._stream(None)                # the current stream, looked up once per step
-        for c in range(self.n_chunks):
-            if self.fused:
-                self.launch_fused(c, stream)
-            else:
-                self.launch_attn(c, stream)
-                self.launch_append(c, stream)
-            if self.export == "chunk":
+        mode = tetri.BATCH_FUSED if self.fused else tetri.BATCH_TWO_LAUNCHES
+        if self.export != "chunk":
+            self.batch.launch(self._layout_ptr, 0, self.n_chunks, *self._batch_args, mode, None)
+        else:
+            for c in range(self.n_chunks):
+                self.batch.launch(self._layout_ptr, c, 1, *self._batch_args, mode, None)
                 # the slice this chunk cached, named by the chunk's own metadata arrays
                 self.chunk_done[c].record()
                 self.side.wait_event(self.chunk_done[c])
-                rc = self._lib.tetri_kv_export(*self._chunk_export_args[c])
-                if rc != tetri.TETRI_OK:
-                    raise tetri.TetriError(rc, tetri.tetri_last_error(self.handle))
-        if self.export == "chunk":
+                self._check(self._lib.tetri_kv_export(*self._chunk_export_args[c]))
             self.side_done.record(self.side)
             torch.cuda.current_stream().wait_event(self.side_done)
-        elif self.export == "request":
-            rc = self._lib.tetri_kv_export(*self._request_export_args, stream)
-            if rc != tetri.TETRI_OK:
-                raise tetri.TetriError(rc, tetri.tetri_last_error(self.handle))
+        if self.export == "request":
+            self._check(self._lib.tetri_kv_export(*self._request_export_args, tetri._stream(None)))
 
     def step(self):
-        slot = self.turn % self.RING
-        self.turn += 1
-        if self.used[slot]:
-            self.events[slot].synchronize()         # the upload that last used this buffer is done
-        self.host_plan(slot)
-        self.meta_dev.copy_(self.stage[slot], non_blocking=True)
-        self.events[slot].record()
-        self.used[slot] = True
+        self.batch.upload(*self._plan_args, None)
         if self.use_graph:
             if self.graph is None:                  # one graph: the launches read meta_dev, whose address is fixed
                 g = torch.cuda.CUDAGraph()

@@ -93,10 +93,33 @@ def lib():
         L.tetri_kv_import.argtypes = [vp, vp, vp, vp, vp, i32, ctypes.c_int64, vp, vp]
         L.tetri_validate_chunk.restype = i32
         L.tetri_validate_chunk.argtypes = [vp, vp, vp, vp, i32, vp]
+        L.tetri_batch_create.restype = i32
+        L.tetri_batch_create.argtypes = [vp, ctypes.c_int64, vp, ctypes.POINTER(vp)]
+        L.tetri_batch_destroy.restype = None
+        L.tetri_batch_destroy.argtypes = [vp]
+        L.tetri_batch_slots.restype = i32
+        L.tetri_batch_slots.argtypes = []
+        L.tetri_batch_slot.restype = ctypes.POINTER(i32)
+        L.tetri_batch_slot.argtypes = [vp, i32]
         L.tetri_set_option.restype = i32
         L.tetri_set_option.argtypes = [vp, ctypes.c_char_p, i32]
         _lib = L
     return _lib
+
+
+_native = None
+
+
+def native():
+    """The CPython module of fast calls, bound to the loaded library (raises if it has not been built)."""
+    global _native
+    if _native is None:
+        lib()
+        from . import _native as module
+        torch.cuda.current_stream()             # (initialises torch's side of the device, as every later call relies on)
+        module.bind(LIB_PATH, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
+        _native = module
+    return _native
 
 
 def _ptr(t):
@@ -202,7 +225,7 @@ class Tetri:
 
     def __init__(self, num_q_heads, num_kv_heads, head_dim, chunk_size, num_pages, max_blocks_per_seq,
                  max_segs_per_chunk, page_size=16, dtype=TETRI_BF16):
-        self.h = None
+        self.h = self._p = None
         self.cfg = Config(num_q_heads, num_kv_heads, head_dim, page_size, chunk_size, num_pages,
                           max_blocks_per_seq, max_segs_per_chunk, dtype)
         h = ctypes.c_void_p()
@@ -210,11 +233,13 @@ class Tetri:
         if rc != TETRI_OK:
             raise TetriError(rc, tetri_last_error())
         self.h = h
+        self._p = h.value           # the same handle as a number
+        self._n = native()
 
     def close(self):
         if self.h is not None:
             lib().tetri_destroy(self.h)
-            self.h = None
+            self.h = self._p = None
 
     def __del__(self):
         try:
@@ -231,77 +256,135 @@ class Tetri:
 
     def tetri_kv_append(self, k_new, v_new, kv_pages, block_table, cu_chunk_q_lens, ctx_lens, num_segs,
                         stream=None):
-        self._check(lib().tetri_kv_append(self.h, _ptr(k_new), _ptr(v_new), _ptr(kv_pages), _ptr(block_table),
-                                          _ptr(cu_chunk_q_lens), _ptr(ctx_lens), int(num_segs), _stream(stream)))
+        rc = self._n.tetri_kv_append(self._p, k_new, v_new, kv_pages, block_table, cu_chunk_q_lens, ctx_lens,
+                                     num_segs, stream)
+        if rc:
+            self._check(rc)
 
     def tetri_chunk_prefill_attn(self, q, k_new, v_new, kv_pages, block_table, cu_chunk_q_lens, ctx_lens,
                                  num_segs, scale, out, stream=None):
-        self._check(lib().tetri_chunk_prefill_attn(self.h, _ptr(q), _ptr(k_new), _ptr(v_new), _ptr(kv_pages),
-                                                   _ptr(block_table), _ptr(cu_chunk_q_lens), _ptr(ctx_lens),
-                                                   int(num_segs), float(scale), _ptr(out), _stream(stream)))
+        rc = self._n.tetri_chunk_prefill_attn(self._p, q, k_new, v_new, kv_pages, block_table, cu_chunk_q_lens,
+                                              ctx_lens, num_segs, scale, out, stream)
+        if rc:
+            self._check(rc)
 
     def tetri_chunk_prefill_attn_append(self, q, k_new, v_new, kv_pages, block_table, cu_chunk_q_lens, ctx_lens,
                                         num_segs, scale, out, stream=None):
-        self._check(lib().tetri_chunk_prefill_attn_append(self.h, _ptr(q), _ptr(k_new), _ptr(v_new), _ptr(kv_pages),
-                                                          _ptr(block_table), _ptr(cu_chunk_q_lens), _ptr(ctx_lens),
-                                                          int(num_segs), float(scale), _ptr(out), _stream(stream)))
+        rc = self._n.tetri_chunk_prefill_attn_append(self._p, q, k_new, v_new, kv_pages, block_table, cu_chunk_q_lens,
+                                                     ctx_lens, num_segs, scale, out, stream)
+        if rc:
+            self._check(rc)
 
     def tetri_decode_attn(self, q, k_new, v_new, kv_pages, block_table, ctx_lens, num_reqs, max_ctx_len, scale, out,
                           stream=None):
-        self._check(lib().tetri_decode_attn(self.h, _ptr(q), _ptr(k_new), _ptr(v_new), _ptr(kv_pages),
-                                            _ptr(block_table), _ptr(ctx_lens), int(num_reqs), int(max_ctx_len),
-                                            float(scale), _ptr(out), _stream(stream)))
+        rc = self._n.tetri_decode_attn(self._p, q, k_new, v_new, kv_pages, block_table, ctx_lens, num_reqs,
+                                       max_ctx_len, scale, out, stream)
+        if rc:
+            self._check(rc)
 
     def tetri_decode_attn_static(self, q, k_new, v_new, kv_pages, block_table, ctx_lens, num_reqs, max_ctx_len, scale, out,
                                  stream=None):
-        self._check(lib().tetri_decode_attn_static(self.h, _ptr(q), _ptr(k_new), _ptr(v_new), _ptr(kv_pages),
-                                                   _ptr(block_table), _ptr(ctx_lens), int(num_reqs), int(max_ctx_len),
-                                                   float(scale), _ptr(out), _stream(stream)))
+        rc = self._n.tetri_decode_attn_static(self._p, q, k_new, v_new, kv_pages, block_table, ctx_lens, num_reqs,
+                                              max_ctx_len, scale, out, stream)
+        if rc:
+            self._check(rc)
 
     def tetri_decode_attn_append(self, q, k_new, v_new, kv_pages, block_table, ctx_lens, num_reqs, max_ctx_len, scale,
                                  out, stream=None):
-        self._check(lib().tetri_decode_attn_append(self.h, _ptr(q), _ptr(k_new), _ptr(v_new), _ptr(kv_pages),
-                                                   _ptr(block_table), _ptr(ctx_lens), int(num_reqs), int(max_ctx_len),
-                                                   float(scale), _ptr(out), _stream(stream)))
+        rc = self._n.tetri_decode_attn_append(self._p, q, k_new, v_new, kv_pages, block_table, ctx_lens, num_reqs,
+                                              max_ctx_len, scale, out, stream)
+        if rc:
+            self._check(rc)
 
     def tetri_kv_export_fp8(self, kv_pages, block_table, cu_tokens, first_tokens, num_reqs, total_tokens, k_scale,
                             v_scale, buf, stream=None):
-        self._check(lib().tetri_kv_export_fp8(self.h, _ptr(kv_pages), _ptr(block_table), _ptr(cu_tokens),
-                                              _ptr(first_tokens), int(num_reqs), int(total_tokens), float(k_scale),
-                                              float(v_scale), _ptr(buf), _stream(stream)))
+        rc = self._n.tetri_kv_export_fp8(self._p, kv_pages, block_table, cu_tokens, first_tokens, num_reqs,
+                                         total_tokens, k_scale, v_scale, buf, stream)
+        if rc:
+            self._check(rc)
 
     def tetri_kv_import_fp8(self, buf, block_table, cu_tokens, first_tokens, num_reqs, total_tokens, kv_pages_fp8,
                             stream=None):
-        self._check(lib().tetri_kv_import_fp8(self.h, _ptr(buf), _ptr(block_table), _ptr(cu_tokens),
-                                              _ptr(first_tokens), int(num_reqs), int(total_tokens), _ptr(kv_pages_fp8),
-                                              _stream(stream)))
+        rc = self._n.tetri_kv_import_fp8(self._p, buf, block_table, cu_tokens, first_tokens, num_reqs, total_tokens,
+                                         kv_pages_fp8, stream)
+        if rc:
+            self._check(rc)
 
     def tetri_decode_attn_fp8(self, q, k_new, v_new, kv_pages_fp8, block_table, ctx_lens, num_reqs, max_ctx_len, scale,
                               k_scale, v_scale, append, out, stream=None):
-        self._check(lib().tetri_decode_attn_fp8(self.h, _ptr(q), _ptr(k_new), _ptr(v_new), _ptr(kv_pages_fp8),
-                                                _ptr(block_table), _ptr(ctx_lens), int(num_reqs), int(max_ctx_len),
-                                                float(scale), float(k_scale), float(v_scale), int(append), _ptr(out),
-                                                _stream(stream)))
+        rc = self._n.tetri_decode_attn_fp8(self._p, q, k_new, v_new, kv_pages_fp8, block_table, ctx_lens, num_reqs,
+                                           max_ctx_len, scale, k_scale, v_scale, append, out, stream)
+        if rc:
+            self._check(rc)
 
     def tetri_chunk_prefill_attn_fp8(self, q, k_new, v_new, kv_pages_fp8, block_table, cu_chunk_q_lens, ctx_lens, num_segs,
                                      scale, k_scale, v_scale, append, out, stream=None):
-        self._check(lib().tetri_chunk_prefill_attn_fp8(self.h, _ptr(q), _ptr(k_new), _ptr(v_new), _ptr(kv_pages_fp8),
-                                                       _ptr(block_table), _ptr(cu_chunk_q_lens), _ptr(ctx_lens),
-                                                       int(num_segs), float(scale), float(k_scale), float(v_scale),
-                                                       int(append), _ptr(out), _stream(stream)))
+        rc = self._n.tetri_chunk_prefill_attn_fp8(self._p, q, k_new, v_new, kv_pages_fp8, block_table,
+                                                  cu_chunk_q_lens, ctx_lens, num_segs, scale, k_scale, v_scale,
+                                                  append, out, stream)
+        if rc:
+            self._check(rc)
+
+    def tetri_chunk_prefill_planned(self, q, k_new, v_new, kv_pages, block_table, cu_chunk_q_lens, ctx_lens, num_segs, scale,
+                                    append, fp8, k_scale, v_scale, host_cu, host_ctx_lens, out, stream=None):
+        rc = self._n.tetri_chunk_prefill_planned(self._p, q, k_new, v_new, kv_pages, block_table, cu_chunk_q_lens,
+                                                 ctx_lens, num_segs, scale, append, fp8, k_scale, v_scale, host_cu,
+                                                 host_ctx_lens, out, stream)
+        if rc:
+            self._check(rc)
 
     def tetri_kv_export(self, kv_pages, block_table, cu_tokens, first_tokens, num_reqs, total_tokens, buf,
                         stream=None):
-        self._check(lib().tetri_kv_export(self.h, _ptr(kv_pages), _ptr(block_table), _ptr(cu_tokens),
-                                          _ptr(first_tokens), int(num_reqs), int(total_tokens), _ptr(buf),
-                                          _stream(stream)))
+        rc = self._n.tetri_kv_export(self._p, kv_pages, block_table, cu_tokens, first_tokens, num_reqs, total_tokens,
+                                     buf, stream)
+        if rc:
+            self._check(rc)
 
     def tetri_kv_import(self, buf, block_table, cu_tokens, first_tokens, num_reqs, total_tokens, kv_pages,
                         stream=None):
-        self._check(lib().tetri_kv_import(self.h, _ptr(buf), _ptr(block_table), _ptr(cu_tokens),
-                                          _ptr(first_tokens), int(num_reqs), int(total_tokens), _ptr(kv_pages),
-                                          _stream(stream)))
+        rc = self._n.tetri_kv_import(self._p, buf, block_table, cu_tokens, first_tokens, num_reqs, total_tokens,
+                                     kv_pages, stream)
+        if rc:
+            self._check(rc)
 
     def tetri_validate_chunk(self, block_table, cu_chunk_q_lens, ctx_lens, num_segs, stream=None):
         self._check(lib().tetri_validate_chunk(self.h, _ptr(block_table), _ptr(cu_chunk_q_lens), _ptr(ctx_lens),
                                                int(num_segs), _stream(stream)))
+
+
+BATCH_TWO_LAUNCHES, BATCH_FUSED, BATCH_ATTENTION = 0, 1, 2
+
+
+class Batch:
+    """A tetri_batch (tetri_batch_create / tetri_batch_destroy): the staging ring of a repeatable step."""
+
+    def __init__(self, handle, meta_len, meta_dev):
+        self.b = None
+        self.handle, self.meta_dev = handle, meta_dev       # both outlive the batch
+        b = ctypes.c_void_p()
+        handle._check(lib().tetri_batch_create(handle.h, int(meta_len), _ptr(meta_dev), ctypes.byref(b)))
+        self.b, self._p, self._n = b, b.value, native()
+        self.slots = [torch.from_numpy(np.ctypeslib.as_array(lib().tetri_batch_slot(b, i), (int(meta_len),)))
+                      for i in range(lib().tetri_batch_slots())]
+
+    def upload(self, *args):
+        rc = self._n.tetri_batch_upload(self._p, *args)
+        if rc:
+            self.handle._check(rc)
+
+    def launch(self, *args):
+        rc = self._n.tetri_batch_launch(self._p, *args)
+        if rc:
+            self.handle._check(rc)
+
+    def close(self):
+        if self.b is not None:
+            self.slots = []
+            lib().tetri_batch_destroy(self.b)
+            self.b = self._p = None
+
+    def __del__(self):
+        try:
+            self.close()
+        except Exception:
+            pass

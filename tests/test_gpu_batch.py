@@ -1,0 +1,51 @@
+"""The staging ring of a repeatable step (tetri_batch_*): every upload carries the plan of its own step, whatever the
+turn of the ring and the stream, and host metadata that is no chunk of the handle is rejected."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2401_11181_amd import synth, tetri
+from paper_2401_11181_amd.prefill import ChunkedPrefill, PrefillPipeline
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.mark.parametrize("one_stream", [True, False])
+def test_ring_uploads_the_plan_of_every_step(one_stream):
+    w = synth.small("ring", [70, 33, 150], 64, 4, 4, 64, seed=5)
+    pipe = PrefillPipeline(w.prompt_lens, [0, 1, 2], 64, 4, 4, 64, w.num_pages, synth.place_pages(w), w.scale, device=DEV)
+    streams = [torch.cuda.Stream(device=DEV) for _ in range(1 if one_stream else 3)]
+    orders = [[0, 1, 2], [2, 1, 0], [1, 0, 2], [1, 2, 0]]
+    got, want = [], []
+    for step in range(3 * tetri.lib().tetri_batch_slots() + 3):
+        pipe.order[:] = orders[step % 4]
+        st = streams[(step // 3) % len(streams)]
+        st.wait_stream(streams[((step - 1) // 3) % len(streams)])     # (one metadata buffer: the copies stay in order)
+        pipe.batch.upload(*pipe._plan_args, st)
+        with torch.cuda.stream(st):
+            got.append(pipe.meta_dev.clone())
+        meta, layout = np.zeros(pipe.meta_len, np.int32), np.zeros((pipe.n_chunks, 4), np.int32)
+        tetri.tetri_plan_metadata(pipe.lens, pipe.order, 64, pipe.req_bt, meta, layout)
+        want.append((meta, layout))
+    torch.cuda.synchronize()
+    for g, (meta, layout) in zip(got, want):
+        g = g.cpu().numpy()
+        for o_cu, o_ctx, o_bt, S in layout:
+            for at, n in ((o_cu, S + 1), (o_ctx, S), (o_bt, S * pipe.max_blocks)):
+                assert np.array_equal(g[at:at + n], meta[at:at + n])
+
+
+@pytest.mark.parametrize("cu, ctx", [([0, 40, 40], [0, 0]), ([1, 40, 64], [0, 0]), ([0, 40, 65], [0, 0]), ([0, 40, 64], [0, -1]),
+                                     ([0, 40, 64], [0, 100])])
+def test_planned_launch_rejects_host_metadata_that_is_no_chunk(cu, ctx):
+    w = synth.small("bad", [40, 90], 64, 4, 4, 64, seed=6)
+    s = ChunkedPrefill(w.prompt_lens, None, 64, 4, 4, 64, w.num_pages, synth.place_pages(w), device=DEV)
+    z = torch.zeros((64, 4, 64), dtype=torch.bfloat16, device=DEV)
+    pool = torch.zeros((w.num_pages, 2, 4, 16, 64), dtype=torch.bfloat16, device=DEV)
+    dcu, dctx, dbt, S = s.meta[0]
+    assert S == 2
+    with pytest.raises(tetri.TetriError) as e:
+        s.handle.tetri_chunk_prefill_planned(z, z, z, pool, dbt, dcu, dctx, S, 0.1, 1, 0, 1.0, 1.0, np.array(cu, np.int32),
+                                             np.array(ctx, np.int32), torch.zeros_like(z))
+    assert e.value.status == tetri.TETRI_ERR_INVALID_ARG and "host metadata" in str(e.value)
