@@ -18,6 +18,8 @@ typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 // for LDS reads then waits for it.)
 typedef __attribute__((address_space(1))) const u32x4 global_u32x4;
 typedef __attribute__((address_space(1))) u32x4 global_u32x4_w;
+typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
+typedef __attribute__((address_space(1))) u32x2 global_u32x2_w;
 
 constexpr int kPage = 16;     // tokens per KV page
 constexpr int kXcd = 8;       // XCDs (L2 domains) workgroups are dealt to round-robin

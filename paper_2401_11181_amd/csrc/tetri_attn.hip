@@ -1292,10 +1292,12 @@ __global__ __launch_bounds__(kSlots * KS * 64, 2) void attn_tile_kernel(AttnPara
     }
     // ---- workgroup id -> (head group, index inside the group).  The workgroups of a head group run
     // on one XCD (they read the same K and V through its L2); an XCD has gpx groups and starts their
-    // workgroups index by index.
+    // workgroups index by index.  With four or fewer groups each runs on 1 << span_shift = 2, 4 or 8 XCDs: the
+    // others would have nothing to do (8 heads sharing 2 kv heads, 2048 rows: 80 us on two XCDs, 35 on all).
     const int xcd = abid % kXcd, local = abid / kXcd;
-    const int widx = magic_div(local, p.gpx_magic);
-    const int grp = xcd * p.gpx + (local - widx * p.gpx);
+    const int lidx = magic_div(local, p.gpx_magic);
+    const int grp = (xcd >> p.span_shift) * p.gpx + (local - lidx * p.gpx);
+    const int widx = (lidx << p.span_shift) + (xcd & ((1 << p.span_shift) - 1));
     const int G = p.stream_wgs;
     // the arrival counters of the next launch that divides tiles: all zero when this launch ends
     if (G != 0 || p.helpers != 0)

@@ -122,26 +122,31 @@ tetri_status tetri_set_option(tetri_ctx *ctx, const char *key, int32_t value)
     if (std::strcmp(key, "split_keys") == 0) {
         if (value < 0 || value > 1) return fail(ctx, TETRI_ERR_INVALID_ARG, "tetri_set_option: split_keys=%d (0 or 1)", value);
         ctx->split_keys = value;
+        ctx->division_set = true;
         return TETRI_OK;
     }
     if (std::strcmp(key, "split_min_stages") == 0) {
         if (value < 2) return fail(ctx, TETRI_ERR_INVALID_ARG, "tetri_set_option: split_min_stages=%d (at least 2)", value);
         ctx->split_min_stages = value;
+        ctx->division_set = true;
         return TETRI_OK;
     }
     if (std::strcmp(key, "split_bias_stages") == 0) {
         if (value < 0) return fail(ctx, TETRI_ERR_INVALID_ARG, "tetri_set_option: split_bias_stages=%d (not negative)", value);
         ctx->split_bias_stages = value;
+        ctx->division_set = true;
         return TETRI_OK;
     }
     if (std::strcmp(key, "split_share_q8") == 0) {
         if (value < 1 || value > 128) return fail(ctx, TETRI_ERR_INVALID_ARG, "tetri_set_option: split_share_q8=%d (1..128)", value);
         ctx->split_share_q8 = value;
+        ctx->division_set = true;
         return TETRI_OK;
     }
     if (std::strcmp(key, "stream_wgs") == 0) {
         if (value < 0 || value > 255) return fail(ctx, TETRI_ERR_INVALID_ARG, "tetri_set_option: stream_wgs=%d (0..255)", value);
         ctx->stream_wgs = value;
+        ctx->division_set = true;
         return TETRI_OK;
     }
     if (std::strcmp(key, "decode_parts") == 0) {
@@ -155,7 +160,7 @@ tetri_status tetri_set_option(tetri_ctx *ctx, const char *key, int32_t value)
         return TETRI_OK;
     }
     if (std::strcmp(key, "attn_variant") == 0) {
-        if (value < 0 || value > 2) return fail(ctx, TETRI_ERR_INVALID_ARG, "tetri_set_option: attn_variant=%d unknown", value);
+        if (value < 0 || value > 3) return fail(ctx, TETRI_ERR_INVALID_ARG, "tetri_set_option: attn_variant=%d unknown", value);
         ctx->attn_variant = value;
         return TETRI_OK;
     }
@@ -374,6 +379,90 @@ tetri_status tetri_decode_attn_append(tetri_ctx *h, const void *q, const void *k
                          num_reqs, max_ctx_len, scale, out, stream);
 }
 
+// Is the stream being captured into a graph?  (If the question fails: take it that it is.)
+static bool stream_captures(hipStream_t hs)
+{
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(hs, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone;
+}
+
+// A launch is about to use the handle's scratch memory and counters: one on another stream must not start before the
+// previous one has ended.  (Asked of the stream, not of an event behind the launch: recording an event per launch costs
+// several microseconds of queue time between 20-us kernels.  A stream that is being captured into a graph takes no
+// queries: the graph orders its nodes.)
+static tetri_status claim_scratch(tetri_ctx *h, const char *fn, hipStream_t hs, bool capturing)
+{
+    // the scratch memory lives on the device the handle was created on
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess || dev != h->device)
+        return fail(h, TETRI_ERR_INVALID_ARG, "%s: the current device is %d, the handle was created on device %d", fn, dev, h->device);
+    if (capturing) return TETRI_OK;
+    if (h->divide_launched && h->last_divide_stream != hs && hipStreamQuery(h->last_divide_stream) == hipErrorNotReady)
+        return fail(h, TETRI_ERR_INVALID_ARG, "%s: the stream of this handle's previous launch that uses its scratch memory still has work "
+                    "pending; launches on one handle must not overlap (use one handle per stream)", fn);
+    return TETRI_OK;
+}
+static void scratch_claimed(tetri_ctx *h, hipStream_t hs)
+{
+    h->last_divide_stream = hs;
+    h->divide_launched = true;
+}
+
+struct ShortShape {
+    int wavefronts;
+    bool preferred;
+};
+
+// The launch of the short kernel for a chunk whose segments the host knows: its row blocks, most work first, and the shape.
+// False if the chunk does not fit the kernel's tables.
+static bool plan_short(const tetri_ctx *h, const int32_t *cu, const int32_t *ctx_lens, int32_t num_segs, bool fp8, ShortParams &p,
+                       ShortShape &shape)
+{
+    if (num_segs > kShortSegs) return false;
+    struct Unit { int32_t steps; uint16_t code; } units[kShortUnits];
+    int n = 0;
+    int64_t steps = 0;                // 32-key steps of all row blocks of one head
+    int32_t most = 0;
+    for (int32_t s = 0; s < num_segs; ++s) {
+        p.cu[s] = cu[s];
+        p.ctx[s] = ctx_lens[s];
+        const int32_t blocks = (cu[s + 1] - cu[s] + 31) / 32, ctx_steps = (ctx_lens[s] + 31) / 32;
+        if (n + blocks > kShortUnits) return false;
+        for (int32_t b = 0; b < blocks; ++b) {
+            units[n++] = {ctx_steps + b + 1, (uint16_t)(s | b << 6)};
+            steps += ctx_steps + b + 1;
+        }
+        most = std::max(most, ctx_steps + blocks);
+    }
+    p.cu[num_segs] = cu[num_segs];
+    std::sort(units, units + n, [](const Unit &a, const Unit &b) { return a.steps > b.steps; });
+    for (int i = 0; i < n; i += 2) p.unit[i / 2] = units[i].code | (i + 1 < n ? (uint32_t)units[i + 1].code << 16 : 0u);
+    p.units = n;
+    p.rows = cu[num_segs];
+    const int64_t Hq = h->cfg.num_q_heads, wgs = n * Hq, cus = std::max(h->num_cus, 1);
+    const int64_t pad_vectors = (int64_t)(h->cfg.chunk_size - p.rows) * Hq * h->cfg.head_dim / 8;
+    p.zero_wgs = (int32_t)std::min<int64_t>(256, (pad_vectors + 1023) / 1024);
+    // A compute unit holds 8 wavefronts of the kernel (head_dim 64: 16).  Few row blocks: as many wavefronts for each as
+    // that leaves room for, up to 8; short key ranges have no steps for more than two.
+    const int64_t room = h->cfg.head_dim == 64 ? 2 * cus : cus, total = steps * Hq;
+    shape.wavefronts = wgs <= room ? 8 : (wgs <= 2 * room ? 4 : (2 * wgs <= 9 * room || total > 16 * wgs ? 2 : 1));
+    if (most <= 4) shape.wavefronts = std::min(shape.wavefronts, 4);
+    // Row blocks for at most half of the compute units: the keys of each are split, down to one step per wavefront.
+    // (More workgroups than compute units lose more by the partial results' way through memory than they win.)
+    const int64_t units_fit = (int64_t)(2 * h->scratch_units) / wgs;
+    p.splits = 1;
+    if (h->split_keys && 2 * wgs <= cus && wgs <= h->n_counters)
+        p.splits = (int32_t)std::max<int64_t>(1, std::min(std::min<int64_t>(cus / wgs, 16), std::min<int64_t>((most + 7) / 8, units_fit)));
+    // Where this kernel is the faster one (measured over 40x128, 32/8x128, 8/2x128, 4x64 and 6/2x64 heads, 64 to 4096
+    // rows, 0 to 30000 cached tokens; figures as total steps of 32 keys x 32 rows): a launch of at most two workgroups
+    // per compute unit up to 120000 steps (0.45-0.95 of the shared-tile kernel's time; above that it is bound by L2, and
+    // loses 20 %), FP8 codes, which cost it their conversion once per row block, up to 15000; bigger launches up to
+    // 20000 (10000) steps, where the shared-tile kernel's fixed part still weighs more.  head_dim 64: always.
+    const int64_t limit = wgs <= 2 * cus ? (fp8 ? (wgs <= cus / 2 ? 120000 : 15000) : 120000) : (fp8 ? 10000 : 20000);
+    shape.preferred = h->cfg.head_dim == 64 || total <= limit;
+    return (uint64_t)(wgs * p.splits + p.zero_wgs) * (uint64_t)std::max<int64_t>(Hq, p.splits) < 0x100000000ull;
+}
+
 static tetri_status attn_common(const char *fn, tetri_ctx *h, const void *q, const void *k_new, const void *v_new,
                                 const void *kv_pages, void *kv_pages_w, const int32_t *block_table, const int32_t *cu,
                                 const int32_t *ctx_lens, int32_t num_segs, float scale, void *out, void *stream,
@@ -405,9 +494,31 @@ static tetri_status attn_common(const char *fn, tetri_ctx *h, const void *q, con
     // while masked scores (-inf) still map to weight 0
     p.c = std::fmax(std::fabs(scale) * 1.4426950408889634f, 1e-30f);
     p.neg = scale < 0.f;
+    hipStream_t hs = static_cast<hipStream_t>(stream);
+    // divisions the kernels do by launch constants, as multiplications
+    auto magic = [](uint32_t d) -> uint32_t { return d <= 1 ? 0u : (uint32_t)((0x100000000ull + d - 1) / d); };
+    const int cus = std::max(h->num_cus, 1);
+    // ---- a chunk with little work, its segments known on the host.  (What is captured into a graph is replayed for other
+    // metadata in the same device arrays: a launch that carries the segments along is not the one to capture.)
+    ShortParams sp;
+    ShortShape shape;
+    // A caller who has set one of the shared-tile kernel's ways of dividing its work gets that kernel.
+    if (host_cu && (h->attn_variant == 3 || (h->attn_variant == 0 && !h->division_set)) && !stream_captures(hs) &&
+        plan_short(h, host_cu, host_ctx, num_segs, fp8, sp, shape) && (shape.preferred || h->attn_variant == 3)) {
+        sp.q = p.q; sp.k_new = p.k_new; sp.v_new = p.v_new; sp.pages = p.pages; sp.bt = p.bt; sp.out = p.out; sp.pages_w = p.pages_w;
+        sp.C = p.C; sp.Hq = p.Hq; sp.Hkv = p.Hkv; sp.g = p.g; sp.max_blocks = p.max_blocks;
+        sp.hq_magic = magic((uint32_t)p.Hq); sp.hkv_magic = magic((uint32_t)p.Hkv); sp.splits_magic = magic((uint32_t)sp.splits);
+        sp.c = p.c; sp.neg = p.neg; sp.k_scale = p.k_scale; sp.v_scale = p.v_scale; sp.k_inv = p.k_inv; sp.v_inv = p.v_inv;
+        sp.scratch = reinterpret_cast<float *>(h->scratch);
+        sp.counters = h->counters + (size_t)h->counter_set * h->n_counters;
+        if (sp.splits > 1 && (st = claim_scratch(h, fn, hs, false)) != TETRI_OK) return st;
+        hipError_t e = tetri_launch_short(h->cfg.head_dim, fp8, sp, shape.wavefronts, hs);
+        if (e != hipSuccess) return fail(h, TETRI_ERR_HIP, "%s: launch failed: %s", fn, hipGetErrorString(e));
+        if (sp.splits > 1) scratch_claimed(h, hs);
+        return TETRI_OK;
+    }
     wave_grouping(p.g, &p.hpw, &p.rb);
     const int groups = p.Hq / p.hpw;
-    const int cus = std::max(h->num_cus, 1);
     // Workgroup size of the shared-tile kernel.  A full chunk has at least C / (rows of a tile) tiles per head
     // group; when that alone gives five workgroups per four compute units or more, four-wavefront workgroups (two
     // to a CU, their barriers independent of each other), one per tile, do best: with two per CU everywhere they run
@@ -451,25 +562,13 @@ static tetri_status attn_common(const char *fn, tetri_ctx *h, const void *q, con
         G = 0;
     if (!counters_fit) p.helpers = 0;
     const bool shares = G > 0 || p.helpers > 0;         // the launch uses the handle's scratch memory and counters
-    hipStream_t hs = static_cast<hipStream_t>(stream);
-    // (a stream that is being captured into a graph takes no event queries or records: the graph orders its nodes)
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    const bool capturing = shares && (hipStreamIsCapturing(hs, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone);
-    if (shares) {
-        // the scratch memory lives on the device the handle was created on
-        int dev = -1;
-        if (hipGetDevice(&dev) != hipSuccess || dev != h->device)
-            return fail(h, TETRI_ERR_INVALID_ARG, "%s: the current device is %d, the handle was created on device %d", fn, dev, h->device);
-        // such launches share the handle's scratch memory and counters: one on another stream must not start
-        // before the previous one has ended.  (Asked of the stream, not of an event behind the launch: recording
-        // an event per launch costs several microseconds of queue time between 20-us kernels.)
-        if (!capturing && h->divide_launched && h->last_divide_stream != hs && hipStreamQuery(h->last_divide_stream) == hipErrorNotReady)
-            return fail(h, TETRI_ERR_INVALID_ARG, "%s: the stream of this handle's previous launch that uses its scratch memory still has work "
-                        "pending; launches on one handle must not overlap (use one handle per stream)", fn);
-    }
+    const bool capturing = shares && stream_captures(hs);
+    if (shares && (st = claim_scratch(h, fn, hs, capturing)) != TETRI_OK) return st;
     p.stream_wgs = G;
     // (in tail mode the bound's last tile and its helper are extra jobs of existing workgroups)
-    p.attn_grid = 8 * p.gpx * (G > 0 ? G : (p.helpers > 0 ? p.tiles + p.helpers - 2 : p.tiles));
+    p.span_shift = groups <= 1 ? 3 : (groups <= 2 ? 2 : (groups <= 4 ? 1 : 0));
+    const int per_group = G > 0 ? G : (p.helpers > 0 ? p.tiles + p.helpers - 2 : p.tiles);
+    p.attn_grid = 8 * p.gpx * ((per_group + (1 << p.span_shift) - 1) >> p.span_shift);
     p.attn_first = p.attn_grid;
     // fused append: a few dozen workgroups, each copying every 64th row of the chunk
     // (every eight-wavefront workgroup of this kernel occupies a whole CU: in stream mode only the CUs the
@@ -480,8 +579,6 @@ static tetri_status attn_common(const char *fn, tetri_ctx *h, const void *q, con
         append_wgs = idle >= 8 ? (idle < 64 ? idle / 8 * 8 : 64) : 8;
     }
     p.append_blocks = kv_pages_w ? (p.C < append_wgs ? p.C : append_wgs) : 0;
-    // divisions the kernel does by launch constants, as multiplications
-    auto magic = [](uint32_t d) -> uint32_t { return d <= 1 ? 0u : (uint32_t)((0x100000000ull + d - 1) / d); };
     auto log2i = [](int v) { int s = 0; while ((1 << s) < v) ++s; return s; };
     p.hpw_shift = log2i(p.hpw);
     p.rb_shift = log2i(p.rb);
@@ -501,10 +598,7 @@ static tetri_status attn_common(const char *fn, tetri_ctx *h, const void *q, con
     if (e != hipSuccess) return fail(h, TETRI_ERR_HIP, "%s: launch failed: %s", fn, hipGetErrorString(e));
     if (shares) {
         h->counter_set = 1 - h->counter_set;
-        if (!capturing) {
-            h->last_divide_stream = hs;
-            h->divide_launched = true;
-        }
+        if (!capturing) scratch_claimed(h, hs);
     }
     return TETRI_OK;
 }

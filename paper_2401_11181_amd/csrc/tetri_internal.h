@@ -15,6 +15,7 @@ struct tetri_ctx {
     int split_min_stages = 8;   // tail mode: the shortest key range that hands its tail to a helper workgroup
     int split_bias_stages = 6;  // a helper's overhead, in stages (see the kernel)
     int split_share_q8 = 85;    // the share of the remaining stages a tile hands over, in 1/256 (a third)
+    bool division_set = false;  // one of the five options above has been set: the caller wants the shared-tile kernel
     int decode_parts = 0;       // key parts per (request, kv head) of the decode kernel (0: the library chooses)
     int transfer_slabs = 0;     // (K / V, head) slabs per workgroup of the export / import kernels (0: the library chooses)
     int device = 0;         // the device the handle was created on; its scratch memory lives there
@@ -52,6 +53,7 @@ struct AttnParams {
     int32_t n_counters;   // size of a set of arrival counters
     int32_t gpx;          // head groups per XCD
     uint32_t gpx_magic;   // ceil(2^32 / gpx), 0 for 1
+    int32_t span_shift;   // a head group runs on 1 << span_shift XCDs (more than one only with gpx = 1)
     char *scratch;        // partial results of tiles shared by several workgroups
     int32_t *counters;    // one per (group, tile, slot), all zero when the launch begins
     int32_t *counters_next;   // the set of the next such launch: zeroed by this one
@@ -66,6 +68,29 @@ struct AttnParams {
     // FP8 cache (the kernel variant that reads a pool of E4M3 codes): cached K / V = value(code) * scale
     float k_scale, v_scale;
     float k_inv, v_inv;   // fl32(1 / scale): the fused append quantises with them
+};
+
+// Launch parameters of the attention kernel for chunks with little work (tetri_short.hip): the chunk's segments and its
+// row blocks travel in them.
+constexpr int kShortSegs = 40, kShortUnits = 128;
+struct ShortParams {
+    const uint16_t *q, *k_new, *v_new, *pages;
+    const int32_t *bt;
+    uint16_t *out, *pages_w;      // pages_w: pool for the fused append (null: none)
+    int32_t C, rows;              // chunk rows, and those that belong to a request
+    int32_t Hq, Hkv, g, max_blocks;
+    uint32_t hq_magic, hkv_magic; // ceil(2^32 / d), 0 for 1
+    int32_t units;                // row blocks of 32 rows; workgroups = units * Hq * splits + zero_wgs
+    int32_t splits;               // workgroups that share the keys of a row block of one head
+    uint32_t splits_magic;
+    float *scratch;               // splits > 1: partial results, [(unit * Hq + head) * splits + part][32 * D + 64] floats
+    int32_t *counters;            // ... and arrival counters, one per (unit, head), zero before and after the launch
+    int32_t zero_wgs;             // workgroups that write the padding rows
+    float c;                      // |scale| * log2(e)
+    int32_t neg;                  // 1 if scale < 0
+    float k_scale, v_scale, k_inv, v_inv;
+    int32_t cu[kShortSegs + 1], ctx[kShortSegs];
+    uint32_t unit[kShortUnits / 2];   // 16 bits per row block, most work first: segment | block of the segment << 6
 };
 
 struct AppendParams {
@@ -102,6 +127,7 @@ struct DecodeParams {
 };
 
 hipError_t tetri_launch_attn(const tetri_ctx *h, const AttnParams &p, int key_parts, bool fp8_pool, hipStream_t stream);
+hipError_t tetri_launch_short(int head_dim, bool fp8_pool, const ShortParams &p, int wavefronts, hipStream_t stream);
 hipError_t tetri_launch_kv_transfer(const tetri_ctx *h, const TransferParams &p, int32_t row_units, int32_t tiles,
                                     bool to_pool, hipStream_t stream);
 hipError_t tetri_launch_kv_export_fp8(const tetri_ctx *h, const TransferParams &p, int32_t tiles, hipStream_t stream);
