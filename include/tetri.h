@@ -244,9 +244,10 @@ TETRI_API tetri_status tetri_chunk_prefill_planned(tetri_ctx *ctx, const void *q
 
 /*
  * A scheduled batch as a repeatable step (Sec. 3.3.3): metadata staged in pinned host memory, uploaded, then one chunk
- * after the other.  tetri_batch_create allocates a ring of staging buffers of meta_len int32 each (pinned); meta_dev is
- * the caller's device buffer of as many int32.  A batch belongs to its handle and is used by one thread at a time.
- *   tetri_batch_slot: the host address of staging buffer i in 0..tetri_batch_slots() - 1.
+ * after the other.  staging: the caller's pinned host memory (hipHostMalloc; anything else is TETRI_ERR_INVALID_ARG), a ring
+ * of tetri_batch_slots() buffers of meta_len int32 each; meta_dev: the caller's device buffer of meta_len int32.  Both
+ * outlive the batch (tetri_batch_destroy waits for the uploads that still read the staging buffers), 16-byte aligned.
+ * A batch belongs to its handle and is used by one thread at a time.
  *   tetri_batch_upload: packs the prompts and writes every chunk's metadata (tetri_plan_metadata: same arguments, same
  *   layout_out) into the next staging buffer and copies it to meta_dev on `stream`.  Waits only if the copy that used
  *   this buffer a whole ring ago is not done yet.  The plan has to have n_chunks chunks (TETRI_ERR_INVALID_ARG if not).
@@ -256,10 +257,10 @@ TETRI_API tetri_status tetri_chunk_prefill_planned(tetri_ctx *ctx, const void *q
  *   q, k_new, v_new, out: host arrays of a device pointer per chunk.
  */
 typedef struct tetri_batch tetri_batch;
-TETRI_API tetri_status tetri_batch_create(tetri_ctx *ctx, int64_t meta_len, int32_t *meta_dev, tetri_batch **out);
+TETRI_API tetri_status tetri_batch_create(tetri_ctx *ctx, int64_t meta_len, int32_t *staging, int32_t *meta_dev,
+                                          tetri_batch **out);
 TETRI_API void tetri_batch_destroy(tetri_batch *batch);
 TETRI_API int32_t tetri_batch_slots(void);
-TETRI_API int32_t *tetri_batch_slot(tetri_batch *batch, int32_t i);
 TETRI_API tetri_status tetri_batch_upload(tetri_batch *batch, const int32_t *prompt_lens, int32_t n_prompts,
                                           const int32_t *order, int32_t n_order, const int32_t *req_block_tables,
                                           int32_t *layout_out, int32_t n_chunks, void *stream);
@@ -444,6 +445,9 @@ TETRI_API tetri_status tetri_validate_chunk(tetri_ctx *ctx, const int32_t *block
  *                       launches of any size with at most 64 segments;
  *   "decode_parts"      workgroups that share the keys of one (request, kv head) in tetri_decode_attn
  *                       (default 0: chosen from num_reqs and max_ctx_len);
+ *   "decode_ranges"     the steps of a decode batch in that many equal ranges per kv head, each a workgroup's,
+ *                       whatever the context lengths (default 0: chosen like decode_parts; decode_parts, where
+ *                       set, comes first);
  *   "transfer_slabs"    (K / V, head) slabs one workgroup of tetri_kv_export / tetri_kv_import moves
  *                       (default 0: chosen from the size of the transfer).
  * Unknown keys or values give TETRI_ERR_INVALID_ARG.  Every setting computes the same

@@ -13,6 +13,8 @@ typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+typedef __attribute__((ext_vector_type(2))) int i32x2;
+typedef __attribute__((address_space(3))) i32x2 lds_i32x2;
 // Accesses through these go out as global-memory instructions whatever the compiler knows about the pointer.  (An
 // access through a generic pointer is a FLAT instruction, which also counts as an LDS operation: every later wait
 // for LDS reads then waits for it.)
@@ -117,6 +119,27 @@ __device__ __forceinline__ void dma16_group2(const void *sbase, uint32_t v0, uin
                  "global_load_lds_dwordx4 %0, %2\n\t"
                  "global_load_lds_dwordx4 %1, %2 offset:1024" ::"v"(v0), "v"(v1), "s"(sbase), "s"(lds_base) : "memory", "m0");
 }
+// The same for data that is read once (cache policy nt: it does not push other data out of the caches).  A decode iteration
+// over 2.7 GB of K and V: 6.5 TB/s with it, 5.9 without.
+template <int N> __device__ __forceinline__ void dma16_stream(const void *sbase, const uint32_t (&v)[N], uint32_t lds_base)
+{
+    static_assert(N == 1 || N == 2 || N == 4, "instructions of a group");
+    sbase = uniform_ptr(sbase);
+    lds_base = __builtin_amdgcn_readfirstlane(lds_base);
+    if constexpr (N == 4)
+        asm volatile("s_mov_b32 m0, %5\n\ts_nop 0\n\t"
+                     "global_load_lds_dwordx4 %0, %4 nt\n\t"
+                     "global_load_lds_dwordx4 %1, %4 offset:1024 nt\n\t"
+                     "global_load_lds_dwordx4 %2, %4 offset:2048 nt\n\t"
+                     "global_load_lds_dwordx4 %3, %4 offset:3072 nt" ::"v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]), "s"(sbase), "s"(lds_base) : "memory", "m0");
+    else if constexpr (N == 2)
+        asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\t"
+                     "global_load_lds_dwordx4 %0, %2 nt\n\t"
+                     "global_load_lds_dwordx4 %1, %2 offset:1024 nt" ::"v"(v[0]), "v"(v[1]), "s"(sbase), "s"(lds_base) : "memory", "m0");
+    else
+        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\t"
+                     "global_load_lds_dwordx4 %0, %1 nt" ::"v"(v[0]), "s"(sbase), "s"(lds_base) : "memory", "m0");
+}
 // Accesses that are coherent across the whole device by themselves (cache policy sc1: they are
 // served by the memory side, not by an XCD's L2), for data handed from one workgroup to another
 // inside a launch.  No cache write-back or invalidation is needed around them, only order:
@@ -218,6 +241,16 @@ __device__ __forceinline__ void codes_to_bf16(const u32x4 &raw, u32x4 &lo, u32x4
         hi[2 * w] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(raw[2 + w], 1.0f, false));
         hi[2 * w + 1] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(raw[2 + w], 1.0f, true));
     }
+}
+// 8 codes to 8 bf16 values.
+__device__ __forceinline__ bf16x8 codes_to_bf16(uint32_t a, uint32_t b)
+{
+    u32x4 r;
+    r[0] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(a, 1.0f, false));
+    r[1] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(a, 1.0f, true));
+    r[2] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(b, 1.0f, false));
+    r[3] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(b, 1.0f, true));
+    return __builtin_bit_cast(bf16x8, r);
 }
 // ... and 8 bf16 values (16 bytes) to their 8 codes under fl32(1 / scale) = inv: fl32(x * inv) clamped to +-448,
 // rounded to nearest even by v_cvt_pk_fp8_f32.

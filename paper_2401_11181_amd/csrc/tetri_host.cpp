@@ -154,6 +154,11 @@ tetri_status tetri_set_option(tetri_ctx *ctx, const char *key, int32_t value)
         ctx->decode_parts = value;
         return TETRI_OK;
     }
+    if (std::strcmp(key, "decode_ranges") == 0) {
+        if (value < 0) return fail(ctx, TETRI_ERR_INVALID_ARG, "tetri_set_option: decode_ranges=%d (>= 0)", value);
+        ctx->decode_ranges = value;
+        return TETRI_OK;
+    }
     if (std::strcmp(key, "transfer_slabs") == 0) {
         if (value < 0) return fail(ctx, TETRI_ERR_INVALID_ARG, "tetri_set_option: transfer_slabs=%d (>= 0)", value);
         ctx->transfer_slabs = value;
@@ -322,24 +327,45 @@ static tetri_status decode_common(const char *fn, tetri_ctx *h, const void *q, c
     p.k_scale = k_scale; p.v_scale = v_scale;
     p.k_inv = 1.0f / k_scale; p.v_inv = 1.0f / v_scale;
     p.out_scale = fp8 ? v_scale : 1.0f;
-    // Few requests: split every request's keys over several workgroups until the device has four
-    // workgroups per compute unit, each with at least eight 32-key steps, as far as the scratch
-    // memory for the parts reaches.
+    p.counters = h->counters + (size_t)h->counter_set * h->n_counters;
     const int64_t pairs = (int64_t)num_reqs * p.Hkv;
     const int64_t steps = ((int64_t)max_ctx_len + 32) / 32;
-    const int64_t per_part = (int64_t)num_reqs * p.Hq * (cfg.head_dim + 2) * 4;        // scratch bytes of one part
     const int64_t room = static_scratch ? (int64_t)h->static_scratch_bytes : (int64_t)(2 * h->scratch_units * h->unit_bytes);
-    if (static_scratch && 2 * per_part > room)
+    if (static_scratch && 2 * (int64_t)num_reqs * p.Hq * (cfg.head_dim + 2) * 4 > room)
         return fail(h, TETRI_ERR_INVALID_ARG, "%s: num_reqs x num_q_heads = %lld exceeds what the static scratch array of %lld bytes "
                     "holds (two parts of head_dim + 2 floats per request and head: at most %lld)", fn,
                     (long long)num_reqs * cfg.num_q_heads, (long long)room, (long long)(room / (2 * (cfg.head_dim + 2) * 4)));
-    const int64_t fit = room / per_part;
-    int64_t parts = (4 * (int64_t)std::max(h->num_cus, 1) + pairs - 1) / pairs;
-    parts = std::min(parts, std::max<int64_t>(1, steps / 8));
-    if (h->decode_parts > 0) parts = h->decode_parts;
-    parts = std::max<int64_t>(1, std::min(parts, std::min<int64_t>(fit, 1024)));
-    p.parts = (int32_t)parts;
-    if (pairs * parts > 0x7fffffff) return fail(h, TETRI_ERR_INVALID_ARG, "%s: too many workgroups", fn);
+    // How the work is cut (see the kernel).  The host knows the longest context, not the others.
+    //  - two (request, kv head) pairs per compute unit or more: a workgroup each, the hardware balances them;
+    //  - fewer, and much to read (if all contexts are that long: 200 MB, about 30 us): the steps of the batch in equal
+    //    ranges, one workgroup per compute unit (two: up to 15 % slower, there are more partial results).  48 requests of
+    //    16 to 8192 tokens, 32/8 heads: 70 us, against 114 with a workgroup per pair and 73 with 3 or 4;
+    //  - fewer, and little to read: every pair in as many parts as fill two workgroups per compute unit, of at least three
+    //    steps (the ranges' look-up and their cuts through short requests cost more than they balance: 10 us against 14 for
+    //    48 requests of up to 1180 tokens, 8/2 heads).
+    // All as far as the scratch memory (a partial result per part, two per range) and the counters reach.
+    const int64_t part_bytes = (int64_t)4 * (p.g * cfg.head_dim + (2 * p.g + 3) / 4 * 4);
+    const int64_t places = room / part_bytes, cus = std::max(h->num_cus, 1);
+    p.hkv_magic = p.Hkv <= 1 ? 0u : (uint32_t)((0x100000000ull + p.Hkv - 1) / p.Hkv);
+    p.ranges = 0;
+    p.min_steps = h->decode_ranges > 0 ? 1 : 4;
+    const bool divisible = num_reqs <= kDecodeLookup && num_reqs * ((int64_t)cfg.max_blocks_per_seq * cfg.page_size / 32 + 1) <= 0x7fffffff;
+    const int64_t most_bytes = pairs * steps * 32 * 2 * cfg.head_dim * (fp8 ? 1 : 2);
+    int64_t parts = h->decode_parts;
+    if (parts == 0) {
+        parts = std::max<int64_t>(1, std::min(2 * cus / pairs, std::min<int64_t>((steps + 2) / 3, 32)));
+        const int64_t most = std::min<int64_t>(places / 2, h->n_counters) / p.Hkv;
+        if (h->decode_ranges > 0 && divisible) p.ranges = (int32_t)std::min<int64_t>(h->decode_ranges, most);
+        else if (pairs < 2 * cus && most_bytes >= 200000000 && divisible) p.ranges = (int32_t)std::min(cus / p.Hkv, most);
+    }
+    if (p.ranges > 1) {
+        p.parts = 0;
+    } else {
+        if (pairs > h->n_counters) parts = 1;
+        p.parts = (int32_t)std::max<int64_t>(1, std::min(std::min(parts, places / pairs), (int64_t)1024));
+    }
+    if (pairs * std::max(p.parts, 1) * (int64_t)p.Hkv >= 0xffffffffll || pairs * std::max(p.parts, 1) > 0x7fffffff)
+        return fail(h, TETRI_ERR_INVALID_ARG, "%s: too many workgroups", fn);
     hipError_t e = tetri_launch_decode(h, p, static_cast<hipStream_t>(stream));
     if (e != hipSuccess) return fail(h, TETRI_ERR_HIP, "%s: launch failed: %s", fn, hipGetErrorString(e));
     return TETRI_OK;
@@ -677,7 +703,8 @@ struct tetri_batch {
 
     hipError_t close_group()          // an event on the last stream covers every upload that has none yet
     {
-        hipError_t e = hipEventRecord(ev[slot], last);
+        hipError_t e = ev[slot] ? hipSuccess : hipEventCreateWithFlags(&ev[slot], hipEventDisableTiming);
+        if (e == hipSuccess) e = hipEventRecord(ev[slot], last);
         if (e != hipSuccess) return e;
         for (int &c : cover)
             if (c == kOpen) c = slot;
@@ -689,38 +716,40 @@ extern "C" {
 
 int32_t tetri_batch_slots(void) { return tetri_batch::kSlots; }
 
-int32_t *tetri_batch_slot(tetri_batch *b, int32_t i)
-{
-    return b && i >= 0 && i < tetri_batch::kSlots ? b->host + (size_t)i * b->len : nullptr;
-}
-
 void tetri_batch_destroy(tetri_batch *b)
 {
     if (!b) return;
+    // the caller may free the staging buffers next: no upload reads them any more
+    if (b->turn != 0 && b->cover[b->slot] == tetri_batch::kOpen) (void)b->close_group();
     for (int i = 0; i < tetri_batch::kSlots; ++i)
-        if (b->ev[i]) (void)hipEventDestroy(b->ev[i]);
-    if (b->host) (void)hipHostFree(b->host);          // (waits for the device: no upload reads it any more)
+        if (b->ev[i]) {
+            (void)hipEventSynchronize(b->ev[i]);
+            (void)hipEventDestroy(b->ev[i]);
+        }
     delete b;
 }
 
-tetri_status tetri_batch_create(tetri_ctx *h, int64_t meta_len, int32_t *meta_dev, tetri_batch **out)
+tetri_status tetri_batch_create(tetri_ctx *h, int64_t meta_len, int32_t *staging, int32_t *meta_dev, tetri_batch **out)
 {
-    if (!h || !out) return fail(h, TETRI_ERR_INVALID_ARG, "tetri_batch_create: null argument");
+    const char *fn = "tetri_batch_create";
+    if (!h || !out) return fail(h, TETRI_ERR_INVALID_ARG, "%s: null argument", fn);
     *out = nullptr;
-    if (!meta_dev || !aligned16(meta_dev)) return fail(h, TETRI_ERR_INVALID_ARG, "tetri_batch_create: meta_dev is null or not 16-byte aligned");
+    if (!staging || !aligned16(staging)) return fail(h, TETRI_ERR_INVALID_ARG, "%s: staging is null or not 16-byte aligned", fn);
+    if (!meta_dev || !aligned16(meta_dev)) return fail(h, TETRI_ERR_INVALID_ARG, "%s: meta_dev is null or not 16-byte aligned", fn);
     if (meta_len < 4 || meta_len % 4 != 0 || meta_len > INT32_MAX - 3)
-        return fail(h, TETRI_ERR_INVALID_ARG, "tetri_batch_create: meta_len=%lld (a positive multiple of 4)", (long long)meta_len);
-    tetri_batch *b = new (std::nothrow) tetri_batch;
-    if (!b) return fail(h, TETRI_ERR_NOMEM, "tetri_batch_create: out of host memory");
-    b->h = h; b->len = meta_len; b->dev = meta_dev;
-    for (int &c : b->cover) c = -1;
-    hipError_t e = hipHostMalloc(reinterpret_cast<void **>(&b->host), (size_t)tetri_batch::kSlots * meta_len * sizeof(int32_t), hipHostMallocDefault);
-    for (int i = 0; i < tetri_batch::kSlots && e == hipSuccess; ++i) e = hipEventCreateWithFlags(&b->ev[i], hipEventDisableTiming);
-    if (e != hipSuccess) {
-        tetri_batch_destroy(b);
-        return fail(h, TETRI_ERR_HIP, "tetri_batch_create: %s", hipGetErrorString(e));
+        return fail(h, TETRI_ERR_INVALID_ARG, "%s: meta_len=%lld (a positive multiple of 4)", fn, (long long)meta_len);
+    // (the upload kernel reads the staging buffers: memory the device cannot reach would fault)
+    for (const int32_t *at : {(const int32_t *)staging, (const int32_t *)staging + tetri_batch::kSlots * meta_len - 1}) {
+        hipPointerAttribute_t a;
+        if (hipPointerGetAttributes(&a, at) != hipSuccess || a.type != hipMemoryTypeHost) {
+            (void)hipGetLastError();
+            return fail(h, TETRI_ERR_INVALID_ARG, "%s: staging is not pinned host memory", fn);
+        }
     }
-    std::memset(b->host, 0, (size_t)tetri_batch::kSlots * meta_len * sizeof(int32_t));
+    tetri_batch *b = new (std::nothrow) tetri_batch;
+    if (!b) return fail(h, TETRI_ERR_NOMEM, "%s: out of host memory", fn);
+    b->h = h; b->len = meta_len; b->host = staging; b->dev = meta_dev;
+    for (int &c : b->cover) c = -1;
     *out = b;
     return TETRI_OK;
 }

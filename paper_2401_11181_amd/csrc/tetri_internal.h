@@ -17,6 +17,7 @@ struct tetri_ctx {
     int split_share_q8 = 85;    // the share of the remaining stages a tile hands over, in 1/256 (a third)
     bool division_set = false;  // one of the five options above has been set: the caller wants the shared-tile kernel
     int decode_parts = 0;       // key parts per (request, kv head) of the decode kernel (0: the library chooses)
+    int decode_ranges = 0;      // equal ranges of a decode batch's steps per kv head (0: the library chooses)
     int transfer_slabs = 0;     // (K / V, head) slabs per workgroup of the export / import kernels (0: the library chooses)
     int device = 0;         // the device the handle was created on; its scratch memory lives there
     int num_cus = 0;
@@ -110,15 +111,22 @@ struct TransferParams {
     float k_inv, v_inv;   // quantising export: fl32(1 / scale) of the K and of the V half
 };
 
-// Launch parameters of the decode-iteration kernels.
+// Most requests of a decode batch whose steps are divided evenly (a lane of a wavefront looks at up to 16 of them).
+constexpr int kDecodeLookup = 1024;
+
+// Launch parameters of the decode-iteration kernel.
 struct DecodeParams {
     const uint16_t *q, *k_new, *v_new, *pages;
     const int32_t *bt, *ctx;
     uint16_t *out;
     uint16_t *pages_w;    // pool for the fused append of the new token (null: no append)
-    float *partial;       // scratch: [(request * Hq + head) * parts + part][D + 2] = unnormalised O, m, l
+    float *partial;       // scratch: partial results of (request, kv head)s shared by workgroups
+    int32_t *counters;    // ... and their arrival counters, zero before and after the launch
     int32_t B, Hq, Hkv, g, max_blocks;
-    int32_t parts;        // workgroups that share one (request, kv head)'s keys
+    uint32_t hkv_magic;   // ceil(2^32 / Hkv), 0 for 1
+    int32_t parts;        // > 0: each (request, kv head)'s keys in that many equal parts, a workgroup each;
+    int32_t ranges;       // parts == 0: the steps of the batch in that many equal ranges, a workgroup each per kv head
+    int32_t min_steps;    // ... of at least this many steps
     float c;              // |scale| * log2(e)
     int32_t neg;          // 1 if scale < 0
     int32_t fp8;          // 1: the pool holds E4M3 codes (one byte per element) with per-tensor scales

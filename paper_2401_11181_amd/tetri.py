@@ -94,13 +94,11 @@ def lib():
         L.tetri_validate_chunk.restype = i32
         L.tetri_validate_chunk.argtypes = [vp, vp, vp, vp, i32, vp]
         L.tetri_batch_create.restype = i32
-        L.tetri_batch_create.argtypes = [vp, ctypes.c_int64, vp, ctypes.POINTER(vp)]
+        L.tetri_batch_create.argtypes = [vp, ctypes.c_int64, vp, vp, ctypes.POINTER(vp)]
         L.tetri_batch_destroy.restype = None
         L.tetri_batch_destroy.argtypes = [vp]
         L.tetri_batch_slots.restype = i32
         L.tetri_batch_slots.argtypes = []
-        L.tetri_batch_slot.restype = ctypes.POINTER(i32)
-        L.tetri_batch_slot.argtypes = [vp, i32]
         L.tetri_set_option.restype = i32
         L.tetri_set_option.argtypes = [vp, ctypes.c_char_p, i32]
         _lib = L
@@ -361,11 +359,12 @@ class Batch:
     def __init__(self, handle, meta_len, meta_dev):
         self.b = None
         self.handle, self.meta_dev = handle, meta_dev       # both outlive the batch
+        n = lib().tetri_batch_slots()
+        staging = torch.empty((n, int(meta_len)), dtype=torch.int32, pin_memory=True)
         b = ctypes.c_void_p()
-        handle._check(lib().tetri_batch_create(handle.h, int(meta_len), _ptr(meta_dev), ctypes.byref(b)))
+        handle._check(lib().tetri_batch_create(handle.h, int(meta_len), _ptr(staging), _ptr(meta_dev), ctypes.byref(b)))
         self.b, self._p, self._n = b, b.value, native()
-        self.slots = [torch.from_numpy(np.ctypeslib.as_array(lib().tetri_batch_slot(b, i), (int(meta_len),)))
-                      for i in range(lib().tetri_batch_slots())]
+        self.slots = [staging[i] for i in range(n)]
 
     def upload(self, *args):
         rc = self._n.tetri_batch_upload(self._p, *args)
@@ -379,9 +378,9 @@ class Batch:
 
     def close(self):
         if self.b is not None:
-            self.slots = []
             lib().tetri_batch_destroy(self.b)
             self.b = self._p = None
+            self.slots = []
 
     def __del__(self):
         try:
