@@ -237,13 +237,19 @@ static tetri_status kv_transfer(const char *fn, tetri_ctx *h, void *kv_pages, vo
     p.buf = static_cast<uint16_t *>(buf);
     p.bt = block_table; p.cu = cu_tokens; p.first = first_tokens;
     p.R = num_reqs; p.Hkv = h->cfg.num_kv_heads; p.max_blocks = h->cfg.max_blocks_per_seq;
-    // enough workgroups for eight per compute unit (a short transfer is bound by the latency of each
-    // workgroup's look-ups, so it wants them all resident at once); beyond that a workgroup takes several slabs, amortises
-    // its page lookups over them and keeps the next slab's loads in flight behind the current one's stores
+    // A workgroup per slab while all of them are resident at once (eight per compute unit: a short transfer is bound by the
+    // latency of each workgroup's look-ups); beyond that two slabs (quantising export: four, of half the bytes) to a
+    // workgroup.  More would amortise the look-ups better, but many small workgroups keep what is read and written
+    // at a time closer together and leave no half-empty last round: 20000 tokens of 40x128 with 40 slabs each 203 us, with
+    // 2 and 4 191.
     const int64_t slabs = 2 * (int64_t)p.Hkv;
-    const int64_t want = 8 * (int64_t)std::max(h->num_cus, 1);
-    p.slabs_per_wg = (int32_t)std::min<int64_t>(slabs, std::max<int64_t>(1, tiles * slabs / want));
-    if (h->transfer_slabs > 0) p.slabs_per_wg = (int32_t)std::min<int64_t>(slabs, h->transfer_slabs);
+    p.slabs_per_wg = tiles * slabs <= 8 * (int64_t)std::max(h->num_cus, 1) ? 1 : (mode == 1 ? 4 : 2);
+    if (h->transfer_slabs > 0) p.slabs_per_wg = h->transfer_slabs;
+    p.slabs_per_wg = (int32_t)std::min<int64_t>(slabs, p.slabs_per_wg);
+    p.slab_groups = (int32_t)((slabs + p.slabs_per_wg - 1) / p.slabs_per_wg);
+    p.groups_magic = p.slab_groups <= 1 ? 0u : (uint32_t)((0x100000000ull + p.slab_groups - 1) / p.slab_groups);
+    if ((tiles + 4) * p.slab_groups >= 0x7fffffff || (uint64_t)(tiles + 4) * p.slab_groups / 4 * p.slab_groups >= 0x100000000ull)
+        return fail(h, TETRI_ERR_INVALID_ARG, "%s: too many tokens for one launch", fn);
     p.k_inv = 1.0f / k_scale; p.v_inv = 1.0f / v_scale;
     hipError_t e = mode == 1 ? tetri_launch_kv_export_fp8(h, p, (int32_t)tiles, static_cast<hipStream_t>(stream))
                              : tetri_launch_kv_transfer(h, p, row_units, (int32_t)tiles, to_pool, static_cast<hipStream_t>(stream));

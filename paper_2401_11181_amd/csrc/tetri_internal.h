@@ -108,6 +108,8 @@ struct TransferParams {
     const int32_t *bt, *cu, *first;   // first may be null: every range starts at token 0
     int32_t R, Hkv, max_blocks;
     int32_t slabs_per_wg; // (K / V, head) slabs one workgroup moves
+    int32_t slab_groups;  // runs of that many slabs
+    uint32_t groups_magic; // ceil(2^32 / slab_groups), 0 for 1
     float k_inv, v_inv;   // quantising export: fl32(1 / scale) of the K and of the V half
 };
 

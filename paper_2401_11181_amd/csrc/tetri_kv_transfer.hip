@@ -9,15 +9,14 @@
 // one contiguous 16 * D * 2 bytes of a page, on the buffer side the tile is contiguous, so both sides
 // are touched in whole cache lines.  The page of a token is looked up once and reused for all slabs.
 // The data is used once: loads and stores are non-temporal.
-#include "tetri_internal.h"
+#include "attn_common.h"
 
 namespace {
 
-constexpr int kPage = 16;
+using namespace tetri_dev;
+
 constexpr int kThreads = 256;
 constexpr int kTileBytes = kThreads * 16;     // one slab of a tile
-
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 // The request that owns tile `tile` when the tiles (TILE tokens each) of all requests are numbered request
 // after request (request r has ceil(n_r / TILE) of them), and the tile's first token inside the request.
@@ -50,15 +49,30 @@ __device__ inline int find_request(const int32_t *cu, int R, int tile, int lane,
     return -1;
 }
 
-// grid: (upper bound of the number of tiles, groups of slabs)
+// Workgroup -> tile and run of slabs.  Four tiles take their first run, then their second one, and so on, then come the
+// next four: what is under way at a time (2048 workgroups) are then about a dozen pages of the pool, each a contiguous
+// 2 * Hkv * 4 KB, and on the buffer's side a few hundred KB of every slab.  Moving one slab of all tiles first touches
+// two thousand pages at a time (16 requests of 51 to 516 tokens: 61 us, this way 56); all slabs of a single tile
+// first spreads the buffer's side as thin (a request of 12485 tokens: 364 us, this way 354).
+constexpr int kTilesAbreast = 4;
+__device__ inline void tile_of(const TransferParams &p, int bid, int &tile, int &group)
+{
+    const int run = bid / kTilesAbreast, block = magic_div(run, p.groups_magic);
+    group = run - block * p.slab_groups;
+    tile = block * kTilesAbreast + bid % kTilesAbreast;
+}
+
+// grid: (upper bound of the number of tiles, rounded up to kTilesAbreast) x runs of slabs
 template <int D, bool TO_POOL>
 __global__ __launch_bounds__(kThreads) void kv_transfer_kernel(TransferParams p)
 {
     constexpr int LPR = D / 8;                 // lanes that move one token's D bf16 of one slab
     constexpr int TILE = kThreads / LPR;       // tokens per workgroup
     const int tid = threadIdx.x;
+    int tile, group;
+    tile_of(p, blockIdx.x, tile, group);
     int j0 = 0;
-    const int r = __builtin_amdgcn_readfirstlane(find_request<TILE>(p.cu, p.R, blockIdx.x, tid & 63, j0));
+    const int r = __builtin_amdgcn_readfirstlane(find_request<TILE>(p.cu, p.R, tile, tid & 63, j0));
     if (r < 0) return;
     j0 = __builtin_amdgcn_readfirstlane(j0);
     const int c0 = p.cu[r];
@@ -72,7 +86,7 @@ __global__ __launch_bounds__(kThreads) void kv_transfer_kernel(TransferParams p)
     // the block-table index is clamped: a range the table cannot describe never forms an address outside it
     const int page = p.bt[(size_t)r * p.max_blocks + min(pos / kPage, p.max_blocks - 1)];
     // slab = kv * Hkv + head in both layouts: from one slab to the next both sides advance by a fixed step
-    const int slab0 = blockIdx.y * p.slabs_per_wg;
+    const int slab0 = group * p.slabs_per_wg;
     int left = min(slabs, slab0 + p.slabs_per_wg) - slab0;
     const size_t pool_step = (size_t)kPage * D, buf_step = (size_t)n * D;
     uint16_t *in_pool = p.pool + ((size_t)page * slabs + slab0) * pool_step + (size_t)(pos % kPage) * D + col;
@@ -105,15 +119,17 @@ __global__ __launch_bounds__(kThreads) void kv_transfer_kernel(TransferParams p)
 // Export with quantisation: the 16-bit pool is gathered into a dense buffer of FP8 E4M3 codes, the K
 // half of every request's block under the K scale, the V half under the V scale (this build's extension:
 // half the bytes on the link between the instances).  A code is fl32(x * inv_scale) clamped to +-448 and
-// rounded to nearest even by v_cvt_pk_fp8_f32.  Same work split as the copy kernel: a lane reads 16 bytes
-// (8 values) and writes 8 codes.
+// rounded to nearest even by v_cvt_pk_fp8_f32.  Same work split as the copy kernel: a lane reads 16 bytes (8 values) and
+// writes 8 codes.  (16 values per lane, two loads 32 bytes apart between lanes and one 16-byte store: 10 % slower.)
 template <int D>
 __global__ __launch_bounds__(kThreads) void kv_export_fp8_kernel(TransferParams p)
 {
     constexpr int LPR = D / 8, TILE = kThreads / LPR;
     const int tid = threadIdx.x;
+    int tile, group;
+    tile_of(p, blockIdx.x, tile, group);
     int j0 = 0;
-    const int r = __builtin_amdgcn_readfirstlane(find_request<TILE>(p.cu, p.R, blockIdx.x, tid & 63, j0));
+    const int r = __builtin_amdgcn_readfirstlane(find_request<TILE>(p.cu, p.R, tile, tid & 63, j0));
     if (r < 0) return;
     j0 = __builtin_amdgcn_readfirstlane(j0);
     const int c0 = p.cu[r];
@@ -125,41 +141,36 @@ __global__ __launch_bounds__(kThreads) void kv_export_fp8_kernel(TransferParams 
     const int slabs = 2 * p.Hkv;
     const int pos = first + j;
     const int page = p.bt[(size_t)r * p.max_blocks + min(pos / kPage, p.max_blocks - 1)];
-    const int slab0 = blockIdx.y * p.slabs_per_wg;
-    const int slab_end = min(slabs, slab0 + p.slabs_per_wg);
+    int slab = group * p.slabs_per_wg;
+    const int slab_end = min(slabs, slab + p.slabs_per_wg);
     const size_t pool_step = (size_t)kPage * D, buf_step = (size_t)n * D;
-    const uint16_t *src = p.pool + ((size_t)page * slabs + slab0) * pool_step + (size_t)(pos % kPage) * D + col;
-    uint8_t *dst = reinterpret_cast<uint8_t *>(p.buf) + (size_t)slabs * D * c0 + slab0 * buf_step + (size_t)j * D + col;
-#pragma unroll 2
-    for (int slab = slab0; slab < slab_end; ++slab) {
+    const uint16_t *src = p.pool + ((size_t)page * slabs + slab) * pool_step + (size_t)(pos % kPage) * D + col;
+    uint8_t *dst = reinterpret_cast<uint8_t *>(p.buf) + (size_t)slabs * D * c0 + slab * buf_step + (size_t)j * D + col;
+    auto ld = [&]() {
         const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(src));
-        const float inv = slab < p.Hkv ? p.k_inv : p.v_inv;
-        uint32_t codes[2];
-#pragma unroll
-        for (int w = 0; w < 2; ++w) {
-            float y[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const uint32_t word = v[2 * w + e / 2];
-                const float x = __builtin_bit_cast(float, (e & 1) ? (word & 0xffff0000u) : (word << 16));
-                y[e] = __builtin_fminf(__builtin_fmaxf(x * inv, -448.0f), 448.0f);
-            }
-            int c = __builtin_amdgcn_cvt_pk_fp8_f32(y[0], y[1], 0, false);
-            c = __builtin_amdgcn_cvt_pk_fp8_f32(y[2], y[3], c, true);
-            codes[w] = (uint32_t)c;
-        }
-        __builtin_nontemporal_store(codes[0], reinterpret_cast<uint32_t *>(dst));
-        __builtin_nontemporal_store(codes[1], reinterpret_cast<uint32_t *>(dst) + 1);
         src += pool_step;
+        return v;
+    };
+    auto st = [&](const u32x4 &v) {
+        const uint2 x = bf16_to_codes(v, slab < p.Hkv ? p.k_inv : p.v_inv);
+        __builtin_nontemporal_store(u32x2{x.x, x.y}, reinterpret_cast<u32x2 *>(dst));
         dst += buf_step;
+        ++slab;
+    };
+#pragma unroll 1
+    while (slab + 4 <= slab_end) {
+        const u32x4 v0 = ld(), v1 = ld(), v2 = ld(), v3 = ld();
+        st(v0), st(v1), st(v2), st(v3);
     }
+#pragma unroll 1
+    while (slab < slab_end) st(ld());
 }
 
 }  // namespace
 
 hipError_t tetri_launch_kv_export_fp8(const tetri_ctx *h, const TransferParams &p, int32_t tiles, hipStream_t stream)
 {
-    dim3 grid(tiles, (2 * p.Hkv + p.slabs_per_wg - 1) / p.slabs_per_wg), block(kThreads);
+    const dim3 grid((unsigned)((tiles + kTilesAbreast - 1) / kTilesAbreast * kTilesAbreast * p.slab_groups)), block(kThreads);
     const int d = h->cfg.head_dim;
     if (d == 128) hipLaunchKernelGGL(kv_export_fp8_kernel<128>, grid, block, 0, stream, p);
     else if (d == 64) hipLaunchKernelGGL(kv_export_fp8_kernel<64>, grid, block, 0, stream, p);
@@ -172,7 +183,7 @@ hipError_t tetri_launch_kv_export_fp8(const tetri_ctx *h, const TransferParams &
 hipError_t tetri_launch_kv_transfer(const tetri_ctx *, const TransferParams &p, int32_t row_units, int32_t tiles,
                                     bool to_pool, hipStream_t stream)
 {
-    dim3 grid(tiles, (2 * p.Hkv + p.slabs_per_wg - 1) / p.slabs_per_wg), block(kThreads);
+    const dim3 grid((unsigned)((tiles + kTilesAbreast - 1) / kTilesAbreast * kTilesAbreast * p.slab_groups)), block(kThreads);
     const int d = row_units;
     if (d == 32) {
         if (to_pool) hipLaunchKernelGGL((kv_transfer_kernel<32, true>), grid, block, 0, stream, p);
