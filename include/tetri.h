@@ -331,18 +331,19 @@ TETRI_API tetri_status tetri_decode_attn(tetri_ctx *ctx, const void *q, const vo
 /*
  * tetri_decode_attn for callers that cannot allocate device memory or hold an allocation: code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, same function and
- * same kernels as tetri_decode_attn; the only difference is where the parts of split requests are kept: not
- * in memory the handle allocated but in a static device array of the library, 8 MiB on every device the
- * library runs on, held until the process ends.  The call allocates nothing (no hipMalloc / hipFree, no
- * allocating library routine); the array's address on the handle's device was looked up by tetri_create.
+ * same kernels as tetri_decode_attn; the only difference is where the parts of split requests and their arrival
+ * counters are kept: not in memory the handle allocated but in static device arrays of the library, 8 MiB on every
+ * device the library runs on, held until the process ends.  So the call shares nothing with other launches of its
+ * handle and may overlap them on another stream.  It allocates nothing (no hipMalloc / hipFree, no
+ * allocating library routine); the arrays' addresses on the handle's device were looked up by tetri_create.
  * Limit: num_reqs * num_q_heads * (head_dim + 2) * 4 bytes * 2 must fit the array (two parts per request and
  * head; 8066 (request, head) pairs at head_dim 128), else TETRI_ERR_INVALID_ARG and nothing is launched;
  * within the limit the keys of a request are split as far as the array reaches, so the split (and with it
  * the rounding, not the function) may differ from tetri_decode_attn's; with the same "decode_parts" the
  * two calls give the same bits.
- * Every call on a device shares that device's array, which keeps the last call's contents (every part is
- * written before it is read, nothing has to start at zero): calls that overlap in time on one device, on
- * any handles or streams, race.
+ * Every call of this function on a device shares that device's arrays, which keep the last call's contents (every
+ * part is written before it is read; a call leaves the counters as it found them, at zero): calls of this function
+ * that overlap in time on one device, on any handles or streams, race.
  */
 TETRI_API tetri_status tetri_decode_attn_static(tetri_ctx *ctx, const void *q, const void *k_new, const void *v_new,
                                                 const void *kv_pages, const int32_t *block_table, const int32_t *ctx_lens,

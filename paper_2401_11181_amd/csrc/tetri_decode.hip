@@ -638,32 +638,33 @@ __global__ __launch_bounds__(NW * 64, 2) void decode_attn_kernel(DecodeParams)
 
 }  // namespace
 
-// Scratch memory of tetri_decode_attn_static: the parts of split requests, in an array that is part
-// of the loaded code object instead of an allocation (8 MiB on every device the library runs on,
-// held until the process ends).  On the host the array's name is only a stand-in for the symbol: the
+// Scratch memory of tetri_decode_attn_static: the parts of split requests and their arrival counters, in arrays that
+// are part of the loaded code object instead of an allocation (8 MiB on every device the library runs on,
+// held until the process ends).  On the host an array's name is only a stand-in for the symbol: the
 // device address is looked up once per device, with that device current, and only that address
 // is ever handed to a kernel.
 static __device__ __align__(256) unsigned char scratch[kDecodeStaticScratchBytes];
+static __device__ __align__(256) int32_t scratch_counters[kDecodeStaticCounters];
 
-hipError_t tetri_decode_static_scratch(float **ptr, size_t *bytes)
+hipError_t tetri_decode_static_memory(DecodeStatic *out)
 {
     constexpr int kMaxDevices = 64;
     static std::mutex lock;
-    static void *per_device[kMaxDevices];               // zero until the device's address is known
+    static DecodeStatic per_device[kMaxDevices];        // null until the device's addresses are known
     int dev = -1;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
     if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
     std::lock_guard<std::mutex> guard(lock);
-    if (!per_device[dev]) {
-        void *p = nullptr;
+    if (!per_device[dev].scratch) {
+        void *p = nullptr, *c = nullptr;
         e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
+        if (e == hipSuccess) e = hipGetSymbolAddress(&c, HIP_SYMBOL(scratch_counters));
         if (e != hipSuccess) return e;
-        if (!p) return hipErrorInvalidSymbol;
-        per_device[dev] = p;
+        if (!p || !c) return hipErrorInvalidSymbol;
+        per_device[dev] = {static_cast<float *>(p), static_cast<int32_t *>(c)};
     }
-    *ptr = static_cast<float *>(per_device[dev]);
-    *bytes = kDecodeStaticScratchBytes;
+    *out = per_device[dev];
     return hipSuccess;
 }
 

@@ -98,9 +98,9 @@ tetri_status tetri_create(const tetri_config *c, tetri_ctx **out)
         tetri_destroy(h);
         return fail(nullptr, TETRI_ERR_HIP, "tetri_create: scratch memory: %s", hipGetErrorString(e));
     }
-    // the static scratch array of tetri_decode_attn_static: its address on this device, looked up here so that the
+    // the static memory of tetri_decode_attn_static: its addresses on this device, looked up here so that the
     // entry point itself makes no runtime call besides the launch
-    if ((e = tetri_decode_static_scratch(&h->static_scratch, &h->static_scratch_bytes)) != hipSuccess) {
+    if ((e = tetri_decode_static_memory(&h->decode_static)) != hipSuccess) {
         tetri_destroy(h);
         return fail(nullptr, TETRI_ERR_HIP, "tetri_create: static scratch array: %s", hipGetErrorString(e));
     }
@@ -322,7 +322,7 @@ static tetri_status decode_common(const char *fn, tetri_ctx *h, const void *q, c
     p.bt = block_table; p.ctx = ctx_lens;
     p.out = static_cast<uint16_t *>(out);
     p.pages_w = static_cast<uint16_t *>(kv_pages_w);
-    p.partial = static_scratch ? h->static_scratch : reinterpret_cast<float *>(h->scratch);
+    p.partial = static_scratch ? h->decode_static.scratch : reinterpret_cast<float *>(h->scratch);
     p.B = num_reqs; p.Hq = cfg.num_q_heads; p.Hkv = cfg.num_kv_heads; p.g = p.Hq / p.Hkv;
     p.max_blocks = cfg.max_blocks_per_seq;
     p.c = std::fmax(std::fabs(scale) * 1.4426950408889634f, 1e-30f);
@@ -333,10 +333,11 @@ static tetri_status decode_common(const char *fn, tetri_ctx *h, const void *q, c
     p.k_scale = k_scale; p.v_scale = v_scale;
     p.k_inv = 1.0f / k_scale; p.v_inv = 1.0f / v_scale;
     p.out_scale = fp8 ? v_scale : 1.0f;
-    p.counters = h->counters + (size_t)h->counter_set * h->n_counters;
+    p.counters = static_scratch ? h->decode_static.counters : h->counters + (size_t)h->counter_set * h->n_counters;
+    const int64_t n_counters = static_scratch ? kDecodeStaticCounters : h->n_counters;
     const int64_t pairs = (int64_t)num_reqs * p.Hkv;
     const int64_t steps = ((int64_t)max_ctx_len + 32) / 32;
-    const int64_t room = static_scratch ? (int64_t)h->static_scratch_bytes : (int64_t)(2 * h->scratch_units * h->unit_bytes);
+    const int64_t room = static_scratch ? (int64_t)kDecodeStaticScratchBytes : (int64_t)(2 * h->scratch_units * h->unit_bytes);
     if (static_scratch && 2 * (int64_t)num_reqs * p.Hq * (cfg.head_dim + 2) * 4 > room)
         return fail(h, TETRI_ERR_INVALID_ARG, "%s: num_reqs x num_q_heads = %lld exceeds what the static scratch array of %lld bytes "
                     "holds (two parts of head_dim + 2 floats per request and head: at most %lld)", fn,
@@ -360,14 +361,14 @@ static tetri_status decode_common(const char *fn, tetri_ctx *h, const void *q, c
     int64_t parts = h->decode_parts;
     if (parts == 0) {
         parts = std::max<int64_t>(1, std::min(2 * cus / pairs, std::min<int64_t>((steps + 2) / 3, 32)));
-        const int64_t most = std::min<int64_t>(places / 2, h->n_counters) / p.Hkv;
+        const int64_t most = std::min<int64_t>(places / 2, n_counters) / p.Hkv;
         if (h->decode_ranges > 0 && divisible) p.ranges = (int32_t)std::min<int64_t>(h->decode_ranges, most);
         else if (pairs < 2 * cus && most_bytes >= 200000000 && divisible) p.ranges = (int32_t)std::min(cus / p.Hkv, most);
     }
     if (p.ranges > 1) {
         p.parts = 0;
     } else {
-        if (pairs > h->n_counters) parts = 1;
+        if (pairs > n_counters) parts = 1;
         p.parts = (int32_t)std::max<int64_t>(1, std::min(std::min(parts, places / pairs), (int64_t)1024));
     }
     if (pairs * std::max(p.parts, 1) * (int64_t)p.Hkv >= 0xffffffffll || pairs * std::max(p.parts, 1) > 0x7fffffff)

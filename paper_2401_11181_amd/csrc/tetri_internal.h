@@ -6,6 +6,15 @@
 
 #include "tetri.h"
 
+// The static device memory behind tetri_decode_attn_static: the parts of split requests, and arrival counters of their own,
+// so that such a call shares nothing with the other launches of its handle.
+constexpr size_t kDecodeStaticScratchBytes = (size_t)8 << 20;
+constexpr int32_t kDecodeStaticCounters = 2048;
+struct DecodeStatic {
+    float *scratch = nullptr;
+    int32_t *counters = nullptr;        // kDecodeStaticCounters, zero when the library is loaded
+};
+
 struct tetri_ctx {
     tetri_config cfg;
     std::string err;
@@ -28,12 +37,8 @@ struct tetri_ctx {
     int counter_set = 0;            // the set the next dividing launch uses
     bool divide_launched = false;       // a launch has used scratch and counters ...
     hipStream_t last_divide_stream = nullptr;   // ... the last one on this stream
-    float *static_scratch = nullptr;    // this device's address of the library's static scratch array (decode parts)
-    size_t static_scratch_bytes = 0;
+    DecodeStatic decode_static;         // this device's memory of tetri_decode_attn_static
 };
-
-// Size of the static device array behind tetri_decode_attn_static.
-constexpr size_t kDecodeStaticScratchBytes = (size_t)8 << 20;
 
 // Launch parameters of the attention kernels (passed by value).
 struct AttnParams {
@@ -142,8 +147,8 @@ hipError_t tetri_launch_kv_transfer(const tetri_ctx *h, const TransferParams &p,
                                     bool to_pool, hipStream_t stream);
 hipError_t tetri_launch_kv_export_fp8(const tetri_ctx *h, const TransferParams &p, int32_t tiles, hipStream_t stream);
 hipError_t tetri_launch_decode(const tetri_ctx *h, const DecodeParams &p, hipStream_t stream);
-// Device address (on the current device) and size of the static scratch array of the decode kernels.
-hipError_t tetri_decode_static_scratch(float **ptr, size_t *bytes);
+// Device addresses (on the current device) of the static memory of tetri_decode_attn_static.
+hipError_t tetri_decode_static_memory(DecodeStatic *out);
 hipError_t tetri_launch_append(const tetri_ctx *h, const AppendParams &p, int32_t chunk_rows, hipStream_t stream);
 
 // Copies len int32 (rounded up to a multiple of 4) from pinned host memory to the device, both 16-byte aligned.

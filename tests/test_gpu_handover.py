@@ -144,6 +144,34 @@ def test_overlapping_launches_on_one_handle_are_refused(oracle):
         assert torch.equal(out_a.view(torch.int16), out_b.view(torch.int16))
 
 
+def test_static_decode_beside_dividing_launches(oracle):
+    """tetri_decode_attn_static with split requests on one stream, launches that divide tiles on another, one handle: the
+    static call has memory and counters of its own, so both give the bits they give alone."""
+    w, sess, c, (q, k, v), pool, _ref_rows = prefilled(oracle, "static-beside", 146)
+    h = sess.handle
+    h.tetri_set_option("stream_wgs", 5)
+    h.tetri_set_option("decode_parts", 6)
+    bt = sess.meta[c][2]
+    ctx = torch.tensor([1000], dtype=torch.int32, device=DEV)
+    decode = lambda out, st: h.tetri_decode_attn_static(q[:1], k[:1], v[:1], pool, bt, ctx, 1, 1000, w.scale, out, st)
+    attn = lambda out, st: sess.attn(c, q, k, v, pool, w.scale, out, st)
+    want = torch.zeros_like(q[:1]), torch.zeros_like(q)
+    decode(want[0], None), attn(want[1], None)
+    torch.cuda.synchronize()
+    st_a, st_b = torch.cuda.Stream(device=DEV), torch.cuda.Stream(device=DEV)
+    outs_a, outs_b = [torch.zeros_like(q) for _ in range(20)], [torch.zeros_like(q[:1]) for _ in range(60)]
+    torch.cuda.synchronize()
+    for i in range(20):
+        attn(outs_a[i], st_a)
+        for o in outs_b[3 * i:3 * i + 3]:
+            decode(o, st_b)
+    torch.cuda.synchronize()
+    for i, o in enumerate(outs_a):
+        assert torch.equal(o.view(torch.int16), want[1].view(torch.int16)), ("prefill", i)
+    for i, o in enumerate(outs_b):
+        assert torch.equal(o.view(torch.int16), want[0].view(torch.int16)), ("decode", i)
+
+
 @pytest.mark.parametrize("fp8", [False, True], ids=["16-bit-pool", "fp8-pool"])
 def test_graph_replays_between_eager_launches(oracle, fp8):
     """A HIP graph that holds an odd number of launches that divide tiles, replayed several times with eager launches of
