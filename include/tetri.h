@@ -89,13 +89,17 @@ typedef struct {
  * Create / destroy a handle carrying the static shape.  The handle owns a fixed amount of device
  * scratch memory (about 34 MB on a 256-CU device, allocated here, freed by tetri_destroy) on the
  * device that is current at creation; launching calls must be made with that device current.
- * tetri_chunk_prefill_attn / _attn_append (launches small enough to be divided over the compute units by
- * stages rather than by row tiles) and tetri_decode_attn keep partial results there: such launches on one
- * handle must not overlap in time; use one handle per stream that runs concurrently.  The attention calls
- * return TETRI_ERR_INVALID_ARG when the handle's previous such launch went to another stream and that stream
- * still has work pending (synchronise the two streams, or use a handle each).  No state survives from one
- * launch to the next: a launch sets the arrival counters it used back to zero, and they are zeroed once more
- * for each launch by the launch before it (and by tetri_create).  The calls may be captured into a HIP graph
+ * The chunk-prefill calls (launches small enough to be divided over the compute units by stages rather than by
+ * row tiles, or to split the keys of their row blocks) and the decode calls (where they split requests) keep
+ * partial results there: such launches on one
+ * handle must not overlap in time; use one handle per stream that runs concurrently.  A chunk-prefill call
+ * returns TETRI_ERR_INVALID_ARG when the handle's previous such chunk-prefill launch went to another stream and that
+ * stream still has work pending (synchronise the two streams, or use a handle each); decode calls neither check
+ * nor are checked for: order the streams, for instance by events.  No state survives from one
+ * launch to the next: a launch sets the arrival counters it used back to zero, and the handle's launches take turns
+ * with several sets of them, each of which another launch zeroes once more before its turn comes again (after
+ * launches that wrongly overlapped, their own results are lost, not those of later launches).  A launch in a HIP
+ * graph keeps the set it was captured with.  The calls may be captured into a HIP graph
  * (a stream that is capturing is not asked whether it has work pending); replays of such a graph and launches
  * outside it may follow each other in any order on one handle, as long as they do not overlap in time.
  * tetri_create checks the configuration (TETRI_ERR_UNSUPPORTED / TETRI_ERR_INVALID_ARG) and
@@ -321,7 +325,7 @@ TETRI_API tetri_status tetri_kv_import(tetri_ctx *ctx, const void *buf, const in
  *   num_reqs >= 1 (not bound by chunk_size or max_segs_per_chunk); max_ctx_len: host scalar, an upper
  *   bound of ctx_lens that only sizes the launch (how far the keys of a request are split over
  *   workgroups when there are few requests); results do not depend on it.
- * Uses the handle's scratch memory when it splits: launches on one handle must not overlap in time.
+ * Uses the handle's scratch memory when it splits: launches on one handle must not overlap in time (see tetri_create).
  * Results are deterministic run to run.  TETRI_ERR_UNSUPPORTED for more than 32 query heads per kv head.
  */
 TETRI_API tetri_status tetri_decode_attn(tetri_ctx *ctx, const void *q, const void *k_new, const void *v_new,
@@ -342,7 +346,8 @@ TETRI_API tetri_status tetri_decode_attn(tetri_ctx *ctx, const void *q, const vo
  * the rounding, not the function) may differ from tetri_decode_attn's; with the same "decode_parts" the
  * two calls give the same bits.
  * Every call of this function on a device shares that device's arrays, which keep the last call's contents (every
- * part is written before it is read; a call leaves the counters as it found them, at zero): calls of this function
+ * part is written before it is read; a call leaves the counters as it found them, at zero, and takes turns with
+ * several sets of them as the launches of a handle do): calls of this function
  * that overlap in time on one device, on any handles or streams, race.
  */
 TETRI_API tetri_status tetri_decode_attn_static(tetri_ctx *ctx, const void *q, const void *k_new, const void *v_new,

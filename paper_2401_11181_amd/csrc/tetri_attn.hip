@@ -1299,7 +1299,7 @@ __global__ __launch_bounds__(kSlots * KS * 64, 2) void attn_tile_kernel(AttnPara
     const int grp = (xcd >> p.span_shift) * p.gpx + (local - lidx * p.gpx);
     const int widx = (lidx << p.span_shift) + (xcd & ((1 << p.span_shift) - 1));
     const int G = p.stream_wgs;
-    // the arrival counters of the next launch that divides tiles: all zero when this launch ends
+    // the arrival counters of a later launch: all zero when this launch ends
     if (G != 0 || p.helpers != 0)
         for (int i = abid * NT + threadIdx.x; i < p.n_counters; i += p.attn_grid * NT) p.counters_next[i] = 0;
     if (grp >= p.groups || widx >= (G != 0 ? G : (p.helpers != 0 ? p.tiles + p.helpers - 2 : p.tiles))) return;

@@ -138,6 +138,10 @@ __global__ __launch_bounds__(NW * 64, 2) void decode_attn_kernel(DecodeParams)
     auto ctx_of = [&](int b) -> int { return min(max(((const const_i32 *)(uintptr_t)p->ctx)[b], 0), max_blocks * kPage); };
 
     const int wg = magic_div(blockIdx.x, p->hkv_magic), kh = blockIdx.x - wg * Hkv;
+    auto clear_next = [&]() {
+        const int n = p->n_counters;
+        for (int i = blockIdx.x * NT + tid; i < n; i += gridDim.x * NT) store_global(p->counters_next + i, 0);
+    };
     // ---- the workgroup's first job; `left` steps of its range behind it
     Job job;
     int left = 0, div_q, div_r = 0, pos;
@@ -149,7 +153,10 @@ __global__ __launch_bounds__(NW * 64, 2) void decode_attn_kernel(DecodeParams)
         div_q = parts == 1 ? job.steps() : (job.steps() + parts - 1) / parts;
         job.begin = pos * div_q;
         job.end = min(job.steps(), job.begin + div_q);
-        if (job.begin >= job.end) return;                // fewer steps than parts: nobody waits for this one
+        if (job.begin >= job.end) {                      // fewer steps than parts: nobody waits for this one
+            clear_next();
+            return;
+        }
     } else {
         // lane l looks at requests l * R .. l * R + R - 1
         const int B = p->B, R = (B + 63) >> 6;
@@ -168,7 +175,10 @@ __global__ __launch_bounds__(NW * 64, 2) void decode_attn_kernel(DecodeParams)
         const int total = __builtin_amdgcn_readlane(incl, 63);
         // equal ranges, but none shorter than min_steps
         const int ranges = min(p->ranges, (int)((uint32_t)(total + p->min_steps - 1) / (uint32_t)p->min_steps));
-        if (wg >= ranges) return;
+        if (wg >= ranges) {
+            clear_next();
+            return;
+        }
         div_q = __builtin_amdgcn_readfirstlane((int)((uint32_t)total / (uint32_t)ranges));
         div_r = total - div_q * ranges;
         pos = wg * div_q + min(wg, div_r);
@@ -634,6 +644,7 @@ __global__ __launch_bounds__(NW * 64, 2) void decode_attn_kernel(DecodeParams)
     next_job(job, left);
     lds_barrier();                                       // everybody is done with stat, area and `arrived`
     }
+    clear_next();
 }
 
 }  // namespace
@@ -644,13 +655,14 @@ __global__ __launch_bounds__(NW * 64, 2) void decode_attn_kernel(DecodeParams)
 // device address is looked up once per device, with that device current, and only that address
 // is ever handed to a kernel.
 static __device__ __align__(256) unsigned char scratch[kDecodeStaticScratchBytes];
-static __device__ __align__(256) int32_t scratch_counters[kDecodeStaticCounters];
+static __device__ __align__(256) int32_t scratch_counters[kCounterSets * kDecodeStaticCounters];
 
 hipError_t tetri_decode_static_memory(DecodeStatic *out)
 {
     constexpr int kMaxDevices = 64;
     static std::mutex lock;
     static DecodeStatic per_device[kMaxDevices];        // null until the device's addresses are known
+    static std::atomic<uint32_t> turns[kMaxDevices];
     int dev = -1;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
@@ -662,7 +674,7 @@ hipError_t tetri_decode_static_memory(DecodeStatic *out)
         if (e == hipSuccess) e = hipGetSymbolAddress(&c, HIP_SYMBOL(scratch_counters));
         if (e != hipSuccess) return e;
         if (!p || !c) return hipErrorInvalidSymbol;
-        per_device[dev] = {static_cast<float *>(p), static_cast<int32_t *>(c)};
+        per_device[dev] = {static_cast<float *>(p), static_cast<int32_t *>(c), &turns[dev]};
     }
     *out = per_device[dev];
     return hipSuccess;

@@ -81,8 +81,7 @@ tetri_status tetri_create(const tetri_config *c, tetri_ctx **out)
     // a launch has at most one workgroup per CU, 4 (row block, head) slots each, and a workgroup leaves at
     // most two partial results per slot (its first and its last job); a partial result is O (32 x head_dim
     // floats), m and the row sum.  Arrival counters: one per (head group, row tile, slot), fewer than two
-    // tiles per CU in such a launch; two sets, because every such launch uses one set and zeroes the other
-    // for the launch after it.
+    // tiles per CU in such a launch; several sets, used in turn.
     hipDeviceProp_t prop;
     if ((e = hipGetDevice(&h->device)) != hipSuccess || (e = hipGetDeviceProperties(&prop, h->device)) != hipSuccess) {
         delete h;
@@ -93,8 +92,8 @@ tetri_status tetri_create(const tetri_config *c, tetri_ctx **out)
     h->unit_bytes = (size_t)32 * c->head_dim * 4 + 2 * 32 * 4;
     h->n_counters = (int32_t)(2 * h->scratch_units);
     if ((e = hipMalloc(reinterpret_cast<void **>(&h->scratch), 2 * h->scratch_units * h->unit_bytes)) != hipSuccess ||
-        (e = hipMalloc(reinterpret_cast<void **>(&h->counters), 2 * (size_t)h->n_counters * sizeof(int32_t))) != hipSuccess ||
-        (e = hipMemset(h->counters, 0, 2 * (size_t)h->n_counters * sizeof(int32_t))) != hipSuccess) {
+        (e = hipMalloc(reinterpret_cast<void **>(&h->counters), kCounterSets * (size_t)h->n_counters * sizeof(int32_t))) != hipSuccess ||
+        (e = hipMemset(h->counters, 0, kCounterSets * (size_t)h->n_counters * sizeof(int32_t))) != hipSuccess) {
         tetri_destroy(h);
         return fail(nullptr, TETRI_ERR_HIP, "tetri_create: scratch memory: %s", hipGetErrorString(e));
     }
@@ -333,7 +332,6 @@ static tetri_status decode_common(const char *fn, tetri_ctx *h, const void *q, c
     p.k_scale = k_scale; p.v_scale = v_scale;
     p.k_inv = 1.0f / k_scale; p.v_inv = 1.0f / v_scale;
     p.out_scale = fp8 ? v_scale : 1.0f;
-    p.counters = static_scratch ? h->decode_static.counters : h->counters + (size_t)h->counter_set * h->n_counters;
     const int64_t n_counters = static_scratch ? kDecodeStaticCounters : h->n_counters;
     const int64_t pairs = (int64_t)num_reqs * p.Hkv;
     const int64_t steps = ((int64_t)max_ctx_len + 32) / 32;
@@ -373,8 +371,16 @@ static tetri_status decode_common(const char *fn, tetri_ctx *h, const void *q, c
     }
     if (pairs * std::max(p.parts, 1) * (int64_t)p.Hkv >= 0xffffffffll || pairs * std::max(p.parts, 1) > 0x7fffffff)
         return fail(h, TETRI_ERR_INVALID_ARG, "%s: too many workgroups", fn);
+    const bool shares = p.parts != 1;
+    p.n_counters = shares ? (int32_t)n_counters : 0;
+    CounterSets cs = {nullptr, nullptr};
+    if (shares) cs = static_scratch ? counter_sets(h->decode_static.counters, p.n_counters, h->decode_static.turn->fetch_add(1))
+                                    : counter_sets(h->counters, p.n_counters, h->counter_turn);
+    p.counters = cs.use;
+    p.counters_next = cs.clear;
     hipError_t e = tetri_launch_decode(h, p, static_cast<hipStream_t>(stream));
     if (e != hipSuccess) return fail(h, TETRI_ERR_HIP, "%s: launch failed: %s", fn, hipGetErrorString(e));
+    if (shares && !static_scratch) ++h->counter_turn;
     return TETRI_OK;
 }
 
@@ -419,8 +425,9 @@ static bool stream_captures(hipStream_t hs)
     return hipStreamIsCapturing(hs, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone;
 }
 
-// A launch is about to use the handle's scratch memory and counters: one on another stream must not start before the
-// previous one has ended.  (Asked of the stream, not of an event behind the launch: recording an event per launch costs
+// A prefill launch is about to use the handle's scratch memory and counters: one on another stream must not start before
+// the previous one has ended.  (Decode launches are not asked for and do not ask: a decode loop may order its streams by
+// events, which a query of the stream cannot tell from an overlap.)  (Asked of the stream, not of an event behind the launch: recording an event per launch costs
 // several microseconds of queue time between 20-us kernels.  A stream that is being captured into a graph takes no
 // queries: the graph orders its nodes.)
 static tetri_status claim_scratch(tetri_ctx *h, const char *fn, hipStream_t hs, bool capturing)
@@ -543,11 +550,17 @@ static tetri_status attn_common(const char *fn, tetri_ctx *h, const void *q, con
         sp.hq_magic = magic((uint32_t)p.Hq); sp.hkv_magic = magic((uint32_t)p.Hkv); sp.splits_magic = magic((uint32_t)sp.splits);
         sp.c = p.c; sp.neg = p.neg; sp.k_scale = p.k_scale; sp.v_scale = p.v_scale; sp.k_inv = p.k_inv; sp.v_inv = p.v_inv;
         sp.scratch = reinterpret_cast<float *>(h->scratch);
-        sp.counters = h->counters + (size_t)h->counter_set * h->n_counters;
+        const CounterSets cs = counter_sets(h->counters, h->n_counters, h->counter_turn);
+        sp.counters = cs.use;
+        sp.counters_next = cs.clear;
+        sp.n_counters = h->n_counters;
         if (sp.splits > 1 && (st = claim_scratch(h, fn, hs, false)) != TETRI_OK) return st;
         hipError_t e = tetri_launch_short(h->cfg.head_dim, fp8, sp, shape.wavefronts, hs);
         if (e != hipSuccess) return fail(h, TETRI_ERR_HIP, "%s: launch failed: %s", fn, hipGetErrorString(e));
-        if (sp.splits > 1) scratch_claimed(h, hs);
+        if (sp.splits > 1) {
+            ++h->counter_turn;
+            scratch_claimed(h, hs);
+        }
         return TETRI_OK;
     }
     wave_grouping(p.g, &p.hpw, &p.rb);
@@ -622,15 +635,16 @@ static tetri_status attn_common(const char *fn, tetri_ctx *h, const void *q, con
     p.split_bias = h->split_bias_stages;
     p.scratch = h->scratch;
     p.n_counters = h->n_counters;
-    p.counters = h->counters + (size_t)h->counter_set * h->n_counters;
-    p.counters_next = h->counters + (size_t)(1 - h->counter_set) * h->n_counters;
+    const CounterSets cs = counter_sets(h->counters, h->n_counters, h->counter_turn);
+    p.counters = cs.use;
+    p.counters_next = cs.clear;
     p.kv_magic = magic((uint32_t)(p.g / p.hpw));
     if ((uint64_t)p.attn_grid * (uint64_t)(p.tiles + G + 1) >= 0x100000000ull)
         return fail(h, TETRI_ERR_UNSUPPORTED, "%s: chunk_size x heads too large for one launch", fn);
     hipError_t e = tetri_launch_attn(h, p, key_parts, fp8, hs);
     if (e != hipSuccess) return fail(h, TETRI_ERR_HIP, "%s: launch failed: %s", fn, hipGetErrorString(e));
     if (shares) {
-        h->counter_set = 1 - h->counter_set;
+        ++h->counter_turn;
         if (!capturing) scratch_claimed(h, hs);
     }
     return TETRI_OK;

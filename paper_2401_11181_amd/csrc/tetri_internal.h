@@ -2,9 +2,22 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <atomic>
 #include <string>
 
 #include "tetri.h"
+
+// Arrival counters of launches whose workgroups share results: kCounterSets sets, used in turn.  A launch leaves the
+// set it used at zero and also zeroes the set after the next: so whatever a launch left behind is gone before its set's turn
+// comes again, and launches that follow each other never touch each other's set, not even if they wrongly overlap.
+constexpr int kCounterSets = 4;
+struct CounterSets {
+    int32_t *use, *clear;
+};
+inline CounterSets counter_sets(int32_t *first, int32_t n, uint32_t turn)
+{
+    return {first + (size_t)(turn % kCounterSets) * n, first + (size_t)((turn + 2) % kCounterSets) * n};
+}
 
 // The static device memory behind tetri_decode_attn_static: the parts of split requests, and arrival counters of their own,
 // so that such a call shares nothing with the other launches of its handle.
@@ -12,7 +25,8 @@ constexpr size_t kDecodeStaticScratchBytes = (size_t)8 << 20;
 constexpr int32_t kDecodeStaticCounters = 2048;
 struct DecodeStatic {
     float *scratch = nullptr;
-    int32_t *counters = nullptr;        // kDecodeStaticCounters, zero when the library is loaded
+    int32_t *counters = nullptr;        // sets of kDecodeStaticCounters, zero when the library is loaded
+    std::atomic<uint32_t> *turn = nullptr;  // the set of the device's next such call
 };
 
 struct tetri_ctx {
@@ -31,11 +45,11 @@ struct tetri_ctx {
     int device = 0;         // the device the handle was created on; its scratch memory lives there
     int num_cus = 0;
     char *scratch = nullptr;        // partial results of tiles shared by workgroups: 2 x scratch_units units
-    int32_t *counters = nullptr;    // two sets of n_counters arrival counters: a launch uses one and zeroes the other
+    int32_t *counters = nullptr;    // sets of n_counters arrival counters
     size_t scratch_units = 0, unit_bytes = 0;
     int32_t n_counters = 0;
-    int counter_set = 0;            // the set the next dividing launch uses
-    bool divide_launched = false;       // a launch has used scratch and counters ...
+    uint32_t counter_turn = 0;      // the set of the next launch that uses one
+    bool divide_launched = false;       // a prefill launch has used scratch and counters ...
     hipStream_t last_divide_stream = nullptr;   // ... the last one on this stream
     DecodeStatic decode_static;         // this device's memory of tetri_decode_attn_static
 };
@@ -62,7 +76,7 @@ struct AttnParams {
     int32_t span_shift;   // a head group runs on 1 << span_shift XCDs (more than one only with gpx = 1)
     char *scratch;        // partial results of tiles shared by several workgroups
     int32_t *counters;    // one per (group, tile, slot), all zero when the launch begins
-    int32_t *counters_next;   // the set of the next such launch: zeroed by this one
+    int32_t *counters_next;   // the set of a later launch: zeroed by this one
     uint32_t kv_magic;    // the same for g / hpw: head group -> kv head
     int32_t max_blocks;
     int32_t tiles;        // upper bound of the number of row tiles of the chunk
@@ -91,6 +105,8 @@ struct ShortParams {
     uint32_t splits_magic;
     float *scratch;               // splits > 1: partial results, [(unit * Hq + head) * splits + part][32 * D + 64] floats
     int32_t *counters;            // ... and arrival counters, one per (unit, head), zero before and after the launch
+    int32_t *counters_next;       // the set of a later launch: zeroed by this one
+    int32_t n_counters;           // size of a set
     int32_t zero_wgs;             // workgroups that write the padding rows
     float c;                      // |scale| * log2(e)
     int32_t neg;                  // 1 if scale < 0
@@ -129,6 +145,8 @@ struct DecodeParams {
     uint16_t *pages_w;    // pool for the fused append of the new token (null: no append)
     float *partial;       // scratch: partial results of (request, kv head)s shared by workgroups
     int32_t *counters;    // ... and their arrival counters, zero before and after the launch
+    int32_t *counters_next;   // the set of a later launch: zeroed by this one
+    int32_t n_counters;   // size of a set; 0: no (request, kv head) is shared, the launch touches no counters
     int32_t B, Hq, Hkv, g, max_blocks;
     uint32_t hkv_magic;   // ceil(2^32 / Hkv), 0 for 1
     int32_t parts;        // > 0: each (request, kv head)'s keys in that many equal parts, a workgroup each;

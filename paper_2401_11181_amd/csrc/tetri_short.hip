@@ -104,7 +104,14 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_short_kernel(ShortParams)
     // the steps of this workgroup: all of them, or a part
     const int spp = splits == 1 ? steps : (steps + splits - 1) / splits;
     const int s_begin = part * spp, s_end = min(steps, s_begin + spp);
-    if (s_begin >= s_end) return;
+    auto clear_next = [&]() {
+        const int n = p->n_counters;
+        for (int i = blockIdx.x * (NW * 64) + tid; i < n; i += attn_wgs * (NW * 64)) store_global(p->counters_next + i, 0);
+    };
+    if (s_begin >= s_end) {
+        if (splits > 1) clear_next();
+        return;
+    }
 
     const const_i32 *bt = (const const_i32 *)(uintptr_t)(p->bt + (size_t)seg * p->max_blocks);
     const int last_entry = p->max_blocks - 1;
@@ -457,6 +464,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_short_kernel(ShortParams)
         }
     }
     if (splits == 1) return;
+    clear_next();
     // ---- the parts of a row block meet in scratch memory: whoever arrives last finds all of them there, merges them in
     // part order (the result does not depend on who that is) and sets the counter back to zero.  Nobody waits.
     const int used = (steps + spp - 1) / spp;

@@ -33,10 +33,16 @@ bool in_handle_memory(const void *p)
     return false;
 }
 
-std::vector<const int32_t *> g_counters;      // the arrival counters of every launch that shares results, in order
+// The arrival counters of every launch that shares results, in order: the set it uses and the one it zeroes.
+struct Counters {
+    const int32_t *use, *clear;
+    int32_t n;
+};
+std::vector<Counters> g_counters;
 
 float g_static_scratch[kDecodeStaticScratchBytes / 4];
-int32_t g_static_counters[kDecodeStaticCounters];
+int32_t g_static_counters[kCounterSets * kDecodeStaticCounters];
+std::atomic<uint32_t> g_static_turn;
 
 }  // namespace
 
@@ -80,22 +86,23 @@ hipError_t hipPointerGetAttributes(hipPointerAttribute_t *a, const void *) { a->
 // ---- the kernel launchers
 hipError_t tetri_launch_attn(const tetri_ctx *, const AttnParams &p, int, bool, hipStream_t)
 {
-    if (p.stream_wgs > 0 || p.helpers > 0) g_counters.push_back(p.counters);
+    if (p.stream_wgs > 0 || p.helpers > 0) g_counters.push_back({p.counters, p.counters_next, p.n_counters});
     return hipSuccess;
 }
 hipError_t tetri_launch_short(int, bool, const ShortParams &p, int, hipStream_t)
 {
-    if (p.splits > 1) g_counters.push_back(p.counters);
+    if (p.splits > 1) g_counters.push_back({p.counters, p.counters_next, p.n_counters});
     return hipSuccess;
 }
 hipError_t tetri_launch_decode(const tetri_ctx *, const DecodeParams &p, hipStream_t)
 {
-    if (p.parts != 1) g_counters.push_back(p.counters);
+    CHECK((p.parts != 1) == (p.n_counters != 0));
+    if (p.parts != 1) g_counters.push_back({p.counters, p.counters_next, p.n_counters});
     return hipSuccess;
 }
 hipError_t tetri_decode_static_memory(DecodeStatic *out)
 {
-    *out = {g_static_scratch, g_static_counters};
+    *out = {g_static_scratch, g_static_counters, &g_static_turn};
     return hipSuccess;
 }
 hipError_t tetri_launch_kv_transfer(const tetri_ctx *, const TransferParams &, int32_t, int32_t, bool, hipStream_t) { return hipSuccess; }
@@ -128,9 +135,9 @@ void static_decode_counters()
     tetri_ctx *h = handle(2, 2, 64);
     tetri_set_option(h, "decode_parts", 5);
     decode(h, false);
-    CHECK(g_counters.size() == 1 && in_handle_memory(g_counters[0]));
+    CHECK(g_counters.size() == 1 && in_handle_memory(g_counters[0].use));
     decode(h, true);
-    CHECK(g_counters.size() == 2 && !in_handle_memory(g_counters[1]));
+    CHECK(g_counters.size() == 2 && !in_handle_memory(g_counters[1].use) && !in_handle_memory(g_counters[1].clear));
     // as many (request, kv head)s as there are counters: a counter each, and not one more
     decode(h, true, kDecodeStaticCounters / 2);
     CHECK(g_counters.size() == 3);
@@ -139,12 +146,60 @@ void static_decode_counters()
     tetri_destroy(h);
 }
 
+// A chunk of one request: with 32 rows the short kernel splits its keys, with 256 the shared-tile kernel divides its stages.
+void prefill(tetri_ctx *h, int32_t rows)
+{
+    const int32_t cu[2] = {0, rows}, ctx[1] = {2000};
+    const int32_t *meta = reinterpret_cast<const int32_t *>(g_any);
+    tetri_set_option(h, "attn_variant", rows == 32 ? 3 : 0);
+    CHECK(tetri_chunk_prefill_planned(h, g_any, g_any, g_any, g_any, meta, meta, meta, 1, 0.1f, 0, 0, 1.f, 1.f, cu, ctx, g_any,
+                                      nullptr) == TETRI_OK);
+}
+
+// Whatever a launch leaves in its counters is zeroed before they are used again, and a launch zeroes neither its own set nor
+// that of the launch before or after it: decode, split short launches and divided ones in any order on one handle, and
+// static decodes of two handles.
+void counters_are_cleared()
+{
+    tetri_ctx *h = handle(8, 2, 128), *other = handle(8, 2, 128);
+    tetri_set_option(h, "decode_parts", 5);
+    tetri_set_option(other, "decode_parts", 5);
+    const char *sequences[] = {"dddddddddd", "ssssssssss", "pppppppppp", "dspdpsddsspdpdssdpppd", "tututtuutuut"};
+    for (const char *seq : sequences) {
+        g_counters.clear();
+        tetri_set_option(h, "stream_wgs", seq[0] == 's' ? 0 : 5);        // (a divided launch, whatever the shape would get)
+        for (const char *c = seq; *c; ++c) {
+            if (*c == 'd') decode(h, false);
+            else if (*c == 's') prefill(h, 32);
+            else if (*c == 'p') prefill(h, 256);
+            else decode(*c == 't' ? h : other, true);
+        }
+        const size_t n = g_counters.size();
+        CHECK(n == std::strlen(seq));
+        for (size_t i = 0; i < n; ++i) {
+            const Counters &x = g_counters[i];
+            CHECK(x.n > 0 && x.clear != nullptr && x.clear != x.use);
+            if (i > 0) CHECK(x.clear != g_counters[i - 1].use && x.use != g_counters[i - 1].use && x.use != g_counters[i - 1].clear);
+            for (size_t j = i + 1; j < n; ++j)
+                if (g_counters[j].use == x.use) {                        // the set's next use: zeroed in between, all of it
+                    bool cleared = false;
+                    for (size_t k = i + 1; k < j; ++k) cleared = cleared || (g_counters[k].clear == x.use && g_counters[k].n == x.n);
+                    CHECK(cleared);
+                    break;
+                }
+        }
+    }
+    tetri_destroy(h);
+    tetri_destroy(other);
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
 {
     const std::string name = argc > 1 ? argv[1] : "";
     if (name == "static_decode_counters") static_decode_counters();
+    else if (name == "counters_are_cleared") counters_are_cleared();
     else return 2;
     std::printf("%s: ok\n", name.c_str());
     return 0;

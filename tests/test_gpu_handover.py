@@ -216,3 +216,38 @@ def test_graph_replays_between_eager_launches(oracle, fp8):
                 launch(tmp)
             torch.cuda.synchronize()
             assert torch.equal(tmp.view(torch.int16), want), (mode_opts, "eager after replay", rep)
+
+
+@pytest.mark.parametrize("how", [("decode_parts", 6), ("decode_ranges", 7)], ids=["parts", "ranges"])
+def test_captured_decode_between_eager_launches(oracle, how):
+    """A captured decode of split requests replayed with eager prefill launches that divide tiles, and eager decodes, on the
+    same handle in between: every result has the bits it has alone, whatever counters the handle has reached."""
+    w, sess, c, (q, k, v), pool, _ref_rows = prefilled(oracle, "captured-decode", 147)
+    h = sess.handle
+    h.tetri_set_option("stream_wgs", 5)
+    h.tetri_set_option(*how)
+    bt = sess.meta[c][2].repeat(3)                             # three requests of different lengths over the same pages
+    ctx = torch.tensor([1000, 31, 517], dtype=torch.int32, device=DEV)
+    decode = lambda out: h.tetri_decode_attn(q[:3], k[:3], v[:3], pool, bt, ctx, 3, 1000, w.scale, out)
+    attn = lambda out: sess.attn(c, q, k, v, pool, w.scale, out)
+    want = torch.zeros_like(q[:3]), torch.zeros_like(q)
+    decode(want[0]), attn(want[1])
+    torch.cuda.synchronize()
+    captured, eager, rows = torch.zeros_like(q[:3]), torch.zeros_like(q[:3]), torch.zeros_like(q)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        decode(captured)
+    for rep in range(10):
+        for t in (captured, eager, rows):
+            t.fill_(7.0)
+        for _ in range(rep % 3):
+            attn(rows)
+        g.replay()
+        attn(rows)
+        for _ in range(rep % 2):
+            decode(eager)
+        torch.cuda.synchronize()
+        assert torch.equal(captured.view(torch.int16), want[0].view(torch.int16)), ("replay", rep)
+        assert torch.equal(rows.view(torch.int16), want[1].view(torch.int16)), ("prefill", rep)
+        if rep % 2:
+            assert torch.equal(eager.view(torch.int16), want[0].view(torch.int16)), ("eager", rep)
