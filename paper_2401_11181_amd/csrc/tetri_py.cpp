@@ -18,6 +18,7 @@
 namespace {
 
 PyObject *s_data_ptr, *s_cuda_stream, *s_value, *s_ctypes, *s_data;     // interned names
+PyObject *g_ndarray;                                                    // numpy.ndarray
 PyObject *g_get_device, *g_get_stream;                                  // torch's current device / raw current stream of a device
 
 struct ConvError {};
@@ -35,6 +36,15 @@ void *address(PyObject *x)
 {
     if (x == Py_None) return nullptr;
     if (PyLong_Check(x)) return (void *)(uintptr_t)number(x);
+    if ((PyObject *)Py_TYPE(x) == g_ndarray) {       // (0.1 us; through its `ctypes` attribute 2 us)
+        Py_buffer view;
+        if (PyObject_GetBuffer(x, &view, PyBUF_SIMPLE) == 0) {
+            void *p = view.buf;
+            PyBuffer_Release(&view);                 // the caller's argument keeps the array alive during the call
+            return p;
+        }
+        PyErr_Clear();                               // (not contiguous)
+    }
     PyObject *r = PyObject_CallMethodNoArgs(x, s_data_ptr);
     if (!r) {
         PyErr_Clear();
@@ -200,5 +210,10 @@ PyMODINIT_FUNC PyInit__native(void)
     s_value = PyUnicode_InternFromString("value");
     s_ctypes = PyUnicode_InternFromString("ctypes");
     s_data = PyUnicode_InternFromString("data");
+    PyObject *numpy = PyImport_ImportModule("numpy");
+    if (!numpy) return nullptr;
+    g_ndarray = PyObject_GetAttrString(numpy, "ndarray");
+    Py_DECREF(numpy);
+    if (!g_ndarray) return nullptr;
     return PyModule_Create(&module);
 }

@@ -147,9 +147,6 @@ class PrefillPipeline:
         self.stage = self.batch.slots
         self.host_plan(0)
         self.layout = [tuple(int(x) for x in row) for row in self.layout_np[:self.n_chunks]]
-        self._plan_args = (self.lens.ctypes.data, len(self.lens), None if self.order is None else self.order.ctypes.data,
-                           len(self.lens) if self.order is None else len(self.order), self.req_bt.ctypes.data,
-                           self.layout_np.ctypes.data, self.n_chunks)
         self.graph = None
         self.use_graph = use_graph
 
@@ -191,6 +188,18 @@ class PrefillPipeline:
         if n != self.n_chunks:
             raise RuntimeError("plan changed between steps")
 
+    @property
+    def _plan_args(self):
+        """A step's arguments of tetri_batch_upload: what lens, order and req_bt hold now (they may be written to or replaced
+        between steps), as arrays that live as long as the tuple."""
+        lens = np.ascontiguousarray(self.lens, dtype=np.int32)
+        order = None if self.order is None else np.ascontiguousarray(self.order, dtype=np.int32)
+        req_bt = np.ascontiguousarray(self.req_bt, dtype=np.int32)
+        if req_bt.ndim != 2 or req_bt.shape[0] < len(lens) or req_bt.shape[1] != self.max_blocks:
+            raise ValueError("req_bt has shape %s: it needs a row of %d pages for each of the %d prompts"
+                             % (req_bt.shape, self.max_blocks, len(lens)))
+        return lens, len(lens), order, len(lens) if order is None else len(order), req_bt, self.layout_np, self.n_chunks
+
     # --- device part of a step ------------------------------------------------------------------
     def _bind_args(self):
         """Marshal the arguments of every launch once (ctypes objects), so that a launch is one foreign call."""
@@ -209,16 +218,15 @@ class PrefillPipeline:
         # the same as arrays of one address per chunk, for the calls that launch many chunks at once
         self._chunk_ptrs = [np.array([t[c].data_ptr() for c in range(self.n_chunks)], dtype=np.uint64) for t in (self.q, self.k, self.v, self.out)]
         q, k, v, o = (a.ctypes.data for a in self._chunk_ptrs)
-        self._layout_ptr = self.layout_np.ctypes.data
         self._batch_args = (q, k, v, self.pool.data_ptr(), o, self.scale)
 
     def launch_attn(self, c, stream=None):
         """One attention launch of chunk c with the metadata currently on the device."""
-        self.batch.launch(self._layout_ptr, c, 1, *self._batch_args, tetri.BATCH_ATTENTION, stream)
+        self.batch.launch(self.layout_np, c, 1, *self._batch_args, tetri.BATCH_ATTENTION, stream)
 
     def launch_fused(self, c, stream=None):
         """Attention and append of chunk c in one launch."""
-        self.batch.launch(self._layout_ptr, c, 1, *self._batch_args, tetri.BATCH_FUSED, stream)
+        self.batch.launch(self.layout_np, c, 1, *self._batch_args, tetri.BATCH_FUSED, stream)
 
     def launch_fused_fp8(self, c, kv_pages_fp8, k_scale, v_scale, append=1, stream=None):
         """Chunk c over a pool of FP8 codes: attention and, with append, the quantising append, in one launch."""
@@ -243,10 +251,10 @@ class PrefillPipeline:
     def _launch_all(self):
         mode = tetri.BATCH_FUSED if self.fused else tetri.BATCH_TWO_LAUNCHES
         if self.export != "chunk":
-            self.batch.launch(self._layout_ptr, 0, self.n_chunks, *self._batch_args, mode, None)
+            self.batch.launch(self.layout_np, 0, self.n_chunks, *self._batch_args, mode, None)
         else:
             for c in range(self.n_chunks):
-                self.batch.launch(self._layout_ptr, c, 1, *self._batch_args, mode, None)
+                self.batch.launch(self.layout_np, c, 1, *self._batch_args, mode, None)
                 # the slice this chunk cached, named by the chunk's own metadata arrays
                 self.chunk_done[c].record()
                 self.side.wait_event(self.chunk_done[c])
