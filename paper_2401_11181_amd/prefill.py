@@ -30,7 +30,8 @@ class ChunkedPrefill:
         max_segs = max([1] + [int(self.offsets[i + 1] - self.offsets[i]) for i in range(self.n_chunks)])
         self.handle = tetri.Tetri(num_q_heads, num_kv_heads, head_dim, chunk_size, num_pages, max_blocks,
                                   max_segs, page_size=page_size)
-        # per-chunk metadata, built on the host by the C library and uploaded once
+        # per-chunk metadata, built on the host by the C library and uploaded once; meta[c] = (cu, ctx_lens, block table,
+        # number of segments) of chunk c is what its launches use (an entry may be replaced)
         self.meta = []
         cus, ctxs, bts = [], [], []
         for c in range(self.n_chunks):
@@ -60,8 +61,9 @@ class ChunkedPrefill:
         # the host's copies: addresses of cu and ctx_lens per chunk (the arrays are kept beside them)
         self._host_arrays = (cus, ctxs)
         self._host_meta = [(cu.ctypes.data, ctx.ctypes.data) for cu, ctx in zip(cus, ctxs)]
-        # ... and the device arrays' addresses
-        self._meta_ptr = [(cu.data_ptr(), ctx.data_ptr(), bt.data_ptr(), S) for cu, ctx, bt, S in self.meta]
+        # ... which stand for the device arrays as long as nobody has changed those
+        self._planned = list(self.meta)
+        self._meta_version = None if self.meta_dev.is_inference() else self.meta_dev._version
 
     def chunk_segments(self, c):
         return [tuple(int(v) for v in s) for s in self.segs[self.offsets[c]:self.offsets[c + 1]]]
@@ -77,16 +79,25 @@ class ChunkedPrefill:
         return rows
 
     def _launch(self, c, q, k_new, v_new, kv_pages, scale, append, fp8, k_scale, v_scale, out, stream):
-        cu, ctx, bt, S = self._meta_ptr[c]
-        host_cu, host_ctx = self._host_meta[c]
-        self.handle.tetri_chunk_prefill_planned(q, k_new, v_new, kv_pages, bt, cu, ctx, S, scale, append, fp8, k_scale, v_scale,
-                                                host_cu, host_ctx, out, stream)
+        meta = self.meta[c]
+        cu, ctx, bt, S = meta
+        if meta is self._planned[c] and (self._meta_version is None or self.meta_dev._version == self._meta_version):
+            host_cu, host_ctx = self._host_meta[c]
+            self.handle.tetri_chunk_prefill_planned(q, k_new, v_new, kv_pages, bt, cu, ctx, S, scale, append, fp8, k_scale, v_scale,
+                                                    host_cu, host_ctx, out, stream)
+        # an entry of `meta` that has been replaced, or written to: the host's copies no longer say what is on the device
+        elif fp8:
+            self.handle.tetri_chunk_prefill_attn_fp8(q, k_new, v_new, kv_pages, bt, cu, ctx, S, scale, k_scale, v_scale, append, out, stream)
+        elif append:
+            self.handle.tetri_chunk_prefill_attn_append(q, k_new, v_new, kv_pages, bt, cu, ctx, S, scale, out, stream)
+        else:
+            self.handle.tetri_chunk_prefill_attn(q, k_new, v_new, kv_pages, bt, cu, ctx, S, scale, out, stream)
 
     def attn(self, c, q, k_new, v_new, kv_pages, scale, out, stream=None):
         self._launch(c, q, k_new, v_new, kv_pages, scale, 0, 0, 1.0, 1.0, out, stream)
 
     def append(self, c, k_new, v_new, kv_pages, stream=None):
-        cu, ctx, bt, S = self._meta_ptr[c]
+        cu, ctx, bt, S = self.meta[c]
         self.handle.tetri_kv_append(k_new, v_new, kv_pages, bt, cu, ctx, S, stream)
 
     def attn_append(self, c, q, k_new, v_new, kv_pages, scale, out, stream=None):

@@ -1,5 +1,6 @@
-"""The host side of prefill.py without a GPU: a step plans from what the pipeline's attributes hold at that moment.  The
-handle and the staging ring are stand-ins; the plan is made by the C library from the arguments they are given."""
+"""The host side of prefill.py without a GPU: a step plans from what the pipeline's attributes hold at that moment, and a
+chunk's launch uses the metadata that `meta` holds at that moment.  The handle and the staging ring are stand-ins; the
+plan is made by the C library from the arguments they are given."""
 import ctypes
 import gc
 
@@ -85,3 +86,27 @@ def test_block_tables_of_another_shape_are_refused(pipe, table):
     pipe.req_bt = table(pipe.req_bt)
     with pytest.raises(ValueError):
         pipe.step()
+
+
+@pytest.mark.parametrize("call, general", [
+    (lambda s: s.attn(1, 0, 0, 0, 0, 0.1, 0), "tetri_chunk_prefill_attn"),
+    (lambda s: s.attn_append(1, 0, 0, 0, 0, 0.1, 0), "tetri_chunk_prefill_attn_append"),
+    (lambda s: s.attn_fp8(1, 0, 0, 0, 0, 0.1, 0.2, 0.3, 1, 0), "tetri_chunk_prefill_attn_fp8"),
+    (lambda s: s.append(1, 0, 0, 0), "tetri_kv_append")], ids=["attn", "attn_append", "attn_fp8", "append"])
+@pytest.mark.parametrize("change", ["nothing", "replaced", "written"])
+def test_launch_uses_the_metadata_of_the_moment(monkeypatch, call, general, change):
+    monkeypatch.setattr(tetri, "Tetri", Recorder)
+    w = synth.small("host-chunk", [70, 33, 150], 64, 4, 4, 64, seed=5)
+    s = prefill.ChunkedPrefill(w.prompt_lens, None, 64, 4, 4, 64, w.num_pages, synth.place_pages(w), device="cpu")
+    if change == "replaced":
+        cu, ctx, bt, S = s.meta[1]
+        s.meta[1] = (cu.clone(), ctx.clone() + 1, bt.clone(), S)
+    elif change == "written":
+        s.meta[1][1].add_(1)
+    call(s)
+    name, args = s.handle.calls[-1]
+    assert name == (general if change != "nothing" or general == "tetri_kv_append" else "tetri_chunk_prefill_planned")
+    cu, ctx, bt, S = s.meta[1]
+    assert any(isinstance(a, int) and a == S for a in args)
+    for t in (cu, ctx, bt):
+        assert any((isinstance(a, torch.Tensor) and a.data_ptr() == t.data_ptr()) or (isinstance(a, int) and a == t.data_ptr()) for a in args)
