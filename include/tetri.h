@@ -254,7 +254,8 @@ TETRI_API tetri_status tetri_chunk_prefill_planned(tetri_ctx *ctx, const void *q
  * A batch belongs to its handle and is used by one thread at a time.
  *   tetri_batch_upload: packs the prompts and writes every chunk's metadata (tetri_plan_metadata: same arguments, same
  *   layout_out) into the next staging buffer and copies it to meta_dev on `stream`.  Waits only if the copy that used
- *   this buffer a whole ring ago is not done yet.  The plan has to have n_chunks chunks (TETRI_ERR_INVALID_ARG if not).
+ *   this buffer a whole ring ago is not done yet.  The plan has to have n_chunks chunks, and the handle's device has to be
+ *   current (TETRI_ERR_INVALID_ARG if not).
  *   tetri_batch_launch: chunks first_chunk .. first_chunk + n - 1 of the plan uploaded last (before the first upload: of
  *   the plan that staging buffer 0 holds and the caller has copied to meta_dev), in order, each as tetri_chunk_prefill_planned
  *   does it: mode 1 with append = 1, mode 2 attention only, mode 0 attention followed by tetri_kv_append.

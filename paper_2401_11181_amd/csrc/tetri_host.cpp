@@ -782,6 +782,9 @@ tetri_status tetri_batch_upload(tetri_batch *b, const int32_t *prompt_lens, int3
     if (!b) return fail(nullptr, TETRI_ERR_INVALID_ARG, "%s: null batch", fn);
     tetri_ctx *h = b->h;
     if (!layout_out || n_chunks < 0) return fail(h, TETRI_ERR_INVALID_ARG, "%s: null layout_out or negative n_chunks", fn);
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess || dev != h->device)
+        return fail(h, TETRI_ERR_INVALID_ARG, "%s: the handle was created on device %d, the current device is %d", fn, h->device, dev);
     hipStream_t hs = static_cast<hipStream_t>(stream);
     hipError_t e = hipSuccess;
     if (b->turn != 0 && hs != b->last && b->cover[b->slot] == tetri_batch::kOpen) e = b->close_group();

@@ -40,6 +40,8 @@ struct Counters {
 };
 std::vector<Counters> g_counters;
 
+int g_uploads = 0;
+
 float g_static_scratch[kDecodeStaticScratchBytes / 4];
 int32_t g_static_counters[kCounterSets * kDecodeStaticCounters];
 std::atomic<uint32_t> g_static_turn;
@@ -108,7 +110,11 @@ hipError_t tetri_decode_static_memory(DecodeStatic *out)
 hipError_t tetri_launch_kv_transfer(const tetri_ctx *, const TransferParams &, int32_t, int32_t, bool, hipStream_t) { return hipSuccess; }
 hipError_t tetri_launch_kv_export_fp8(const tetri_ctx *, const TransferParams &, int32_t, hipStream_t) { return hipSuccess; }
 hipError_t tetri_launch_append(const tetri_ctx *, const AppendParams &, int32_t, hipStream_t) { return hipSuccess; }
-hipError_t tetri_launch_upload(const int32_t *, int32_t *, int64_t, hipStream_t) { return hipSuccess; }
+hipError_t tetri_launch_upload(const int32_t *, int32_t *, int64_t, hipStream_t)
+{
+    ++g_uploads;
+    return hipSuccess;
+}
 
 namespace {
 
@@ -193,6 +199,40 @@ void counters_are_cleared()
     tetri_destroy(other);
 }
 
+// A batch of one prompt, staged in ordinary memory (which the stub takes for pinned).
+struct BatchOfOne {
+    static constexpr int64_t kLen = 1024;
+    tetri_ctx *h = handle(8, 2, 128);
+    int32_t *staging = static_cast<int32_t *>(std::aligned_alloc(256, tetri_batch_slots() * kLen * 4));
+    alignas(16) int32_t dev[4] = {};
+    tetri_batch *b = nullptr;
+    std::vector<int32_t> pages = std::vector<int32_t>(1024);
+    BatchOfOne() { CHECK(tetri_batch_create(h, kLen, staging, dev, &b) == TETRI_OK); }
+    tetri_status upload(hipStream_t stream)
+    {
+        const int32_t len = 100;
+        int32_t layout[4];
+        return tetri_batch_upload(b, &len, 1, nullptr, 1, pages.data(), layout, 1, stream);
+    }
+    ~BatchOfOne()
+    {
+        tetri_batch_destroy(b);
+        tetri_destroy(h);
+        std::free(staging);
+    }
+};
+
+// The upload is a kernel: with another device current it would run there.
+void upload_checks_the_device()
+{
+    BatchOfOne x;
+    CHECK(x.upload(nullptr) == TETRI_OK && g_uploads == 1);
+    g_device = 1;
+    CHECK(x.upload(nullptr) == TETRI_ERR_INVALID_ARG && std::strstr(tetri_last_error(x.h), "device") && g_uploads == 1);
+    g_device = 0;
+    CHECK(x.upload(nullptr) == TETRI_OK && g_uploads == 2);
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
@@ -200,6 +240,7 @@ int main(int argc, char **argv)
     const std::string name = argc > 1 ? argv[1] : "";
     if (name == "static_decode_counters") static_decode_counters();
     else if (name == "counters_are_cleared") counters_are_cleared();
+    else if (name == "upload_checks_the_device") upload_checks_the_device();
     else return 2;
     std::printf("%s: ok\n", name.c_str());
     return 0;
