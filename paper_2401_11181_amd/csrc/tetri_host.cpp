@@ -707,30 +707,17 @@ tetri_status tetri_chunk_prefill_planned(tetri_ctx *h, const void *q, const void
 
 }  // extern "C"
 
-// A ring of pinned staging buffers.  A buffer may be written again when the upload that read it is done.  An event behind
-// every upload would say so, but costs its own packet in the queue (1.3 us of a step of 20): one event covers
-// the uploads of half a ring, because work on a stream is done in order.
+// A ring of pinned staging buffers.  A buffer may be written again when the upload that read it is done: the kernel's own
+// completion signals an event (tetri_launch_upload), in the call that launches it, so that no stream is named again later.
 struct tetri_batch {
-    static constexpr int kSlots = 8, kGroup = kSlots / 2;
+    static constexpr int kSlots = 8;
     tetri_ctx *h = nullptr;
     int32_t *host = nullptr, *dev = nullptr;
     int64_t len = 0;                  // int32 per buffer, a multiple of 4
-    hipEvent_t ev[kSlots] = {};
-    int cover[kSlots];                // the event behind a buffer's last upload; -1: none was made, kOpen: not recorded yet
-    static constexpr int kOpen = -2;
+    hipEvent_t done[kSlots] = {};     // the buffer's last upload
+    bool pending[kSlots] = {};        // ... has not been waited for
     uint64_t turn = 0;
     int slot = 0;                     // the buffer of the last upload
-    hipStream_t last = nullptr;       // ... and its stream
-
-    hipError_t close_group()          // an event on the last stream covers every upload that has none yet
-    {
-        hipError_t e = ev[slot] ? hipSuccess : hipEventCreateWithFlags(&ev[slot], hipEventDisableTiming);
-        if (e == hipSuccess) e = hipEventRecord(ev[slot], last);
-        if (e != hipSuccess) return e;
-        for (int &c : cover)
-            if (c == kOpen) c = slot;
-        return hipSuccess;
-    }
 };
 
 extern "C" {
@@ -741,12 +728,10 @@ void tetri_batch_destroy(tetri_batch *b)
 {
     if (!b) return;
     // the caller may free the staging buffers next: no upload reads them any more
-    if (b->turn != 0 && b->cover[b->slot] == tetri_batch::kOpen) (void)b->close_group();
-    for (int i = 0; i < tetri_batch::kSlots; ++i)
-        if (b->ev[i]) {
-            (void)hipEventSynchronize(b->ev[i]);
-            (void)hipEventDestroy(b->ev[i]);
-        }
+    for (int i = 0; i < tetri_batch::kSlots; ++i) {
+        if (b->pending[i]) (void)hipEventSynchronize(b->done[i]);
+        if (b->done[i]) (void)hipEventDestroy(b->done[i]);
+    }
     delete b;
 }
 
@@ -770,7 +755,11 @@ tetri_status tetri_batch_create(tetri_ctx *h, int64_t meta_len, int32_t *staging
     tetri_batch *b = new (std::nothrow) tetri_batch;
     if (!b) return fail(h, TETRI_ERR_NOMEM, "%s: out of host memory", fn);
     b->h = h; b->len = meta_len; b->host = staging; b->dev = meta_dev;
-    for (int &c : b->cover) c = -1;
+    for (hipEvent_t &ev : b->done)
+        if (hipError_t e = hipEventCreateWithFlags(&ev, hipEventDisableTiming)) {
+            tetri_batch_destroy(b);
+            return fail(h, TETRI_ERR_HIP, "%s: %s", fn, hipGetErrorString(e));
+        }
     *out = b;
     return TETRI_OK;
 }
@@ -786,12 +775,11 @@ tetri_status tetri_batch_upload(tetri_batch *b, const int32_t *prompt_lens, int3
     if (hipGetDevice(&dev) != hipSuccess || dev != h->device)
         return fail(h, TETRI_ERR_INVALID_ARG, "%s: the handle was created on device %d, the current device is %d", fn, h->device, dev);
     hipStream_t hs = static_cast<hipStream_t>(stream);
-    hipError_t e = hipSuccess;
-    if (b->turn != 0 && hs != b->last && b->cover[b->slot] == tetri_batch::kOpen) e = b->close_group();
     const int slot = (int)(b->turn % tetri_batch::kSlots);
-    if (e == hipSuccess && b->cover[slot] >= 0 && hipEventQuery(b->ev[b->cover[slot]]) == hipErrorNotReady)
-        e = hipEventSynchronize(b->ev[b->cover[slot]]);
+    hipError_t e = hipSuccess;
+    if (b->pending[slot] && hipEventQuery(b->done[slot]) == hipErrorNotReady) e = hipEventSynchronize(b->done[slot]);
     if (e != hipSuccess) return fail(h, TETRI_ERR_HIP, "%s: %s", fn, hipGetErrorString(e));
+    b->pending[slot] = false;
     int32_t *host = b->host + (size_t)slot * b->len;
     int64_t len = 0;
     const int32_t got = tetri_plan_metadata(prompt_lens, n_prompts, order, n_order, h->cfg.chunk_size, req_block_tables,
@@ -799,15 +787,14 @@ tetri_status tetri_batch_upload(tetri_batch *b, const int32_t *prompt_lens, int3
     if (got < 0) return fail(h, (tetri_status)got, "%s: %s", fn, tetri_thread_error());
     if (got != n_chunks) return fail(h, TETRI_ERR_INVALID_ARG, "%s: the plan has %d chunks, expected %d", fn, got, n_chunks);
     if (len > 0) {
-        e = tetri_launch_upload(host, b->dev, len, hs);
+        // (captured into a graph, the upload runs in replays, of which no event tells)
+        const bool capturing = stream_captures(hs);
+        e = tetri_launch_upload(host, b->dev, len, hs, capturing ? nullptr : b->done[slot]);
         if (e != hipSuccess) return fail(h, TETRI_ERR_HIP, "%s: launch failed: %s", fn, hipGetErrorString(e));
+        b->pending[slot] = !capturing;
     }
     b->slot = slot;
-    b->last = hs;
-    b->cover[slot] = tetri_batch::kOpen;
     ++b->turn;
-    if (b->turn % tetri_batch::kGroup == 0 && (e = b->close_group()) != hipSuccess)
-        return fail(h, TETRI_ERR_HIP, "%s: %s", fn, hipGetErrorString(e));
     return TETRI_OK;
 }
 

@@ -169,5 +169,6 @@ hipError_t tetri_launch_decode(const tetri_ctx *h, const DecodeParams &p, hipStr
 hipError_t tetri_decode_static_memory(DecodeStatic *out);
 hipError_t tetri_launch_append(const tetri_ctx *h, const AppendParams &p, int32_t chunk_rows, hipStream_t stream);
 
-// Copies len int32 (rounded up to a multiple of 4) from pinned host memory to the device, both 16-byte aligned.
-hipError_t tetri_launch_upload(const int32_t *pinned, int32_t *dev, int64_t len, hipStream_t stream);
+// Copies len int32 (rounded up to a multiple of 4) from pinned host memory to the device, both 16-byte aligned; `done` (null:
+// none) is signalled when that has ended.
+hipError_t tetri_launch_upload(const int32_t *pinned, int32_t *dev, int64_t len, hipStream_t stream, hipEvent_t done);

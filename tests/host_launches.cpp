@@ -40,7 +40,14 @@ struct Counters {
 };
 std::vector<Counters> g_counters;
 
-int g_uploads = 0;
+struct Event { bool pending = false; };       // pending: work in front of it that nobody has waited for
+Event &event(hipEvent_t e) { return *reinterpret_cast<Event *>(e); }
+hipStream_t g_destroyed = nullptr;            // a stream that no longer exists
+struct Upload {
+    const int32_t *pinned;
+    hipEvent_t done;
+};
+std::vector<Upload> g_uploads;
 
 float g_static_scratch[kDecodeStaticScratchBytes / 4];
 int32_t g_static_counters[kCounterSets * kDecodeStaticCounters];
@@ -75,13 +82,27 @@ hipError_t hipFree(void *p)
 hipError_t hipMemset(void *p, int v, size_t n) { std::memset(p, v, n); return hipSuccess; }
 hipError_t hipMemcpy(void *d, const void *s, size_t n, hipMemcpyKind) { std::memcpy(d, s, n); return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
-hipError_t hipStreamQuery(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamQuery(hipStream_t s) { CHECK(s != g_destroyed); return hipSuccess; }
 hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus *s) { *s = hipStreamCaptureStatusNone; return hipSuccess; }
-hipError_t hipEventCreateWithFlags(hipEvent_t *, unsigned) { return hipErrorUnknown; }
-hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipErrorUnknown; }
-hipError_t hipEventQuery(hipEvent_t) { return hipErrorUnknown; }
-hipError_t hipEventSynchronize(hipEvent_t) { return hipErrorUnknown; }
-hipError_t hipEventDestroy(hipEvent_t) { return hipErrorUnknown; }
+hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned)
+{
+    *e = reinterpret_cast<hipEvent_t>(new Event);
+    return hipSuccess;
+}
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t s)
+{
+    CHECK(s != g_destroyed);
+    event(e).pending = true;
+    return hipSuccess;
+}
+hipError_t hipEventQuery(hipEvent_t e) { return event(e).pending ? hipErrorNotReady : hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t e) { event(e).pending = false; return hipSuccess; }
+hipError_t hipEventDestroy(hipEvent_t e)
+{
+    CHECK(!event(e).pending);                 // (somebody has waited for the work in front of it)
+    delete &event(e);
+    return hipSuccess;
+}
 hipError_t hipPointerGetAttributes(hipPointerAttribute_t *a, const void *) { a->type = hipMemoryTypeHost; return hipSuccess; }
 }
 
@@ -110,9 +131,16 @@ hipError_t tetri_decode_static_memory(DecodeStatic *out)
 hipError_t tetri_launch_kv_transfer(const tetri_ctx *, const TransferParams &, int32_t, int32_t, bool, hipStream_t) { return hipSuccess; }
 hipError_t tetri_launch_kv_export_fp8(const tetri_ctx *, const TransferParams &, int32_t, hipStream_t) { return hipSuccess; }
 hipError_t tetri_launch_append(const tetri_ctx *, const AppendParams &, int32_t, hipStream_t) { return hipSuccess; }
-hipError_t tetri_launch_upload(const int32_t *, int32_t *, int64_t, hipStream_t)
+hipError_t tetri_launch_upload(const int32_t *pinned, int32_t *, int64_t, hipStream_t, hipEvent_t done)
 {
-    ++g_uploads;
+    if (done) {
+        // the upload that read this buffer before has been waited for
+        for (const Upload &u : g_uploads) CHECK(u.pinned != pinned || !event(u.done).pending);
+        event(done).pending = true;
+        g_uploads.push_back({pinned, done});
+    } else {
+        g_uploads.push_back({pinned, nullptr});
+    }
     return hipSuccess;
 }
 
@@ -226,11 +254,29 @@ struct BatchOfOne {
 void upload_checks_the_device()
 {
     BatchOfOne x;
-    CHECK(x.upload(nullptr) == TETRI_OK && g_uploads == 1);
+    CHECK(x.upload(nullptr) == TETRI_OK && g_uploads.size() == 1);
     g_device = 1;
-    CHECK(x.upload(nullptr) == TETRI_ERR_INVALID_ARG && std::strstr(tetri_last_error(x.h), "device") && g_uploads == 1);
+    CHECK(x.upload(nullptr) == TETRI_ERR_INVALID_ARG && std::strstr(tetri_last_error(x.h), "device") && g_uploads.size() == 1);
     g_device = 0;
-    CHECK(x.upload(nullptr) == TETRI_OK && g_uploads == 2);
+    CHECK(x.upload(nullptr) == TETRI_OK && g_uploads.size() == 2);
+}
+
+// Every upload leaves an event behind itself in its own call: a staging buffer is waited for before it is written again and
+// before the batch ends, and no stream is named in a later call (its owner may have destroyed it).
+void uploads_name_no_stream_later()
+{
+    for (int rounds : {1, 5, 8, 21}) {
+        g_uploads.clear();
+        g_destroyed = nullptr;
+        BatchOfOne x;
+        for (int i = 0; i < rounds; ++i) {
+            const hipStream_t s = reinterpret_cast<hipStream_t>(uintptr_t(64 + i / 3));
+            CHECK(x.upload(s) == TETRI_OK && g_uploads.size() == size_t(i + 1));
+            CHECK(g_uploads.back().done != nullptr && event(g_uploads.back().done).pending);
+            if (i % 3 == 2) g_destroyed = s;
+        }
+        g_destroyed = reinterpret_cast<hipStream_t>(uintptr_t(64 + (rounds - 1) / 3));
+    }
 }
 
 }  // namespace
@@ -241,6 +287,7 @@ int main(int argc, char **argv)
     if (name == "static_decode_counters") static_decode_counters();
     else if (name == "counters_are_cleared") counters_are_cleared();
     else if (name == "upload_checks_the_device") upload_checks_the_device();
+    else if (name == "uploads_name_no_stream_later") uploads_name_no_stream_later();
     else return 2;
     std::printf("%s: ok\n", name.c_str());
     return 0;

@@ -36,6 +36,37 @@ def test_ring_uploads_the_plan_of_every_step(one_stream):
                 assert np.array_equal(g[at:at + n], meta[at:at + n])
 
 
+def test_ring_waits_for_uploads_that_have_not_run():
+    """More uploads than the ring has buffers while the stream is still busy with other work: a buffer is not written again
+    before its upload has run, so every plan arrives."""
+    w = synth.small("ring-busy", [70, 33, 150], 64, 4, 4, 64, seed=5)
+    pipe = PrefillPipeline(w.prompt_lens, [0, 1, 2], 64, 4, 4, 64, w.num_pages, synth.place_pages(w), w.scale, device=DEV)
+    big = torch.randn(8192, 8192, device=DEV).to(torch.bfloat16)
+    acc = torch.empty_like(big)
+    torch.matmul(big, big, out=acc)
+    st = torch.cuda.Stream(device=DEV)
+    torch.cuda.synchronize()
+    orders, got, want = [[0, 1, 2], [2, 1, 0], [1, 0, 2], [1, 2, 0], [2, 0, 1]], [], []
+    with torch.cuda.stream(st):
+        for _ in range(40):                                 # some ten milliseconds of work ahead of the uploads
+            torch.matmul(big, big, out=acc)
+        for step in range(2 * tetri.lib().tetri_batch_slots() + 3):
+            pipe.order = orders[step % 5]
+            pipe.batch.upload(*pipe._plan_args, st)
+            got.append(pipe.meta_dev.clone())
+            meta, layout = np.zeros(pipe.meta_len, np.int32), np.zeros((pipe.n_chunks, 4), np.int32)
+            tetri.tetri_plan_metadata(pipe.lens, pipe.order, 64, pipe.req_bt, meta, layout)
+            want.append((meta, layout))
+            if step == 0:
+                assert not st.query(), "the stream should still be busy"
+    torch.cuda.synchronize()
+    for g, (meta, layout) in zip(got, want):
+        g = g.cpu().numpy()
+        for o_cu, o_ctx, o_bt, S in layout:
+            for at, n in ((o_cu, S + 1), (o_ctx, S), (o_bt, S * pipe.max_blocks)):
+                assert np.array_equal(g[at:at + n], meta[at:at + n])
+
+
 @pytest.mark.parametrize("cu, ctx", [([0, 40, 40], [0, 0]), ([1, 40, 64], [0, 0]), ([0, 40, 65], [0, 0]), ([0, 40, 64], [0, -1]),
                                      ([0, 40, 64], [0, 100])])
 def test_planned_launch_rejects_host_metadata_that_is_no_chunk(cu, ctx):

@@ -25,7 +25,8 @@ def driver(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("check", ["static_decode_counters", "counters_are_cleared", "upload_checks_the_device"])
+@pytest.mark.parametrize("check", ["static_decode_counters", "counters_are_cleared", "upload_checks_the_device",
+                                   "uploads_name_no_stream_later"])
 def test_host_layer(driver, check):
     res = subprocess.run([driver, check], capture_output=True, text=True, timeout=120)
     assert res.returncode == 0 and check + ": ok" in res.stdout, res.stdout + res.stderr
