@@ -39,6 +39,7 @@ struct Counters {
     int32_t n;
 };
 std::vector<Counters> g_counters;
+std::string g_kernel;                         // the attention kernel launched last
 
 struct Event { bool pending = false; };       // pending: work in front of it that nobody has waited for
 Event &event(hipEvent_t e) { return *reinterpret_cast<Event *>(e); }
@@ -109,11 +110,13 @@ hipError_t hipPointerGetAttributes(hipPointerAttribute_t *a, const void *) { a->
 // ---- the kernel launchers
 hipError_t tetri_launch_attn(const tetri_ctx *, const AttnParams &p, int, bool, hipStream_t)
 {
+    g_kernel = "shared";
     if (p.stream_wgs > 0 || p.helpers > 0) g_counters.push_back({p.counters, p.counters_next, p.n_counters});
     return hipSuccess;
 }
 hipError_t tetri_launch_short(int, bool, const ShortParams &p, int, hipStream_t)
 {
+    g_kernel = "short";
     if (p.splits > 1) g_counters.push_back({p.counters, p.counters_next, p.n_counters});
     return hipSuccess;
 }
@@ -279,6 +282,28 @@ void uploads_name_no_stream_later()
     }
 }
 
+// Which kernel takes a chunk: what its longest row block leaves to one wavefront counts, not the total alone.
+void choice_of_kernel()
+{
+    const tetri_config c = {32, 8, 128, 16, 512, 1024, 2048, 8, TETRI_BF16};
+    tetri_ctx *h = nullptr;
+    CHECK(tetri_create(&c, &h) == TETRI_OK);
+    const int32_t *meta = reinterpret_cast<const int32_t *>(g_any);
+    auto taken = [&](std::vector<int32_t> cu, std::vector<int32_t> ctx, int fp8) {
+        CHECK(tetri_chunk_prefill_planned(h, g_any, g_any, g_any, g_any, meta, meta, meta, (int32_t)ctx.size(), 0.1f, 0, fp8, 1.f, 1.f,
+                                          cu.data(), ctx.data(), g_any, nullptr) == TETRI_OK);
+        return g_kernel;
+    };
+    // 544 workgroups of two wavefronts, the longest block alone: 40 steps, 22, 44, 45
+    CHECK(taken({0, 36, 512}, {1191, 0}, 1) == "shared" && taken({0, 36, 512}, {1191, 0}, 0) == "short");
+    CHECK(taken({0, 36, 512}, {640, 0}, 1) == "short" && taken({0, 36, 512}, {641, 0}, 1) == "shared");
+    CHECK(taken({0, 36, 512}, {1344, 0}, 0) == "short" && taken({0, 36, 512}, {1345, 0}, 0) == "shared");
+    // 512 workgroups: the total counts (32 x (16 x context steps + 136))
+    CHECK(taken({0, 512}, {640, }, 1) == "short" && taken({0, 512}, {673, }, 1) == "shared");
+    CHECK(taken({0, 512}, {7000, }, 0) == "short" && taken({0, 512}, {7300, }, 0) == "shared");
+    tetri_destroy(h);
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
@@ -288,6 +313,7 @@ int main(int argc, char **argv)
     else if (name == "counters_are_cleared") counters_are_cleared();
     else if (name == "upload_checks_the_device") upload_checks_the_device();
     else if (name == "uploads_name_no_stream_later") uploads_name_no_stream_later();
+    else if (name == "choice_of_kernel") choice_of_kernel();
     else return 2;
     std::printf("%s: ok\n", name.c_str());
     return 0;
