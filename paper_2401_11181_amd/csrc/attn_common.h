@@ -78,6 +78,36 @@ __device__ __forceinline__ float half_swap_sum(float x)
     return a + b;
 }
 
+// Parts of the softmax of a wavefront's 32-key step.  Masked scores are infinite; c < 0 where the scale is.
+__device__ __forceinline__ float step_max(const f32x16 &sc, float c)
+{
+    float mx = sc[0] * c;
+#pragma unroll
+    for (int v = 1; v < 16; ++v) mx = fmaxf(mx, sc[v] * c);
+    return half_swap_max(mx);
+}
+// Has a weight of any lane reached 2 (bf16 patterns with the top exponent bit set)?
+__device__ __forceinline__ bool weights_reach_two(const bf16x8 (&pf)[2])
+{
+    const u32x4 a = __builtin_bit_cast(u32x4, pf[0]), b = __builtin_bit_cast(u32x4, pf[1]);
+    const uint32_t any = (a[0] | a[1] | a[2]) | (a[3] | b[0] | b[1]) | (b[2] | b[3]);
+    return __builtin_amdgcn_ballot_w64((any & 0x40004000u) != 0) != 0;
+}
+// Adds the weights, as rounded, to this lane's part of the row sum.
+__device__ __forceinline__ void add_weights(const bf16x8 (&pf)[2], float &lsum)
+{
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const u32x4 a = __builtin_bit_cast(u32x4, pf[j]);
+        float lo = 0.f, hi = 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            lo += __builtin_bit_cast(float, a[i] << 16);
+            hi += __builtin_bit_cast(float, a[i] & 0xffff0000u);
+        }
+        lsum += lo + hi;
+    }
+}
 
 // Direct global -> LDS load of 16 bytes per lane, issued from inline assembly: lane l's 16 bytes
 // land at LDS byte address lds_base + 16*l (lds_base is wave-uniform and goes to M0).  The

@@ -62,8 +62,8 @@ hipError_t tetri_launch_upload(const int32_t *pinned, int32_t *dev, int64_t len,
     const dim3 grid(blocks < 256 ? blocks : 256);
     const uint4 *src = reinterpret_cast<const uint4 *>(pinned);
     uint4 *dst = reinterpret_cast<uint4 *>(dev);
-    // (the event rides on the kernel's own completion signal: 0.3 us of a step of 26; recorded behind the kernel, with a packet of
-    // its own in the queue, 2.1)
+    // (the event rides on the kernel's own completion signal: 0.9 us of a step of 26; recorded behind the kernel, with a packet of
+    // its own in the queue, 2.8)
     if (done) hipExtLaunchKernelGGL(upload_kernel, grid, dim3(256), 0, stream, nullptr, done, 0, src, dst, n);
     else hipLaunchKernelGGL(upload_kernel, grid, dim3(256), 0, stream, src, dst, n);
     return hipGetLastError();

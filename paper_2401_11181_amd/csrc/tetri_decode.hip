@@ -194,7 +194,7 @@ __global__ __launch_bounds__(NW * 64, 2) void decode_attn_kernel(DecodeParams)
             }
         const int src = __builtin_ctzll(__builtin_amdgcn_ballot_w64(found >= 0) | (1ull << 63));
         job.b = __builtin_amdgcn_readlane(found, src);
-        if (job.b < 0) return;                           // cannot happen
+        if (job.b < 0) return;                           // (ctx_lens written to while the launch runs: no address is formed from it)
         job.L = __builtin_amdgcn_readlane(fl, src);
         job.begin = pos - __builtin_amdgcn_readlane(fbase, src);
         job.end = min(job.steps(), job.begin + left);
@@ -350,30 +350,23 @@ __global__ __launch_bounds__(NW * 64, 2) void decode_attn_kernel(DecodeParams)
                 if (key_of(v) > new_row - (FP8 ? 1 : 0)) sc[v] = masked;
         }
         bf16x8 pf[2];
-        auto weights = [&]() {
+        // (a lambda: as a function shared by the kernels it made the short kernel 4 % slower)
+        auto weights = [&]() {                           // rounded to bf16 for the PV product
 #pragma unroll
             for (int v = 0; v < 16; v += 2) {
                 pf[v / 8][v % 8] = (__bf16)__builtin_amdgcn_exp2f(__builtin_fmaf(sc[v], c, -m));
                 pf[v / 8][v % 8 + 1] = (__bf16)__builtin_amdgcn_exp2f(__builtin_fmaf(sc[v + 1], c, -m));
             }
         };
-        auto row_max = [&]() -> float {
-            float mx = sc[0] * c;
-#pragma unroll
-            for (int v = 1; v < 16; ++v) mx = fmaxf(mx, sc[v] * c);
-            return half_swap_max(mx);
-        };
         if (first) {
-            m = fmaxf(m, row_max());                     // (a step without a key, FP8 only, leaves m and the weights 0)
+            m = fmaxf(m, step_max(sc, c));                     // (a step without a key, FP8 only, leaves m and the weights 0)
             first = false;
             weights();
         } else {
-            // m stays as it is unless a weight reaches 2 (bf16 patterns with the top exponent bit set)
+            // m stays as it is unless a weight reaches 2
             weights();
-            const u32x4 a = __builtin_bit_cast(u32x4, pf[0]), b = __builtin_bit_cast(u32x4, pf[1]);
-            const uint32_t any = (a[0] | a[1] | a[2]) | (a[3] | b[0] | b[1]) | (b[2] | b[3]);
-            if (__builtin_amdgcn_ballot_w64((any & 0x40004000u) != 0) != 0) {
-                const float m_new = fmaxf(m, row_max());
+            if (weights_reach_two(pf)) {
+                const float m_new = fmaxf(m, step_max(sc, c));
                 const float alpha = __builtin_amdgcn_exp2f(m - m_new);
                 m = m_new;
                 lsum *= alpha;
@@ -384,17 +377,7 @@ __global__ __launch_bounds__(NW * 64, 2) void decode_attn_kernel(DecodeParams)
                 weights();
             }
         }
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {                    // the row sum is over the rounded weights
-            const u32x4 a = __builtin_bit_cast(u32x4, pf[j]);
-            float lo = 0.f, hi = 0.f;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                lo += __builtin_bit_cast(float, a[i] << 16);
-                hi += __builtin_bit_cast(float, a[i] & 0xffff0000u);
-            }
-            lsum += lo + hi;
-        }
+        add_weights(pf, lsum);
         // V has landed when only what was issued after it is outstanding
         if constexpr (FP8) {
             if (far) wait_vm<3 * NI>();

@@ -24,11 +24,6 @@ using namespace tetri_dev;
 
 typedef __attribute__((address_space(4))) const ShortParams const_params;
 
-template <int D>
-struct TileOffsets {
-    uint32_t k, v;              // per-lane byte offsets of a load instruction's rows inside a (page, head) block
-};
-
 // 32 rows of K or V, as two halves of 16 rows with a scalar base each, into a wavefront's tile (swizzled like
 // everywhere); rows of a half are row_bytes apart.
 template <int D>
@@ -289,30 +284,23 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_short_kernel(ShortParams)
                 if ((v / 4) * 8 + 4 * half + (v % 4) > bound) sc[v] = masked;
         }
         bf16x8 pf[2];
-        auto weights = [&]() {
+        // (a lambda: as a function shared by the kernels it made the short kernel 4 % slower)
+        auto weights = [&]() {                           // rounded to bf16 for the PV product
 #pragma unroll
             for (int v = 0; v < 16; v += 2) {
                 pf[v / 8][v % 8] = (__bf16)__builtin_amdgcn_exp2f(__builtin_fmaf(sc[v], c, -m));
                 pf[v / 8][v % 8 + 1] = (__bf16)__builtin_amdgcn_exp2f(__builtin_fmaf(sc[v + 1], c, -m));
             }
         };
-        auto row_max = [&]() -> float {
-            float mx = sc[0] * c;
-#pragma unroll
-            for (int v = 1; v < 16; ++v) mx = fmaxf(mx, sc[v] * c);
-            return half_swap_max(mx);
-        };
         if (first) {
-            m = fmaxf(m, row_max());
+            m = fmaxf(m, step_max(sc, c));
             first = false;
             weights();
         } else {
-            // m stays as it is unless a weight reaches 2 (bf16 patterns with the top exponent bit set)
+            // m stays as it is unless a weight reaches 2
             weights();
-            const u32x4 a = __builtin_bit_cast(u32x4, pf[0]), b = __builtin_bit_cast(u32x4, pf[1]);
-            const uint32_t any = (a[0] | a[1] | a[2]) | (a[3] | b[0] | b[1]) | (b[2] | b[3]);
-            if (__builtin_amdgcn_ballot_w64((any & 0x40004000u) != 0) != 0) {
-                const float m_new = fmaxf(m, row_max());
+            if (weights_reach_two(pf)) {
+                const float m_new = fmaxf(m, step_max(sc, c));
                 const float alpha = __builtin_amdgcn_exp2f(m - m_new);
                 m = m_new;
                 lsum *= alpha;
@@ -323,17 +311,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_short_kernel(ShortParams)
                 weights();
             }
         }
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {                    // the row sum is over the rounded weights
-            const u32x4 a = __builtin_bit_cast(u32x4, pf[j]);
-            float lo = 0.f, hi = 0.f;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                lo += __builtin_bit_cast(float, a[i] << 16);
-                hi += __builtin_bit_cast(float, a[i] & 0xffff0000u);
-            }
-            lsum += lo + hi;
-        }
+        add_weights(pf, lsum);
         if (!(F8 && ctx)) {
             if (more) wait_vm<NI>();                     // V of this step: behind it only the next step's K
             else wait_vm<0>();
