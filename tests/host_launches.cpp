@@ -39,6 +39,7 @@ struct Counters {
     int32_t n;
 };
 std::vector<Counters> g_counters;
+int g_parts = 0, g_ranges = 0;                // how the last decode was cut
 std::string g_kernel;                         // the attention kernel launched last
 
 struct Event { bool pending = false; };       // pending: work in front of it that nobody has waited for
@@ -123,6 +124,8 @@ hipError_t tetri_launch_short(int, bool, const ShortParams &p, int, hipStream_t)
 hipError_t tetri_launch_decode(const tetri_ctx *, const DecodeParams &p, hipStream_t)
 {
     CHECK((p.parts != 1) == (p.n_counters != 0));
+    g_parts = p.parts;
+    g_ranges = p.ranges;
     if (p.parts != 1) g_counters.push_back({p.counters, p.counters_next, p.n_counters});
     return hipSuccess;
 }
@@ -304,6 +307,32 @@ void choice_of_kernel()
     tetri_destroy(h);
 }
 
+// How the host cuts a decode batch: equal ranges where there is much to read and fewer than two pairs per compute unit
+// (the batches of test_gpu_decode_ranges.py's default rule are among these), equal parts or whole pairs otherwise.
+void decode_division()
+{
+    const tetri_config c = {16, 8, 128, 16, 64, 64, 300, 8, TETRI_BF16};
+    tetri_ctx *h = nullptr;
+    CHECK(tetri_create(&c, &h) == TETRI_OK);
+    const int32_t *meta = reinterpret_cast<const int32_t *>(g_any);
+    auto cut = [&](int requests, int max_ctx, int fp8) {
+        const tetri_status st = fp8 ? tetri_decode_attn_fp8(h, g_any, g_any, g_any, g_any, meta, meta, requests, max_ctx, 0.1f, 1.f, 1.f, 0, g_any, nullptr)
+                                    : tetri_decode_attn(h, g_any, g_any, g_any, g_any, meta, meta, requests, max_ctx, 0.1f, g_any, nullptr);
+        CHECK(st == TETRI_OK);
+    };
+    cut(12, 4700, 0);                             // 96 pairs x 147 steps x 16 KB = 231 MB
+    CHECK(g_ranges == 32 && g_parts == 0);
+    cut(12, 4000, 0);                             // 126 steps: 198 MB
+    CHECK(g_ranges == 0 && g_parts == 5);
+    cut(22, 4700, 1);                             // codes: 176 pairs x 147 x 8 KB = 212 MB
+    CHECK(g_ranges == 32 && g_parts == 0);
+    cut(12, 4700, 1);
+    CHECK(g_ranges == 0 && g_parts == 5);
+    cut(64, 4700, 0);                             // two pairs per compute unit
+    CHECK(g_ranges == 0 && g_parts == 1);
+    tetri_destroy(h);
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
@@ -314,6 +343,7 @@ int main(int argc, char **argv)
     else if (name == "upload_checks_the_device") upload_checks_the_device();
     else if (name == "uploads_name_no_stream_later") uploads_name_no_stream_later();
     else if (name == "choice_of_kernel") choice_of_kernel();
+    else if (name == "decode_division") decode_division();
     else return 2;
     std::printf("%s: ok\n", name.c_str());
     return 0;
