@@ -237,6 +237,9 @@ TETRI_API tetri_status tetri_chunk_prefill_attn_append(tetri_ctx *ctx, const voi
  *   append: 1 = as tetri_chunk_prefill_attn_append, 0 = as tetri_chunk_prefill_attn.
  *   fp8: 1 = kv_pages is a pool of E4M3 codes (tetri_chunk_prefill_attn_fp8 below) under k_scale and v_scale, which are
  *   otherwise ignored.
+ * Such a launch may go to another kernel than the calls without host metadata ("attn_variant" below): the same function to
+ * the same tolerance, not the same bits.  Under graph capture it takes the kernel of those calls (a replay reads cu and
+ * ctx_lens from the device arrays, whatever they hold by then), so a replay gives the bits of those calls.
  * Errors as for those entry points; host arrays that are no chunk of this handle (cu not ascending from 0 to at
  * most chunk_size, a negative context, more tokens than max_blocks_per_seq pages hold): TETRI_ERR_INVALID_ARG.
  */

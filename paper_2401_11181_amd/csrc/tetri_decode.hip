@@ -7,13 +7,15 @@
 // per cached token against 4 * D * g flops).  Design:
 //   * the g query heads that share a kv head are the columns of one matrix product, so K and V are read once for
 //     all of them; a step is 32 keys of one (request, kv head);
-//   * the steps of the whole batch, request after request, are cut into equal ranges, for every kv head the same ones; a
-//     workgroup has one range of one kv head, so that all of them have the same number of steps however the context
-//     lengths fall.  The division is worked out on the device from the context lengths.  (A grid of request x kv head x
-//     parts, all requests cut alike, left a batch of 16 to 8192 tokens waiting for its longest: 4.2 TB/s.)  Neighbouring
-//     workgroups take different kv heads of the same range: what they read at a time lies in the same pages (ranges cut
-//     across the heads instead had 2048 pages in use at once and were 10 % slower);
-//   * the wavefronts of a workgroup take the range's steps in turn, each with K and V tiles of its own; the loads of a
+//   * a batch is cut in one of three ways, which the host chooses (tetri_host.cpp, decode_common): a workgroup per
+//     (request, kv head); every (request, kv head) in equal parts, a workgroup each, where there are few of them and little to
+//     read; or, where there are few and much to read, the steps of the whole batch, request after request, in equal ranges,
+//     for every kv head the same ones: a workgroup has one range of one kv head, so that all of them have the same number
+//     of steps however the context lengths fall.  That division is worked out on the device from the context lengths.
+//     (Equal parts left a batch of 16 to 8192 tokens waiting for its longest: 4.2 TB/s.)  Neighbouring workgroups take
+//     different kv heads of the same range or part: what they read at a time lies in the same pages (ranges cut across the
+//     heads instead had 2048 pages in use at once and were 10 % slower);
+//   * the wavefronts of a workgroup take its steps in turn, each with K and V tiles of its own; the loads of a
 //     wavefront's next step are in flight while it computes, across requests, and no barrier stands between steps.  Eight
 //     wavefronts to a compute unit keep about 100 KB of loads in flight there;
 //   * K and V go straight from global memory into the tiles (16 bytes per lane per instruction, swizzled so that the

@@ -12,8 +12,9 @@
 //     unit has work; the last one to finish merges;
 //   * the wavefront that does the step on the diagonal has the block's new K and V rows in LDS and writes them to their
 //     page slots from there (fused append), so there are no workgroups for that.
-// K and V serve 32 rows per load instead of 128, so long key ranges would be bound by L2: the host chooses
-// (tetri_host.cpp, prefer_short).
+// What bounds it in turn: the chain of steps of the wavefront with the most of them, about 0.9 us a step (FP8 codes 1.7),
+// because a wavefront has one step of loads in flight and the tiles of a step serve 32 rows instead of 128.  Long chains go
+// to the shared-tile kernel: the host chooses (tetri_host.cpp, plan_short).
 // Arithmetic is that of the shared-tile kernel: bf16 operands, fp32 accumulation, weights rounded to bf16 before the PV
 // product and summed as rounded, parts of the keys merged in a fixed order.
 #include "attn_common.h"

@@ -121,7 +121,8 @@ class PrefillPipeline:
     progress variable of each request is the `start` field of its next segment).
     Inputs (per-chunk q, k_new, v_new) and the page pool are resident in HBM before a step.
     With use_graph the launches of a step are replayed from a HIP graph; packing, metadata and the
-    upload still run every step.
+    upload still run every step.  A captured launch does not carry the chunk's segments along, so chunks with little work
+    go to another kernel than without a graph: the same results to the tolerances, not the same bits.
     """
 
     def __init__(self, prompt_lens, order, chunk_size, num_q_heads, num_kv_heads, head_dim, num_pages,
@@ -240,7 +241,8 @@ class PrefillPipeline:
         self.batch.launch(self.layout_np, c, 1, *self._batch_args, tetri.BATCH_FUSED, stream)
 
     def launch_fused_fp8(self, c, kv_pages_fp8, k_scale, v_scale, append=1, stream=None):
-        """Chunk c over a pool of FP8 codes: attention and, with append, the quantising append, in one launch."""
+        """Chunk c over a pool of FP8 codes: attention and, with append, the quantising append, in one launch.  (Through the
+        call without host metadata: always the shared-tile kernel.  ChunkedPrefill.attn_fp8 lets the library choose.)"""
         import ctypes
         h, q, k, v, _pool, bt, cu, ctx, S, scale, o = self._attn_args[c]
         self._check(self._lib.tetri_chunk_prefill_attn_fp8(h, q, k, v, ctypes.c_void_p(kv_pages_fp8.data_ptr()), bt, cu, ctx, S, scale,
