@@ -493,18 +493,21 @@ static bool plan_short(const tetri_ctx *h, const int32_t *cu, const int32_t *ctx
     p.splits = 1;
     if (h->split_keys && 2 * wgs <= cus && wgs <= h->n_counters)
         p.splits = (int32_t)std::max<int64_t>(1, std::min(std::min<int64_t>(cus / wgs, 16), std::min<int64_t>((most + 7) / 8, units_fit)));
-    // Where this kernel is the faster one.  A launch of at most two workgroups per compute unit (FP8 codes, whose conversion
-    // is paid once per row block: of half a workgroup): 0.42-0.95 of the shared-tile kernel's time at up to 45000 steps of
-    // 32 keys x 32 rows, taken up to 120000; FP8 up to 15000 (0.49-0.95; 1.0 at 18000, 1.28 at 45000).  A bigger launch gives a row block
-    // one or two wavefronts, and what it takes is their chain of steps, which the total does not show: with two, at 544
-    // workgroups, a longest block of 40 steps took 27 us (FP8 codes 43) however little the others had, the shared-tile kernel 29
-    // (31).  Up to 22 steps on a wavefront (FP8 11), and 30000 (15000) in all, the choice costs 2 % over 360 such chunks
-    // (40x128, 32/8x128, 16/2x128, chunks of 512 and 1024 rows, 0 to 1500 cached tokens) against the better kernel
-    // each time, and with limits on the total alone 5 %.  head_dim 64: always (1.3 % over 224 chunks of 40x64 and 12/4x64, up to
-    // 24 % on single ones; a limit on the chain gains nothing).
+    // Where this kernel is the faster one (both timed on 650 chunks of 40x128, 32/8x128, 24/8x128, 16x128, 16/2x128 and
+    // 8/2x128 heads, 128 to 1024 rows in 1 to 10 segments, 0 to 30000 cached tokens; times as a part of the shared-tile kernel's):
+    //  - at most a workgroup per compute unit, eight wavefronts to a row block: always (16-bit 0.22-0.83, FP8 codes
+    //    0.28-0.93; the longest were 30000 cached tokens, 120 steps to a wavefront);
+    //  - at most two: up to 65000 steps of 32 keys x 32 rows (0.53 at the smallest, 1.0 there, 1.1 at 130000, 1.2-1.4 at 300000);
+    //    FP8, whose conversion is paid once per row block, up to 20000 (0.97-1.15 there, 1.5 at 130000);
+    //  - more: a row block has one or two wavefronts, and what a launch takes is their chain of steps, which the total does not
+    //    show.  With two, at 544 workgroups, a longest block of 40 steps took 27 us (FP8 43) however little the others
+    //    had, the shared-tile kernel 29 (31).  Up to 22 steps on a wavefront (FP8 11), and 30000 (15000) in all.
+    // The choice costs 0.7 % on average against the better kernel each time.  head_dim 64: always (1.3 % over 224 chunks of 40x64
+    // and 12/4x64, up to 24 % on single ones; a limit on the chain gains nothing).
     const int64_t chain = (most + shape.wavefronts - 1) / shape.wavefronts;
     if (h->cfg.head_dim == 64) shape.preferred = true;
-    else if (wgs <= 2 * cus) shape.preferred = total <= (fp8 && 2 * wgs > cus ? 15000 : 120000);
+    else if (wgs <= cus) shape.preferred = chain <= 128;
+    else if (wgs <= 2 * cus) shape.preferred = total <= (fp8 ? 20000 : 65000);
     else shape.preferred = total <= (fp8 ? 15000 : 30000) && chain <= (fp8 ? 11 : 22);
     return (uint64_t)(wgs * p.splits + p.zero_wgs) * (uint64_t)std::max<int64_t>(Hq, p.splits) < 0x100000000ull;
 }

@@ -288,7 +288,7 @@ void uploads_name_no_stream_later()
 // Which kernel takes a chunk: what its longest row block leaves to one wavefront counts, not the total alone.
 void choice_of_kernel()
 {
-    const tetri_config c = {32, 8, 128, 16, 512, 1024, 2048, 8, TETRI_BF16};
+    const tetri_config c = {32, 8, 128, 16, 512, 4096, 2100, 8, TETRI_BF16};
     tetri_ctx *h = nullptr;
     CHECK(tetri_create(&c, &h) == TETRI_OK);
     const int32_t *meta = reinterpret_cast<const int32_t *>(g_any);
@@ -302,8 +302,10 @@ void choice_of_kernel()
     CHECK(taken({0, 36, 512}, {640, 0}, 1) == "short" && taken({0, 36, 512}, {641, 0}, 1) == "shared");
     CHECK(taken({0, 36, 512}, {1344, 0}, 0) == "short" && taken({0, 36, 512}, {1345, 0}, 0) == "shared");
     // 512 workgroups: the total counts (32 x (16 x context steps + 136))
-    CHECK(taken({0, 512}, {640, }, 1) == "short" && taken({0, 512}, {673, }, 1) == "shared");
-    CHECK(taken({0, 512}, {7000, }, 0) == "short" && taken({0, 512}, {7300, }, 0) == "shared");
+    CHECK(taken({0, 512}, {960}, 1) == "short" && taken({0, 512}, {992}, 1) == "shared");
+    CHECK(taken({0, 512}, {3776}, 0) == "short" && taken({0, 512}, {3808}, 0) == "shared");
+    // 256 workgroups of eight: whatever the total, up to 128 steps on a wavefront
+    CHECK(taken({0, 256}, {32000}, 1) == "short" && taken({0, 256}, {32500}, 0) == "short" && taken({0, 256}, {32513}, 0) == "shared");
     tetri_destroy(h);
 }
 

@@ -6,7 +6,8 @@ import pytest
 import torch
 
 from oracle import tetri_oracle
-from paper_2401_11181_amd import synth
+from oracle import fp8 as ofp8
+from paper_2401_11181_amd import synth, tetri
 import gpu_common as gc
 
 pytestmark = pytest.mark.gpu
@@ -59,3 +60,44 @@ def test_softmax_scales(scale):
     outs, _pool, _sess, _ = gc.gpu_prefill(w, qs, ks, vs, tables, variant=3)
     ref, _, _ = gc.oracle_prefill(tetri_oracle, w, qs, ks, vs, tables)
     gc.compare(outs, ref, label=w.name)
+
+
+@pytest.mark.parametrize("fp8", [0, 1], ids=["16-bit", "fp8"])
+@pytest.mark.parametrize("hq, hkv, rows, ctx", [(8, 2, 33, 20011), (32, 8, 250, 3017), (24, 8, 500, 3003)],
+                         ids=["split", "eight-wavefronts", "four-wavefronts"])
+def test_long_contexts(hq, hkv, rows, ctx, fp8):
+    """Chunks behind long cached contexts that the library's own rule gives to this kernel (but for the codes of the last one),
+    all rows against attention in 64 bits over the same values."""
+    d, mb = 128, -(-(ctx + rows) // 16)
+    g = torch.Generator().manual_seed(751)
+    rnd = lambda *shape: torch.randn(shape, generator=g).to(torch.bfloat16)
+    q, k, v = rnd(rows, hq, d), rnd(rows, hkv, d), rnd(rows, hkv, d)
+    past = rnd(2, hkv, mb * 16, d)
+    ks, vs = (0.0137, 0.0171) if fp8 else (1.0, 1.0)
+    if fp8:
+        codes = np.stack([ofp8.quantize(past[i].float().numpy(), s) for i, s in ((0, ks), (1, vs))])
+        values = np.stack([ofp8.dequantize(codes[i], s) for i, s in ((0, ks), (1, vs))])
+        past, held = torch.from_numpy(values), torch.from_numpy(codes)
+        held[:, :, ctx:] = gc.NAN_CODE
+    else:
+        held = past.clone()
+        held[:, :, ctx:] = float("nan")
+    order = torch.randperm(mb, generator=g)
+    pool = torch.empty((mb, 2, hkv, 16, d), dtype=held.dtype)
+    pool[order] = held.reshape(2, hkv, mb, 16, d).permute(2, 0, 1, 3, 4)
+    cu, cl = np.array([0, rows], np.int32), np.array([ctx], np.int32)
+    h = tetri.Tetri(hq, hkv, d, rows, mb, mb, 1)
+    out = torch.full((rows, hq, d), 7.0, dtype=torch.bfloat16, device=gc.DEV)
+    dev = [t.to(gc.DEV) for t in (q, k, v, pool, order.to(torch.int32), torch.from_numpy(cu), torch.from_numpy(cl))]
+    h.tetri_chunk_prefill_planned(*dev, 1, d ** -0.5, 0, fp8, ks, vs, cu, cl, out)
+    torch.cuda.synchronize()
+    want = torch.empty((rows, hq, d), dtype=torch.float64)
+    for head in range(hq):
+        kh = head // (hq // hkv)
+        keys = torch.cat([past[0, kh, :ctx].double(), k[:, kh].double()])
+        vals = torch.cat([past[1, kh, :ctx].double(), v[:, kh].double()])
+        s = q[:, head].double() @ keys.T * d ** -0.5
+        s.masked_fill_(torch.arange(ctx + rows)[None, :] > torch.arange(rows)[:, None] + ctx, float("-inf"))
+        want[:, head] = s.softmax(dim=1) @ vals
+    gc.compare([out.cpu()], [want.numpy()], label="long context")
+    h.close()
