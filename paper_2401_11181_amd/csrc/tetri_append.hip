@@ -2,6 +2,7 @@
 // TetriInfer Sec. 2.1 (prefill generates the KV cache) and Sec. 3.4 (the cache is paged).
 // Pure 16-byte vector copy, HBM-bound: no arithmetic, bit-exact by construction.
 #include <hip/hip_ext.h>
+#include <string.h>
 
 #include "tetri_internal.h"
 
@@ -53,7 +54,42 @@ __global__ __launch_bounds__(256) void upload_kernel(const uint4 *__restrict__ s
     }
 }
 
+// A small batch's metadata, at most N vectors, in the kernel's own arguments: the launch copies them, so the staging buffer is
+// free again at once and no event has to say so.  Bound by one round trip to the arguments instead of two (the staging
+// buffer behind them): a step of four small chunks 26.7 us through the staging buffer and its event, 24.8 this way.
+template <int N> struct InlineUpload {
+    uint4 *dst;
+    int n;
+    uint4 v[N];
+};
+template <int N> __global__ __launch_bounds__(N < 256 ? N : 256) void upload_inline_kernel(InlineUpload<N>)
+{
+    typedef __attribute__((address_space(4))) const InlineUpload<N> const_args;
+    const const_args *p = (const const_args *)__builtin_amdgcn_kernarg_segment_ptr();
+    const int i = threadIdx.x;
+    if (i < p->n) {
+        const auto *v = (__attribute__((address_space(4))) const uint32_t *)&p->v[i];
+        p->dst[i] = make_uint4(v[0], v[1], v[2], v[3]);
+    }
+}
+
+template <int N> hipError_t launch_inline(const int32_t *host, int32_t *dev, int64_t len, hipStream_t stream)
+{
+    InlineUpload<N> a;
+    a.dst = reinterpret_cast<uint4 *>(dev);
+    a.n = (int)((len + 3) / 4);
+    memcpy(a.v, host, (size_t)a.n * 16);
+    hipLaunchKernelGGL(upload_inline_kernel<N>, dim3(1), dim3(N), 0, stream, a);
+    return hipGetLastError();
+}
+
 }  // namespace
+
+hipError_t tetri_launch_upload_inline(const int32_t *host, int32_t *dev, int64_t len, hipStream_t stream)
+{
+    static_assert(kUploadInline == 4 * 224, "the larger size");
+    return len <= 4 * 64 ? launch_inline<64>(host, dev, len, stream) : launch_inline<224>(host, dev, len, stream);
+}
 
 hipError_t tetri_launch_upload(const int32_t *pinned, int32_t *dev, int64_t len, hipStream_t stream, hipEvent_t done)
 {

@@ -716,8 +716,9 @@ tetri_status tetri_chunk_prefill_planned(tetri_ctx *h, const void *q, const void
 
 }  // extern "C"
 
-// A ring of pinned staging buffers.  A buffer may be written again when the upload that read it is done: the kernel's own
-// completion signals an event (tetri_launch_upload), in the call that launches it, so that no stream is named again later.
+// A ring of pinned staging buffers.  A buffer may be written again when the upload that read it is done: at once where the
+// plan travelled in the kernel's arguments, otherwise the kernel's own completion signals an event (tetri_launch_upload), in
+// the call that launches it, so that no stream is named again later.
 struct tetri_batch {
     static constexpr int kSlots = 8;
     tetri_ctx *h = nullptr;
@@ -796,11 +797,13 @@ tetri_status tetri_batch_upload(tetri_batch *b, const int32_t *prompt_lens, int3
     if (got < 0) return fail(h, (tetri_status)got, "%s: %s", fn, tetri_thread_error());
     if (got != n_chunks) return fail(h, TETRI_ERR_INVALID_ARG, "%s: the plan has %d chunks, expected %d", fn, got, n_chunks);
     if (len > 0) {
-        // (captured into a graph, the upload runs in replays, of which no event tells)
-        const bool capturing = stream_captures(hs);
-        e = tetri_launch_upload(host, b->dev, len, hs, capturing ? nullptr : b->done[slot]);
+        // Small plans travel in the kernel's arguments.  (Captured into a graph, the upload runs in replays: they read the staging
+        // buffer, whatever it holds by then, and no event tells of them.)
+        const bool capturing = stream_captures(hs), inside = len <= kUploadInline && !capturing;
+        e = inside ? tetri_launch_upload_inline(host, b->dev, len, hs)
+                   : tetri_launch_upload(host, b->dev, len, hs, capturing ? nullptr : b->done[slot]);
         if (e != hipSuccess) return fail(h, TETRI_ERR_HIP, "%s: launch failed: %s", fn, hipGetErrorString(e));
-        b->pending[slot] = !capturing;
+        b->pending[slot] = !capturing && !inside;
     }
     b->slot = slot;
     ++b->turn;

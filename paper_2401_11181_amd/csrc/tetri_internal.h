@@ -172,3 +172,6 @@ hipError_t tetri_launch_append(const tetri_ctx *h, const AppendParams &p, int32_
 // Copies len int32 (rounded up to a multiple of 4) from pinned host memory to the device, both 16-byte aligned; `done` (null:
 // none) is signalled when that has ended.
 hipError_t tetri_launch_upload(const int32_t *pinned, int32_t *dev, int64_t len, hipStream_t stream, hipEvent_t done);
+// The same for at most kUploadInline int32, which travel in the kernel's arguments: host memory is read before this returns.
+constexpr int64_t kUploadInline = 896;
+hipError_t tetri_launch_upload_inline(const int32_t *host, int32_t *dev, int64_t len, hipStream_t stream);

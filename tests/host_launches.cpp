@@ -149,14 +149,20 @@ hipError_t tetri_launch_upload(const int32_t *pinned, int32_t *, int64_t, hipStr
     }
     return hipSuccess;
 }
+hipError_t tetri_launch_upload_inline(const int32_t *, int32_t *, int64_t len, hipStream_t)
+{
+    CHECK(len > 0 && len <= kUploadInline);
+    g_uploads.push_back({nullptr, nullptr});
+    return hipSuccess;
+}
 
 namespace {
 
 alignas(16) char g_any[64];                   // stands for every device array: nothing is read
 
-tetri_ctx *handle(int hq, int hkv, int d)
+tetri_ctx *handle(int hq, int hkv, int d, int max_blocks = 256)
 {
-    const tetri_config c = {hq, hkv, d, 16, 256, 1024, 256, 8, TETRI_BF16};
+    const tetri_config c = {hq, hkv, d, 16, 256, 1024, max_blocks, 8, TETRI_BF16};
     tetri_ctx *h = nullptr;
     CHECK(tetri_create(&c, &h) == TETRI_OK);
     return h;
@@ -235,13 +241,18 @@ void counters_are_cleared()
 
 // A batch of one prompt, staged in ordinary memory (which the stub takes for pinned).
 struct BatchOfOne {
-    static constexpr int64_t kLen = 1024;
-    tetri_ctx *h = handle(8, 2, 128);
-    int32_t *staging = static_cast<int32_t *>(std::aligned_alloc(256, tetri_batch_slots() * kLen * 4));
+    tetri_ctx *h;
+    const int64_t len;                        // a plan's int32: the two small arrays and the block table
+    int32_t *staging;
     alignas(16) int32_t dev[4] = {};
     tetri_batch *b = nullptr;
-    std::vector<int32_t> pages = std::vector<int32_t>(1024);
-    BatchOfOne() { CHECK(tetri_batch_create(h, kLen, staging, dev, &b) == TETRI_OK); }
+    std::vector<int32_t> pages;
+    explicit BatchOfOne(int max_blocks)
+        : h(handle(8, 2, 128, max_blocks)), len(8 + max_blocks), staging(static_cast<int32_t *>(std::aligned_alloc(16, tetri_batch_slots() * len * 4))),
+          pages(max_blocks)
+    {
+        CHECK(tetri_batch_create(h, len, staging, dev, &b) == TETRI_OK);
+    }
     tetri_status upload(hipStream_t stream)
     {
         const int32_t len = 100;
@@ -259,7 +270,7 @@ struct BatchOfOne {
 // The upload is a kernel: with another device current it would run there.
 void upload_checks_the_device()
 {
-    BatchOfOne x;
+    BatchOfOne x(256);
     CHECK(x.upload(nullptr) == TETRI_OK && g_uploads.size() == 1);
     g_device = 1;
     CHECK(x.upload(nullptr) == TETRI_ERR_INVALID_ARG && std::strstr(tetri_last_error(x.h), "device") && g_uploads.size() == 1);
@@ -267,14 +278,17 @@ void upload_checks_the_device()
     CHECK(x.upload(nullptr) == TETRI_OK && g_uploads.size() == 2);
 }
 
-// Every upload leaves an event behind itself in its own call: a staging buffer is waited for before it is written again and
-// before the batch ends, and no stream is named in a later call (its owner may have destroyed it).
+// Every upload that reads a staging buffer leaves an event behind itself in its own call: the buffer is waited for before it
+// is written again and before the batch ends, and no stream is named in a later call (its owner may have destroyed it).
+// Plans that fit the kernel's arguments are not read from the staging buffer at all.
 void uploads_name_no_stream_later()
 {
     for (int rounds : {1, 5, 8, 21}) {
         g_uploads.clear();
         g_destroyed = nullptr;
-        BatchOfOne x;
+        BatchOfOne x(kUploadInline - 4), y(kUploadInline - 8);
+        CHECK(y.upload(nullptr) == TETRI_OK && g_uploads.size() == 1 && g_uploads[0].pinned == nullptr);
+        g_uploads.clear();
         for (int i = 0; i < rounds; ++i) {
             const hipStream_t s = reinterpret_cast<hipStream_t>(uintptr_t(64 + i / 3));
             CHECK(x.upload(s) == TETRI_OK && g_uploads.size() == size_t(i + 1));

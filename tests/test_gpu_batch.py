@@ -36,11 +36,15 @@ def test_ring_uploads_the_plan_of_every_step(one_stream):
                 assert np.array_equal(g[at:at + n], meta[at:at + n])
 
 
-def test_ring_waits_for_uploads_that_have_not_run():
+@pytest.mark.parametrize("spare", [0, 300], ids=["in-the-arguments", "staged"])
+def test_ring_waits_for_uploads_that_have_not_run(spare):
     """More uploads than the ring has buffers while the stream is still busy with other work: a buffer is not written again
-    before its upload has run, so every plan arrives."""
+    before its upload has run, so every plan arrives.  (Block tables with room to spare make the plan too large for the
+    upload kernel's arguments.)"""
     w = synth.small("ring-busy", [70, 33, 150], 64, 4, 4, 64, seed=5)
-    pipe = PrefillPipeline(w.prompt_lens, [0, 1, 2], 64, 4, 4, 64, w.num_pages, synth.place_pages(w), w.scale, device=DEV)
+    tables = [[int(p) for p in t] + [0] * spare for t in synth.place_pages(w)]
+    pipe = PrefillPipeline(w.prompt_lens, [0, 1, 2], 64, 4, 4, 64, w.num_pages, tables, w.scale, device=DEV)
+    assert (pipe.meta_len > 896) == (spare > 0)
     big = torch.randn(8192, 8192, device=DEV).to(torch.bfloat16)
     acc = torch.empty_like(big)
     torch.matmul(big, big, out=acc)
@@ -65,6 +69,28 @@ def test_ring_waits_for_uploads_that_have_not_run():
         for o_cu, o_ctx, o_bt, S in layout:
             for at, n in ((o_cu, S + 1), (o_ctx, S), (o_bt, S * pipe.max_blocks)):
                 assert np.array_equal(g[at:at + n], meta[at:at + n])
+
+
+@pytest.mark.parametrize("table", [1, 2, 3, 4, 5, 244, 247, 248, 249, 252, 253, 884, 887, 888, 889, 892, 893, 1500])
+def test_uploads_of_every_length(table):
+    """Plans around the sizes at which the upload changes its form (256 and 896 int32): what arrives is the plan, and nothing
+    behind it is written."""
+    n = min(16 * table, 60)
+    tables = [list(range(table))]
+    pipe = PrefillPipeline([n], None, 64, 4, 4, 64, table, tables, 0.1, device=DEV)
+    pipe.req_bt[0] = np.random.default_rng(table).permutation(table)
+    dev = torch.full((pipe.meta_len + 64,), -5, dtype=torch.int32, device=DEV)
+    batch = tetri.Batch(pipe.handle, pipe.meta_len, dev)
+    for _ in range(3):
+        batch.upload(*pipe._plan_args, None)
+    torch.cuda.synchronize()
+    meta, layout = np.full(pipe.meta_len, -7, np.int32), np.zeros((1, 4), np.int32)
+    tetri.tetri_plan_metadata(pipe.lens, None, 64, pipe.req_bt, meta, layout)
+    got = dev.cpu().numpy()
+    o_cu, o_ctx, o_bt, S = layout[0]
+    for at, ln in ((o_cu, S + 1), (o_ctx, S), (o_bt, S * table)):
+        assert np.array_equal(got[at:at + ln], meta[at:at + ln])
+    assert (got[pipe.meta_len:] == -5).all()
 
 
 @pytest.mark.parametrize("cu, ctx", [([0, 40, 40], [0, 0]), ([1, 40, 64], [0, 0]), ([0, 40, 65], [0, 0]), ([0, 40, 64], [0, -1]),
