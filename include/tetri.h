@@ -438,7 +438,9 @@ TETRI_API tetri_status tetri_validate_chunk(tetri_ctx *ctx, const int32_t *block
  *                       more) and, where it is told the chunk's segments (tetri_chunk_prefill_planned, tetri_batch_launch),
  *                       whether the chunk goes to the kernel for chunks with little work (not once one of the
  *                       split_* options or stream_wgs has been set, and not under graph capture); 1 / 2 = 4- / 8-wavefront
- *                       workgroups; 3 = that kernel wherever its tables hold the chunk;
+ *                       workgroups; 3 = that kernel wherever its tables hold the chunk; 4 / 5 = a division of the
+ *                       launch made on the host, with row tiles of 8 / 4 (head, 32-row block) slots, wherever the call
+ *                       knows the chunk's segments and the tables hold it (head_dim 128);
  *   "split_keys"        1 (default) = a launch with fewer than five row tiles per four compute units divides the key
  *                       ranges of its tiles among more workgroups than it has tiles.  If the tiles and one helper
  *                       workgroup per two tiles fit the compute units, every tile with a long key range hands the

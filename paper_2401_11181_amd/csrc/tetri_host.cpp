@@ -27,14 +27,14 @@ tetri_status fail(tetri_ctx *h, tetri_status st, const char *fmt, ...)
 
 bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
-// Query-head grouping of a workgroup: its 4 row/head slots are
+// Query-head grouping of a workgroup: its 4 (host's division: 8) row/head slots are
 // (hpw heads that share a kv head) x (rb blocks of 32 rows).
-void wave_grouping(int g, int *hpw, int *rb)
+void wave_grouping(int g, int slots, int *hpw, int *rb)
 {
     if (g % 4 == 0) *hpw = 4;
     else if (g % 2 == 0) *hpw = 2;
     else *hpw = 1;
-    *rb = 4 / *hpw;
+    *rb = slots / *hpw;
 }
 
 // Upper bound of the number of row tiles of a chunk: each of the S segments and the padding
@@ -164,7 +164,7 @@ tetri_status tetri_set_option(tetri_ctx *ctx, const char *key, int32_t value)
         return TETRI_OK;
     }
     if (std::strcmp(key, "attn_variant") == 0) {
-        if (value < 0 || value > 3) return fail(ctx, TETRI_ERR_INVALID_ARG, "tetri_set_option: attn_variant=%d unknown", value);
+        if (value < 0 || value > 5) return fail(ctx, TETRI_ERR_INVALID_ARG, "tetri_set_option: attn_variant=%d unknown", value);
         ctx->attn_variant = value;
         return TETRI_OK;
     }
@@ -512,6 +512,145 @@ static bool plan_short(const tetri_ctx *h, const int32_t *cu, const int32_t *ctx
     return (uint64_t)(wgs * p.splits + p.zero_wgs) * (uint64_t)std::max<int64_t>(Hq, p.splits) < 0x100000000ull;
 }
 
+// The division of a launch of the shared-tile kernel over the compute units, for a chunk whose segments the host knows.
+// A job is a stretch of stages (128 keys) of one row tile (8 slots of 32 rows); p says how heads and rows share the slots.
+// The work of a pool (its head groups' tiles) goes to one workgroup per compute unit so that all end together: a tile longer
+// than q stages is cut into pieces of q for a workgroup each, the remainders and the tiles that are shorter are packed, the
+// longest first, into the workgroups that are left; q is the smallest for which they fit.  False if the tables do not hold it.
+static bool plan_tiles(const tetri_ctx *h, const int32_t *cu, const int32_t *ctx_lens, int32_t num_segs, const AttnParams &p, TilePlan &plan)
+{
+    constexpr int kStage = 128;
+    constexpr int kSlack = 1;         // a remainder of this many stages stays with the piece before it
+    constexpr int kMinPiece = 3;      // the shortest pieces a tile is cut into
+    constexpr int kJobCost = 1;       // a workgroup's further jobs: what each costs besides its stages, in stages
+    const int wgs = (std::max(h->num_cus, 8) / 8) << p.span_shift, pools = 8 >> p.span_shift, rows = 32 * p.rb;
+    if (num_segs > kPlanSegs || p.C > 0xffff || wgs > kPlanJobs || p.gpx > 1023) return false;
+    struct Item { int32_t n; uint16_t seg, grp, t0, begin; uint16_t place; uint8_t piece, npieces; };
+    Item tiles[kPlanJobs];
+    int nt = 0;
+    int64_t total = 0;
+    int32_t longest = 0;
+    for (int32_t s = 0; s < num_segs; ++s) {
+        const int32_t n = cu[s + 1] - cu[s], ctx_stages = (ctx_lens[s] + kStage - 1) / kStage;
+        plan.seg[s][0] = cu[s]; plan.seg[s][1] = n; plan.seg[s][2] = ctx_lens[s]; plan.seg[s][3] = 0;
+        for (int32_t t0 = 0; t0 < n; t0 += rows) {
+            const int32_t stages = ctx_stages + (std::min(n, t0 + rows) + kStage - 1) / kStage;
+            if (nt + p.gpx > kPlanJobs || stages > 0xffff) return false;
+            for (int g = 0; g < p.gpx; ++g) tiles[nt++] = {stages, (uint16_t)s, (uint16_t)g, (uint16_t)t0, 0, 0, 0, 1};
+            total += (int64_t)stages * p.gpx;
+            longest = std::max(longest, stages);
+        }
+    }
+    std::sort(tiles, tiles + nt, [](const Item &a, const Item &b) { return a.n > b.n; });
+    const int64_t places_fit = std::min<int64_t>((int64_t)(2 * h->scratch_units), h->n_counters) / (p.hpw * p.rb * pools);
+    for (int32_t q = (int32_t)std::max<int64_t>((total + wgs - 1) / wgs, kMinPiece);; q += std::max(1, q / 64)) {
+        if (!h->split_keys) q = std::max(q, longest);
+        // pieces of q stages, a workgroup each; what remains is packed
+        Item rest[kPlanJobs];
+        int nr = 0, full = 0, places = 0, jobs = 0;
+        bool fits = true;
+        for (int i = 0; i < nt && fits; ++i) {
+            Item it = tiles[i];
+            const int cuts = it.n <= q + kSlack ? 0 : (it.n - kSlack - 1) / q;
+            if (cuts > 0) {
+                if (cuts > 254 || places + cuts + 1 > places_fit || full + cuts > wgs) { fits = false; break; }
+                it.npieces = (uint8_t)(cuts + 1);
+                it.place = (uint16_t)places;
+                places += cuts + 1;
+                for (int c = 0; c < cuts; ++c) {
+                    plan.job[full++] = {(uint16_t)(it.seg | it.grp << 6), it.t0, (uint16_t)(c * q), (uint16_t)((c + 1) * q), it.place, (uint8_t)c, it.npieces, 0, 0};
+                }
+                it.begin = (uint16_t)(cuts * q);
+                it.n -= cuts * q;
+                it.piece = (uint8_t)cuts;
+            }
+            rest[nr++] = it;
+        }
+        if (!fits) continue;
+        // the workgroups that are left: the longest remainder first, to the least loaded one that may take it.  A workgroup does
+        // at most two pieces of shared tiles there, the second as its last job (it can leave one hand-over open).
+        std::sort(rest, rest + nr, [](const Item &a, const Item &b) { return a.n > b.n; });
+        const int left = wgs - full;
+        struct Bin { int32_t load; int16_t first, last, tail; } bins[kPlanJobs];     // tail: the piece that is its last job
+        for (int i = 0; i < left; ++i) {
+            bins[i] = {0, -1, -1, -1};
+            plan.job[full + i] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+        }
+        int16_t link[kPlanJobs];
+        for (int i = 0; i < nr && fits; ++i) {
+            const bool is_piece = rest[i].npieces > 1;
+            Bin *to = nullptr;
+            for (int k = 0; k < left; ++k)
+                if ((to == nullptr || bins[k].load < to->load) && !(is_piece && bins[k].tail >= 0)) to = &bins[k];
+            const bool empty = to != nullptr && to->first < 0 && to->tail < 0;
+            const int32_t load = to == nullptr ? 0 : to->load + rest[i].n + (empty ? 0 : kJobCost);
+            if (to == nullptr || (load > q + kSlack && q < longest)) { fits = false; break; }
+            to->load = load;
+            if (is_piece && to->first >= 0 && rest[to->first].npieces > 1) {
+                to->tail = (int16_t)i;
+            } else if (is_piece) {                      // in front of the whole tiles
+                link[i] = to->first;
+                to->first = (int16_t)i;
+                if (to->last < 0) to->last = (int16_t)i;
+            } else {
+                link[i] = -1;
+                if (to->last >= 0) link[to->last] = (int16_t)i;
+                else to->first = (int16_t)i;
+                to->last = (int16_t)i;
+            }
+        }
+        if (!fits) continue;
+        jobs = wgs;
+        for (int k = 0; k < left; ++k) {
+            if (bins[k].tail >= 0) {
+                link[bins[k].tail] = -1;
+                link[bins[k].last] = bins[k].tail;
+            }
+            int at = full + k;
+            for (int i = bins[k].first; i >= 0; i = link[i]) {
+                const bool more = link[i] >= 0;
+                if (more && jobs >= kPlanJobs) return false;
+                plan.job[at] = {(uint16_t)(rest[i].seg | rest[i].grp << 6), rest[i].t0, rest[i].begin, (uint16_t)(rest[i].begin + rest[i].n), rest[i].place,
+                                rest[i].piece, rest[i].npieces, (uint16_t)(more ? jobs : 0), 0};
+                at = jobs;
+                jobs += (int)more;
+            }
+        }
+        plan.places = places;
+        plan.wgs = wgs;
+        plan.rows = cu[num_segs];
+        plan.pad = 0;
+        return true;
+    }
+}
+
+// The slots (head, 32-row block) of a workgroup for a chunk that goes to the shared-tile kernel on a division of the host's:
+// 8, each a wavefront that does all keys, or 4 with two key parts; 0: the launch divides itself (tetri_attn.hip).  A workgroup of
+// 8 slots stages a key for 256 rows instead of 128 and waits at half as many barriers for the same work (gqa, 16384 rows of
+// 4 x 32 heads at 12000 cached tokens: 3.5 us for 8 blocks per SIMD, with 4 slots 2.1 us for 4); with 4 slots the pieces are half
+// as long, which divides short launches better.  Timed on 120 chunks each of the 16-bit and the FP8 cache (40x128, 32/8, 24/8,
+// 16 and 8/2 heads, 256 to 2048 rows, 0 to 20000 cached tokens): up to 75000 steps of 32 keys x 32 rows 4 slots (0.85 to 1.05 of
+// the time of 8), beyond 8 (0.75 to 1.05 of that of 4).  Chunks of a multi-head model with few steps, evenly spread over their row blocks, stay with
+// the launch that divides itself: its tiles of a head walk the keys side by side (512 rows of 40 heads after 1500 tokens: 39.6 us
+// against 40.9 and 42.2; but 100 rows after 3000 tokens with 412 new ones: 43.6 against 31.2 and 30.2).
+static int planned_slots(const tetri_ctx *h, const int32_t *cu, const int32_t *ctx_lens, int32_t num_segs)
+{
+    if (h->cfg.head_dim != 128) return 0;
+    if (h->attn_variant == 4) return 8;
+    if (h->attn_variant == 5) return 4;
+    if (h->attn_variant != 0 || h->division_set) return 0;
+    int64_t steps = 0, all = 0, most = 0;             // of one head, its row blocks, the longest of them
+    for (int32_t s = 0; s < num_segs; ++s) {
+        const int64_t blocks = (cu[s + 1] - cu[s] + 31) / 32, ctx_steps = (ctx_lens[s] + 31) / 32;
+        steps += blocks * ctx_steps + blocks * (blocks + 1) / 2;
+        all += blocks;
+        most = std::max(most, ctx_steps + blocks);
+    }
+    const int g = h->cfg.num_q_heads / h->cfg.num_kv_heads;
+    if (g % 2 != 0 && steps * h->cfg.num_q_heads < 60000 && most * all <= 2 * steps) return 0;
+    return steps * h->cfg.num_q_heads < 75000 ? 4 : 8;
+}
+
 static tetri_status attn_common(const char *fn, tetri_ctx *h, const void *q, const void *k_new, const void *v_new,
                                 const void *kv_pages, void *kv_pages_w, const int32_t *block_table, const int32_t *cu,
                                 const int32_t *ctx_lens, int32_t num_segs, float scale, void *out, void *stream,
@@ -527,6 +666,7 @@ static tetri_status attn_common(const char *fn, tetri_ctx *h, const void *q, con
     if (fp8 && !(std::isfinite(k_scale) && std::isfinite(v_scale) && k_scale > 0.f && v_scale > 0.f))
         return fail(h, TETRI_ERR_INVALID_ARG, "%s: k_scale and v_scale must be positive and finite", fn);
     AttnParams p;
+    p.plan = nullptr;
     p.k_scale = k_scale; p.v_scale = v_scale;
     p.k_inv = 1.0f / k_scale; p.v_inv = 1.0f / v_scale;
     p.q = static_cast<const uint16_t *>(q);
@@ -572,7 +712,41 @@ static tetri_status attn_common(const char *fn, tetri_ctx *h, const void *q, con
         }
         return TETRI_OK;
     }
-    wave_grouping(p.g, &p.hpw, &p.rb);
+    auto log2i = [](int v) { int s = 0; while ((1 << s) < v) ++s; return s; };
+    // ---- the other chunks whose segments the host knows: the shared-tile kernel on a division made here
+    TilePlan plan;
+    const int slots = host_cu && !stream_captures(hs) ? planned_slots(h, host_cu, host_ctx, num_segs) : 0;
+    if (slots != 0) {
+        wave_grouping(p.g, slots, &p.hpw, &p.rb);
+        p.groups = p.Hq / p.hpw;
+        p.hpw_shift = log2i(p.hpw);
+        p.rb_shift = log2i(p.rb);
+        p.span_shift = p.groups <= 1 ? 3 : (p.groups <= 2 ? 2 : (p.groups <= 4 ? 1 : 0));
+        p.gpx = (p.groups + (8 >> p.span_shift) - 1) / (8 >> p.span_shift);
+        if (plan_tiles(h, host_cu, host_ctx, num_segs, p, plan)) {
+            if (plan.places != 0 && (st = claim_scratch(h, fn, hs, false)) != TETRI_OK) return st;
+            p.plan = &plan;
+            p.gpx_magic = magic((uint32_t)p.gpx);
+            p.kv_magic = magic((uint32_t)(p.g / p.hpw));
+            p.tiles = p.stream_wgs = p.helpers = p.tail_q8 = p.split_min = p.split_bias = 0;
+            p.attn_grid = 8 * ((plan.wgs + (1 << p.span_shift) - 1) >> p.span_shift);
+            p.attn_first = p.attn_grid;
+            p.append_blocks = 0;                    // (the workgroups cache the rows of their tiles)
+            p.scratch = h->scratch;
+            p.n_counters = h->n_counters;
+            const CounterSets cs = counter_sets(h->counters, h->n_counters, h->counter_turn);
+            p.counters = cs.use;
+            p.counters_next = cs.clear;
+            hipError_t e = tetri_launch_attn(h, p, 2, fp8, hs);
+            if (e != hipSuccess) return fail(h, TETRI_ERR_HIP, "%s: launch failed: %s", fn, hipGetErrorString(e));
+            if (plan.places != 0) {
+                ++h->counter_turn;
+                scratch_claimed(h, hs);
+            }
+            return TETRI_OK;
+        }
+    }
+    wave_grouping(p.g, 4, &p.hpw, &p.rb);
     const int groups = p.Hq / p.hpw;
     // Workgroup size of the shared-tile kernel.  A full chunk has at least C / (rows of a tile) tiles per head
     // group; when that alone gives five workgroups per four compute units or more, four-wavefront workgroups (two
@@ -634,7 +808,6 @@ static tetri_status attn_common(const char *fn, tetri_ctx *h, const void *q, con
         append_wgs = idle >= 8 ? (idle < 64 ? idle / 8 * 8 : 64) : 8;
     }
     p.append_blocks = kv_pages_w ? (p.C < append_wgs ? p.C : append_wgs) : 0;
-    auto log2i = [](int v) { int s = 0; while ((1 << s) < v) ++s; return s; };
     p.hpw_shift = log2i(p.hpw);
     p.rb_shift = log2i(p.rb);
     p.groups = groups;

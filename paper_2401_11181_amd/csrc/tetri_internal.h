@@ -54,6 +54,28 @@ struct tetri_ctx {
     DecodeStatic decode_static;         // this device's memory of tetri_decode_attn_static
 };
 
+// The shared-tile kernel on a division made by the host (tetri_planned.hip): the jobs travel in the kernel arguments.  The eight
+// XCDs form pools (one XCD each, or 2, 4 or 8 where there are few head groups); every pool has the same jobs, for its own
+// head groups.
+constexpr int kPlanSegs = 40, kPlanJobs = 160;
+struct PlanJob {
+    uint16_t seg_grp;             // segment | head group within the pool << 6
+    uint16_t t0;                  // first row of the tile in its segment
+    uint16_t begin, end;          // stages of the tile's key range (begin == end: none)
+    uint16_t place;               // where in the pool the partial result of the tile's first piece goes
+    uint8_t piece, npieces;
+    uint16_t next;                // the workgroup's next job (always a later one), 0: none
+    uint16_t pad;
+};
+struct __attribute__((aligned(16))) TilePlan {
+    PlanJob job[kPlanJobs];       // workgroup w of a pool starts with job w
+    int32_t seg[kPlanSegs][4];    // first row, rows, cached tokens of a segment
+    int32_t rows;                 // chunk rows that belong to a request
+    int32_t places;               // partial results of a pool (0: no tile is shared)
+    int32_t wgs;                  // workgroups of a pool
+    int32_t pad;
+};
+
 // Launch parameters of the attention kernels (passed by value).
 struct AttnParams {
     const uint16_t *q, *k_new, *v_new, *pages;   // bf16 bit patterns
@@ -88,6 +110,7 @@ struct AttnParams {
     // FP8 cache (the kernel variant that reads a pool of E4M3 codes): cached K / V = value(code) * scale
     float k_scale, v_scale;
     float k_inv, v_inv;   // fl32(1 / scale): the fused append quantises with them
+    const TilePlan *plan; // host memory: the host's division of the launch (null: none)
 };
 
 // Launch parameters of the attention kernel for chunks with little work (tetri_short.hip): the chunk's segments and its
@@ -160,6 +183,7 @@ struct DecodeParams {
 };
 
 hipError_t tetri_launch_attn(const tetri_ctx *h, const AttnParams &p, int key_parts, bool fp8_pool, hipStream_t stream);
+hipError_t tetri_launch_planned(const AttnParams &p, bool fp8_pool, hipStream_t stream);      // (tetri_launch_attn's, for p.plan)
 hipError_t tetri_launch_short(int head_dim, bool fp8_pool, const ShortParams &p, int wavefronts, hipStream_t stream);
 hipError_t tetri_launch_kv_transfer(const tetri_ctx *h, const TransferParams &p, int32_t row_units, int32_t tiles,
                                     bool to_pool, hipStream_t stream);

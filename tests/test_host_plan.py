@@ -1,0 +1,34 @@
+"""The division of a shared-tile launch that the host makes for a chunk whose segments it knows: every stage of every row
+tile once, partial results inside the handle's memory and each in a place of its own (tests/host_plan.cpp)."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+HIP_INCLUDE = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "include")
+
+pytestmark = pytest.mark.skipif(shutil.which("g++") is None or not os.path.isdir(os.path.join(HIP_INCLUDE, "hip")),
+                                reason="needs g++ and the HIP headers")
+
+
+@pytest.fixture(scope="module")
+def driver(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("plan") / "host_plan")
+    csrc = os.path.join(ROOT, "paper_2401_11181_amd", "csrc")
+    subprocess.run(["g++", "-std=c++17", "-g", "-O1", "-fsanitize=address,undefined", "-fno-sanitize-recover=all",
+                    "-static-libasan", "-static-libubsan", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-I", HIP_INCLUDE,
+                    "-I", os.path.join(ROOT, "include"), "-I", csrc, os.path.join(ROOT, "tests", "host_plan.cpp"),
+                    os.path.join(csrc, "tetri_host.cpp"), os.path.join(csrc, "tetri_plan.cpp"), "-o", exe], check=True)
+    return exe
+
+
+# head groups per XCD of 5, 1, 2 (some XCDs with fewer), one to four groups (several XCDs to a group), more jobs than the table holds
+@pytest.mark.parametrize("heads, chunk", [((40, 40), 512), ((40, 40), 2048), ((32, 8), 2048), ((24, 8), 500), ((12, 12), 1000),
+                                          ((8, 2), 4096), ((6, 2), 77), ((4, 4), 4096), ((32, 8), 1), ((40, 8), 8192)])
+def test_division(driver, heads, chunk):
+    res = subprocess.run([driver, "17", "300", str(heads[0]), str(heads[1]), str(chunk)], capture_output=True, text=True, timeout=120)
+    assert res.returncode == 0, res.stdout + res.stderr
+    launches, planned = (int(x) for x in res.stdout.split() if x.isdigit())
+    assert launches == 300 and planned >= 100, res.stdout
