@@ -27,8 +27,8 @@ def hipcc():
 
 def build(force=True, verbose=False, extra_flags=()):
     """Compile every source and link libtetri.so.  Returns its path."""
-    objs = []
-    for src in SOURCES:
+    objs, jobs = [], []
+    for src in SOURCES:                              # compiled side by side
         path = os.path.join(CSRC, src)
         obj = os.path.join(CSRC, os.path.splitext(src)[0] + ".o")
         deps = [path] + HEADERS
@@ -37,14 +37,18 @@ def build(force=True, verbose=False, extra_flags=()):
                    "-DTETRI_BUILDING=1"] + HIP_FLAGS + list(extra_flags)
             if verbose:
                 print(" ".join(cmd), flush=True)
-            res = subprocess.run(cmd, capture_output=True, text=True)
-            noise = "is not a recognized feature for this target"
-            err = "\n".join(l for l in res.stderr.splitlines() if noise not in l)
-            if res.returncode != 0:
-                raise RuntimeError("hipcc failed for %s:\n%s" % (src, err))
-            if err.strip() and verbose:
-                print(err, file=sys.stderr)
+            jobs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.PIPE, text=True)))
         objs.append(obj)
+    failed = []
+    for src, job in jobs:
+        noise = "is not a recognized feature for this target"
+        err = "\n".join(l for l in job.communicate()[1].splitlines() if noise not in l)
+        if job.returncode != 0:
+            failed.append("hipcc failed for %s:\n%s" % (src, err))
+        elif err.strip() and verbose:
+            print(err, file=sys.stderr)
+    if failed:
+        raise RuntimeError("\n".join(failed))
     cmd = [hipcc(), "-shared", "-fPIC", "--offload-arch=gfx950", "-o", LIB] + objs
     if verbose:
         print(" ".join(cmd), flush=True)

@@ -91,9 +91,10 @@ tetri_status tetri_create(const tetri_config *c, tetri_ctx **out)
     h->scratch_units = (size_t)h->num_cus * 4;
     h->unit_bytes = (size_t)32 * c->head_dim * 4 + 2 * 32 * 4;
     h->n_counters = (int32_t)(2 * h->scratch_units);
+    const size_t counter_bytes = kCounterSets * (size_t)h->n_counters * sizeof(int32_t) + 256;
     if ((e = hipMalloc(reinterpret_cast<void **>(&h->scratch), 2 * h->scratch_units * h->unit_bytes)) != hipSuccess ||
-        (e = hipMalloc(reinterpret_cast<void **>(&h->counters), kCounterSets * (size_t)h->n_counters * sizeof(int32_t))) != hipSuccess ||
-        (e = hipMemset(h->counters, 0, kCounterSets * (size_t)h->n_counters * sizeof(int32_t))) != hipSuccess) {
+        (e = hipMalloc(reinterpret_cast<void **>(&h->counters), counter_bytes)) != hipSuccess ||
+        (e = hipMemset(h->counters, 0, counter_bytes)) != hipSuccess) {
         tetri_destroy(h);
         return fail(nullptr, TETRI_ERR_HIP, "tetri_create: scratch memory: %s", hipGetErrorString(e));
     }
@@ -449,7 +450,7 @@ static void scratch_claimed(tetri_ctx *h, hipStream_t hs)
 }
 
 struct ShortShape {
-    int wavefronts;
+    int nwl;                          // log2 of a workgroup's wavefronts
     bool preferred;
 };
 
@@ -459,34 +460,37 @@ static bool plan_short(const tetri_ctx *h, const int32_t *cu, const int32_t *ctx
                        ShortShape &shape)
 {
     if (num_segs > kShortSegs) return false;
-    struct Unit { int32_t steps; uint16_t code; } units[kShortUnits];
+    struct Unit { int32_t steps, seg, t0; } units[kShortUnits];
     int n = 0;
     int64_t steps = 0;                // 32-key steps of all row blocks of one head
     int32_t most = 0;
     for (int32_t s = 0; s < num_segs; ++s) {
-        p.cu[s] = cu[s];
-        p.ctx[s] = ctx_lens[s];
         const int32_t blocks = (cu[s + 1] - cu[s] + 31) / 32, ctx_steps = (ctx_lens[s] + 31) / 32;
         if (n + blocks > kShortUnits) return false;
         for (int32_t b = 0; b < blocks; ++b) {
-            units[n++] = {ctx_steps + b + 1, (uint16_t)(s | b << 6)};
+            units[n++] = {ctx_steps + b + 1, s, 32 * b};
             steps += ctx_steps + b + 1;
         }
         most = std::max(most, ctx_steps + blocks);
+        if (ctx_lens[s] >= 1 << 26) return false;
     }
-    p.cu[num_segs] = cu[num_segs];
     std::sort(units, units + n, [](const Unit &a, const Unit &b) { return a.steps > b.steps; });
-    for (int i = 0; i < n; i += 2) p.unit[i / 2] = units[i].code | (i + 1 < n ? (uint32_t)units[i + 1].code << 16 : 0u);
+    for (int i = 0; i < n; ++i) {
+        const int32_t s = units[i].seg;
+        const uint32_t row0 = (uint32_t)cu[s], rows = (uint32_t)(cu[s + 1] - cu[s]);
+        p.unit[i][0] = (uint32_t)s | (uint32_t)units[i].t0 / 32 << 6 | rows << 13 | row0 << 26;
+        p.unit[i][1] = (uint32_t)ctx_lens[s] | (row0 >> 6) << 26;
+    }
     p.units = n;
     p.rows = cu[num_segs];
     const int64_t Hq = h->cfg.num_q_heads, wgs = n * Hq, cus = std::max(h->num_cus, 1);
     const int64_t pad_vectors = (int64_t)(h->cfg.chunk_size - p.rows) * Hq * h->cfg.head_dim / 8;
     p.zero_wgs = (int32_t)std::min<int64_t>(256, (pad_vectors + 1023) / 1024);
-    // A compute unit holds 8 wavefronts of the kernel (head_dim 64: 16).  Few row blocks: as many wavefronts for each as
-    // that leaves room for, up to 8; short key ranges have no steps for more than two.
+    // The measure that the choice below is made by: wavefronts to a row block if all had as many (a compute unit holds 8, at
+    // head_dim 64 16).
     const int64_t room = h->cfg.head_dim == 64 ? 2 * cus : cus, total = steps * Hq;
-    shape.wavefronts = wgs <= room ? 8 : (wgs <= 2 * room ? 4 : (2 * wgs <= 9 * room || total > 16 * wgs ? 2 : 1));
-    if (most <= 4) shape.wavefronts = std::min(shape.wavefronts, 4);
+    int wavefronts = wgs <= room ? 8 : (wgs <= 2 * room ? 4 : (2 * wgs <= 9 * room || total > 16 * wgs ? 2 : 1));
+    if (most <= 4) wavefronts = std::min(wavefronts, 4);
     // Row blocks for at most half of the compute units: the keys of each are split, down to one step per wavefront.
     // (More workgroups than compute units lose more by the partial results' way through memory than they win.)
     const int64_t units_fit = (int64_t)(2 * h->scratch_units) / wgs;
@@ -504,12 +508,42 @@ static bool plan_short(const tetri_ctx *h, const int32_t *cu, const int32_t *ctx
     //    had, the shared-tile kernel 29 (31).  Up to 22 steps on a wavefront (FP8 11), and 30000 (15000) in all.
     // The choice costs 0.7 % on average against the better kernel each time.  head_dim 64: always (1.3 % over 224 chunks of 40x64
     // and 12/4x64, up to 24 % on single ones; a limit on the chain gains nothing).
-    const int64_t chain = (most + shape.wavefronts - 1) / shape.wavefronts;
+    const int64_t chain = (most + wavefronts - 1) / wavefronts;
     if (h->cfg.head_dim == 64) shape.preferred = true;
     else if (wgs <= cus) shape.preferred = chain <= 128;
     else if (wgs <= 2 * cus) shape.preferred = total <= (fp8 ? 20000 : 65000);
     else shape.preferred = total <= (fp8 ? 15000 : 30000) && chain <= (fp8 ? 11 : 22);
-    return (uint64_t)(wgs * p.splits + p.zero_wgs) * (uint64_t)std::max<int64_t>(Hq, p.splits) < 0x100000000ull;
+    // ---- the shape of the launch.  A row block of one head is the work of a team of 1, 2, 4 or 8 wavefronts: as many as leave at
+    // most `cap` steps to each, cap the least for which all wavefronts of the launch are on the chip at once.  (Teams of one
+    // size made the launch as long as its longest row block: 64 packed chunks of 40 heads 18.0 us each, now 15.8.)
+    const int Hkv = h->cfg.num_kv_heads;
+    p.rshift = Hkv % 8 == 0 ? 3 : (Hkv % 4 == 0 ? 2 : (Hkv % 2 == 0 ? 1 : 0));
+    p.hpx = (int32_t)Hq >> p.rshift;
+    p.hkx = Hkv >> p.rshift;
+    // workgroups of 8 wavefronts, one to a compute unit, where there are no more row blocks than that; else of 4
+    const int nwl = p.splits > 1 || (wgs <= room && most > 4) ? 3 : 2;
+    const int64_t slots = 8 * room;
+    // (of a row block of n steps, at most `cap` to a wavefront)
+    auto team = [&](int32_t st, int32_t cap) { int t = 0; while (t < nwl && (cap << t) < st) ++t; return t; };
+    int32_t cap = 1;
+    for (; cap < most; cap += std::max(1, cap / 4)) {
+        int64_t waves = 0;
+        for (int i = 0; i < n; ++i) waves += Hq << team(units[i].steps, cap);
+        if (waves <= slots) break;
+    }
+    p.spread = wgs <= cus;
+    int32_t first_wg = 0;
+    for (int tl = 3, i = 0; tl >= 0; --tl) {
+        const int begin = i;
+        p.first_wg[tl] = first_wg;
+        p.first_unit[tl] = begin;
+        while (i < n && (p.splits > 1 ? nwl : team(units[i].steps, cap)) == tl) ++i;
+        const int64_t per = p.spread ? 1 : ((int64_t)1 << nwl) >> tl;  // teams of a workgroup
+        if (i > begin) first_wg += (int32_t)((((int64_t)(i - begin) * p.hpx + per - 1) / per << p.rshift) * p.splits);
+    }
+    p.attn_wgs = first_wg;
+    shape.nwl = nwl;
+    return (uint64_t)(wgs * p.splits + p.zero_wgs + 8) * (uint64_t)std::max<int64_t>(Hq, p.splits) < 0x100000000ull;   // (the divisions by multiplication)
 }
 
 // The division of a launch of the shared-tile kernel over the compute units, for a chunk whose segments the host knows.
@@ -696,15 +730,16 @@ static tetri_status attn_common(const char *fn, tetri_ctx *h, const void *q, con
         plan_short(h, host_cu, host_ctx, num_segs, fp8, sp, shape) && (shape.preferred || h->attn_variant == 3)) {
         sp.q = p.q; sp.k_new = p.k_new; sp.v_new = p.v_new; sp.pages = p.pages; sp.bt = p.bt; sp.out = p.out; sp.pages_w = p.pages_w;
         sp.C = p.C; sp.Hq = p.Hq; sp.Hkv = p.Hkv; sp.g = p.g; sp.max_blocks = p.max_blocks;
-        sp.hq_magic = magic((uint32_t)p.Hq); sp.hkv_magic = magic((uint32_t)p.Hkv); sp.splits_magic = magic((uint32_t)sp.splits);
+        sp.hpx_magic = magic((uint32_t)sp.hpx); sp.hkx_magic = magic((uint32_t)sp.hkx); sp.splits_magic = magic((uint32_t)sp.splits);
         sp.c = p.c; sp.neg = p.neg; sp.k_scale = p.k_scale; sp.v_scale = p.v_scale; sp.k_inv = p.k_inv; sp.v_inv = p.v_inv;
+        sp.zero = h->counters + kCounterSets * (size_t)h->n_counters;
         sp.scratch = reinterpret_cast<float *>(h->scratch);
         const CounterSets cs = counter_sets(h->counters, h->n_counters, h->counter_turn);
         sp.counters = cs.use;
         sp.counters_next = cs.clear;
         sp.n_counters = h->n_counters;
         if (sp.splits > 1 && (st = claim_scratch(h, fn, hs, false)) != TETRI_OK) return st;
-        hipError_t e = tetri_launch_short(h->cfg.head_dim, fp8, sp, shape.wavefronts, hs);
+        hipError_t e = tetri_launch_short(h->cfg.head_dim, fp8, sp, 1 << shape.nwl, hs);
         if (e != hipSuccess) return fail(h, TETRI_ERR_HIP, "%s: launch failed: %s", fn, hipGetErrorString(e));
         if (sp.splits > 1) {
             ++h->counter_turn;

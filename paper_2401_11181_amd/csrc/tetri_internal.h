@@ -45,7 +45,7 @@ struct tetri_ctx {
     int device = 0;         // the device the handle was created on; its scratch memory lives there
     int num_cus = 0;
     char *scratch = nullptr;        // partial results of tiles shared by workgroups: 2 x scratch_units units
-    int32_t *counters = nullptr;    // sets of n_counters arrival counters
+    int32_t *counters = nullptr;    // sets of n_counters arrival counters, and behind them a row of zeros
     size_t scratch_units = 0, unit_bytes = 0;
     int32_t n_counters = 0;
     uint32_t counter_turn = 0;      // the set of the next launch that uses one
@@ -113,29 +113,41 @@ struct AttnParams {
     const TilePlan *plan; // host memory: the host's division of the launch (null: none)
 };
 
-// Launch parameters of the attention kernel for chunks with little work (tetri_short.hip): the chunk's segments and its
-// row blocks travel in them.
+// Launch parameters of the attention kernel for chunks with little work (tetri_short.hip): the chunk's row blocks travel in them.
 constexpr int kShortSegs = 40, kShortUnits = 128;
 struct ShortParams {
+    // (read together at the kernel's start, 64 bytes)
+    int32_t first_wg[4];          // of the row blocks of 1, 2, 4 and 8 wavefronts: the classes follow each other from 8 down ...
+    int32_t first_unit[4];        // ... and their first row blocks
+    int32_t attn_wgs;             // workgroups but for those that write the padding rows
+    int32_t splits;               // workgroups that share the keys of a row block of one head (> 1: one class, the whole workgroup)
+    uint32_t splits_magic;        // ceil(2^32 / d), 0 for 1
+    int32_t hpx;                  // query heads whose kv head is x modulo 1 << rshift: as many for every x
+    uint32_t hpx_magic;
+    int32_t hkx;                  // ... and such kv heads
+    uint32_t hkx_magic;
+    int32_t rshift;
+    // (64 more)
     const uint16_t *q, *k_new, *v_new, *pages;
     const int32_t *bt;
     uint16_t *out, *pages_w;      // pages_w: pool for the fused append (null: none)
+    const void *zero;             // a row of zeros
+    // (64 more)
     int32_t C, rows;              // chunk rows, and those that belong to a request
     int32_t Hq, Hkv, g, max_blocks;
-    uint32_t hq_magic, hkv_magic; // ceil(2^32 / d), 0 for 1
-    int32_t units;                // row blocks of 32 rows; workgroups = units * Hq * splits + zero_wgs
-    int32_t splits;               // workgroups that share the keys of a row block of one head
-    uint32_t splits_magic;
-    float *scratch;               // splits > 1: partial results, [(unit * Hq + head) * splits + part][32 * D + 64] floats
-    int32_t *counters;            // ... and arrival counters, one per (unit, head), zero before and after the launch
-    int32_t *counters_next;       // the set of a later launch: zeroed by this one
-    int32_t n_counters;           // size of a set
+    int32_t units;                // row blocks of 32 rows
     int32_t zero_wgs;             // workgroups that write the padding rows
     float c;                      // |scale| * log2(e)
     int32_t neg;                  // 1 if scale < 0
     float k_scale, v_scale, k_inv, v_inv;
-    int32_t cu[kShortSegs + 1], ctx[kShortSegs];
-    uint32_t unit[kShortUnits / 2];   // 16 bits per row block, most work first: segment | block of the segment << 6
+    int32_t n_counters;           // size of a set
+    int32_t spread;               // 1: one team to a workgroup
+    float *scratch;               // splits > 1: partial results, [(unit * Hq + head) * splits + part][32 * D + 64] floats
+    int32_t *counters;            // ... and arrival counters, one per (unit, head), zero before and after the launch
+    int32_t *counters_next;       // the set of a later launch: zeroed by this one
+    int64_t pad2;
+    // most work first, 64 bits each: segment (6), row block in it (7), the segment's rows (13) and first row (12), cached tokens (26)
+    uint32_t unit[kShortUnits][2];
 };
 
 struct AppendParams {

@@ -1,22 +1,32 @@
 // Chunked-prefill causal attention for chunks with little work in them, gfx950.
 //
-// The shared-tile kernel (tetri_attn.hip) is made for key ranges of thousands of keys: its workgroups of 128 rows walk
-// stages of 128 keys that all wavefronts enter together, and a launch costs it about 12 us before and after that loop.
+// The shared-tile kernel (tetri_attn.hip, tetri_planned.hip) is made for key ranges of thousands of keys: its workgroups of 128 or 256
+// rows walk stages of 128 keys that all wavefronts enter together, and a launch costs it 9 to 12 us before and after that loop.
 // A chunk of short prompts has a few hundred keys per row and is over before that pays.  What bounds such a launch is
 // the chain of memory round trips and the number of wavefronts at work, not a throughput.  Here
-//   * a workgroup owns 32 rows of one query head and its NW wavefronts share the keys: step s (32 keys) goes to
-//     wavefront s % NW, each with K and V tiles of its own in LDS and no barrier in the loop (as in the decode kernel);
-//   * the host, which knows the segments of the chunk, sends them and the list of row blocks, longest first,
-//     along in the kernel arguments: a workgroup's first memory access is its page ids, the second K and V;
+//   * a row block of 32 rows of one query head is the work of a team of 1, 2, 4 or 8 wavefronts that share its keys: step s (32
+//     keys) goes to wavefront s modulo the team, each with two regions of its own in LDS and no barrier in the loop (as in the
+//     decode kernel).  The host, which knows the segments of the chunk, gives each row block the team that leaves its
+//     wavefronts about as many steps as those of the others and fills the chip's places for wavefronts (plan_short): with one
+//     size of team for all row blocks a launch lasted as long as its longest one (512 rows of 40 heads: 18.3 us, now 14.0; 286 short
+//     prompts of 40 heads in 64 chunks: 1154 us, now 1012);
+//   * the row blocks, longest first, travel in the kernel arguments: a workgroup's first memory access after those is its page
+//     ids, the second Q, K and V;
 //   * few row blocks with long key ranges: the keys of a row block are split over several workgroups, so that every compute
 //     unit has work; the last one to finish merges;
+//   * codes of an FP8 cache stay codes in LDS, a step in the place of one matrix of a 16-bit step, and become bf16 (exactly) where
+//     their fragments are read: two steps in flight and no second trip through registers and LDS (512 rows of 32/8 heads at 1000 cached
+//     tokens: 38 us, now 29.5);
 //   * the wavefront that does the step on the diagonal has the block's new K and V rows in LDS and writes them to their
 //     page slots from there (fused append), so there are no workgroups for that.
-// What bounds it in turn: the chain of steps of the wavefront with the most of them, about 0.9 us a step (FP8 codes 1.7),
-// because a wavefront has one step of loads in flight and the tiles of a step serve 32 rows instead of 128.  Long chains go
-// to the shared-tile kernel: the host chooses (tetri_host.cpp, plan_short).
+// What bounds it in turn: the chain of steps of the wavefront with the most of them, 1.0 to 1.3 us a step, because a wavefront
+// has one step of loads in flight (codes two) and the keys of a step serve 32 rows instead of 256.  Long chains go to the shared-tile
+// kernel: the host chooses.  Of a launch of 64 packed chunks (15.6 us each) 3.5 us lie between two launches, 9 are loads (16 MB that no
+// launch before has touched), 2.3 the merge and the output, 2 to 3 the append.
 // Arithmetic is that of the shared-tile kernel: bf16 operands, fp32 accumulation, weights rounded to bf16 before the PV
 // product and summed as rounded, parts of the keys merged in a fixed order.
+#include <type_traits>
+
 #include "attn_common.h"
 
 namespace {
@@ -62,166 +72,266 @@ __device__ __forceinline__ void load_four_partials(const char *const (&po)[4], c
                  : "v"(po[0]), "v"(po[1]), "v"(po[2]), "v"(po[3]), "v"(ps[0]), "v"(ps[1]), "v"(ps[2]), "v"(ps[3]) : "memory");
 }
 
+// 16 codes per lane and instruction: how the 32 rows of a step of cached keys lie in a region, K codes then V codes (rows of D
+// bytes, 16-byte chunks XOR-ed by the row).
+template <int D> struct CodeTile {
+    static constexpr int CH = D / 16, BYTES = 32 * D, RPI = 1024 / D, NI = BYTES / 1024, PI = 16 / RPI;
+    static __device__ __forceinline__ constexpr int swizzle(int row) { return D == 128 ? row & 7 : (row >> 2) & 3; }
+};
+
 template <int D, bool F8, int NW>
-__global__ __launch_bounds__(NW * 64, 2) void attn_short_kernel(ShortParams)
+__global__ __launch_bounds__(NW * 64, D == 64 ? (F8 ? 3 : 4) : 2) void attn_short_kernel(ShortParams)
 {
+    typedef CodeTile<D> CT;
     constexpr int KSTEPS = D / 16, DBLK = D / 32, NI = D / 16, CH = D / 8, RPI = 64 / CH;
     constexpr int ROW = D * 2, TILE_BYTES = 32 * ROW;
-    constexpr int ESZ = F8 ? 1 : 2;
-    constexpr int LPR = D / 16, RPC = 64 / LPR, NL = 32 / RPC;      // codes: lanes per row, rows per load, loads per tile
+    constexpr int ESZ = F8 ? 1 : 2, NWL = NW == 8 ? 3 : 2;
+    static_assert(2 * CT::NI == NI && 2 * CT::BYTES == TILE_BYTES, "a step of codes takes a region");
     __shared__ __attribute__((aligned(1024))) char smem[NW * 2 * TILE_BYTES];
     __shared__ float stat[NW][2][32];
     __shared__ int last;
     const const_params *p = (const const_params *)__builtin_amdgcn_kernarg_segment_ptr();
 
+    // the launch's shape and pointers, in one round trip: read where they are used, they are four or five
+    typedef __attribute__((ext_vector_type(16))) int i32x16;
+    typedef __attribute__((address_space(4))) const i32x16 const_i32x16;
+    static_assert(offsetof(ShortParams, q) == 64 && offsetof(ShortParams, C) == 128, "read as three vectors");
+    i32x16 hd = ((const const_i32x16 *)p)[0], hp = ((const const_i32x16 *)p)[1], hc = ((const const_i32x16 *)p)[2];
+    asm volatile("" : "+s"(hd), "+s"(hp), "+s"(hc));
+    auto pointer = [&](auto i) __attribute__((always_inline)) -> char * {
+        constexpr int I = decltype(i)::value;
+        return reinterpret_cast<char *>((uintptr_t)((uint64_t)(uint32_t)hp[2 * I] | (uint64_t)(uint32_t)hp[2 * I + 1] << 32));
+    };
+    typedef std::integral_constant<int, 0> R0;
+    typedef std::integral_constant<int, 1> R1;
+    char *const p_q = pointer(R0()), *const p_k_new = pointer(R1()), *const p_v_new = pointer(std::integral_constant<int, 2>()),
+         *const p_pages = pointer(std::integral_constant<int, 3>()), *const p_bt = pointer(std::integral_constant<int, 4>()),
+         *const p_out = pointer(std::integral_constant<int, 5>()), *const p_pages_w = pointer(std::integral_constant<int, 6>()),
+         *const p_zero = pointer(std::integral_constant<int, 7>());
+    const int C = hc[0], rows = hc[1], Hq = hc[2], Hkv = hc[3], heads_per_kv = hc[4], max_blocks = hc[5], units = hc[6];
+    const int attn_wgs = hd[8], splits = hd[9], hpx = hd[11], hkx = hd[13], rshift = hd[15];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int half = lane >> 5, l32 = lane & 31;
-    const int Hq = p->Hq, Hkv = p->Hkv;
-    const int splits = p->splits;
-    const int x0 = magic_div(blockIdx.x, p->splits_magic), part = blockIdx.x - x0 * splits;
-    const int u = magic_div(x0, p->hq_magic), hidx = x0 - u * Hq;
-    const int attn_wgs = p->units * Hq * splits;
-    if ((int)blockIdx.x >= attn_wgs) {
+    const int bid = blockIdx.x;
+    if (bid >= attn_wgs) {
         // ---- padding rows [rows, C) are written as +0, 16 bytes per lane and pass
-        const size_t first = (size_t)p->rows * Hq * CH, n = (size_t)p->C * Hq * CH;
+        const size_t first = (size_t)rows * Hq * CH, n = (size_t)C * Hq * CH;
         const size_t stride = (size_t)(gridDim.x - attn_wgs) * (NW * 64);
-        for (size_t i = first + (size_t)(blockIdx.x - attn_wgs) * (NW * 64) + tid; i < n; i += stride)
-            reinterpret_cast<global_u32x4_w *>((uintptr_t)p->out)[i] = u32x4{0u, 0u, 0u, 0u};
+        for (size_t i = first + (size_t)(bid - attn_wgs) * (NW * 64) + tid; i < n; i += stride)
+            reinterpret_cast<global_u32x4_w *>((uintptr_t)p_out)[i] = u32x4{0u, 0u, 0u, 0u};
         return;
     }
-    // consecutive workgroups take different kv heads: the heads that share one run on one XCD (when Hkv is a multiple of 8)
-    const int hgrp = magic_div(hidx, p->hkv_magic), kh = hidx - hgrp * Hkv, head = kh * p->g + hgrp;
-    const uint32_t code = p->unit[u >> 1] >> ((u & 1) * 16);
-    const int seg = code & 63, t0 = ((code >> 6) & 1023) * 32;
-    const int row0 = p->cu[seg], n_s = p->cu[seg + 1] - row0, L = p->ctx[seg];
+    // ---- the wavefront's row block, head and place in its team.  Row blocks come in classes of 8, 4, 2 or 1 wavefronts (1 <<
+    // tl), the longest first.  The heads whose kv head is x modulo R (R = 1 << rshift) sit in workgroups x modulo R: those
+    // that share a kv head run on one XCD (R = 8).
+    const int tl = bid >= hd[0] ? 0 : (bid >= hd[1] ? 1 : (bid >= hd[2] ? 2 : 3));
+    const int T = 1 << tl;
+    int j = bid - (tl == 0 ? hd[0] : (tl == 1 ? hd[1] : (tl == 2 ? hd[2] : hd[3])));
+    const int u_first = tl == 0 ? hd[4] : (tl == 1 ? hd[5] : (tl == 2 ? hd[6] : hd[7]));
+    const int u_end = tl == 0 ? units : (tl == 1 ? hd[4] : (tl == 2 ? hd[5] : hd[6]));
+    int part = 0;
+    if (splits > 1) {
+        const int q = magic_div(j, hd[10]);
+        part = j - q * splits;
+        j = q;
+    }
+    const int x = j & ((1 << rshift) - 1);
+    const int pack = hc[15] != 0 ? 0 : NWL - tl;             // log2 of a workgroup's teams (few row blocks: one, on a compute unit of its own)
+    const int team_ = wave >> tl, item_ = ((j >> rshift) << pack) + team_, rank = wave & (T - 1), team0 = wave - rank;
+    const int ul = magic_div(item_, hd[12]), hh = item_ - ul * hpx;
+    const int hgrp = magic_div(hh, hd[14]), kh = x + ((hh - hgrp * hkx) << rshift);
+    const bool valid = u_first + ul < u_end && (team_ >> pack) == 0;
+    const int u = valid ? u_first + ul : u_first;
+    const uint32_t unit_lo = p->unit[u][0], unit_hi = p->unit[u][1];
+    const int seg = unit_lo & 63, t0 = ((unit_lo >> 6) & 127) * 32, n_s = (unit_lo >> 13) & 8191, L = unit_hi & 0x3ffffff;
+    const int row0 = (int)(unit_lo >> 26) | (int)(unit_hi >> 26) << 6;
+    const int head = kh * heads_per_kv + hgrp;
     const int ctx_steps = (L + 31) >> 5, steps = ctx_steps + (t0 >> 5) + 1;   // the last one holds the diagonal
 
-    // the steps of this workgroup: all of them, or a part
+    // the steps of this team: all of the row block's, or a part
     const int spp = splits == 1 ? steps : (steps + splits - 1) / splits;
     const int s_begin = part * spp, s_end = min(steps, s_begin + spp);
     auto clear_next = [&]() {
         const int n = p->n_counters;
-        for (int i = blockIdx.x * (NW * 64) + tid; i < n; i += attn_wgs * (NW * 64)) store_global(p->counters_next + i, 0);
+        for (int i = bid * (NW * 64) + tid; i < n; i += attn_wgs * (NW * 64)) store_global(p->counters_next + i, 0);
     };
-    if (s_begin >= s_end) {
-        if (splits > 1) clear_next();
+    if (splits > 1 && s_begin >= s_end) {
+        clear_next();
         return;
     }
 
-    const const_i32 *bt = (const const_i32 *)(uintptr_t)(p->bt + (size_t)seg * p->max_blocks);
-    const int last_entry = p->max_blocks - 1;
+    const const_i32 *bt = (const const_i32 *)(uintptr_t)(p_bt + (size_t)seg * max_blocks * 4);
+    const int last_entry = max_blocks - 1;
     const size_t head_bytes = (size_t)kPage * D * ESZ, page_bytes = 2 * (size_t)Hkv * head_bytes;
-    const char *pool_k = reinterpret_cast<const char *>(p->pages) + (size_t)kh * head_bytes;
+    const char *pool_k = p_pages + (size_t)kh * head_bytes;
     const size_t v_delta = (size_t)Hkv * head_bytes;
     const uint32_t new_row_bytes = Hkv * ROW;
-    const char *new_k = reinterpret_cast<const char *>(p->k_new) + ((size_t)row0 * Hkv + kh) * ROW;
-    const char *new_v = reinterpret_cast<const char *>(p->v_new) + ((size_t)row0 * Hkv + kh) * ROW;
+    const char *new_k = p_k_new + ((size_t)row0 * Hkv + kh) * ROW;
+    const char *new_v = p_v_new + ((size_t)row0 * Hkv + kh) * ROW;
     char *my = smem + wave * (2 * TILE_BYTES);
-    const uint32_t k_lds = lds_address(my);
+    const uint32_t my_lds = lds_address(my);
 
-    int st = s_begin + wave;
-    // pages of the step whose loads come next (entries past the table's end are clamped and never used)
-    int pg0 = bt[min(2 * st, last_entry)], pg1 = bt[min(2 * st + 1, last_entry)];
+    // The wavefront's steps: every T-th of the team's, upwards: codes first (O is scaled once, where the new keys begin).  (From the
+    // diagonal down, with the block's own rows cached in the first step: 226 registers instead of 179, 2 % less for 286 short
+    // prompts of 40 heads, 1 to 7 % more for chunks of 32/8 and 24/8.)
+    int st = s_begin + rank;
+    int left = valid ? (s_end - s_begin - rank + T - 1) >> tl : 0;             // steps the wavefront still has
+    const int parts = min(s_end - s_begin, T);                                  // wavefronts of the team that have any
+    const bool owns_diagonal = s_end == steps && rank == ((steps - 1 - s_begin) & (T - 1));
+    const bool appends = p_pages_w != nullptr && hgrp == 0 && left > 0 && owns_diagonal;
 
+    // ---- The loads are a stream of regions of TILE_BYTES, NI instructions each, that alternate between the wavefront's two: K
+    // and V rows of a 16-bit step, or K and V codes of one step; a region's next load goes out when its rows have been read.
+    // (codes: the first region is chosen so that the last step of codes lies in region 1)
+    const int code_steps = F8 ? min(left, max(0, (ctx_steps - st + T - 1) >> tl)) : 0;
+    int fs = st, fleft = left;                           // the step whose loads go out next, and how many with it are left
+    int pg0 = 0, pg1 = 0;                                // its pages (entries past the table's end are clamped and never used)
+    auto pages_of = [&](int s) __attribute__((always_inline)) {
+        pg0 = bt[min(max(2 * s, 0), last_entry)];
+        pg1 = bt[min(max(2 * s + 1, 0), last_entry)];
+    };
+    pages_of(fs);
     const int r0 = lane / CH;
     const uint32_t k_off = r0 * ROW + (((lane % CH) ^ k_swizzle<D>(r0)) << 4);
     const uint32_t v_off = r0 * ROW + (((lane % CH) ^ v_swizzle<D>(r0)) << 4);
-
-    // K or V of step s: cached keys from the two pages, new keys from k_new / v_new
-    auto issue = [&](int s, bool is_v) {
+    // K or V rows of step fs: cached keys from the two pages, new keys from k_new / v_new
+    auto issue_rows = [&](bool is_v, uint32_t lds) __attribute__((always_inline)) {
+        const int s = fs;
         const bool ctx = s < ctx_steps;
         const int j0 = ctx ? s * 32 : (s - ctx_steps) * 32;
         const int limit = ctx ? L : n_s;
         const char *b0, *b1;
         uint32_t stride;                             // bytes from one row to the next
-        if (ctx) {
+        if (!F8 && ctx) {
             b0 = pool_k + (size_t)pg0 * page_bytes + (is_v ? v_delta : 0);
             b1 = pool_k + (size_t)pg1 * page_bytes + (is_v ? v_delta : 0);
             stride = ROW;
         } else {
-            b0 = (is_v ? new_v : new_k) + (size_t)j0 * new_row_bytes;
+            b0 = (is_v ? new_v + 0 : new_k + 0) + (size_t)j0 * new_row_bytes;
             b1 = b0 + (size_t)16 * new_row_bytes;
             stride = new_row_bytes;
         }
-        const uint32_t lds = k_lds + (is_v ? TILE_BYTES : 0);
-        const uint32_t off = (is_v ? v_off : k_off) + (uint32_t)r0 * (stride - ROW);
+        const uint32_t off = (is_v ? +v_off : +k_off) + (uint32_t)r0 * (stride - ROW);
         const uint32_t step = RPI * (stride - ROW);
         if (j0 + 32 <= limit) {
             issue_half<D>(b0, off, is_v, step, lds);
             issue_half<D>(b1, off, is_v, step, lds + 16 * ROW);
         } else {
             // ragged end of the key range: rows past it come from a row of zeros
-            const char *zero = reinterpret_cast<const char *>(g_zero_row);
+            int ln = lane;
+            if constexpr (D == 64) asm volatile("" : "+v"(ln));       // (worked out here, not kept across the loop)
+            const int rl = ln / CH;
 #pragma unroll
             for (int i = 0; i < NI; ++i) {
                 const int ri = RPI * i;
                 const uint32_t swz = (uint32_t)((is_v ? v_swizzle<D>(ri & 15) : k_swizzle<D>(ri & 15)) * 16);
                 const char *base = ri < 16 ? b0 : b1;
                 const char *src = base + ((off ^ swz) + (uint32_t)(ri & 15) * stride);
-                dma16(j0 + ri + r0 < limit ? src : zero, lds + 1024 * i);
+                dma16(j0 + ri + rl < limit ? src : p_zero, lds + 1024 * i);
             }
         }
     };
-    // a pool of FP8 codes: the codes of a step of cached keys travel through registers
-    [[maybe_unused]] u32x4 rk[NL], rv[NL];
-    [[maybe_unused]] auto load_codes = [&](int s, bool is_v, u32x4 (&raw)[NL]) {
+    // the codes of step fs, K then V
+    [[maybe_unused]] auto issue_codes = [&](uint32_t lds) __attribute__((always_inline)) {
         int ln = lane;
-        asm volatile("" : "+v"(ln));                 // (addresses worked out here, not kept across the loop)
+        asm volatile("" : "+v"(ln));                 // (offsets worked out here, not kept across the loop)
+        const int rc = ln / CT::CH;
+        const uint32_t off = rc * D + (((ln % CT::CH) ^ CT::swizzle(rc)) << 4);
+        const bool full = fs * 32 + 32 <= L;
 #pragma unroll
-        for (int i = 0; i < NL; ++i) {
-            const int r = i * RPC + ln / LPR;
-            const char *src = pool_k + (size_t)((i * RPC) / kPage == 0 ? pg0 : pg1) * page_bytes + (is_v ? v_delta : 0)
-                              + (size_t)(r % kPage) * D + (ln % LPR) * 16;
-            u32x4 v = {0u, 0u, 0u, 0u};
-            if (s * 32 + r < L) v = *reinterpret_cast<global_u32x4 *>((uintptr_t)src);
-            raw[i] = v;
+        for (int mat = 0; mat < 2; ++mat) {
+            const char *b0 = pool_k + (size_t)pg0 * page_bytes + (mat ? v_delta : 0), *b1 = pool_k + (size_t)pg1 * page_bytes + (mat ? v_delta : 0);
+            const uint32_t at = lds + mat * CT::BYTES;
+            if (full) {
+                if constexpr (CT::PI == 2) {
+                    dma16_group2(b0, off, off, at);
+                    dma16_group2(b1, off, off, at + 2048);
+                } else {
+                    dma16(b0 + off, at);
+                    dma16(b1 + off, at + 1024);
+                }
+            } else {
+    #pragma unroll
+                for (int i = 0; i < CT::NI; ++i) {
+                    const int r = CT::RPI * i;
+                    const char *src = (r < 16 ? b0 : b1) + (r & 15) * D + off;
+                    dma16(fs * 32 + r + rc < L ? src : p_zero, at + 1024 * i);
+                }
+            }
         }
     };
-    [[maybe_unused]] auto write_codes = [&](const u32x4 (&raw)[NL], bool is_v) {
-        int ln = lane;
-        asm volatile("" : "+v"(ln));
-#pragma unroll
-        for (int i = 0; i < NL; ++i) {
-            const int r = i * RPC + ln / LPR, c16 = ln % LPR;
-            u32x4 lo, hi;
-            codes_to_bf16(raw[i], lo, hi);
-            const int swz = is_v ? v_swizzle<D>(r) : k_swizzle<D>(r);
-            char *row = my + (is_v ? TILE_BYTES : 0) + r * ROW;
-            *reinterpret_cast<u32x4 *>(row + (((2 * c16) ^ swz) << 4)) = lo;
-            *reinterpret_cast<u32x4 *>(row + (((2 * c16 + 1) ^ swz) << 4)) = hi;
-            __builtin_amdgcn_sched_barrier(0);       // (one load's codes converted at a time: all at once do not fit the registers)
+    // the stream's next load, into `region` (of 16-bit rows: K into 0, V into 1)
+    auto feed = [&](auto reg) __attribute__((always_inline)) {
+        constexpr int region = decltype(reg)::value;
+        if (fleft <= 0) return;
+        const uint32_t lds = my_lds + region * TILE_BYTES;
+        bool step_done;
+        if (F8 && fs < ctx_steps) {
+            issue_codes(lds);
+            step_done = true;
+        } else {
+            issue_rows(region == 1, lds);
+            step_done = region == 1;
+        }
+        if (step_done) {
+            fs += T;
+            --fleft;
+            pages_of(fs);
         }
     };
-    auto request = [&](int s, bool is_v) {
-        if (F8 && s < ctx_steps) load_codes(s, is_v, is_v ? rv : rk);
-        else issue(s, is_v);
-    };
 
-    // Q fragments (B operand of S^T = K Q^T): column l32 is row t0 + l32; rows past the segment's end read its row t0
-    bf16x8 qf[KSTEPS];
-    if (st < s_end) {
-        const global_u32x4 *qp = reinterpret_cast<const global_u32x4 *>((uintptr_t)(p->q + ((size_t)(row0 + t0 + (t0 + l32 < n_s ? l32 : 0)) * Hq + head) * D));
-#pragma unroll
-        for (int s = 0; s < KSTEPS; ++s) qf[s] = __builtin_bit_cast(bf16x8, u32x4(qp[2 * s + half]));
-        request(st, false);
-        request(st, true);
-        pg0 = bt[min(2 * (st + NW), last_entry)];
-        pg1 = bt[min(2 * (st + NW) + 1, last_entry)];
-    }
-    // pages of the block's own rows, for the append: positions L + t0 .. L + t0 + 31 touch up to three
-    const bool appends = p->pages_w != nullptr && hgrp == 0;
-    const int ap = (L + t0) / kPage;
-    const int ap0 = bt[min(ap, last_entry)], ap1 = bt[min(ap + 1, last_entry)], ap2 = bt[min(ap + 2, last_entry)];
-
-    // fragment addresses in the wavefront's tiles: those of step s / block db are the first one's with a constant XOR-ed in
-    // (worked out where they are used: kept, they would take ten registers more)
-    uint32_t kbase0 = l32 * ROW + ((half ^ k_swizzle<D>(l32)) << 4), vbase0;
+    // fragment addresses in the regions: those of step s / block db are the first one's with a constant XOR-ed in (worked out
+    // where they are used: kept, they would take ten registers more).  16-bit rows: accumulator element v is key 8 * (v / 4)
+    // + 4 * half + v % 4 of the step.  Codes: a V fragment holds 8 consecutive keys, so K rows are read in the order that makes
+    // element v key 16 * (v / 8) + 8 * half + v % 8 (bits 2 and 3 of the row index change places).
+    uint32_t kbase0 = l32 * ROW + ((half ^ k_swizzle<D>(l32)) << 4), vbase0, kcode0 = 0, vcode0 = 0;
     {
         const int blk = lane >> 4, i16 = lane & 15;
         const int rv_ = 4 * half + (i16 >> 2), d0 = 16 * (blk & 1) + 4 * (i16 & 3);
         vbase0 = TILE_BYTES + rv_ * ROW + (((d0 >> 3) ^ v_swizzle<D>(rv_)) << 4) + ((d0 & 7) << 1);
+        if constexpr (F8) {
+            const int row = (l32 & 19) | (l32 & 4) << 1 | (l32 & 8) >> 1;
+            kcode0 = row * D + (CT::swizzle(row) << 4) + 8 * half;
+            const int rc = 8 * half + (i16 >> 1);
+            vcode0 = CT::BYTES + rc * D + (((blk & 1) ^ CT::swizzle(rc)) << 4) + 8 * (i16 & 1);
+        }
     }
+    // Q fragments (B operand of S^T = K Q^T): column l32 is row t0 + l32; rows past the segment's end are its row t0.  The rows
+    // come by way of the region that the stream needs second, whole rows of 256 bytes per instruction: as fragments, 32 bytes of
+    // 32 rows each, they took 1.6 us more of a launch with 1920 wavefronts.  (Fragments loaded from inline assembly with the
+    // wait further down are not safe: where the compiler spills, it spills registers that the load has yet to write.)
+    const int n_here = min(32, n_s - t0);
+    bf16x8 qf[KSTEPS];
+    int region = F8 ? (code_steps & 1) : 0;                   // of the step about to run (a 16-bit step: 0, and 1 for V)
+    if (left > 0) {
+        const uint32_t q_row = Hq * ROW, q_lds = my_lds + (region ^ 1) * TILE_BYTES;
+        const char *qb = p_q + ((size_t)(row0 + t0) * Hq + head) * ROW;
+        if (n_here == 32) {
+            const uint32_t off = r0 * q_row + (((lane % CH) ^ k_swizzle<D>(r0)) << 4), step = RPI * q_row - 1024;
+            issue_half<D>(qb, off, false, step, q_lds);
+            issue_half<D>(qb + (size_t)16 * q_row, off, false, step, q_lds + 16 * ROW);
+        } else {
+#pragma unroll
+            for (int i = 0; i < NI; ++i) {
+                const int r = RPI * i + r0;
+                dma16(qb + (size_t)(r < n_here ? r : 0) * q_row + (((lane % CH) ^ k_swizzle<D>(r)) << 4), q_lds + 1024 * i);
+            }
+        }
+        if (F8 && region != 0) feed(R1());
+        else feed(R0());
+        wait_vm<NI>();                                   // behind Q only the first load of the stream
+        const char *qt = my + (region ^ 1) * TILE_BYTES;
+#pragma unroll
+        for (int s = 0; s < KSTEPS; ++s) qf[s] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(qt + (kbase0 ^ (s << 5))));
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        if (F8 && region != 0) feed(R0());
+        else feed(R1());
+    }
+    // pages of the block's own rows, for the append: positions L + t0 .. L + t0 + 31 touch up to three
+    const int ap = (L + t0) / kPage;
+    const int ap0 = bt[min(ap, last_entry)], ap1 = bt[min(ap + 1, last_entry)], ap2 = bt[min(ap + 2, last_entry)];
+
     f32x16 o[DBLK];
 #pragma unroll
     for (int i = 0; i < DBLK; ++i)
@@ -230,63 +340,67 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_short_kernel(ShortParams)
     const float c_new = p->neg ? -p->c : p->c;
     float m = -1e30f, lsum = 0.f;                        // reference exponent of the row (not its exact maximum), this lane's row sum
     bool first = true;
-    [[maybe_unused]] bool o_scaled = st >= ctx_steps;    // FP8: O is in units of code values until the first new keys
+    [[maybe_unused]] bool o_scaled = code_steps == 0;    // FP8: O is in units of code values until the first new keys
 
-    for (; st < s_end; st += NW) {
-        const bool more = st + NW < s_end, ctx = st < ctx_steps;
-        const bool next_codes = F8 && st + NW < ctx_steps;       // the next step's rows come as codes
+    for (; left > 0; --left, st += T) {
+        const bool more = left > 1, ctx = st < ctx_steps, codes = F8 && ctx;
         float c = c_new;
         if constexpr (F8) {
             // the K scale rides on the score factor of cached keys, the V scale is applied to O once, before the first
             // new keys add to it (or behind the loop)
             if (ctx) {
                 c = c_new * p->k_scale;
-                write_codes(rk, false);
-                write_codes(rv, true);
-                if (next_codes) {
-                    load_codes(st + NW, false, rk);
-                    load_codes(st + NW, true, rv);
-                }
-                asm volatile("" ::: "memory");           // the fragment reads below stay behind the tile writes
-            } else {
-                if (!o_scaled) {
-                    const float vs = p->v_scale;
+            } else if (!o_scaled) {
+                const float vs = p->v_scale;
 #pragma unroll
-                    for (int i = 0; i < DBLK; ++i)
+                for (int i = 0; i < DBLK; ++i)
 #pragma unroll
-                        for (int v = 0; v < 16; ++v) o[i][v] *= vs;
-                    o_scaled = true;
-                }
-                wait_vm<NI>();
+                    for (int v = 0; v < 16; ++v) o[i][v] *= vs;
+                o_scaled = true;
             }
+        }
+        // K has landed when only what was issued after it is outstanding: the other region's load (behind a step of codes, if there
+        // is one; the V rows of a 16-bit step) and the second half of a step of codes
+        if (codes) {
+            if (more) wait_vm<NI + NI / 2>();
+            else wait_vm<NI / 2>();
         } else {
-            wait_vm<NI>();                               // K has landed; behind it only V
+            wait_vm<NI>();
         }
         asm volatile("" : "+v"(kbase0), "+v"(vbase0));
+        if constexpr (F8) asm volatile("" : "+v"(kcode0), "+v"(vcode0));
+        const char *tile = my + region * TILE_BYTES;     // (a step of codes)
         bf16x8 kf[KSTEPS];
+        if (codes) {
 #pragma unroll
-        for (int s = 0; s < KSTEPS; ++s) kf[s] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(my + (kbase0 ^ (s << 5))));
-        // fragments are in registers: the tile may be overwritten (unless the new rows in it are still to be cached: then
-        // this is the last step and nothing follows)
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        if (more && !next_codes) issue(st + NW, false);
+            for (int s = 0; s < KSTEPS; ++s) {
+                const uint2 y = *reinterpret_cast<const uint2 *>(tile + (kcode0 ^ (s << 4)));
+                kf[s] = codes_to_bf16(y.x, y.y);
+            }
+        } else {
+#pragma unroll
+            for (int s = 0; s < KSTEPS; ++s) kf[s] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(my + (kbase0 ^ (s << 5))));
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the rows are in registers: the region may be overwritten
+        if (!codes && more) feed(R0());
         f32x16 sc;
 #pragma unroll
         for (int v = 0; v < 16; ++v) sc[v] = 0.f;
 #pragma unroll
         for (int s = 0; s < KSTEPS; ++s) sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[s], qf[s], sc, 0, 0, 0);
-        // accumulator element v is key 8 * (v / 4) + 4 * half + v % 4 of the step; keys past `bound` (the end of the cached
-        // context, or the lane's own row on the diagonal) get weight exp2(-inf) = 0
+        // keys past `bound` (the end of the cached context, or the lane's own row on the diagonal) get weight exp2(-inf) = 0
         if (st == steps - 1 || (ctx && st * 32 + 32 > L)) {
             const int bound = ctx ? L - 1 - st * 32 : l32;
             const float masked = c < 0.f ? INFINITY : -INFINITY;
 #pragma unroll
-            for (int v = 0; v < 16; ++v)
-                if ((v / 4) * 8 + 4 * half + (v % 4) > bound) sc[v] = masked;
+            for (int v = 0; v < 16; ++v) {
+                const int key = codes ? 16 * (v / 8) + 8 * half + v % 8 : 8 * (v / 4) + 4 * half + v % 4;
+                if (key > bound) sc[v] = masked;
+            }
         }
         bf16x8 pf[2];
         // (a lambda: as a function shared by the kernels it made the short kernel 4 % slower)
-        auto weights = [&]() {                           // rounded to bf16 for the PV product
+        auto weights = [&]() __attribute__((always_inline)) {                           // rounded to bf16 for the PV product
 #pragma unroll
             for (int v = 0; v < 16; v += 2) {
                 pf[v / 8][v % 8] = (__bf16)__builtin_amdgcn_exp2f(__builtin_fmaf(sc[v], c, -m));
@@ -313,31 +427,48 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_short_kernel(ShortParams)
             }
         }
         add_weights(pf, lsum);
-        if (!(F8 && ctx)) {
-            if (more) wait_vm<NI>();                     // V of this step: behind it only the next step's K
+        // V has landed: behind it only the next load of the stream
+        if (codes) {
+            if (more) wait_vm<NI>();
             else wait_vm<0>();
+        } else if (more) {
+            wait_vm<NI>();
+        } else {
+            wait_vm<0>();
         }
-        s16x8 vf[2 * DBLK];
+        bf16x8 vf[2 * DBLK];
+        if (codes) {
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+            for (int jj = 0; jj < 2; ++jj)
 #pragma unroll
-            for (int db = 0; db < DBLK; ++db) {
-                const char *a = my + (vbase0 ^ (db << 6)) + j * (16 * ROW);
-                const s16x4 va = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)a);
-                const s16x4 vb = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(a + 8 * ROW));
-                vf[j * DBLK + db] = __builtin_shufflevector(va, vb, 0, 1, 2, 3, 4, 5, 6, 7);
-            }
+                for (int db = 0; db < DBLK; ++db) {
+                    const i32x2 y = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_i32x2 *)(tile + (vcode0 ^ (db << 5)) + jj * (16 * D)));
+                    vf[jj * DBLK + db] = codes_to_bf16((uint32_t)y[0], (uint32_t)y[1]);
+                }
+        } else {
+#pragma unroll
+            for (int jj = 0; jj < 2; ++jj)
+#pragma unroll
+                for (int db = 0; db < DBLK; ++db) {
+                    const char *a = my + (vbase0 ^ (db << 6)) + jj * (16 * ROW);
+                    const s16x4 va = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)a);
+                    const s16x4 vb = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(a + 8 * ROW));
+                    vf[jj * DBLK + db] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(va, vb, 0, 1, 2, 3, 4, 5, 6, 7));
+                }
+        }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        if (more) {
-            if (!next_codes) issue(st + NW, true);
-            pg0 = bt[min(2 * (st + 2 * NW), last_entry)];
-            pg1 = bt[min(2 * (st + 2 * NW) + 1, last_entry)];
+        if (codes) {
+            if (region != 0) feed(R1());
+            else feed(R0());
+            region ^= 1;
+        } else if (more) {
+            feed(R1());
         }
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int jj = 0; jj < 2; ++jj)
 #pragma unroll
             for (int db = 0; db < DBLK; ++db)
-                o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, vf[j * DBLK + db]), pf[j], o[db], 0, 0, 0);
+                o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[jj * DBLK + db], pf[jj], o[db], 0, 0, 0);
     }
     if constexpr (F8) {
         if (!o_scaled) {
@@ -348,24 +479,22 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_short_kernel(ShortParams)
                 for (int v = 0; v < 16; ++v) o[i][v] *= vs;
         }
     }
-
-    // ---- fused append: the wavefront of the last step has rows t0 .. t0 + 31 of K and V in its tiles
-    if (appends && s_end == steps && wave == ((steps - 1 - s_begin) & (NW - 1))) {
-        const int pos0 = L + t0, n_here = min(32, n_s - t0);
+    // ---- fused append: the wavefront of the last step has rows t0 .. t0 + 31 of K and V in its regions
+    if (appends) {
 #pragma unroll
         for (int mat = 0; mat < 2; ++mat)
 #pragma unroll
             for (int i = 0; i < NI; ++i) {
                 const int r = RPI * i + r0, ch = lane % CH;
                 if (r < n_here) {
-                    const int pos = pos0 + r, e = pos / kPage - ap;
+                    const int pos = L + t0 + r, e = pos / kPage - ap;
                     const int page = e == 0 ? ap0 : (e == 1 ? ap1 : ap2);
                     const u32x4 v = *reinterpret_cast<const u32x4 *>(my + mat * TILE_BYTES + r * ROW + ((ch ^ (mat ? v_swizzle<D>(r) : k_swizzle<D>(r))) << 4));
-                    const size_t at = (size_t)page * page_bytes + (size_t)(mat * Hkv + kh) * head_bytes + (size_t)((pos % kPage) * CH + ch) * (8 * ESZ);
-                    char *dst = reinterpret_cast<char *>(p->pages_w) + at;
+                    char *dst = p_pages_w + (size_t)page * page_bytes + (size_t)(mat * Hkv + kh) * head_bytes
+                                + (size_t)((pos % kPage) * CH + ch) * (8 * ESZ);
                     if constexpr (F8) {
-                        const uint2 x = bf16_to_codes(v, mat ? p->v_inv : p->k_inv);
-                        *reinterpret_cast<global_u32x2_w *>((uintptr_t)dst) = u32x2{x.x, x.y};
+                        const uint2 y = bf16_to_codes(v, mat ? p->v_inv : p->k_inv);
+                        *reinterpret_cast<global_u32x2_w *>((uintptr_t)dst) = u32x2{y.x, y.y};
                     } else {
                         *reinterpret_cast<global_u32x4_w *>((uintptr_t)dst) = v;
                     }
@@ -373,33 +502,10 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_short_kernel(ShortParams)
             }
     }
 
-    // ---- the wavefronts meet in LDS: each leaves its unnormalised O in its own tiles (vector (db * 4 + q4) of lane l at
-    // index (db * 4 + q4) * 64 + l: no bank conflicts), m and the row sum beside; then every wavefront finishes
-    // some of the columns.  Wavefronts that had no step are not looked at.
-    const int parts = min(s_end - s_begin, NW);
-    if (wave < parts) {
-        const float ltot = half_swap_sum(lsum);
-        f32x4 *mine = reinterpret_cast<f32x4 *>(my);
-        static_assert(DBLK * 4 * 64 * 16 == 2 * TILE_BYTES, "an O fits a wavefront's tiles");
-        asm volatile("" ::: "memory");
-#pragma unroll
-        for (int db = 0; db < DBLK; ++db)
-#pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4) {
-                f32x4 x;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) x[e] = o[db][q4 * 4 + e];
-                mine[(db * 4 + q4) * 64 + lane] = x;
-            }
-        if (half == 0) { stat[wave][0][l32] = m; stat[wave][1][l32] = ltot; }
-    }
-    lds_barrier();
     const int t = t0 + l32;
-    float ms = stat[0][0][l32];
-    for (int w = 1; w < parts; ++w) ms = fmaxf(ms, stat[w][0][l32]);
     // normalises vectors vec and vec + 1 of O and writes them: the half-waves exchange what they hold of the two, 16 bytes
     // per lane and store
-    auto finish = [&](int vec, const f32x4 &a, const f32x4 &b, float l) {
+    auto finish = [&](int vec, const f32x4 &a, const f32x4 &b, float l) __attribute__((always_inline)) {
         const float inv = __builtin_amdgcn_rcpf(l);
         bf16x4 wa, wb;
 #pragma unroll
@@ -407,23 +513,60 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_short_kernel(ShortParams)
             wa[e] = (__bf16)(a[e] * inv);
             wb[e] = (__bf16)(b[e] * inv);
         }
-        uint2 x = __builtin_bit_cast(uint2, wa), y = __builtin_bit_cast(uint2, wb);
-        asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %2\n\tv_permlane32_swap_b32 %1, %3\n\ts_nop 1" : "+v"(x.x), "+v"(x.y), "+v"(y.x), "+v"(y.y));
-        if (t < n_s) {
-            uint16_t *orow = p->out + ((size_t)(row0 + t) * Hq + head) * D;
-            *reinterpret_cast<global_u32x4_w *>((uintptr_t)(orow + (vec + half) * 8)) = u32x4{x.x, x.y, y.x, y.y};
+        uint2 y = __builtin_bit_cast(uint2, wa), z = __builtin_bit_cast(uint2, wb);
+        asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %2\n\tv_permlane32_swap_b32 %1, %3\n\ts_nop 1" : "+v"(y.x), "+v"(y.y), "+v"(z.x), "+v"(z.y));
+        if (valid && t < n_s) {
+            uint16_t *orow = reinterpret_cast<uint16_t *>(p_out) + ((size_t)(row0 + t) * Hq + head) * D;
+            __builtin_nontemporal_store(u32x4{y.x, y.y, z.x, z.y}, reinterpret_cast<global_u32x4_w *>((uintptr_t)(orow + (vec + half) * 8)));
         }
     };
+    const float ltot = half_swap_sum(lsum);
+    if (tl == 0) {                                       // a wavefront by itself
+#pragma unroll
+        for (int db = 0; db < DBLK; ++db)
+#pragma unroll
+            for (int q4 = 0; q4 < 4; q4 += 2) {
+                f32x4 a, b;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    a[e] = o[db][q4 * 4 + e];
+                    b[e] = o[db][q4 * 4 + 4 + e];
+                }
+                finish(db * 4 + q4, a, b, ltot);
+            }
+        return;
+    }
+    // ---- the wavefronts of a team meet in LDS: each leaves its unnormalised O in its own regions (vector (db * 4 + q4) of lane l
+    // at index (db * 4 + q4) * 64 + l: no bank conflicts), m and the row sum beside; then every wavefront finishes
+    // some of the columns.  Wavefronts that had no step are not looked at.
+    if (rank < parts) {
+        f32x4 *mine = reinterpret_cast<f32x4 *>(my);
+        static_assert(DBLK * 4 * 64 * 16 == 2 * TILE_BYTES, "an O fits a wavefront's regions");
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (int db = 0; db < DBLK; ++db)
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4) {
+                f32x4 y;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) y[e] = o[db][q4 * 4 + e];
+                mine[(db * 4 + q4) * 64 + lane] = y;
+            }
+        if (half == 0) { stat[wave][0][l32] = m; stat[wave][1][l32] = ltot; }
+    }
+    lds_barrier();
+    float ms = stat[team0][0][l32];
+    for (int w = 1; w < parts; ++w) ms = fmaxf(ms, stat[team0 + w][0][l32]);
     auto partial = [&](int i) -> float * { return p->scratch + ((size_t)(u * Hq + head) * splits + i) * (32 * D + 64); };
     // an item is 16 of the columns, two neighbouring vectors: 2 * DBLK of them
-    for (int item = wave; item < 2 * DBLK; item += NW) {
+    for (int item = rank; item < 2 * DBLK; item += T) {
         const int vec = item * 2;                        // = db * 4 + q4 with q4 in {0, 2}
         f32x4 a = {0.f, 0.f, 0.f, 0.f}, b = a;
         float l = 0.f;
         for (int w = 0; w < parts; ++w) {
-            const float wgt = __builtin_amdgcn_exp2f(stat[w][0][l32] - ms);
-            l = __builtin_fmaf(stat[w][1][l32], wgt, l);
-            const f32x4 *src = reinterpret_cast<const f32x4 *>(smem + w * (2 * TILE_BYTES)) + lane;
+            const float wgt = __builtin_amdgcn_exp2f(stat[team0 + w][0][l32] - ms);
+            l = __builtin_fmaf(stat[team0 + w][1][l32], wgt, l);
+            const f32x4 *src = reinterpret_cast<const f32x4 *>(smem + (team0 + w) * (2 * TILE_BYTES)) + lane;
             const f32x4 xa = src[vec * 64], xb = src[(vec + 1) * 64];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
@@ -454,7 +597,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_short_kernel(ShortParams)
     if (!last) return;
     if (tid == 0) store_global(p->counters + (u * Hq + head), 0);
     // (read with coherent loads, four parts per round trip; an acquire fence would empty the XCD's L2 under everybody)
-    for (int item = wave; item < 2 * DBLK; item += NW) {
+    for (int item = rank; item < 2 * DBLK; item += T) {
         const int vec = item * 2;
         f32x4 a = {0.f, 0.f, 0.f, 0.f}, b = a;
         float l = 0.f, mm = -INFINITY;
@@ -490,10 +633,8 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_short_kernel(ShortParams)
 template <int D, bool F8>
 hipError_t launch(const ShortParams &p, int wavefronts, hipStream_t stream)
 {
-    const dim3 grid(p.units * p.Hq * p.splits + p.zero_wgs);
+    const dim3 grid(p.attn_wgs + p.zero_wgs);
     if (wavefronts == 8) hipLaunchKernelGGL((attn_short_kernel<D, F8, 8>), grid, dim3(512), 0, stream, p);
-    else if (wavefronts == 2) hipLaunchKernelGGL((attn_short_kernel<D, F8, 2>), grid, dim3(128), 0, stream, p);
-    else if (wavefronts == 1) hipLaunchKernelGGL((attn_short_kernel<D, F8, 1>), grid, dim3(64), 0, stream, p);
     else hipLaunchKernelGGL((attn_short_kernel<D, F8, 4>), grid, dim3(256), 0, stream, p);
     return hipGetLastError();
 }
