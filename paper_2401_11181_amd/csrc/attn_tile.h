@@ -451,6 +451,41 @@ __device__ __forceinline__ void request_q(const AttnParams &p, const Job &J, int
     for (int st = 0; st < D / 16; ++st) qf[st] = __builtin_bit_cast(bf16x8, u32x4(qp[2 * st + (lane >> 5)]));
 }
 
+// The same for a workgroup's first job, whose stage buffers are empty but for its first stage: the wavefront's 32 rows, whole rows
+// per instruction, to a place of its own in the other stage buffer (q_lds), and from there, once they have arrived, as fragments.
+// (As fragments straight from memory each instruction asks for 32 bytes of 32 rows, and the stage's loads go out behind them or
+// wait for the page ids in front of them: the first stage was there 5.5 us after the launch's start, now 4.7; 16384 tokens of 40 heads in
+// 32 chunks -0.5 to -1.5 %, 32/8 heads over FP8 codes -0.4 to -1.5 %.)
+template <int D>
+__device__ __forceinline__ void request_q_rows(const AttnParams &p, const Job &J, int head, int rbk, int lane, uint32_t q_lds)
+{
+    constexpr int CH = D / 8, RPI = 64 / CH, NI = 32 / RPI;
+    const int first = J.t0 + 32 * rbk, r0 = lane / CH;
+    const uint32_t q_row = p.Hq * (D * 2);
+    const char *qb = reinterpret_cast<const char *>(p.q) + ((size_t)J.seg_cu * p.Hq + head) * (D * 2);
+    if (D == 128 && first + 32 <= J.n_s) {
+        const uint32_t off = r0 * q_row + (((lane % CH) ^ k_swizzle<D>(r0)) << 4), step = RPI * q_row - 1024;
+        auto x = [&](int i) -> uint32_t { return (off ^ k_inst_xor<D>(i)) + i * step; };
+#pragma unroll
+        for (int h = 0; h < 2; ++h) dma16_group4(qb + (size_t)(first + 16 * h) * q_row, x(0), x(1), x(2), x(3), q_lds + 4096 * h);
+    } else {
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            const int r = RPI * i + r0, t = first + r;
+            dma16(qb + (size_t)(t < J.n_s ? t : 0) * q_row + (((lane % CH) ^ k_swizzle<D>(r)) << 4), q_lds + 1024 * i);
+        }
+    }
+}
+template <int D>
+__device__ __forceinline__ void read_q_rows(const char *q_tile, int lane, bf16x8 (&qf)[D / 16])
+{
+    const int half = lane >> 5, l32 = lane & 31;
+#pragma unroll
+    for (int st = 0; st < D / 16; ++st)
+        qf[st] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(q_tile + l32 * (D * 2) + (((2 * st + half) ^ k_swizzle<D>(l32)) << 4)));
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+}
+
 // The tile's own rows (new keys t0 .. t0 + rows of a tile - 1 of the segment) in the stage buffers go to their page slots:
 // wavefront `wave` takes the 16 rows of each stage it has loaded.  Same result as the stand-alone append kernel, bit for bit.
 template <int D, int KS, bool F8>

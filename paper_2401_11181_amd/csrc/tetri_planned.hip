@@ -86,10 +86,13 @@ __global__ __launch_bounds__(Shape<KS>::WAVES * 64, 2) void attn_planned_kernel(
     if (!find_job(p, widx, J, after)) return;
     TETRI_MARK(9);
 
-    // ---- the first job's first stage and its Q rows
+    // ---- the first job's Q rows, by way of the second stage buffer (8 KB a wavefront; its first loads go out behind the job's
+    // first barrier), and its first stage
     Carry<D> cy;
     cy.par = J.it_begin & 1;                         // the first stage goes to buffer 0
     {
+        char *q_tile = reinterpret_cast<char *>(smem + (wave < 4 ? 1 : 3) * STAGE_U4) + (wave & 3) * (32 * D * 2);
+        request_q_rows<D>(p, J, J.grp * p.hpw + (slot & (p.hpw - 1)), slot >> p.hpw_shift, lane, lds_address(q_tile));
         const WaveSrc ws = make_wave_src<D, KS, F8>(p, J.kh);
         LaneOffsets<D> lo;
         init_lane_offsets<D>(lo, lane);
@@ -97,10 +100,15 @@ __global__ __launch_bounds__(Shape<KS>::WAVES * 64, 2) void attn_planned_kernel(
         StageLoads sl;
         const bool full = describe_stage_loads<D, KS, F8>(J.src, ws, lo, page, J.it_begin, wave, p.Hkv * D * 2, lds_address(smem), sl);
         cy.have_codes = F8 && sl.codes;
-        if (F8 && sl.codes) fetch_stage_codes<D>(sl, full, cy.codes);
-        else issue_stage_loads<D, KS>(sl, full);
+        if (F8 && sl.codes) {
+            fetch_stage_codes<D>(sl, full, cy.codes);
+            wait_vm<0>();
+        } else {
+            issue_stage_loads<D, KS>(sl, full);
+            wait_vm<2 * (D / 32)>();                 // (all but the stage's)
+        }
         cy.page = load_stage_page<KS>(p.bt + J.src.bt_off, p.max_blocks, J.it_begin + 1, wave);
-        request_q<D>(p, J, J.grp * p.hpw + (slot & (p.hpw - 1)), slot >> p.hpw_shift, lane, cy.qf);
+        read_q_rows<D>(q_tile, lane, cy.qf);
     }
     TETRI_MARK(1);
 
