@@ -497,22 +497,6 @@ static bool plan_short(const tetri_ctx *h, const int32_t *cu, const int32_t *ctx
     p.splits = 1;
     if (h->split_keys && 2 * wgs <= cus && wgs <= h->n_counters)
         p.splits = (int32_t)std::max<int64_t>(1, std::min(std::min<int64_t>(cus / wgs, 16), std::min<int64_t>((most + 7) / 8, units_fit)));
-    // Where this kernel is the faster one (both timed on 650 chunks of 40x128, 32/8x128, 24/8x128, 16x128, 16/2x128 and
-    // 8/2x128 heads, 128 to 1024 rows in 1 to 10 segments, 0 to 30000 cached tokens; times as a part of the shared-tile kernel's):
-    //  - at most a workgroup per compute unit, eight wavefronts to a row block: always (16-bit 0.22-0.83, FP8 codes
-    //    0.28-0.93; the longest were 30000 cached tokens, 120 steps to a wavefront);
-    //  - at most two: up to 65000 steps of 32 keys x 32 rows (0.53 at the smallest, 1.0 there, 1.1 at 130000, 1.2-1.4 at 300000);
-    //    FP8, whose conversion is paid once per row block, up to 20000 (0.97-1.15 there, 1.5 at 130000);
-    //  - more: a row block has one or two wavefronts, and what a launch takes is their chain of steps, which the total does not
-    //    show.  With two, at 544 workgroups, a longest block of 40 steps took 27 us (FP8 43) however little the others
-    //    had, the shared-tile kernel 29 (31).  Up to 22 steps on a wavefront (FP8 11), and 30000 (15000) in all.
-    // The choice costs 0.7 % on average against the better kernel each time.  head_dim 64: always (1.3 % over 224 chunks of 40x64
-    // and 12/4x64, up to 24 % on single ones; a limit on the chain gains nothing).
-    const int64_t chain = (most + wavefronts - 1) / wavefronts;
-    if (h->cfg.head_dim == 64) shape.preferred = true;
-    else if (wgs <= cus) shape.preferred = chain <= 128;
-    else if (wgs <= 2 * cus) shape.preferred = total <= (fp8 ? 20000 : 65000);
-    else shape.preferred = total <= (fp8 ? 15000 : 30000) && chain <= (fp8 ? 11 : 22);
     // ---- the shape of the launch.  A row block of one head is the work of a team of 1, 2, 4 or 8 wavefronts: as many as leave at
     // most `cap` steps to each, cap the least for which all wavefronts of the launch are on the chip at once.  (Teams of one
     // size made the launch as long as its longest row block: 64 packed chunks of 40 heads 18.0 us each, now 15.8.)
@@ -531,6 +515,8 @@ static bool plan_short(const tetri_ctx *h, const int32_t *cu, const int32_t *ctx
         for (int i = 0; i < n; ++i) waves += Hq << team(units[i].steps, cap);
         if (waves <= slots) break;
     }
+    int32_t longest = 0;              // steps on a wavefront
+    for (int i = 0; i < n; ++i) longest = std::max(longest, (units[i].steps + (1 << team(units[i].steps, cap)) - 1) >> team(units[i].steps, cap));
     p.spread = wgs <= cus;
     int32_t first_wg = 0;
     for (int tl = 3, i = 0; tl >= 0; --tl) {
@@ -543,6 +529,28 @@ static bool plan_short(const tetri_ctx *h, const int32_t *cu, const int32_t *ctx
     }
     p.attn_wgs = first_wg;
     shape.nwl = nwl;
+    // Where this kernel is the faster one (both timed on 650 chunks of 40x128, 32/8x128, 24/8x128, 16x128, 16/2x128 and 8/2x128 heads, 32 to
+    // 1024 rows in 1 to 10 segments, 0 to 32000 cached tokens; times as a part of the shared-tile kernel's, FP8 codes in brackets):
+    //  - exactly a workgroup per compute unit, eight wavefronts to a row block: up to 128 steps to a wavefront (0.4 at the shortest, 1.0
+    //    at 17 steps, 1.25 (1.4) at 80);
+    //  - fewer: three or more workgroups to a row block, up to 128 steps too (0.5 to 0.99 (1.07) at 31); two, up to 20 (15) steps
+    //    (0.93 to 0.98 (0.96 to 1.02) at 16, 1.05 (1.1) at 24, 1.2 (1.3) at 63); one, which leaves compute units without work, up to 16
+    //    (12) (0.8 to 0.9 at 9, 1.0 (1.1 to 1.2) at 16, 1.15 (1.3) at 24, 1.4 to 1.9 at 95);
+    //  - exactly two workgroups per compute unit: up to 65000 (20000) steps of 32 keys x 32 rows in all; between one and two, which leaves
+    //    some compute units half empty, also up to 27 (14) steps on a wavefront times the part of the two (256 rows of 40 heads:
+    //    1.05 (1.18) at 14 steps, 1.14 (1.3) at 22, 1.26 (1.4) at 32; 512 rows of 24/8 heads: 0.98 (1.07) at 16, 1.03 (1.14) at 24);
+    //  - more: what a launch takes is the chain of steps of its longest row blocks, which the total does not show: up to 30000 (15000)
+    //    steps in all with 22 (11) on a wavefront, at two to a row block.  Where the work is even over the row blocks of several segments,
+    //    the shared-tile kernel's tiles are ragged and teams keep the chains short: up to 30000 whatever the chain, over codes 20000
+    //    unless every query head has K and V of its own (40 heads, 300 rows at 1000 and 212 at 200 cached tokens: 0.75 (0.75); 200 at 2000
+    //    and 312 at 600: 0.87 (0.94); 32/8 heads, the same: 1.0 (1.1), 345 at 1353 and 167 at 0: 0.85 (0.95)).
+    // head_dim 64: always (1.3 % over 224 chunks of 40x64 and 12/4x64, up to 24 % on single ones; a limit on the chain gains nothing).
+    const int64_t chain = (most + wavefronts - 1) / wavefronts;
+    if (h->cfg.head_dim == 64) shape.preferred = true;
+    else if (wgs <= cus) shape.preferred = chain <= (wgs == cus || p.splits > 2 ? 128 : (p.splits == 2 ? 2 * (fp8 ? 15 : 20) : (fp8 ? 12 : 16)));
+    else if (wgs <= 2 * cus) shape.preferred = total <= (fp8 ? 20000 : 65000) && (wgs == 2 * cus || 2 * cus * longest <= (fp8 ? 14 : 27) * wgs);
+    else if (num_segs > 1 && (int64_t)most * n <= 2 * steps) shape.preferred = total <= (fp8 && Hq != Hkv ? 20000 : 30000);
+    else shape.preferred = total <= (fp8 ? 15000 : 30000) && chain <= (fp8 ? 11 : 22);
     return (uint64_t)(wgs * p.splits + p.zero_wgs + 8) * (uint64_t)std::max<int64_t>(Hq, p.splits) < 0x100000000ull;   // (the divisions by multiplication)
 }
 
@@ -550,15 +558,16 @@ static bool plan_short(const tetri_ctx *h, const int32_t *cu, const int32_t *ctx
 // A job is a stretch of stages (128 keys) of one row tile (8 slots of 32 rows); p says how heads and rows share the slots.
 // The work of a pool (its head groups' tiles) goes to one workgroup per compute unit so that all end together: a tile longer
 // than q stages is cut into pieces of q for a workgroup each, the remainders and the tiles that are shorter are packed, the
-// longest first, into the workgroups that are left; q is the smallest for which they fit.  False if the tables do not hold it.
-static bool plan_tiles(const tetri_ctx *h, const int32_t *cu, const int32_t *ctx_lens, int32_t num_segs, const AttnParams &p, TilePlan &plan)
+// longest first, into the workgroups that are left; q is the smallest for which they fit.  Returns the longest workgroup's stages, 0 if the
+// tables do not hold the division.
+static int32_t plan_tiles(const tetri_ctx *h, const int32_t *cu, const int32_t *ctx_lens, int32_t num_segs, const AttnParams &p, TilePlan &plan)
 {
     constexpr int kStage = 128;
     constexpr int kSlack = 1;         // a remainder of this many stages stays with the piece before it
     constexpr int kMinPiece = 3;      // the shortest pieces a tile is cut into
     constexpr int kJobCost = 1;       // a workgroup's further jobs: what each costs besides its stages, in stages
     const int wgs = (std::max(h->num_cus, 8) / 8) << p.span_shift, pools = 8 >> p.span_shift, rows = 32 * p.rb;
-    if (num_segs > kPlanSegs || p.C > 0xffff || wgs > kPlanJobs || p.gpx > 1023) return false;
+    if (num_segs > kPlanSegs || p.C > 0xffff || wgs > kPlanJobs || p.gpx > 1023) return 0;
     struct Item { int32_t n; uint16_t seg, grp, t0, begin; uint16_t place; uint8_t piece, npieces; };
     Item tiles[kPlanJobs];
     int nt = 0;
@@ -569,7 +578,7 @@ static bool plan_tiles(const tetri_ctx *h, const int32_t *cu, const int32_t *ctx
         plan.seg[s][0] = cu[s]; plan.seg[s][1] = n; plan.seg[s][2] = ctx_lens[s]; plan.seg[s][3] = 0;
         for (int32_t t0 = 0; t0 < n; t0 += rows) {
             const int32_t stages = ctx_stages + (std::min(n, t0 + rows) + kStage - 1) / kStage;
-            if (nt + p.gpx > kPlanJobs || stages > 0xffff) return false;
+            if (nt + p.gpx > kPlanJobs || stages > 0xffff) return 0;
             for (int g = 0; g < p.gpx; ++g) tiles[nt++] = {stages, (uint16_t)s, (uint16_t)g, (uint16_t)t0, 0, 0, 0, 1};
             total += (int64_t)stages * p.gpx;
             longest = std::max(longest, stages);
@@ -643,7 +652,7 @@ static bool plan_tiles(const tetri_ctx *h, const int32_t *cu, const int32_t *ctx
             int at = full + k;
             for (int i = bins[k].first; i >= 0; i = link[i]) {
                 const bool more = link[i] >= 0;
-                if (more && jobs >= kPlanJobs) return false;
+                if (more && jobs >= kPlanJobs) return 0;
                 plan.job[at] = {(uint16_t)(rest[i].seg | rest[i].grp << 6), rest[i].t0, rest[i].begin, (uint16_t)(rest[i].begin + rest[i].n), rest[i].place,
                                 rest[i].piece, rest[i].npieces, (uint16_t)(more ? jobs : 0), 0};
                 at = jobs;
@@ -654,35 +663,42 @@ static bool plan_tiles(const tetri_ctx *h, const int32_t *cu, const int32_t *ctx
         plan.wgs = wgs;
         plan.rows = cu[num_segs];
         plan.pad = 0;
-        return true;
+        int32_t load = full > 0 ? q : 0;
+        for (int k = 0; k < left; ++k) load = std::max(load, bins[k].load);
+        return load;
     }
 }
 
-// The slots (head, 32-row block) of a workgroup for a chunk that goes to the shared-tile kernel on a division of the host's:
-// 8, each a wavefront that does all keys, or 4 with two key parts; 0: the launch divides itself (tetri_attn.hip).  A workgroup of
-// 8 slots stages a key for 256 rows instead of 128 and waits at half as many barriers for the same work (gqa, 16384 rows of
-// 4 x 32 heads at 12000 cached tokens: 3.5 us for 8 blocks per SIMD, with 4 slots 2.1 us for 4); with 4 slots the pieces are half
-// as long, which divides short launches better.  Timed on 120 chunks each of the 16-bit and the FP8 cache (40x128, 32/8, 24/8,
-// 16 and 8/2 heads, 256 to 2048 rows, 0 to 20000 cached tokens): up to 75000 steps of 32 keys x 32 rows 4 slots (0.85 to 1.05 of
-// the time of 8), beyond 8 (0.75 to 1.05 of that of 4).  Chunks of a multi-head model with few steps, evenly spread over their row blocks, stay with
-// the launch that divides itself: its tiles of a head walk the keys side by side (512 rows of 40 heads after 1500 tokens: 39.6 us
-// against 40.9 and 42.2; but 100 rows after 3000 tokens with 412 new ones: 43.6 against 31.2 and 30.2).
-static int planned_slots(const tetri_ctx *h, const int32_t *cu, const int32_t *ctx_lens, int32_t num_segs)
+// The shared-tile kernel on a division of the host's comes with 8 slots (head, 32-row block) to a workgroup, each a wavefront that
+// does all keys, or with 4 and two key parts.  A workgroup of 8 stages a key for 256 rows instead of 128 and waits at half as many
+// barriers for the same work (gqa, 16384 rows of 4 x 32 heads at 12000 cached tokens: 3.5 us for 8 blocks per SIMD, with 4 slots 2.1
+// us for 4); with 4 the pieces are half as long, which divides short launches better.  Which slots a chunk may have: 4 below 30000 steps of
+// 32 keys x 32 rows, 8 from 75000 on; in between both divisions are laid out and their longest workgroups compared: 4 where it has
+// fewer than 1.7 times the stages of 8 and 2 more.  Timed on 127 chunks of the 16-bit and the FP8 cache (40x128, 32/8, 24/8 and 16
+// heads, 256 to 2048 rows, 0 to 8000 cached tokens): 0.7 % on average against the better shape each time, 9 % at most (by the number
+// of steps alone 1.3 % and 21 %).  None: where the launch that divides itself fills the chip with row tiles and their helpers, whose
+// wavefronts walk a head's keys side by side (an odd number of query heads to a kv head, evenly spread work, under 50000 steps: 512 rows of
+// 40 heads at 1000 cached tokens 34.3 us (FP8 37.8) against 38.2 (44.2); at 2560, 56000 steps, 48.2 against 46.8; 384 rows,
+// which fill 200 compute units: 41.0 against 37.3).
+struct SlotChoice { bool four, eight; };
+static SlotChoice planned_slots(const tetri_ctx *h, const int32_t *cu, const int32_t *ctx_lens, int32_t num_segs)
 {
-    if (h->cfg.head_dim != 128) return 0;
-    if (h->attn_variant == 4) return 8;
-    if (h->attn_variant == 5) return 4;
-    if (h->attn_variant != 0 || h->division_set) return 0;
-    int64_t steps = 0, all = 0, most = 0;             // of one head, its row blocks, the longest of them
+    if (h->cfg.head_dim != 128) return {false, false};
+    if (h->attn_variant == 4) return {false, true};
+    if (h->attn_variant == 5) return {true, false};
+    if (h->attn_variant != 0 || h->division_set) return {false, false};
+    int64_t steps = 0, all = 0, tiles = 0, most = 0;  // of one head: steps, row blocks, row tiles, steps of the longest block
     for (int32_t s = 0; s < num_segs; ++s) {
         const int64_t blocks = (cu[s + 1] - cu[s] + 31) / 32, ctx_steps = (ctx_lens[s] + 31) / 32;
         steps += blocks * ctx_steps + blocks * (blocks + 1) / 2;
         all += blocks;
+        tiles += (blocks + 3) / 4;
         most = std::max(most, ctx_steps + blocks);
     }
-    const int g = h->cfg.num_q_heads / h->cfg.num_kv_heads;
-    if (g % 2 != 0 && steps * h->cfg.num_q_heads < 60000 && most * all <= 2 * steps) return 0;
-    return steps * h->cfg.num_q_heads < 75000 ? 4 : 8;
+    const int64_t Hq = h->cfg.num_q_heads, self = (tiles + tiles / 2) * Hq;
+    if (Hq / h->cfg.num_kv_heads % 2 != 0 && steps * Hq < 50000 && most * all <= 2 * steps && self <= h->num_cus && 8 * self > 7 * h->num_cus)
+        return {false, false};
+    return {steps * Hq < 75000, steps * Hq >= 30000};
 }
 
 static tetri_status attn_common(const char *fn, tetri_ctx *h, const void *q, const void *k_new, const void *v_new,
@@ -749,16 +765,26 @@ static tetri_status attn_common(const char *fn, tetri_ctx *h, const void *q, con
     }
     auto log2i = [](int v) { int s = 0; while ((1 << s) < v) ++s; return s; };
     // ---- the other chunks whose segments the host knows: the shared-tile kernel on a division made here
-    TilePlan plan;
-    const int slots = host_cu && !stream_captures(hs) ? planned_slots(h, host_cu, host_ctx, num_segs) : 0;
-    if (slots != 0) {
-        wave_grouping(p.g, slots, &p.hpw, &p.rb);
-        p.groups = p.Hq / p.hpw;
-        p.hpw_shift = log2i(p.hpw);
-        p.rb_shift = log2i(p.rb);
-        p.span_shift = p.groups <= 1 ? 3 : (p.groups <= 2 ? 2 : (p.groups <= 4 ? 1 : 0));
-        p.gpx = (p.groups + (8 >> p.span_shift) - 1) / (8 >> p.span_shift);
-        if (plan_tiles(h, host_cu, host_ctx, num_segs, p, plan)) {
+    if (host_cu && !stream_captures(hs)) {
+        TilePlan plans[2];
+        AttnParams shapes[2];                          // 4 and 8 slots
+        int32_t load[2] = {0, 0};
+        const SlotChoice may = planned_slots(h, host_cu, host_ctx, num_segs);
+        for (int i = 0; i < 2; ++i) {
+            if (!(i == 0 ? may.four : may.eight)) continue;
+            AttnParams &x = shapes[i] = p;
+            wave_grouping(x.g, 4 << i, &x.hpw, &x.rb);
+            x.groups = x.Hq / x.hpw;
+            x.hpw_shift = log2i(x.hpw);
+            x.rb_shift = log2i(x.rb);
+            x.span_shift = x.groups <= 1 ? 3 : (x.groups <= 2 ? 2 : (x.groups <= 4 ? 1 : 0));
+            x.gpx = (x.groups + (8 >> x.span_shift) - 1) / (8 >> x.span_shift);
+            load[i] = plan_tiles(h, host_cu, host_ctx, num_segs, x, plans[i]);
+        }
+        if (load[0] + load[1] != 0) {
+            const int pick = load[1] == 0 || (load[0] != 0 && 10 * load[0] < 17 * load[1] + 20) ? 0 : 1;
+            const TilePlan &plan = plans[pick];
+            p = shapes[pick];
             if (plan.places != 0 && (st = claim_scratch(h, fn, hs, false)) != TETRI_OK) return st;
             p.plan = &plan;
             p.gpx_magic = magic((uint32_t)p.gpx);

@@ -1,8 +1,9 @@
-// Driver of tests/test_host_short.py: the host layer (tetri_host.cpp, tetri_plan.cpp) with a launcher that walks the grid of the
+// Driver of tests/test_host_short.py and tests/test_host_choice.py: the host layer (tetri_host.cpp, tetri_plan.cpp) with a launcher that walks the grid of the
 // kernel for chunks with little work as its wavefronts do, instead of running it.  Draws chunks (argv: seed, number of draws, heads, kv
 // heads, head dim, chunk size) and fails if a 32-key step of a row block is missing or done twice, a row block is not the
 // chunk's, or a partial result lies outside the handle's memory.  Prints how many row blocks had teams of 1, 2, 4 and 8 wavefronts
-// and how many had their keys split over workgroups.
+// and how many had their keys split over workgroups.  With the heads alone (argv: heads, kv heads) it reads chunks from the standard input (FP8
+// or not, number of segments, rows and cached tokens of each) and prints the kernel the library's own rule gives each of them.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -52,21 +53,53 @@ hipError_t tetri_launch_append(const tetri_ctx *, const AppendParams &, int32_t,
 hipError_t tetri_launch_upload(const int32_t *, int32_t *, int64_t, hipStream_t, hipEvent_t) { return hipSuccess; }
 hipError_t tetri_launch_upload_inline(const int32_t *, int32_t *, int64_t, hipStream_t) { return hipSuccess; }
 
-hipError_t tetri_launch_attn(const tetri_ctx *, const AttnParams &, int, bool, hipStream_t) { return hipSuccess; }
-
 namespace {
 
 std::vector<int32_t> g_cu, g_ctx;
+const char *g_taken = "";
 const tetri_ctx *g_h = nullptr;
 int g_launches = 0, g_teams[4] = {0, 0, 0, 0}, g_split = 0;
 
 uint32_t div_by(uint32_t n, uint32_t magic) { return magic == 0 ? n : (uint32_t)(((uint64_t)n * magic) >> 32); }
 
+int choices(int hq, int hkv)
+{
+    alignas(16) static char any[64];
+    const int32_t *meta = reinterpret_cast<const int32_t *>(any);
+    int fp8, segs;
+    while (std::scanf("%d %d", &fp8, &segs) == 2) {
+        std::vector<int32_t> cu(1, 0), ctx;
+        for (int i = 0; i < segs; ++i) {
+            int rows, cached;
+            CHECK(std::scanf("%d %d", &rows, &cached) == 2);
+            cu.push_back(cu.back() + rows);
+            ctx.push_back(cached);
+        }
+        const tetri_config c = {hq, hkv, 128, 16, cu.back(), 1 << 20, 4096, std::min(cu.back(), 64), TETRI_BF16};
+        tetri_ctx *h = nullptr;
+        CHECK(tetri_create(&c, &h) == TETRI_OK);
+        g_cu = cu;
+        g_ctx = ctx;
+        CHECK(tetri_chunk_prefill_planned(h, any, any, any, any, meta, meta, meta, segs, 0.1f, 0, fp8, 1.f, 1.f, cu.data(), ctx.data(), any, nullptr) == TETRI_OK);
+        std::printf("%s\n", g_taken);
+        tetri_destroy(h);
+    }
+    return 0;
+}
+
 }  // namespace
+
+hipError_t tetri_launch_attn(const tetri_ctx *, const AttnParams &p, int, bool, hipStream_t)
+{
+    g_taken = p.plan == nullptr ? "self" : (p.hpw * p.rb == 8 ? "eight" : "four");
+    return hipSuccess;
+}
 
 hipError_t tetri_launch_short(int D, bool, const ShortParams &p, int wavefronts, hipStream_t)
 {
     ++g_launches;
+    g_taken = "short";
+    if (g_h == nullptr) return hipSuccess;
     CHECK(wavefronts == 4 || wavefronts == 8);
     const int nwl = wavefronts == 8 ? 3 : 2;
     CHECK(p.units >= 1 && p.units <= kShortUnits && p.rows == g_cu.back() && p.hpx << p.rshift == p.Hq && p.hkx << p.rshift == p.Hkv);
@@ -120,6 +153,7 @@ hipError_t tetri_launch_short(int D, bool, const ShortParams &p, int wavefronts,
 
 int main(int argc, char **argv)
 {
+    if (argc == 3) return choices(std::atoi(argv[1]), std::atoi(argv[2]));
     CHECK(argc == 7);
     std::mt19937 rng((unsigned)std::atoi(argv[1]));
     const int draws = std::atoi(argv[2]), hq = std::atoi(argv[3]), hkv = std::atoi(argv[4]), d = std::atoi(argv[5]), chunk = std::atoi(argv[6]);

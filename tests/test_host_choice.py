@@ -1,0 +1,55 @@
+"""Which kernel a chunk whose segments the host knows goes to, on both sides of the lines of the rule (tests/host_short.cpp): "short" (the
+kernel for chunks with little work), "four" or "eight" (the shared-tile kernel on the host's division, 4 or 8 slots to a
+workgroup), "self" (the launch that divides itself)."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+HIP_INCLUDE = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "include")
+
+pytestmark = pytest.mark.skipif(shutil.which("g++") is None or not os.path.isdir(os.path.join(HIP_INCLUDE, "hip")),
+                                reason="needs g++ and the HIP headers")
+
+
+@pytest.fixture(scope="module")
+def driver(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("short") / "host_short")
+    csrc = os.path.join(ROOT, "paper_2401_11181_amd", "csrc")
+    subprocess.run(["g++", "-std=c++17", "-g", "-O1", "-fsanitize=address,undefined", "-fno-sanitize-recover=all",
+                    "-static-libasan", "-static-libubsan", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-I", HIP_INCLUDE,
+                    "-I", os.path.join(ROOT, "include"), "-I", csrc, os.path.join(ROOT, "tests", "host_short.cpp"),
+                    os.path.join(csrc, "tetri_host.cpp"), os.path.join(csrc, "tetri_plan.cpp"), "-o", exe], check=True)
+    return exe
+
+
+# heads, kv heads, FP8, segments (rows, cached tokens), kernel; 256 compute units
+CHOICES = [
+    # fewer row blocks than compute units, one workgroup to each: 16 steps on a wavefront, over codes 12
+    (40, 40, 0, [(128, 3900)], "short"), (40, 40, 0, [(128, 4000)], "four"), (40, 40, 1, [(100, 2900)], "short"), (40, 40, 1, [(100, 3000)], "four"),
+    # two: 20, 15
+    (32, 8, 0, [(128, 10000)], "short"), (32, 8, 0, [(128, 10300)], "four"), (8, 2, 1, [(512, 7100)], "short"), (8, 2, 1, [(512, 7300)], "four"),
+    # more: 128
+    (32, 8, 0, [(64, 32000)], "short"), (8, 2, 1, [(128, 32500)], "short"),
+    # more row blocks than compute units, not two each
+    (40, 40, 0, [(256, 1700)], "short"), (40, 40, 0, [(256, 2100)], "four"), (40, 40, 1, [(256, 700)], "short"), (40, 40, 1, [(256, 1100)], "four"),
+    # even work over several segments; uneven work
+    (32, 8, 1, [(300, 1000), (212, 200)], "short"), (32, 8, 1, [(36, 1191), (476, 0)], "four"), (40, 40, 1, [(200, 2000), (312, 600)], "short"),
+    (32, 8, 1, [(200, 2000), (312, 600)], "four"),
+    # row tiles and helpers that fill the chip; not even, not filling, too long
+    (40, 40, 1, [(512, 1000)], "self"), (40, 40, 0, [(100, 3000), (412, 0)], "four"), (40, 40, 0, [(384, 3000)], "four"), (40, 40, 0, [(512, 2560)], "eight"),
+    # 4 or 8 slots
+    (40, 40, 0, [(512, 6144)], "eight"), (24, 8, 0, [(512, 4000)], "four"), (16, 16, 0, [(1024, 2560)], "short"), (16, 16, 0, [(1024, 4200)], "eight"),
+    (32, 8, 0, [(2048, 300)], "eight"),
+]
+
+
+def test_choice(driver):
+    for heads in sorted({c[:2] for c in CHOICES}):
+        cases = [c for c in CHOICES if c[:2] == heads]
+        text = "".join("%d %d %s\n" % (c[2], len(c[3]), " ".join("%d %d" % s for s in c[3])) for c in cases)
+        res = subprocess.run([driver, str(heads[0]), str(heads[1])], input=text, capture_output=True, text=True, timeout=60)
+        assert res.returncode == 0, res.stderr
+        assert list(zip([c[2:4] for c in cases], res.stdout.split())) == [(c[2:4], c[4]) for c in cases]
