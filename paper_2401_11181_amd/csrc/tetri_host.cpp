@@ -498,36 +498,54 @@ static bool plan_short(const tetri_ctx *h, const int32_t *cu, const int32_t *ctx
     if (h->split_keys && 2 * wgs <= cus && wgs <= h->n_counters)
         p.splits = (int32_t)std::max<int64_t>(1, std::min(std::min<int64_t>(cus / wgs, 16), std::min<int64_t>((most + 7) / 8, units_fit)));
     // ---- the shape of the launch.  A row block of one head is the work of a team of 1, 2, 4 or 8 wavefronts: as many as leave at
-    // most `cap` steps to each, cap the least for which all wavefronts of the launch are on the chip at once.  (Teams of one
-    // size made the launch as long as its longest row block: 64 packed chunks of 40 heads 18.0 us each, now 15.8.)
+    // most `cap` steps to each, cap the least for which all workgroups of the launch are on the chip at once.  (Teams of one
+    // size made the launch as long as its longest row block: 64 packed chunks of 40 heads 18.0 us each, now 15.8.  Counted in
+    // wavefronts instead of workgroups, a launch could need a few workgroups more than there is room for: 512 rows of 40 heads at 100
+    // cached tokens 20.3 us (FP8 25.3), now 17.2 (20.3).)
     const int Hkv = h->cfg.num_kv_heads;
     p.rshift = Hkv % 8 == 0 ? 3 : (Hkv % 4 == 0 ? 2 : (Hkv % 2 == 0 ? 1 : 0));
     p.hpx = (int32_t)Hq >> p.rshift;
     p.hkx = Hkv >> p.rshift;
-    // workgroups of 8 wavefronts, one to a compute unit, where there are no more row blocks than that; else of 4
-    const int nwl = p.splits > 1 || (wgs <= room && most > 4) ? 3 : 2;
-    const int64_t slots = 8 * room;
-    // (of a row block of n steps, at most `cap` to a wavefront)
-    auto team = [&](int32_t st, int32_t cap) { int t = 0; while (t < nwl && (cap << t) < st) ++t; return t; };
-    int32_t cap = 1;
-    for (; cap < most; cap += std::max(1, cap / 4)) {
-        int64_t waves = 0;
-        for (int i = 0; i < n; ++i) waves += Hq << team(units[i].steps, cap);
-        if (waves <= slots) break;
-    }
-    int32_t longest = 0;              // steps on a wavefront
-    for (int i = 0; i < n; ++i) longest = std::max(longest, (units[i].steps + (1 << team(units[i].steps, cap)) - 1) >> team(units[i].steps, cap));
     p.spread = wgs <= cus;
-    int32_t first_wg = 0;
-    for (int tl = 3, i = 0; tl >= 0; --tl) {
-        const int begin = i;
-        p.first_wg[tl] = first_wg;
-        p.first_unit[tl] = begin;
-        while (i < n && (p.splits > 1 ? nwl : team(units[i].steps, cap)) == tl) ++i;
-        const int64_t per = p.spread ? 1 : ((int64_t)1 << nwl) >> tl;  // teams of a workgroup
-        if (i > begin) first_wg += (int32_t)((((int64_t)(i - begin) * p.hpx + per - 1) / per << p.rshift) * p.splits);
+    // (of a row block of n steps, at most `cap` to a wavefront)
+    auto team = [](int32_t st, int32_t cap, int nwl) { int t = 0; while (t < nwl && (cap << t) < st) ++t; return t; };
+    auto lay_out = [&](int nwl, int32_t cap) -> int32_t {
+        int32_t first_wg = 0;
+        for (int tl = 3, i = 0; tl >= 0; --tl) {
+            const int begin = i;
+            p.first_wg[tl] = first_wg;
+            p.first_unit[tl] = begin;
+            while (i < n && (p.splits > 1 ? nwl : team(units[i].steps, cap, nwl)) == tl) ++i;
+            const int64_t per = p.spread ? 1 : ((int64_t)1 << nwl) >> tl;  // teams of a workgroup
+            if (i > begin) first_wg += (int32_t)((((int64_t)(i - begin) * p.hpx + per - 1) / per << p.rshift) * p.splits);
+        }
+        return first_wg;
+    };
+    // the least cap for which all workgroups are on the chip at once, and the steps on a wavefront
+    auto search = [&](int nwl, int32_t &longest) -> int32_t {
+        int32_t cap = 1;
+        while (cap < most && lay_out(nwl, cap) > 8 * room >> nwl) cap += std::max(1, cap / 4);
+        longest = 0;
+        for (int i = 0; i < n; ++i) {
+            const int t = team(units[i].steps, cap, nwl);
+            longest = std::max(longest, (units[i].steps + (1 << t) - 1) >> t);
+        }
+        return cap;
+    };
+    // Workgroups of 8 wavefronts, one to a compute unit, where there are no more row blocks than that; else of 4, unless those
+    // of 8, whose longest row blocks have teams of 8, leave at most 0.7 times as many steps to a wavefront: timed on 280 chunks of
+    // 40, 32/8, 24/8 and 8/2 heads of 128, 224 to 2048 rows, 0 to 2000 cached tokens, 0.79 to 1.0 of the time where they are
+    // chosen (384 rows of 32/8 heads in segments at 50, 300 and 700: 14.4 us, now 11.4), 1.03 to 1.2 where they are not; head_dim 64: never
+    // (0.86 to 1.16).
+    int32_t longest = 0;
+    int nwl = p.splits > 1 || (wgs <= room && most > 4) ? 3 : 2;
+    int32_t cap = search(nwl, longest);
+    if (nwl == 2 && longest > 3 && h->cfg.head_dim == 128) {
+        int32_t longest8;
+        const int32_t cap8 = search(3, longest8);
+        if (10 * longest8 <= 7 * longest) { nwl = 3; cap = cap8; longest = longest8; }
     }
-    p.attn_wgs = first_wg;
+    p.attn_wgs = lay_out(nwl, cap);
     shape.nwl = nwl;
     // Where this kernel is the faster one (both timed on 650 chunks of 40x128, 32/8x128, 24/8x128, 16x128, 16/2x128 and 8/2x128 heads, 32 to
     // 1024 rows in 1 to 10 segments, 0 to 32000 cached tokens; times as a part of the shared-tile kernel's, FP8 codes in brackets):

@@ -17,6 +17,7 @@ CASES = {
     "many-heads": (40, 40, 128, [(17, 900), (70, 160), (1, 1), (31, 32), (64, 0), (300, 0)]),
     "odd-heads": (24, 8, 128, [(100, 1500), (37, 95), (63, 0), (200, 0)]),
     "one-to-a-workgroup": (6, 3, 128, [(40, 450), (60, 97), (32, 0)]),
+    "eight-wavefronts-in-packs": (32, 8, 128, [(120, 50), (128, 301), (97, 700), (33, 0)]),
     "long": (24, 8, 128, [(500, 3003)]),
     "head-dim-64": (12, 4, 64, [(33, 1203), (64, 129), (90, 0), (301, 17), (2, 600)]),
     "head-dim-64-many": (40, 40, 64, [(50, 1100), (400, 30), (128, 0)]),
