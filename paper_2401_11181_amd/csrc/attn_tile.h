@@ -455,7 +455,8 @@ __device__ __forceinline__ void request_q(const AttnParams &p, const Job &J, int
 // per instruction, to a place of its own in the other stage buffer (q_lds), and from there, once they have arrived, as fragments.
 // (As fragments straight from memory each instruction asks for 32 bytes of 32 rows, and the stage's loads go out behind them or
 // wait for the page ids in front of them: the first stage was there 5.5 us after the launch's start, now 4.7; 16384 tokens of 40 heads in
-// 32 chunks -0.5 to -1.5 %, 32/8 heads over FP8 codes -0.4 to -1.5 %.)
+// 32 chunks -0.5 to -1.5 %, 32/8 heads over FP8 codes -0.4 to -1.5 %.  In the launch that divides itself, 512 rows of 40 heads at 1536 and
+// 2048 cached tokens: 40.1 -> 39.8 us and 45.1 -> 43.7, over codes 44.5 -> 43.6.)
 template <int D>
 __device__ __forceinline__ void request_q_rows(const AttnParams &p, const Job &J, int head, int rbk, int lane, uint32_t q_lds)
 {

@@ -397,6 +397,9 @@ __global__ __launch_bounds__(Shape<KS>::WAVES * 64, 2) void attn_tile_kernel(Att
     Carry<D> cy;
     cy.par = J.it_begin & 1;                         // the first stage goes to buffer 0
     {
+        // the job's Q rows, by way of the second stage buffer (its first loads go out behind the job's first barrier)
+        char *q_tile = reinterpret_cast<char *>(smem + (wave < Shape<KS>::WAVES / 2 ? 1 : 3) * STAGE_U4) + (wave % (Shape<KS>::WAVES / 2)) * (32 * D * 2);
+        request_q_rows<D>(p, J, grp * p.hpw + (slot & (p.hpw - 1)), slot >> p.hpw_shift, lane, lds_address(q_tile));
         const int new_row_bytes = p.Hkv * D * 2;
         LaneOffsets<D> lo;
         init_lane_offsets<D>(lo, lane);
@@ -415,6 +418,7 @@ __global__ __launch_bounds__(Shape<KS>::WAVES * 64, 2) void attn_tile_kernel(Att
             const bool full = describe_stage_loads<D, KS, F8>(J.src, ws, lo, page, J.it_begin, wave, new_row_bytes, lds_address(smem), sl);
             fetch_stage_codes<D>(sl, full, cy.codes);
             cy.have_codes = true;
+            wait_vm<0>();
         } else if (kq == 0) {
             if (J.it_begin != 0 || !pages_fetched) {     // the lookup fetched the pages of stage 0 of its first tile
                 page = row_entry(J.it_begin * PPS + wave);
@@ -427,10 +431,12 @@ __global__ __launch_bounds__(Shape<KS>::WAVES * 64, 2) void attn_tile_kernel(Att
                                                               new_row_bytes, lds_address(smem), sl);
                 issue_stage_loads<D, KS>(sl, full);
             }
+            wait_vm<Shape<KS>::PARTS * 2 * (D / 32)>();      // (all but the stage's)
+        } else {
+            wait_vm<0>();
         }
         cy.page = row_entry((J.it_begin + 1) * PPS + wave);
-        const int hh = slot & (p.hpw - 1), rbk = slot >> p.hpw_shift;
-        request_q<D>(p, J, grp * p.hpw + hh, rbk, lane, cy.qf);
+        read_q_rows<D>(q_tile, lane, cy.qf);
     }
     TETRI_MARK(1);
 
