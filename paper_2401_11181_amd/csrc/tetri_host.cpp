@@ -581,9 +581,11 @@ static bool plan_short(const tetri_ctx *h, const int32_t *cu, const int32_t *ctx
 static int32_t plan_tiles(const tetri_ctx *h, const int32_t *cu, const int32_t *ctx_lens, int32_t num_segs, const AttnParams &p, TilePlan &plan)
 {
     constexpr int kStage = 128;
-    constexpr int kSlack = 1;         // a remainder of this many stages stays with the piece before it
-    constexpr int kMinPiece = 3;      // the shortest pieces a tile is cut into
-    constexpr int kJobCost = 1;       // a workgroup's further jobs: what each costs besides its stages, in stages
+    // (timed on 120 chunks of 40, 32/8 and 8/2 heads, 256 to 2048 rows, 0 to 13000 cached tokens, both shapes: against pieces of at least
+    // 3 stages, 1 for a further job and remainders one stage longer than q 1.0 to 2.0 % on average, 300 rows at 1000 and 212 at 200 cached
+    // tokens of 32/8 heads 25 %; 3 or 4 for a further job the same or less)
+    constexpr int kMinPiece = 2;      // the shortest pieces a tile is cut into
+    constexpr int kJobCost = 2;       // a workgroup's further jobs: what each costs besides its stages, in stages
     const int wgs = (std::max(h->num_cus, 8) / 8) << p.span_shift, pools = 8 >> p.span_shift, rows = 32 * p.rb;
     if (num_segs > kPlanSegs || p.C > 0xffff || wgs > kPlanJobs || p.gpx > 1023) return 0;
     struct Item { int32_t n; uint16_t seg, grp, t0, begin; uint16_t place; uint8_t piece, npieces; };
@@ -612,7 +614,7 @@ static int32_t plan_tiles(const tetri_ctx *h, const int32_t *cu, const int32_t *
         bool fits = true;
         for (int i = 0; i < nt && fits; ++i) {
             Item it = tiles[i];
-            const int cuts = it.n <= q + kSlack ? 0 : (it.n - kSlack - 1) / q;
+            const int cuts = (it.n - 1) / q;
             if (cuts > 0) {
                 if (cuts > 254 || places + cuts + 1 > places_fit || full + cuts > wgs) { fits = false; break; }
                 it.npieces = (uint8_t)(cuts + 1);
@@ -645,7 +647,7 @@ static int32_t plan_tiles(const tetri_ctx *h, const int32_t *cu, const int32_t *
                 if ((to == nullptr || bins[k].load < to->load) && !(is_piece && bins[k].tail >= 0)) to = &bins[k];
             const bool empty = to != nullptr && to->first < 0 && to->tail < 0;
             const int32_t load = to == nullptr ? 0 : to->load + rest[i].n + (empty ? 0 : kJobCost);
-            if (to == nullptr || (load > q + kSlack && q < longest)) { fits = false; break; }
+            if (to == nullptr || (load > q && q < longest)) { fits = false; break; }
             to->load = load;
             if (is_piece && to->first >= 0 && rest[to->first].npieces > 1) {
                 to->tail = (int16_t)i;
@@ -692,9 +694,9 @@ static int32_t plan_tiles(const tetri_ctx *h, const int32_t *cu, const int32_t *
 // barriers for the same work (gqa, 16384 rows of 4 x 32 heads at 12000 cached tokens: 3.5 us for 8 blocks per SIMD, with 4 slots 2.1
 // us for 4); with 4 the pieces are half as long, which divides short launches better.  Which slots a chunk may have: 4 below 30000 steps of
 // 32 keys x 32 rows, 8 from 75000 on; in between both divisions are laid out and their longest workgroups compared: 4 where it has
-// fewer than 1.7 times the stages of 8 and 2 more.  Timed on 127 chunks of the 16-bit and the FP8 cache (40x128, 32/8, 24/8 and 16
-// heads, 256 to 2048 rows, 0 to 8000 cached tokens): 0.7 % on average against the better shape each time, 9 % at most (by the number
-// of steps alone 1.3 % and 21 %).  None: where the launch that divides itself fills the chip with row tiles and their helpers, whose
+// fewer stages than 1.7 times those of 8 and half a stage for each piece that the tiles of 8 are cut into (the merge).  Timed on 33 such
+// chunks of the 16-bit and the FP8 cache (40x128, 32/8 and 8/2 heads, 256 to 2048 rows, 0 to 13000 cached tokens): 0.4 % on average
+// against the better shape each time, 6 % at most (without the merge 2.5 % and 26 %, by the number of steps alone 1.3 % and 21 %).  None: where the launch that divides itself fills the chip with row tiles and their helpers, whose
 // wavefronts walk a head's keys side by side (an odd number of query heads to a kv head, evenly spread work, under 50000 steps: 512 rows of
 // 40 heads at 1000 cached tokens 34.3 us (FP8 37.8) against 38.2 (44.2); at 2560, 56000 steps, 48.2 against 46.8; 384 rows,
 // which fill 200 compute units: 41.0 against 37.3).
@@ -800,7 +802,9 @@ static tetri_status attn_common(const char *fn, tetri_ctx *h, const void *q, con
             load[i] = plan_tiles(h, host_cu, host_ctx, num_segs, x, plans[i]);
         }
         if (load[0] + load[1] != 0) {
-            const int pick = load[1] == 0 || (load[0] != 0 && 10 * load[0] < 17 * load[1] + 20) ? 0 : 1;
+            int32_t pieces = 0;                        // of a tile of the second
+            for (int w = 0; load[1] != 0 && w < plans[1].wgs; ++w) pieces = std::max<int32_t>(pieces, plans[1].job[w].npieces);
+            const int pick = load[1] == 0 || (load[0] != 0 && 10 * load[0] < 17 * load[1] + 5 * pieces) ? 0 : 1;
             const TilePlan &plan = plans[pick];
             p = shapes[pick];
             if (plan.places != 0 && (st = claim_scratch(h, fn, hs, false)) != TETRI_OK) return st;
