@@ -9,7 +9,7 @@
 // of the kernel arguments away (1.0 us), and its new K and V rows go to their pages out of the stage buffers instead of through
 // further workgroups.  With 8 slots a staged key serves 256 rows: half the bytes into LDS and half the barriers per product.
 // What bounds it: the loop (attn_tile.h), 3.5 us for 8 blocks of 32 x 32 on each SIMD with the chip's clock at 1.8 to 2.05 GHz under
-// that load; where tiles are shared, about 8 us from the end of the loops to the last row written.
+// that load; where tiles are shared, 6.6 us from the end of the last loop to the last row written.
 // 2048 rows of 32/8 heads at 20000 cached tokens 688 -> 618 us, 300 rows at 20000 and 1700 at 0 371 -> 153, 512 rows of 40 heads at
 // 8000 111 -> 103, 512 rows of 32/8 heads over FP8 codes at 3000 59.6 -> 49.6.
 #include "attn_tile.h"
