@@ -87,15 +87,21 @@ typedef struct {
 
 /*
  * Create / destroy a handle carrying the static shape.  The handle owns a fixed amount of device
- * scratch memory (about 34 MB on a 256-CU device, allocated here, freed by tetri_destroy) on the
+ * scratch memory (on a 256-CU device about 102 MB, at head_dim 64 17 MB; allocated here, freed by tetri_destroy) on the
  * device that is current at creation; launching calls must be made with that device current.
- * The chunk-prefill calls (launches small enough to be divided over the compute units by stages rather than by
- * row tiles, or to split the keys of their row blocks) and the decode calls (where they split requests) keep
- * partial results there: such launches on one
- * handle must not overlap in time; use one handle per stream that runs concurrently.  A chunk-prefill call
- * returns TETRI_ERR_INVALID_ARG when the handle's previous such chunk-prefill launch went to another stream and that
- * stream still has work pending (synchronise the two streams, or use a handle each); decode calls neither check
- * nor are checked for: order the streams, for instance by events.  No state survives from one
+ * Partial results are kept there, in two parts.
+ *   - One part is shared by the chunk-prefill launches that divide themselves (all without host metadata, and those with it that
+ *     "attn_variant" below names) where they are small enough to be divided over the compute units by stages rather than by row
+ *     tiles, by those for little work that split the keys of their row blocks, and by the decode calls where they split
+ *     requests: such launches on one handle must not overlap in time; use one handle per stream that runs concurrently.  A
+ *     chunk-prefill call returns TETRI_ERR_INVALID_ARG when the handle's previous such chunk-prefill launch went to another
+ *     stream and that stream still has work pending (synchronise the two streams, or use a handle each); decode calls neither
+ *     check nor are checked for: order the streams, for instance by events.
+ *   - Launches on a division made by the host (tetri_chunk_prefill_planned, tetri_batch_launch), which cut row tiles of launches
+ *     of any size, have memory of their own and may overlap the others and each other on several streams.  There is room for
+ *     those of the first stream that makes one and for one more stream at a time; a launch beside those two cuts no tile (the
+ *     same function to the same tolerance, not the same bits, and slower).
+ * No state survives from one
  * launch to the next: a launch sets the arrival counters it used back to zero, and the handle's launches take turns
  * with several sets of them, each of which another launch zeroes once more before its turn comes again (after
  * launches that wrongly overlapped, their own results are lost, not those of later launches).  A launch in a HIP
@@ -436,19 +442,21 @@ TETRI_API tetri_status tetri_validate_chunk(tetri_ctx *ctx, const int32_t *block
  *   "attn_variant"      0 = the library chooses the workgroup size (8 wavefronts; 4, two workgroups to a
  *                       compute unit, when a full chunk alone gives five row tiles per four compute units or
  *                       more) and, where it is told the chunk's segments (tetri_chunk_prefill_planned, tetri_batch_launch),
- *                       whether the chunk goes to the kernel for chunks with little work (not once one of the
- *                       split_* options or stream_wgs has been set, and not under graph capture); 1 / 2 = 4- / 8-wavefront
- *                       workgroups; 3 = that kernel wherever its tables hold the chunk; 4 / 5 = a division of the
- *                       launch made on the host, with row tiles of 8 / 4 (head, 32-row block) slots, wherever the call
- *                       knows the chunk's segments and the tables hold it (head_dim 128);
- *   "split_keys"        1 (default) = a launch with fewer than five row tiles per four compute units divides the key
- *                       ranges of its tiles among more workgroups than it has tiles.  If the tiles and one helper
+ *                       whether the chunk goes to the kernel for chunks with little work, to a division of the launch made on the
+ *                       host or to the launch that divides itself (always the last once one of the
+ *                       split_* options or stream_wgs has been set, and under graph capture); 1 / 2 = 4- / 8-wavefront
+ *                       workgroups of that launch; 3 = the kernel for chunks with little work wherever its tables hold
+ *                       the chunk; 4 / 5 = a division of the launch made on the host, with row tiles of 8 / 4 (head, 32-row
+ *                       block) slots, wherever the call knows the chunk's segments and the tables hold it (head_dim 128);
+ *   "split_keys"        1 (default) = a launch that divides itself, with fewer than five row tiles per four compute units, divides
+ *                       the key ranges of its tiles among more workgroups than it has tiles (a launch on the host's division of any
+ *                       size: see attn_variant 4 / 5).  If the tiles and one helper
  *                       workgroup per two tiles fit the compute units, every tile with a long key range hands the
  *                       tail of it to its helper; otherwise (and only for chunks whose segments have 256 rows or
  *                       more on average, and at most 64 segments) the stages (64 or 128 keys each) of all row
  *                       tiles of a head group are laid end to end and every workgroup of the group gets an equal
  *                       range of them.  Tiles shared by several workgroups are finished from partial results in
- *                       the handle's scratch memory (see tetri_create).  0 = always one workgroup per row tile;
+ *                       the handle's scratch memory (see tetri_create).  0 = no tile is shared;
  *   "split_min_stages"  tails: key ranges of fewer stages than this are not divided (default 8; at least 2);
  *   "split_bias_stages" tails: stages a tile keeps before the rest is shared (default 6; not negative);
  *   "split_share_q8"    tails: share of that rest the helper takes, in 1/256 (default 85; 1..128);

@@ -81,7 +81,8 @@ tetri_status tetri_create(const tetri_config *c, tetri_ctx **out)
     // a launch has at most one workgroup per CU, 4 (row block, head) slots each, and a workgroup leaves at
     // most two partial results per slot (its first and its last job); a partial result is O (32 x head_dim
     // floats), m and the row sum.  Arrival counters: one per (head group, row tile, slot), fewer than two
-    // tiles per CU in such a launch; several sets, used in turn.
+    // tiles per CU in such a launch; several sets, used in turn.  As much twice more for launches on a division of the
+    // host's, whose kernels are for head_dim 128.
     hipDeviceProp_t prop;
     if ((e = hipGetDevice(&h->device)) != hipSuccess || (e = hipGetDeviceProperties(&prop, h->device)) != hipSuccess) {
         delete h;
@@ -91,12 +92,18 @@ tetri_status tetri_create(const tetri_config *c, tetri_ctx **out)
     h->scratch_units = (size_t)h->num_cus * 4;
     h->unit_bytes = (size_t)32 * c->head_dim * 4 + 2 * 32 * 4;
     h->n_counters = (int32_t)(2 * h->scratch_units);
-    const size_t counter_bytes = kCounterSets * (size_t)h->n_counters * sizeof(int32_t) + 256;
-    if ((e = hipMalloc(reinterpret_cast<void **>(&h->scratch), 2 * h->scratch_units * h->unit_bytes)) != hipSuccess ||
+    const size_t copies = c->head_dim == 128 ? 3 : 1, scratch_bytes = 2 * h->scratch_units * h->unit_bytes;
+    const size_t set_bytes = kCounterSets * (size_t)h->n_counters * sizeof(int32_t), counter_bytes = set_bytes + 256 + (copies - 1) * set_bytes;
+    if ((e = hipMalloc(reinterpret_cast<void **>(&h->scratch), copies * scratch_bytes)) != hipSuccess ||
         (e = hipMalloc(reinterpret_cast<void **>(&h->counters), counter_bytes)) != hipSuccess ||
-        (e = hipMemset(h->counters, 0, counter_bytes)) != hipSuccess) {
+        (e = hipMemset(h->counters, 0, counter_bytes)) != hipSuccess ||
+        (e = hipEventCreateWithFlags(&h->plan_done, hipEventDisableTiming)) != hipSuccess) {
         tetri_destroy(h);
         return fail(nullptr, TETRI_ERR_HIP, "tetri_create: scratch memory: %s", hipGetErrorString(e));
+    }
+    for (size_t i = 1; i < copies; ++i) {
+        h->plan_memory[i - 1].scratch = h->scratch + i * scratch_bytes;
+        h->plan_memory[i - 1].counters = h->counters + (256 + i * set_bytes) / sizeof(int32_t);
     }
     // the static memory of tetri_decode_attn_static: its addresses on this device, looked up here so that the
     // entry point itself makes no runtime call besides the launch
@@ -113,6 +120,8 @@ void tetri_destroy(tetri_ctx *ctx)
     if (!ctx) return;
     if (ctx->scratch) (void)hipFree(ctx->scratch);
     if (ctx->counters) (void)hipFree(ctx->counters);
+    if (ctx->plan_lent) (void)hipEventSynchronize(ctx->plan_done);
+    if (ctx->plan_done) (void)hipEventDestroy(ctx->plan_done);
     delete ctx;
 }
 
@@ -449,6 +458,23 @@ static void scratch_claimed(tetri_ctx *h, hipStream_t hs)
     h->divide_launched = true;
 }
 
+// Which of the handle's two memories for partial results a launch on a division of the host's may use on stream hs: 0, 1 or, where
+// another stream's launch is still at work in the one it would get, -1: none.  No call names another stream than hs: it may
+// be capturing by now, or gone.  (hipStreamPerThread is another stream in every thread.)
+static int plan_memory(const tetri_ctx *h, hipStream_t hs)
+{
+    const bool named = hs != hipStreamPerThread;
+    if (named && (!h->plan_owned || h->plan_owner == hs)) return 0;
+    if (!h->plan_lent || (named && h->plan_borrower == hs) || hipEventQuery(h->plan_done) == hipSuccess) return 1;
+    return -1;
+}
+static void plan_memory_used(tetri_ctx *h, int mem, hipStream_t hs)
+{
+    ++h->plan_memory[mem].turn;
+    (mem == 0 ? h->plan_owned : h->plan_lent) = true;
+    (mem == 0 ? h->plan_owner : h->plan_borrower) = hs;
+}
+
 struct ShortShape {
     int nwl;                          // log2 of a workgroup's wavefronts
     bool preferred;
@@ -577,8 +603,8 @@ static bool plan_short(const tetri_ctx *h, const int32_t *cu, const int32_t *ctx
 // The work of a pool (its head groups' tiles) goes to one workgroup per compute unit so that all end together: a tile longer
 // than q stages is cut into pieces of q for a workgroup each, the remainders and the tiles that are shorter are packed, the
 // longest first, into the workgroups that are left; q is the smallest for which they fit.  Returns the longest workgroup's stages, 0 if the
-// tables do not hold the division.
-static int32_t plan_tiles(const tetri_ctx *h, const int32_t *cu, const int32_t *ctx_lens, int32_t num_segs, const AttnParams &p, TilePlan &plan)
+// tables do not hold the division.  share: tiles may be cut at all.
+static int32_t plan_tiles(const tetri_ctx *h, const int32_t *cu, const int32_t *ctx_lens, int32_t num_segs, const AttnParams &p, bool share, TilePlan &plan)
 {
     constexpr int kStage = 128;
     // (timed on 120 chunks of 40, 32/8 and 8/2 heads, 256 to 2048 rows, 0 to 13000 cached tokens, both shapes: against pieces of at least
@@ -607,7 +633,7 @@ static int32_t plan_tiles(const tetri_ctx *h, const int32_t *cu, const int32_t *
     std::sort(tiles, tiles + nt, [](const Item &a, const Item &b) { return a.n > b.n; });
     const int64_t places_fit = std::min<int64_t>((int64_t)(2 * h->scratch_units), h->n_counters) / (p.hpw * p.rb * pools);
     for (int32_t q = (int32_t)std::max<int64_t>((total + wgs - 1) / wgs, kMinPiece);; q += std::max(1, q / 64)) {
-        if (!h->split_keys) q = std::max(q, longest);
+        if (!share) q = std::max(q, longest);
         // pieces of q stages, a workgroup each; what remains is packed
         Item rest[kPlanJobs];
         int nr = 0, full = 0, places = 0, jobs = 0;
@@ -790,6 +816,7 @@ static tetri_status attn_common(const char *fn, tetri_ctx *h, const void *q, con
         AttnParams shapes[2];                          // 4 and 8 slots
         int32_t load[2] = {0, 0};
         const SlotChoice may = planned_slots(h, host_cu, host_ctx, num_segs);
+        const int mem = may.four || may.eight ? plan_memory(h, hs) : -1;
         for (int i = 0; i < 2; ++i) {
             if (!(i == 0 ? may.four : may.eight)) continue;
             AttnParams &x = shapes[i] = p;
@@ -799,15 +826,17 @@ static tetri_status attn_common(const char *fn, tetri_ctx *h, const void *q, con
             x.rb_shift = log2i(x.rb);
             x.span_shift = x.groups <= 1 ? 3 : (x.groups <= 2 ? 2 : (x.groups <= 4 ? 1 : 0));
             x.gpx = (x.groups + (8 >> x.span_shift) - 1) / (8 >> x.span_shift);
-            load[i] = plan_tiles(h, host_cu, host_ctx, num_segs, x, plans[i]);
+            load[i] = plan_tiles(h, host_cu, host_ctx, num_segs, x, h->split_keys && mem >= 0, plans[i]);
         }
         if (load[0] + load[1] != 0) {
             int32_t pieces = 0;                        // of a tile of the second
             for (int w = 0; load[1] != 0 && w < plans[1].wgs; ++w) pieces = std::max<int32_t>(pieces, plans[1].job[w].npieces);
             const int pick = load[1] == 0 || (load[0] != 0 && 10 * load[0] < 17 * load[1] + 5 * pieces) ? 0 : 1;
-            const TilePlan &plan = plans[pick];
+            TilePlan &plan = plans[pick];
             p = shapes[pick];
-            if (plan.places != 0 && (st = claim_scratch(h, fn, hs, false)) != TETRI_OK) return st;
+            int dev = -1;
+            if (plan.places != 0 && (hipGetDevice(&dev) != hipSuccess || dev != h->device))
+                return fail(h, TETRI_ERR_INVALID_ARG, "%s: the current device is %d, the handle was created on device %d", fn, dev, h->device);
             p.plan = &plan;
             p.gpx_magic = magic((uint32_t)p.gpx);
             p.kv_magic = magic((uint32_t)(p.g / p.hpw));
@@ -815,17 +844,16 @@ static tetri_status attn_common(const char *fn, tetri_ctx *h, const void *q, con
             p.attn_grid = 8 * ((plan.wgs + (1 << p.span_shift) - 1) >> p.span_shift);
             p.attn_first = p.attn_grid;
             p.append_blocks = 0;                    // (the workgroups cache the rows of their tiles)
-            p.scratch = h->scratch;
+            PlanMemory &memory = h->plan_memory[std::max(mem, 0)];
+            p.scratch = memory.scratch;
             p.n_counters = h->n_counters;
-            const CounterSets cs = counter_sets(h->counters, h->n_counters, h->counter_turn);
+            const CounterSets cs = counter_sets(memory.counters, h->n_counters, memory.turn);
             p.counters = cs.use;
             p.counters_next = cs.clear;
+            plan.done = plan.places != 0 && mem == 1 ? h->plan_done : nullptr;
             hipError_t e = tetri_launch_attn(h, p, 2, fp8, hs);
             if (e != hipSuccess) return fail(h, TETRI_ERR_HIP, "%s: launch failed: %s", fn, hipGetErrorString(e));
-            if (plan.places != 0) {
-                ++h->counter_turn;
-                scratch_claimed(h, hs);
-            }
+            if (plan.places != 0) plan_memory_used(h, mem, hs);
             return TETRI_OK;
         }
     }

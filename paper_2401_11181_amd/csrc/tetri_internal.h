@@ -29,10 +29,18 @@ struct DecodeStatic {
     std::atomic<uint32_t> *turn = nullptr;  // the set of the device's next such call
 };
 
+// Partial results and arrival counters of launches on a division of the host's, which cuts tiles of launches of any size: apart
+// from the handle's other scratch memory (decode, launches that divide themselves), whose users such launches may overlap.
+struct PlanMemory {
+    char *scratch = nullptr;        // 2 x scratch_units units
+    int32_t *counters = nullptr;    // kCounterSets sets of n_counters
+    uint32_t turn = 0;
+};
+
 struct tetri_ctx {
     tetri_config cfg;
     std::string err;
-    int attn_variant = 0;   // 0 = library's choice, 1 / 2 = shared-tile kernel with 1 / 2 key parts
+    int attn_variant = 0;   // 0 = library's choice, 1 / 2 = shared-tile kernel with 1 / 2 key parts, 3 = short kernel, 4 / 5 = host's division with 8 / 4 slots
     int split_keys = 1;     // 1 = launches with fewer than two row tiles per CU divide the stages of every head group evenly over the CUs
     int stream_wgs = 0;     // workgroups per head group of such a launch (0: as many as the device has CUs for); > 0 forces the mode
     int split_min_stages = 8;   // tail mode: the shortest key range that hands its tail to a helper workgroup
@@ -52,6 +60,12 @@ struct tetri_ctx {
     bool divide_launched = false;       // a prefill launch has used scratch and counters ...
     hipStream_t last_divide_stream = nullptr;   // ... the last one on this stream
     DecodeStatic decode_static;         // this device's memory of tetri_decode_attn_static
+    // The first stream with such a launch owns the first of these for good (its launches follow each other: no event, which costs
+    // a launch 0.5 to 0.9 us); all others take turns with the second, each launch signalling an event.
+    PlanMemory plan_memory[2];
+    bool plan_owned = false, plan_lent = false;     // the first has an owner, the second a last user
+    hipStream_t plan_owner = nullptr, plan_borrower = nullptr;     // (compared, never named to the runtime: they may be gone)
+    hipEvent_t plan_done = nullptr;     // the second's last launch
 };
 
 // The shared-tile kernel on a division made by the host (tetri_planned.hip): the jobs travel in the kernel arguments.  The eight
@@ -74,6 +88,7 @@ struct __attribute__((aligned(16))) TilePlan {
     int32_t places;               // partial results of a pool (0: no tile is shared)
     int32_t wgs;                  // workgroups of a pool
     int32_t pad;
+    hipEvent_t done;              // for the host: signalled when the launch has ended (null: none)
 };
 
 // Launch parameters of the attention kernels (passed by value).

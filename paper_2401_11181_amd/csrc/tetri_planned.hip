@@ -12,6 +12,8 @@
 // that load; where tiles are shared, 6.6 us from the end of the last loop to the last row written.
 // 2048 rows of 32/8 heads at 20000 cached tokens 688 -> 618 us, 300 rows at 20000 and 1700 at 0 371 -> 153, 512 rows of 40 heads at
 // 8000 111 -> 103, 512 rows of 32/8 heads over FP8 codes at 3000 59.6 -> 49.6.
+#include <hip/hip_ext.h>
+
 #include "attn_tile.h"
 
 namespace {
@@ -150,12 +152,10 @@ __global__ __launch_bounds__(Shape<KS>::WAVES * 64, 2) void attn_planned_kernel(
 hipError_t tetri_launch_planned(const AttnParams &p, bool fp8_pool, hipStream_t stream)
 {
     static_assert(sizeof(AttnParams) + sizeof(TilePlan) + 16 <= 4096, "kernel arguments");
-    if (p.hpw * p.rb == 4) {
-        if (fp8_pool) hipLaunchKernelGGL((attn_planned_kernel<128, 2, true>), dim3(p.attn_grid), dim3(512), 0, stream, p, *p.plan);
-        else hipLaunchKernelGGL((attn_planned_kernel<128, 2, false>), dim3(p.attn_grid), dim3(512), 0, stream, p, *p.plan);
-        return hipGetLastError();
-    }
-    if (fp8_pool) hipLaunchKernelGGL((attn_planned_kernel<128, 3, true>), dim3(p.attn_grid), dim3(512), 0, stream, p, *p.plan);
-    else hipLaunchKernelGGL((attn_planned_kernel<128, 3, false>), dim3(p.attn_grid), dim3(512), 0, stream, p, *p.plan);
+    auto kernel = p.hpw * p.rb == 4 ? (fp8_pool ? attn_planned_kernel<128, 2, true> : attn_planned_kernel<128, 2, false>)
+                                    : (fp8_pool ? attn_planned_kernel<128, 3, true> : attn_planned_kernel<128, 3, false>);
+    // (the event rides on the kernel's own completion signal)
+    if (p.plan->done) hipExtLaunchKernelGGL(kernel, dim3(p.attn_grid), dim3(512), 0, stream, nullptr, p.plan->done, 0, p, *p.plan);
+    else hipLaunchKernelGGL(kernel, dim3(p.attn_grid), dim3(512), 0, stream, p, *p.plan);
     return hipGetLastError();
 }

@@ -41,10 +41,13 @@ struct Counters {
 std::vector<Counters> g_counters;
 int g_parts = 0, g_ranges = 0;                // how the last decode was cut
 std::string g_kernel;                         // the attention kernel launched last
+const char *g_partials = nullptr;             // where the last attention or decode launch keeps partial results
+int g_places = 0;                             // of the last division made by the host: tiles' pieces there
 
 struct Event { bool pending = false; };       // pending: work in front of it that nobody has waited for
 Event &event(hipEvent_t e) { return *reinterpret_cast<Event *>(e); }
 hipStream_t g_destroyed = nullptr;            // a stream that no longer exists
+bool g_busy = false;                          // every stream has work pending
 struct Upload {
     const int32_t *pinned;
     hipEvent_t done;
@@ -84,7 +87,7 @@ hipError_t hipFree(void *p)
 hipError_t hipMemset(void *p, int v, size_t n) { std::memset(p, v, n); return hipSuccess; }
 hipError_t hipMemcpy(void *d, const void *s, size_t n, hipMemcpyKind) { std::memcpy(d, s, n); return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
-hipError_t hipStreamQuery(hipStream_t s) { CHECK(s != g_destroyed); return hipSuccess; }
+hipError_t hipStreamQuery(hipStream_t s) { CHECK(s == nullptr || s != g_destroyed); return g_busy ? hipErrorNotReady : hipSuccess; }
 hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus *s) { *s = hipStreamCaptureStatusNone; return hipSuccess; }
 hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned)
 {
@@ -112,7 +115,12 @@ hipError_t hipPointerGetAttributes(hipPointerAttribute_t *a, const void *) { a->
 hipError_t tetri_launch_attn(const tetri_ctx *, const AttnParams &p, int, bool, hipStream_t)
 {
     g_kernel = "shared";
-    if (p.stream_wgs > 0 || p.helpers > 0) g_counters.push_back({p.counters, p.counters_next, p.n_counters});
+    g_partials = p.scratch;
+    if (p.plan != nullptr) {
+        g_places = p.plan->places;
+        if (g_places != 0) g_counters.push_back({p.counters, p.counters_next, p.n_counters});
+        if (p.plan->done != nullptr) event(p.plan->done).pending = true;
+    } else if (p.stream_wgs > 0 || p.helpers > 0) g_counters.push_back({p.counters, p.counters_next, p.n_counters});
     return hipSuccess;
 }
 hipError_t tetri_launch_short(int, bool, const ShortParams &p, int, hipStream_t)
@@ -124,6 +132,7 @@ hipError_t tetri_launch_short(int, bool, const ShortParams &p, int, hipStream_t)
 hipError_t tetri_launch_decode(const tetri_ctx *, const DecodeParams &p, hipStream_t)
 {
     CHECK((p.parts != 1) == (p.n_counters != 0));
+    g_partials = reinterpret_cast<const char *>(p.partial);
     g_parts = p.parts;
     g_ranges = p.ranges;
     if (p.parts != 1) g_counters.push_back({p.counters, p.counters_next, p.n_counters});
@@ -192,12 +201,13 @@ void static_decode_counters()
     tetri_destroy(h);
 }
 
-// A chunk of one request: with 32 rows the short kernel splits its keys, with 256 the shared-tile kernel divides its stages.
+// A chunk of one request: with 32 rows the short kernel splits its keys, with 256 the shared-tile kernel divides its stages, with 250
+// they are divided by the host.
 void prefill(tetri_ctx *h, int32_t rows)
 {
     const int32_t cu[2] = {0, rows}, ctx[1] = {2000};
     const int32_t *meta = reinterpret_cast<const int32_t *>(g_any);
-    tetri_set_option(h, "attn_variant", rows == 32 ? 3 : 0);
+    tetri_set_option(h, "attn_variant", rows == 32 ? 3 : (rows == 250 ? 5 : 0));
     CHECK(tetri_chunk_prefill_planned(h, g_any, g_any, g_any, g_any, meta, meta, meta, 1, 0.1f, 0, 0, 1.f, 1.f, cu, ctx, g_any,
                                       nullptr) == TETRI_OK);
 }
@@ -210,7 +220,7 @@ void counters_are_cleared()
     tetri_ctx *h = handle(8, 2, 128), *other = handle(8, 2, 128);
     tetri_set_option(h, "decode_parts", 5);
     tetri_set_option(other, "decode_parts", 5);
-    const char *sequences[] = {"dddddddddd", "ssssssssss", "pppppppppp", "dspdpsddsspdpdssdpppd", "tututtuutuut"};
+    const char *sequences[] = {"dddddddddd", "ssssssssss", "pppppppppp", "dspdpsddsspdpdssdpppd", "tututtuutuut", "hhhhhhhhhh", "hdhhphsdpsdhhhhdps"};
     for (const char *seq : sequences) {
         g_counters.clear();
         tetri_set_option(h, "stream_wgs", seq[0] == 's' ? 0 : 5);        // (a divided launch, whatever the shape would get)
@@ -218,6 +228,7 @@ void counters_are_cleared()
             if (*c == 'd') decode(h, false);
             else if (*c == 's') prefill(h, 32);
             else if (*c == 'p') prefill(h, 256);
+            else if (*c == 'h') prefill(h, 250);
             else decode(*c == 't' ? h : other, true);
         }
         const size_t n = g_counters.size();
@@ -237,6 +248,79 @@ void counters_are_cleared()
     }
     tetri_destroy(h);
     tetri_destroy(other);
+}
+
+// Launches on a division of the host's cut tiles of launches of any size.  On several streams at once they disturb neither decode nor
+// launches that divide themselves nor each other, are not refused, and name no stream but their own; where there is no memory left
+// for their pieces, they cut nothing.
+void planned_launches_overlap()
+{
+    tetri_config c = {40, 40, 128, 16, 2048, 8192, 512, 8, TETRI_BF16};
+    tetri_ctx *h = nullptr;
+    CHECK(tetri_create(&c, &h) == TETRI_OK);
+    const int32_t *meta = reinterpret_cast<const int32_t *>(g_any);
+    const size_t bytes = 2 * h->scratch_units * h->unit_bytes;
+    auto stream = [](uintptr_t i) { return reinterpret_cast<hipStream_t>(64 * i); };
+    struct Memory { const char *partials; Counters counters; };
+    auto last = [&]() { return Memory{g_partials, g_counters.back()}; };
+    auto apart = [&](const Memory &a, const Memory &b) {
+        CHECK(in_handle_memory(a.partials) && in_handle_memory(a.partials + bytes - 1) && in_handle_memory(a.counters.use + a.counters.n - 1));
+        CHECK(a.partials + bytes <= b.partials || b.partials + bytes <= a.partials);
+        for (const int32_t *x : {a.counters.use, a.counters.clear})
+            for (const int32_t *y : {b.counters.use, b.counters.clear}) CHECK(x + a.counters.n <= y || y + b.counters.n <= x);
+    };
+    auto prefill = [&](int32_t rows, int32_t ctx, hipStream_t s) {
+        const int32_t cu[2] = {0, rows};
+        return tetri_chunk_prefill_planned(h, g_any, g_any, g_any, g_any, meta, meta, meta, 1, 0.1f, 1, 0, 1.f, 1.f, cu, &ctx, g_any, s);
+    };
+    auto split_decode = [&](hipStream_t s) {
+        CHECK(tetri_decode_attn(h, g_any, g_any, g_any, g_any, meta, meta, 2, 3000, 0.1f, g_any, s) == TETRI_OK && g_parts > 1);
+    };
+    g_busy = true;
+    CHECK(prefill(2048, 0, stream(1)) == TETRI_OK && g_places > 0);
+    const Memory first = last();
+    for (int i = 0; i < 5; ++i) {                  // (five take all turns of the counters)
+        split_decode(stream(2));
+        apart(first, last());
+    }
+    CHECK(prefill(1024, 4096, stream(2)) == TETRI_OK && g_places > 0);
+    const Memory second = last();
+    apart(first, second);
+    split_decode(stream(3));
+    apart(second, last());
+    // a third stream beside the second's launch, and when that has ended
+    const size_t n = g_counters.size();
+    CHECK(prefill(2048, 0, stream(3)) == TETRI_OK && g_places == 0 && g_counters.size() == n);
+    CHECK(prefill(2048, 0, hipStreamPerThread) == TETRI_OK && g_places == 0);
+    CHECK(event(h->plan_done).pending);
+    event(h->plan_done).pending = false;
+    CHECK(prefill(2048, 0, stream(3)) == TETRI_OK && g_places > 0 && last().partials == second.partials);
+    // the streams of earlier launches are gone
+    g_destroyed = stream(3);
+    CHECK(prefill(2048, 0, stream(4)) == TETRI_OK && g_places == 0);
+    event(h->plan_done).pending = false;
+    CHECK(prefill(2048, 0, stream(4)) == TETRI_OK && g_places > 0 && last().partials == second.partials);
+    CHECK(prefill(2048, 0, stream(4)) == TETRI_OK && g_places > 0);
+    // hipStreamPerThread is another stream in every thread: no launch on it follows another
+    event(h->plan_done).pending = false;
+    CHECK(prefill(2048, 0, hipStreamPerThread) == TETRI_OK && g_places > 0);
+    CHECK(prefill(2048, 0, hipStreamPerThread) == TETRI_OK && g_places == 0);
+    // the first stream's launches follow each other
+    g_destroyed = stream(4);
+    CHECK(prefill(2048, 0, stream(1)) == TETRI_OK && g_places > 0 && last().partials == first.partials);
+    event(h->plan_done).pending = false;
+    tetri_destroy(h);
+    // launches that divide themselves beside them; two of those are held apart as ever
+    c.chunk_size = 512;
+    CHECK(tetri_create(&c, &h) == TETRI_OK);
+    CHECK(prefill(512, 4000, stream(1)) == TETRI_OK && g_places > 0);
+    const Memory planned = last();
+    CHECK(tetri_set_option(h, "stream_wgs", 5) == TETRI_OK);
+    CHECK(prefill(512, 4000, stream(5)) == TETRI_OK);
+    apart(planned, last());
+    CHECK(prefill(512, 4000, stream(6)) == TETRI_ERR_INVALID_ARG && std::strstr(tetri_last_error(h), "overlap"));
+    g_busy = false;
+    tetri_destroy(h);
 }
 
 // A batch of one prompt, staged in ordinary memory (which the stub takes for pinned).
@@ -356,6 +440,7 @@ int main(int argc, char **argv)
     const std::string name = argc > 1 ? argv[1] : "";
     if (name == "static_decode_counters") static_decode_counters();
     else if (name == "counters_are_cleared") counters_are_cleared();
+    else if (name == "planned_launches_overlap") planned_launches_overlap();
     else if (name == "upload_checks_the_device") upload_checks_the_device();
     else if (name == "uploads_name_no_stream_later") uploads_name_no_stream_later();
     else if (name == "choice_of_kernel") choice_of_kernel();

@@ -172,6 +172,44 @@ def test_static_decode_beside_dividing_launches(oracle):
         assert torch.equal(o.view(torch.int16), want[0].view(torch.int16)), ("decode", i)
 
 
+def test_planned_launches_beside_each_other_and_decode(oracle):
+    """Launches on a division of the host's, with shared tiles, on two streams at once, and split decode launches of the same
+    handle on a third: each has memory of its own, so all give the bits they give alone."""
+    w, sess, c, (q, k, v), pool, ref_rows = prefilled(oracle, "planned-beside", 147)
+    h = sess.handle
+    h.tetri_set_option("attn_variant", 5)
+    h.tetri_set_option("decode_parts", 6)
+    bt = sess.meta[c][2]
+    ctx = torch.tensor([1000], dtype=torch.int32, device=DEV)
+    decode = lambda out, st: h.tetri_decode_attn(q[:1], k[:1], v[:1], pool, bt, ctx, 1, 1000, w.scale, out, st)
+    attn = lambda out, st: sess.attn(c, q, k, v, pool, w.scale, out, st)
+    st_a, st_b, st_c = (torch.cuda.Stream(device=DEV) for _ in range(3))
+    want = torch.zeros_like(q[:1]), torch.zeros_like(q)
+    torch.cuda.synchronize()
+    decode(want[0], st_c), attn(want[1], st_a)
+    torch.cuda.synchronize()
+    check(want[1], ref_rows, "alone")
+    outs_a, outs_b, outs_c = [torch.zeros_like(q) for _ in range(20)], [torch.zeros_like(q) for _ in range(20)], [torch.zeros_like(q[:1]) for _ in range(60)]
+    torch.cuda.synchronize()
+    for i in range(20):
+        attn(outs_a[i], st_a)
+        attn(outs_b[i], st_b)
+        for o in outs_c[3 * i:3 * i + 3]:
+            decode(o, st_c)
+    torch.cuda.synchronize()
+    for i, o in enumerate(outs_a + outs_b):
+        assert torch.equal(o.view(torch.int16), want[1].view(torch.int16)), ("prefill", i)
+    for i, o in enumerate(outs_c):
+        assert torch.equal(o.view(torch.int16), want[0].view(torch.int16)), ("decode", i)
+    # a third stream beside the second's launches may get a division that shares nothing: the same function
+    out = torch.zeros_like(q)
+    torch.cuda.synchronize()
+    attn(outs_b[0], st_b)
+    attn(out, st_c)
+    torch.cuda.synchronize()
+    check(out, ref_rows, "third stream")
+
+
 @pytest.mark.parametrize("fp8", [False, True], ids=["16-bit-pool", "fp8-pool"])
 def test_graph_replays_between_eager_launches(oracle, fp8):
     """A HIP graph that holds an odd number of launches that divide tiles, replayed several times with eager launches of

@@ -25,7 +25,7 @@ def driver(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("check", ["static_decode_counters", "counters_are_cleared", "upload_checks_the_device",
+@pytest.mark.parametrize("check", ["static_decode_counters", "counters_are_cleared", "planned_launches_overlap", "upload_checks_the_device",
                                    "uploads_name_no_stream_later", "choice_of_kernel",
                                    "decode_division"])
 def test_host_layer(driver, check):
