@@ -6,6 +6,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <functional>
 #include <new>
 #include <vector>
 
@@ -480,8 +481,8 @@ struct ShortShape {
     bool preferred;
 };
 
-// The launch of the short kernel for a chunk whose segments the host knows: its row blocks, most work first, and the shape.
-// False if the chunk does not fit the kernel's tables.
+// The launch of the short kernel for a chunk whose segments the host knows, if it is preferred (or asked for by "attn_variant"): its row
+// blocks, most work first, and the shape.  False if the chunk does not fit the kernel's tables.
 static bool plan_short(const tetri_ctx *h, const int32_t *cu, const int32_t *ctx_lens, int32_t num_segs, bool fp8, ShortParams &p,
                        ShortShape &shape)
 {
@@ -500,13 +501,6 @@ static bool plan_short(const tetri_ctx *h, const int32_t *cu, const int32_t *ctx
         most = std::max(most, ctx_steps + blocks);
         if (ctx_lens[s] >= 1 << 26) return false;
     }
-    std::sort(units, units + n, [](const Unit &a, const Unit &b) { return a.steps > b.steps; });
-    for (int i = 0; i < n; ++i) {
-        const int32_t s = units[i].seg;
-        const uint32_t row0 = (uint32_t)cu[s], rows = (uint32_t)(cu[s + 1] - cu[s]);
-        p.unit[i][0] = (uint32_t)s | (uint32_t)units[i].t0 / 32 << 6 | rows << 13 | row0 << 26;
-        p.unit[i][1] = (uint32_t)ctx_lens[s] | (row0 >> 6) << 26;
-    }
     p.units = n;
     p.rows = cu[num_segs];
     const int64_t Hq = h->cfg.num_q_heads, wgs = n * Hq, cus = std::max(h->num_cus, 1);
@@ -523,12 +517,42 @@ static bool plan_short(const tetri_ctx *h, const int32_t *cu, const int32_t *ctx
     p.splits = 1;
     if (h->split_keys && 2 * wgs <= cus && wgs <= h->n_counters)
         p.splits = (int32_t)std::max<int64_t>(1, std::min(std::min<int64_t>(cus / wgs, 16), std::min<int64_t>((most + 7) / 8, units_fit)));
+    // Where this kernel is the faster one (both timed on 650 chunks of 40x128, 32/8x128, 24/8x128, 16x128, 16/2x128 and 8/2x128 heads, 32 to
+    // 1024 rows in 1 to 10 segments, 0 to 32000 cached tokens; times as a part of the shared-tile kernel's, FP8 codes in brackets):
+    //  - exactly a workgroup per compute unit, eight wavefronts to a row block: up to 128 steps to a wavefront (0.4 at the shortest, 1.0
+    //    at 17 steps, 1.25 (1.4) at 80);
+    //  - fewer: three or more workgroups to a row block, up to 128 steps too (0.5 to 0.99 (1.07) at 31); two, up to 20 (15) steps
+    //    (0.93 to 0.98 (0.96 to 1.02) at 16, 1.05 (1.1) at 24, 1.2 (1.3) at 63); one, which leaves compute units without work, up to 16
+    //    (12) (0.8 to 0.9 at 9, 1.0 (1.1 to 1.2) at 16, 1.15 (1.3) at 24, 1.4 to 1.9 at 95);
+    //  - exactly two workgroups per compute unit: up to 65000 (20000) steps of 32 keys x 32 rows in all; between one and two, which leaves
+    //    some compute units half empty, also up to 27 (14) steps on a wavefront times the part of the two (256 rows of 40 heads:
+    //    1.05 (1.18) at 14 steps, 1.14 (1.3) at 22, 1.26 (1.4) at 32; 512 rows of 24/8 heads: 0.98 (1.07) at 16, 1.03 (1.14) at 24);
+    //  - more: what a launch takes is the chain of steps of its longest row blocks, which the total does not show: up to 30000 (15000)
+    //    steps in all with 22 (11) on a wavefront, at two to a row block.  Where the work is even over the row blocks of several segments,
+    //    the shared-tile kernel's tiles are ragged and teams keep the chains short: up to 30000 whatever the chain, over codes 20000
+    //    unless every query head has K and V of its own (40 heads, 300 rows at 1000 and 212 at 200 cached tokens: 0.75 (0.75); 200 at 2000
+    //    and 312 at 600: 0.87 (0.94); 32/8 heads, the same: 1.0 (1.1), 345 at 1353 and 167 at 0: 0.85 (0.95)).
+    // head_dim 64: always (1.3 % over 224 chunks of 40x64 and 12/4x64, up to 24 % on single ones; a limit on the chain gains nothing).
+    const int Hkv = h->cfg.num_kv_heads;
+    const int64_t chain = (most + wavefronts - 1) / wavefronts;
+    if (h->cfg.head_dim == 64) shape.preferred = true;
+    else if (wgs <= cus) shape.preferred = chain <= (wgs == cus || p.splits > 2 ? 128 : (p.splits == 2 ? 2 * (fp8 ? 15 : 20) : (fp8 ? 12 : 16)));
+    else if (wgs <= 2 * cus) shape.preferred = total <= (fp8 ? 20000 : 65000);        // (the steps on a wavefront: below)
+    else if (num_segs > 1 && (int64_t)most * n <= 2 * steps) shape.preferred = total <= (fp8 && Hq != Hkv ? 20000 : 30000);
+    else shape.preferred = total <= (fp8 ? 15000 : 30000) && chain <= (fp8 ? 11 : 22);
+    if (!shape.preferred && h->attn_variant != 3) return true;      // (not to be laid out)
+    std::sort(units, units + n, [](const Unit &a, const Unit &b) { return a.steps > b.steps; });
+    for (int i = 0; i < n; ++i) {
+        const int32_t s = units[i].seg;
+        const uint32_t row0 = (uint32_t)cu[s], rows = (uint32_t)(cu[s + 1] - cu[s]);
+        p.unit[i][0] = (uint32_t)s | (uint32_t)units[i].t0 / 32 << 6 | rows << 13 | row0 << 26;
+        p.unit[i][1] = (uint32_t)ctx_lens[s] | (row0 >> 6) << 26;
+    }
     // ---- the shape of the launch.  A row block of one head is the work of a team of 1, 2, 4 or 8 wavefronts: as many as leave at
     // most `cap` steps to each, cap the least for which all workgroups of the launch are on the chip at once.  (Teams of one
     // size made the launch as long as its longest row block: 64 packed chunks of 40 heads 18.0 us each, now 15.8.  Counted in
     // wavefronts instead of workgroups, a launch could need a few workgroups more than there is room for: 512 rows of 40 heads at 100
     // cached tokens 20.3 us (FP8 25.3), now 17.2 (20.3).)
-    const int Hkv = h->cfg.num_kv_heads;
     p.rshift = Hkv % 8 == 0 ? 3 : (Hkv % 4 == 0 ? 2 : (Hkv % 2 == 0 ? 1 : 0));
     p.hpx = (int32_t)Hq >> p.rshift;
     p.hkx = Hkv >> p.rshift;
@@ -573,28 +597,7 @@ static bool plan_short(const tetri_ctx *h, const int32_t *cu, const int32_t *ctx
     }
     p.attn_wgs = lay_out(nwl, cap);
     shape.nwl = nwl;
-    // Where this kernel is the faster one (both timed on 650 chunks of 40x128, 32/8x128, 24/8x128, 16x128, 16/2x128 and 8/2x128 heads, 32 to
-    // 1024 rows in 1 to 10 segments, 0 to 32000 cached tokens; times as a part of the shared-tile kernel's, FP8 codes in brackets):
-    //  - exactly a workgroup per compute unit, eight wavefronts to a row block: up to 128 steps to a wavefront (0.4 at the shortest, 1.0
-    //    at 17 steps, 1.25 (1.4) at 80);
-    //  - fewer: three or more workgroups to a row block, up to 128 steps too (0.5 to 0.99 (1.07) at 31); two, up to 20 (15) steps
-    //    (0.93 to 0.98 (0.96 to 1.02) at 16, 1.05 (1.1) at 24, 1.2 (1.3) at 63); one, which leaves compute units without work, up to 16
-    //    (12) (0.8 to 0.9 at 9, 1.0 (1.1 to 1.2) at 16, 1.15 (1.3) at 24, 1.4 to 1.9 at 95);
-    //  - exactly two workgroups per compute unit: up to 65000 (20000) steps of 32 keys x 32 rows in all; between one and two, which leaves
-    //    some compute units half empty, also up to 27 (14) steps on a wavefront times the part of the two (256 rows of 40 heads:
-    //    1.05 (1.18) at 14 steps, 1.14 (1.3) at 22, 1.26 (1.4) at 32; 512 rows of 24/8 heads: 0.98 (1.07) at 16, 1.03 (1.14) at 24);
-    //  - more: what a launch takes is the chain of steps of its longest row blocks, which the total does not show: up to 30000 (15000)
-    //    steps in all with 22 (11) on a wavefront, at two to a row block.  Where the work is even over the row blocks of several segments,
-    //    the shared-tile kernel's tiles are ragged and teams keep the chains short: up to 30000 whatever the chain, over codes 20000
-    //    unless every query head has K and V of its own (40 heads, 300 rows at 1000 and 212 at 200 cached tokens: 0.75 (0.75); 200 at 2000
-    //    and 312 at 600: 0.87 (0.94); 32/8 heads, the same: 1.0 (1.1), 345 at 1353 and 167 at 0: 0.85 (0.95)).
-    // head_dim 64: always (1.3 % over 224 chunks of 40x64 and 12/4x64, up to 24 % on single ones; a limit on the chain gains nothing).
-    const int64_t chain = (most + wavefronts - 1) / wavefronts;
-    if (h->cfg.head_dim == 64) shape.preferred = true;
-    else if (wgs <= cus) shape.preferred = chain <= (wgs == cus || p.splits > 2 ? 128 : (p.splits == 2 ? 2 * (fp8 ? 15 : 20) : (fp8 ? 12 : 16)));
-    else if (wgs <= 2 * cus) shape.preferred = total <= (fp8 ? 20000 : 65000) && (wgs == 2 * cus || 2 * cus * longest <= (fp8 ? 14 : 27) * wgs);
-    else if (num_segs > 1 && (int64_t)most * n <= 2 * steps) shape.preferred = total <= (fp8 && Hq != Hkv ? 20000 : 30000);
-    else shape.preferred = total <= (fp8 ? 15000 : 30000) && chain <= (fp8 ? 11 : 22);
+    if (h->cfg.head_dim != 64 && wgs > cus && wgs < 2 * cus) shape.preferred = shape.preferred && 2 * cus * longest <= (fp8 ? 14 : 27) * wgs;
     return (uint64_t)(wgs * p.splits + p.zero_wgs + 8) * (uint64_t)std::max<int64_t>(Hq, p.splits) < 0x100000000ull;   // (the divisions by multiplication)
 }
 
@@ -612,95 +615,157 @@ static int32_t plan_tiles(const tetri_ctx *h, const int32_t *cu, const int32_t *
     // tokens of 32/8 heads 25 %; 3 or 4 for a further job the same or less)
     constexpr int kMinPiece = 2;      // the shortest pieces a tile is cut into
     constexpr int kJobCost = 2;       // a workgroup's further jobs: what each costs besides its stages, in stages
-    const int wgs = (std::max(h->num_cus, 8) / 8) << p.span_shift, pools = 8 >> p.span_shift, rows = 32 * p.rb;
-    if (num_segs > kPlanSegs || p.C > 0xffff || wgs > kPlanJobs || p.gpx > 1023) return 0;
-    struct Item { int32_t n; uint16_t seg, grp, t0, begin; uint16_t place; uint8_t piece, npieces; };
-    Item tiles[kPlanJobs];
-    int nt = 0;
+    const int wgs = (std::max(h->num_cus, 8) / 8) << p.span_shift, pools = 8 >> p.span_shift, rows = 32 * p.rb, gpx = p.gpx;
+    if (num_segs > kPlanSegs || p.C > 0xffff || wgs > kPlanJobs || gpx > 1023) return 0;
+    // The tiles of a head group, longest first: stages << 8 | 255 - index.  Tile t of the pool's group g is item t * gpx + g.
+    uint32_t key[kPlanJobs];
+    struct Tile { int32_t n; uint16_t seg, t0; } tile[kPlanJobs], found[kPlanJobs];
+    int tiles = 0;
     int64_t total = 0;
-    int32_t longest = 0;
     for (int32_t s = 0; s < num_segs; ++s) {
         const int32_t n = cu[s + 1] - cu[s], ctx_stages = (ctx_lens[s] + kStage - 1) / kStage;
         plan.seg[s][0] = cu[s]; plan.seg[s][1] = n; plan.seg[s][2] = ctx_lens[s]; plan.seg[s][3] = 0;
         for (int32_t t0 = 0; t0 < n; t0 += rows) {
             const int32_t stages = ctx_stages + (std::min(n, t0 + rows) + kStage - 1) / kStage;
-            if (nt + p.gpx > kPlanJobs || stages > 0xffff) return 0;
-            for (int g = 0; g < p.gpx; ++g) tiles[nt++] = {stages, (uint16_t)s, (uint16_t)g, (uint16_t)t0, 0, 0, 0, 1};
-            total += (int64_t)stages * p.gpx;
-            longest = std::max(longest, stages);
+            if ((tiles + 1) * gpx > kPlanJobs || stages > 0xffff) return 0;
+            found[tiles] = {stages, (uint16_t)s, (uint16_t)t0};
+            key[tiles] = (uint32_t)stages << 8 | (uint32_t)(255 - tiles);
+            ++tiles;
+            total += (int64_t)stages * gpx;
         }
     }
-    std::sort(tiles, tiles + nt, [](const Item &a, const Item &b) { return a.n > b.n; });
+    std::sort(key, key + tiles, std::greater<uint32_t>());
+    for (int t = 0; t < tiles; ++t) tile[t] = found[255 - (key[t] & 255)];
+    const int nt = tiles * gpx;
+    const int32_t longest = tile[0].n;
     const int64_t places_fit = std::min<int64_t>((int64_t)(2 * h->scratch_units), h->n_counters) / (p.hpw * p.rb * pools);
-    for (int32_t q = (int32_t)std::max<int64_t>((total + wgs - 1) / wgs, kMinPiece);; q += std::max(1, q / 64)) {
-        if (!share) q = std::max(q, longest);
-        // pieces of q stages, a workgroup each; what remains is packed
-        Item rest[kPlanJobs];
-        int nr = 0, full = 0, places = 0, jobs = 0;
-        bool fits = true;
-        for (int i = 0; i < nt && fits; ++i) {
-            Item it = tiles[i];
-            const int cuts = (it.n - 1) / q;
-            if (cuts > 0) {
-                if (cuts > 254 || places + cuts + 1 > places_fit || full + cuts > wgs) { fits = false; break; }
-                it.npieces = (uint8_t)(cuts + 1);
-                it.place = (uint16_t)places;
-                places += cuts + 1;
-                for (int c = 0; c < cuts; ++c) {
-                    plan.job[full++] = {(uint16_t)(it.seg | it.grp << 6), it.t0, (uint16_t)(c * q), (uint16_t)((c + 1) * q), it.place, (uint8_t)c, it.npieces, 0, 0};
-                }
-                it.begin = (uint16_t)(cuts * q);
-                it.n -= cuts * q;
-                it.piece = (uint8_t)cuts;
-            }
-            rest[nr++] = it;
+    // What any division has to meet at pieces of q stages, longer q meeting it too: the whole workgroups' pieces, the remainders
+    // and the further jobs' costs fit, at most two pieces to a workgroup, places for all pieces.
+    int cut = 0, full = 0;            // (of the q looked at last) tiles of a head group that are cut, and pieces of q of the pool
+    auto may_fit = [&](int32_t q) -> bool {
+        int64_t cuts = 0;
+        for (cut = 0; cut < tiles && tile[cut].n > q; ++cut) {
+            const int c = (tile[cut].n - 1) / q;
+            cuts += c;
+            if (c > 254) return false;
         }
-        if (!fits) continue;
-        // the workgroups that are left: the longest remainder first, to the least loaded one that may take it.  A workgroup does
-        // at most two pieces of shared tiles there, the second as its last job (it can leave one hand-over open).
-        std::sort(rest, rest + nr, [](const Item &a, const Item &b) { return a.n > b.n; });
+        if (cuts * gpx > wgs) return false;
+        full = (int)cuts * gpx;
         const int left = wgs - full;
-        struct Bin { int32_t load; int16_t first, last, tail; } bins[kPlanJobs];     // tail: the piece that is its last job
-        for (int i = 0; i < left; ++i) {
-            bins[i] = {0, -1, -1, -1};
-            plan.job[full + i] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+        return (cuts + cut) * gpx <= places_fit && cut * gpx <= 2 * left && left > 0
+               && total + kJobCost * std::max(0, nt - left) <= (int64_t)q * wgs;
+    };
+    int32_t q = (int32_t)std::min<int64_t>(std::max<int64_t>((total + wgs - 1) / wgs, kMinPiece), longest);
+    if (!share) q = longest;
+    for (int32_t above = longest; q < above;) {          // the shortest that may fit
+        const int32_t mid = q + (above - q) / 2;
+        if (may_fit(mid)) above = mid;
+        else q = mid + 1;
+    }
+    struct Bin { int32_t load; int16_t first, last, tail; } bins[kPlanJobs];     // tail: the piece that is its last job
+    uint8_t rest[kPlanJobs];          // the items, longest remainder first
+    int32_t rem[kPlanJobs];           // remainders of the tiles that are cut
+    int16_t link[kPlanJobs];
+    for (;; q += std::max(1, q / 64)) {
+        q = std::min(q, longest);
+        (void)may_fit(q);
+        // what remains of the tiles that are cut, in between the whole ones
+        for (int t = 0; t < cut; ++t) {
+            rem[t] = (tile[t].n - 1) % q + 1;
+            key[t] = (uint32_t)rem[t] << 8 | (uint32_t)(255 - t);
         }
-        int16_t link[kPlanJobs];
-        for (int i = 0; i < nr && fits; ++i) {
-            const bool is_piece = rest[i].npieces > 1;
-            Bin *to = nullptr;
-            for (int k = 0; k < left; ++k)
-                if ((to == nullptr || bins[k].load < to->load) && !(is_piece && bins[k].tail >= 0)) to = &bins[k];
-            const bool empty = to != nullptr && to->first < 0 && to->tail < 0;
-            const int32_t load = to == nullptr ? 0 : to->load + rest[i].n + (empty ? 0 : kJobCost);
-            if (to == nullptr || (load > q && q < longest)) { fits = false; break; }
-            to->load = load;
-            if (is_piece && to->first >= 0 && rest[to->first].npieces > 1) {
-                to->tail = (int16_t)i;
-            } else if (is_piece) {                      // in front of the whole tiles
-                link[i] = to->first;
-                to->first = (int16_t)i;
-                if (to->last < 0) to->last = (int16_t)i;
+        std::sort(key, key + cut, std::greater<uint32_t>());
+        int nr = 0;
+        for (int x = 0, y = cut; x < cut || y < tiles;) {
+            const bool piece = y == tiles || (x < cut && (int32_t)(key[x] >> 8) >= tile[y].n);
+            const int t = piece ? 255 - (int)(key[x++] & 255) : y++;
+            for (int g = 0; g < gpx; ++g) rest[nr++] = (uint8_t)(t * gpx + g);
+        }
+        auto stages = [&](int item) -> int32_t { const int t = item / gpx; return t < cut ? rem[t] : tile[t].n; };
+        const int left = wgs - full;
+        const bool any = q >= longest;                   // nothing is cut: whatever the loads
+        // (two of the left + 1 longest meet in a workgroup)
+        if (!any && nr > left && stages(rest[left - 1]) + stages(rest[left]) + kJobCost > q) continue;
+        // The workgroups that are left: the longest remainder first, to the least loaded one that may take it (a heap of load << 8 |
+        // workgroup).  A workgroup does at most two pieces of shared tiles there, the second as its last job (it can leave one
+        // hand-over open).
+        const int filled = std::min(nr, left);
+        uint32_t heap[kPlanJobs];
+        int n_heap = 0;
+        for (int k = 0; k < left; ++k) {
+            bins[k] = {0, -1, -1, -1};
+            if (k >= filled) continue;
+            bins[k] = {stages(rest[k]), (int16_t)rest[k], (int16_t)rest[k], -1};
+            link[rest[k]] = -1;
+            if (nr > left) heap[n_heap++] = (uint32_t)bins[k].load << 8 | (uint32_t)k;
+        }
+        std::make_heap(heap, heap + n_heap, std::greater<uint32_t>());
+        bool fits = true;
+        for (int r = filled; r < nr; ++r) {
+            const int item = rest[r];
+            const bool piece = item / gpx < cut;
+            uint32_t aside[kPlanJobs];                   // those that have their last job
+            int n_aside = 0;
+            while (piece && n_heap > 0 && bins[heap[0] & 255].tail >= 0) {
+                aside[n_aside++] = heap[0];
+                std::pop_heap(heap, heap + n_heap--, std::greater<uint32_t>());
+            }
+            const int32_t load = n_heap == 0 ? 0 : (int32_t)(heap[0] >> 8) + stages(item) + kJobCost;
+            if (n_heap == 0 || (load > q && !any)) { fits = false; break; }
+            const int k = (int)(heap[0] & 255);
+            Bin &to = bins[k];
+            to.load = load;
+            const uint32_t moved = (uint32_t)load << 8 | (uint32_t)k;
+            int at = 0;                                  // the top sinks to its place
+            for (int c; (c = 2 * at + 1) < n_heap; at = c) {
+                c += (int)(c + 1 < n_heap && heap[c + 1] < heap[c]);
+                if (heap[c] >= moved) break;
+                heap[at] = heap[c];
+            }
+            heap[at] = moved;
+            while (n_aside > 0) {
+                heap[n_heap++] = aside[--n_aside];
+                std::push_heap(heap, heap + n_heap, std::greater<uint32_t>());
+            }
+            if (piece && to.first / gpx < cut) {
+                to.tail = (int16_t)item;
+            } else if (piece) {                         // in front of the whole tiles
+                link[item] = to.first;
+                to.first = (int16_t)item;
             } else {
-                link[i] = -1;
-                if (to->last >= 0) link[to->last] = (int16_t)i;
-                else to->first = (int16_t)i;
-                to->last = (int16_t)i;
+                link[item] = -1;
+                link[to.last] = (int16_t)item;
+                to.last = (int16_t)item;
             }
         }
         if (!fits) continue;
+        if (nr > left && full + nr > kPlanJobs) return 0;
+        // ---- the jobs: the pieces of q stages, then the other workgroups' chains
+        int places = 0, jobs = 0;
+        uint16_t place[kPlanJobs];                       // of a cut tile's first group
+        for (int t = 0; t < cut; ++t) {
+            const int cuts = (tile[t].n - rem[t]) / q;
+            place[t] = (uint16_t)places;
+            for (int g = 0; g < gpx; ++g, places += cuts + 1)
+                for (int c = 0; c < cuts; ++c)
+                    plan.job[jobs++] = {(uint16_t)(tile[t].seg | g << 6), tile[t].t0, (uint16_t)(c * q), (uint16_t)((c + 1) * q), (uint16_t)places,
+                                        (uint8_t)c, (uint8_t)(cuts + 1), 0, 0};
+        }
         jobs = wgs;
+        int32_t load = full > 0 ? q : 0;
         for (int k = 0; k < left; ++k) {
+            load = std::max(load, bins[k].load);
             if (bins[k].tail >= 0) {
                 link[bins[k].tail] = -1;
                 link[bins[k].last] = bins[k].tail;
             }
             int at = full + k;
+            if (bins[k].first < 0) plan.job[at] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
             for (int i = bins[k].first; i >= 0; i = link[i]) {
                 const bool more = link[i] >= 0;
-                if (more && jobs >= kPlanJobs) return 0;
-                plan.job[at] = {(uint16_t)(rest[i].seg | rest[i].grp << 6), rest[i].t0, rest[i].begin, (uint16_t)(rest[i].begin + rest[i].n), rest[i].place,
-                                rest[i].piece, rest[i].npieces, (uint16_t)(more ? jobs : 0), 0};
+                const int t = i / gpx, g = i % gpx, cuts = t < cut ? (tile[t].n - rem[t]) / q : 0;
+                plan.job[at] = {(uint16_t)(tile[t].seg | g << 6), tile[t].t0, (uint16_t)(cuts * q), (uint16_t)tile[t].n,
+                                (uint16_t)(t < cut ? place[t] + g * (cuts + 1) : 0), (uint8_t)cuts, (uint8_t)(cuts + 1), (uint16_t)(more ? jobs : 0), 0};
                 at = jobs;
                 jobs += (int)more;
             }
@@ -709,8 +774,6 @@ static int32_t plan_tiles(const tetri_ctx *h, const int32_t *cu, const int32_t *
         plan.wgs = wgs;
         plan.rows = cu[num_segs];
         plan.pad = 0;
-        int32_t load = full > 0 ? q : 0;
-        for (int k = 0; k < left; ++k) load = std::max(load, bins[k].load);
         return load;
     }
 }
