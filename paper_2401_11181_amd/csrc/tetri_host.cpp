@@ -490,6 +490,7 @@ static bool plan_short(const tetri_ctx *h, const int32_t *cu, const int32_t *ctx
     struct Unit { int32_t steps, seg, t0; } units[kShortUnits];
     int n = 0;
     int64_t steps = 0;                // 32-key steps of all row blocks of one head
+    int64_t cached = 0;               // tokens of all contexts
     int32_t most = 0;
     for (int32_t s = 0; s < num_segs; ++s) {
         const int32_t blocks = (cu[s + 1] - cu[s] + 31) / 32, ctx_steps = (ctx_lens[s] + 31) / 32;
@@ -499,10 +500,17 @@ static bool plan_short(const tetri_ctx *h, const int32_t *cu, const int32_t *ctx
             steps += ctx_steps + b + 1;
         }
         most = std::max(most, ctx_steps + blocks);
+        cached += ctx_lens[s];
         if (ctx_lens[s] >= 1 << 26) return false;
     }
     p.units = n;
     p.rows = cu[num_segs];
+    // Where Q, K, V and the output fit the L2 caches (8 x 4 MB) together, the output is stored past them: less is left to write back
+    // when the launch ends (packed short prompts, 26 MB and below: 640 rows of 40 heads 0.5 %, 512 2.4, 768 of 32/8 6.2, 1280 3.0, 1024 of
+    // 24/8 5.7, 1536 of 16 1.9).  Beyond, such stores are the slower ones (31 MB: 768 rows of 40 heads 2.8 %, 1536 of 32/8 7.7; 2048 of 16 3.4, of
+    // 40 7.7, of 32/8 11.8).
+    const int64_t row_bytes = 2 * h->cfg.head_dim;
+    p.out_past_l2 = (int32_t)(2 * row_bytes * p.rows * h->cfg.num_q_heads + 2 * row_bytes * (p.rows + cached / (fp8 ? 2 : 1)) * h->cfg.num_kv_heads <= 28000000);
     const int64_t Hq = h->cfg.num_q_heads, wgs = n * Hq, cus = std::max(h->num_cus, 1);
     const int64_t pad_vectors = (int64_t)(h->cfg.chunk_size - p.rows) * Hq * h->cfg.head_dim / 8;
     p.zero_wgs = (int32_t)std::min<int64_t>(256, (pad_vectors + 1023) / 1024);

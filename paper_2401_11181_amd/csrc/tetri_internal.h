@@ -160,7 +160,8 @@ struct ShortParams {
     float *scratch;               // splits > 1: partial results, [(unit * Hq + head) * splits + part][32 * D + 64] floats
     int32_t *counters;            // ... and arrival counters, one per (unit, head), zero before and after the launch
     int32_t *counters_next;       // the set of a later launch: zeroed by this one
-    int64_t pad2;
+    int32_t out_past_l2;          // 1: the output rows are stored past the caches
+    int32_t pad2;
     // most work first, 64 bits each: segment (6), row block in it (7), the segment's rows (13) and first row (12), cached tokens (26)
     uint32_t unit[kShortUnits][2];
 };

@@ -97,7 +97,8 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? (F8 ? 3 : 4) : 2) void attn_shor
     typedef __attribute__((address_space(4))) const i32x16 const_i32x16;
     static_assert(offsetof(ShortParams, q) == 64 && offsetof(ShortParams, C) == 128, "read as three vectors");
     i32x16 hd = ((const const_i32x16 *)p)[0], hp = ((const const_i32x16 *)p)[1], hc = ((const const_i32x16 *)p)[2];
-    asm volatile("" : "+s"(hd), "+s"(hp), "+s"(hc));
+    int out_past_l2 = p->out_past_l2;
+    asm volatile("" : "+s"(hd), "+s"(hp), "+s"(hc), "+s"(out_past_l2));
     auto pointer = [&](auto i) __attribute__((always_inline)) -> char * {
         constexpr int I = decltype(i)::value;
         return reinterpret_cast<char *>((uintptr_t)((uint64_t)(uint32_t)hp[2 * I] | (uint64_t)(uint32_t)hp[2 * I + 1] << 32));
@@ -517,7 +518,11 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? (F8 ? 3 : 4) : 2) void attn_shor
         asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %2\n\tv_permlane32_swap_b32 %1, %3\n\ts_nop 1" : "+v"(y.x), "+v"(y.y), "+v"(z.x), "+v"(z.y));
         if (valid && t < n_s) {
             uint16_t *orow = reinterpret_cast<uint16_t *>(p_out) + ((size_t)(row0 + t) * Hq + head) * D;
-            __builtin_nontemporal_store(u32x4{y.x, y.y, z.x, z.y}, reinterpret_cast<global_u32x4_w *>((uintptr_t)(orow + (vec + half) * 8)));
+            global_u32x4_w *at = reinterpret_cast<global_u32x4_w *>((uintptr_t)(orow + (vec + half) * 8));
+            const u32x4 row = {y.x, y.y, z.x, z.y};
+            // (written out: of two stores that differ in a hint the compiler makes one without)
+            if (out_past_l2 != 0) asm volatile("global_store_dwordx4 %0, %1, off nt" :: "v"(at), "v"(row) : "memory");
+            else *at = row;
         }
     };
     const float ltot = half_swap_sum(lsum);

@@ -42,6 +42,7 @@ std::vector<Counters> g_counters;
 int g_parts = 0, g_ranges = 0;                // how the last decode was cut
 std::string g_kernel;                         // the attention kernel launched last
 const char *g_partials = nullptr;             // where the last attention or decode launch keeps partial results
+int g_out_past_l2 = -1;                       // how the last launch of the short kernel stores its output
 int g_places = 0;                             // of the last division made by the host: tiles' pieces there
 
 struct Event { bool pending = false; };       // pending: work in front of it that nobody has waited for
@@ -126,6 +127,7 @@ hipError_t tetri_launch_attn(const tetri_ctx *, const AttnParams &p, int, bool, 
 hipError_t tetri_launch_short(int, bool, const ShortParams &p, int, hipStream_t)
 {
     g_kernel = "short";
+    g_out_past_l2 = p.out_past_l2;
     if (p.splits > 1) g_counters.push_back({p.counters, p.counters_next, p.n_counters});
     return hipSuccess;
 }
@@ -407,6 +409,25 @@ void choice_of_kernel()
     tetri_destroy(h);
 }
 
+// The short kernel's output goes past the caches where Q, K, V and the output fit them together (28 MB), not in larger launches.
+void short_output_stores()
+{
+    const tetri_config c = {40, 40, 128, 16, 2048, 8192, 512, 40, TETRI_BF16};
+    tetri_ctx *h = nullptr;
+    CHECK(tetri_create(&c, &h) == TETRI_OK && tetri_set_option(h, "attn_variant", 3) == TETRI_OK);
+    const int32_t *meta = reinterpret_cast<const int32_t *>(g_any);
+    auto past = [&](int32_t rows, int32_t ctx, int fp8) {
+        const int32_t cu[2] = {0, rows};
+        CHECK(tetri_chunk_prefill_planned(h, g_any, g_any, g_any, g_any, meta, meta, meta, 1, 0.1f, 1, fp8, 1.f, 1.f, cu, &ctx, g_any, nullptr) == TETRI_OK);
+        CHECK(g_kernel == "short");
+        return g_out_past_l2;
+    };
+    // 40 heads: 40 KB a row, 20 a cached token (codes: 10)
+    CHECK(past(683, 0, 0) == 1 && past(684, 0, 0) == 0 && past(2048, 0, 1) == 0 && past(1, 0, 1) == 1);
+    CHECK(past(512, 343, 0) == 1 && past(512, 344, 0) == 0 && past(512, 686, 1) == 1 && past(512, 688, 1) == 0);
+    tetri_destroy(h);
+}
+
 // How the host cuts a decode batch: equal ranges where there is much to read and fewer than two pairs per compute unit
 // (the batches of test_gpu_decode_ranges.py's default rule are among these), equal parts or whole pairs otherwise.
 void decode_division()
@@ -444,6 +465,7 @@ int main(int argc, char **argv)
     else if (name == "upload_checks_the_device") upload_checks_the_device();
     else if (name == "uploads_name_no_stream_later") uploads_name_no_stream_later();
     else if (name == "choice_of_kernel") choice_of_kernel();
+    else if (name == "short_output_stores") short_output_stores();
     else if (name == "decode_division") decode_division();
     else return 2;
     std::printf("%s: ok\n", name.c_str());

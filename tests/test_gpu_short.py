@@ -25,6 +25,7 @@ CASES = {
     "two": ([512, 70], 512, 40, 8, 128),                             # 513..1152
     "one": ([17] * 30, 512, 40, 40, 128),                            # more, short key ranges
     "one-then-two": ([20] * 28 + [400], 1024, 32, 8, 128),
+    "wide": ([60] * 10 + [131], 731, 40, 40, 128),                # 30 MB read and written: output by way of the caches
 }
 
 
