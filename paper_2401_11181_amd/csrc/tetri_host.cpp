@@ -614,8 +614,9 @@ static bool plan_short(const tetri_ctx *h, const int32_t *cu, const int32_t *ctx
 // The work of a pool (its head groups' tiles) goes to one workgroup per compute unit so that all end together: a tile longer
 // than q stages is cut into pieces of q for a workgroup each, the remainders and the tiles that are shorter are packed, the
 // longest first, into the workgroups that are left; q is the smallest for which they fit.  Returns the longest workgroup's stages, 0 if the
-// tables do not hold the division.  share: tiles may be cut at all.
-static int32_t plan_tiles(const tetri_ctx *h, const int32_t *cu, const int32_t *ctx_lens, int32_t num_segs, const AttnParams &p, bool share, TilePlan &plan)
+// tables do not hold the division.  share: tiles may be cut at all.  average: the stages (with the jobs' costs) of a workgroup if all had as many.
+static int32_t plan_tiles(const tetri_ctx *h, const int32_t *cu, const int32_t *ctx_lens, int32_t num_segs, const AttnParams &p, bool share,
+                          TilePlan &plan, int32_t &average)
 {
     constexpr int kStage = 128;
     // (timed on 120 chunks of 40, 32/8 and 8/2 heads, 256 to 2048 rows, 0 to 13000 cached tokens, both shapes: against pieces of at least
@@ -646,6 +647,7 @@ static int32_t plan_tiles(const tetri_ctx *h, const int32_t *cu, const int32_t *
     for (int t = 0; t < tiles; ++t) tile[t] = found[255 - (key[t] & 255)];
     const int nt = tiles * gpx;
     const int32_t longest = tile[0].n;
+    average = (int32_t)((total + kJobCost * std::max(0, nt - wgs)) / wgs);
     const int64_t places_fit = std::min<int64_t>((int64_t)(2 * h->scratch_units), h->n_counters) / (p.hpw * p.rb * pools);
     // What any division has to meet at pieces of q stages, longer q meeting it too: the whole workgroups' pieces, the remainders
     // and the further jobs' costs fit, at most two pieces to a workgroup, places for all pieces.
@@ -798,12 +800,43 @@ static int32_t plan_tiles(const tetri_ctx *h, const int32_t *cu, const int32_t *
 // 40 heads at 1000 cached tokens 34.3 us (FP8 37.8) against 38.2 (44.2); at 2560, 56000 steps, 48.2 against 46.8; 384 rows,
 // which fill 200 compute units: 41.0 against 37.3).
 struct SlotChoice { bool four, eight; };
+
+// Does a full chunk of the handle have five row tiles of 4 slots or more for every four compute units?  Then the launch that divides
+// itself runs a workgroup of four wavefronts per tile, two of them to a compute unit.
+static bool tiles_fill(const tetri_ctx *h)
+{
+    int hpw, rb;
+    wave_grouping(h->cfg.num_q_heads / h->cfg.num_kv_heads, 4, &hpw, &rb);
+    return (int64_t)(h->cfg.chunk_size / (32 * rb)) * (h->cfg.num_q_heads / hpw) * 4 >= 5 * (int64_t)std::max(h->num_cus, 1);
+}
+
+// Chunks of short tiles that such a launch takes faster: a job on the host's division costs its loads' and its output's round trips
+// over again, with nobody else on the compute unit meanwhile, and there is nothing to balance.  Up to 5 stages to the longest tile, 7
+// where the longest is at most 1.35 times a compute unit's share of all stages.  Timed on 900 chunks of 40, 32/8, 24/8, 20, 16, 16/2 and
+// 8/2 heads, 512 to 4096 rows, over 16-bit rows and codes: the host's division takes 0.98 to 1.49 times as long at up to 5 stages (packed
+// short prompts: 4096 rows of 32/8 heads 34.0 us, with it 47.2), 0.98 to 1.20 at 6 and 7 where that is so, 0.68 to 0.91 at 6 to 8 where it is not.
+static bool short_even_tiles(const tetri_ctx *h, const int32_t *cu, const int32_t *ctx_lens, int32_t num_segs)
+{
+    int hpw, rb;
+    wave_grouping(h->cfg.num_q_heads / h->cfg.num_kv_heads, 4, &hpw, &rb);
+    const int64_t groups = h->cfg.num_q_heads / hpw, rows = 32 * rb, cus = std::max(h->num_cus, 1);
+    int64_t tiles = 0, stages = 0, longest = 0;
+    for (int32_t s = 0; s < num_segs; ++s) {
+        const int64_t n = cu[s + 1] - cu[s], ctx_stages = (ctx_lens[s] + 127) / 128;
+        longest = std::max(longest, ctx_stages + (n + 127) / 128);
+        if (longest > 7) return false;
+        for (int64_t t0 = 0; t0 < n; t0 += rows, ++tiles) stages += ctx_stages + (std::min(n, t0 + rows) + 127) / 128;
+    }
+    return 4 * tiles * groups >= 5 * cus && (longest <= 5 || 20 * longest * cus <= 27 * stages * groups);
+}
+
 static SlotChoice planned_slots(const tetri_ctx *h, const int32_t *cu, const int32_t *ctx_lens, int32_t num_segs)
 {
     if (h->cfg.head_dim != 128) return {false, false};
     if (h->attn_variant == 4) return {false, true};
     if (h->attn_variant == 5) return {true, false};
     if (h->attn_variant != 0 || h->division_set) return {false, false};
+    if (tiles_fill(h) && short_even_tiles(h, cu, ctx_lens, num_segs)) return {false, false};
     int64_t steps = 0, all = 0, tiles = 0, most = 0;  // of one head: steps, row blocks, row tiles, steps of the longest block
     for (int32_t s = 0; s < num_segs; ++s) {
         const int64_t blocks = (cu[s + 1] - cu[s] + 31) / 32, ctx_steps = (ctx_lens[s] + 31) / 32;
@@ -885,11 +918,14 @@ static tetri_status attn_common(const char *fn, tetri_ctx *h, const void *q, con
     if (host_cu && !stream_captures(hs)) {
         TilePlan plans[2];
         AttnParams shapes[2];                          // 4 and 8 slots
-        int32_t load[2] = {0, 0};
+        int32_t load[2] = {0, 0}, average[2] = {0, 0};
         const SlotChoice may = planned_slots(h, host_cu, host_ctx, num_segs);
         const int mem = may.four || may.eight ? plan_memory(h, hs) : -1;
-        for (int i = 0; i < 2; ++i) {
-            if (!(i == 0 ? may.four : may.eight)) continue;
+        for (int i = 1; i >= 0; --i) {
+            // (a few more tiles of 8 than workgroups, too long to be cut: one workgroup has two, most have one.  40 heads, 609 and 779 rows at
+            // 11600 cached tokens with five short segments: 626 us, on 4 slots 510)
+            const bool uneven = h->attn_variant == 0 && load[1] != 0 && 20 * (int64_t)load[1] > 29 * (int64_t)average[1];
+            if (!(i == 0 ? may.four || uneven : may.eight)) continue;
             AttnParams &x = shapes[i] = p;
             wave_grouping(x.g, 4 << i, &x.hpw, &x.rb);
             x.groups = x.Hq / x.hpw;
@@ -897,7 +933,7 @@ static tetri_status attn_common(const char *fn, tetri_ctx *h, const void *q, con
             x.rb_shift = log2i(x.rb);
             x.span_shift = x.groups <= 1 ? 3 : (x.groups <= 2 ? 2 : (x.groups <= 4 ? 1 : 0));
             x.gpx = (x.groups + (8 >> x.span_shift) - 1) / (8 >> x.span_shift);
-            load[i] = plan_tiles(h, host_cu, host_ctx, num_segs, x, h->split_keys && mem >= 0, plans[i]);
+            load[i] = plan_tiles(h, host_cu, host_ctx, num_segs, x, h->split_keys && mem >= 0, plans[i], average[i]);
         }
         if (load[0] + load[1] != 0) {
             int32_t pieces = 0;                        // of a tile of the second
@@ -937,7 +973,7 @@ static tetri_status attn_common(const char *fn, tetri_ctx *h, const void *q, con
     // still 4 % faster than eight-wavefront workgroups that divide the stages of a head among them.  On smaller
     // launches the eight-wavefront workgroup, which puts twice the wavefronts on its tile's CU, is the better one.
     int key_parts = h->attn_variant == 1 ? 1 : 2;
-    if (h->attn_variant == 0 && h->stream_wgs == 0 && (int64_t)(p.C / (32 * p.rb)) * groups * 4 >= 5 * (int64_t)cus) key_parts = 1;
+    if (h->attn_variant == 0 && h->stream_wgs == 0 && tiles_fill(h)) key_parts = 1;
     p.tiles = tile_bound(p.C, p.S, 32 * p.rb);
     p.gpx = (groups + 7) / 8;
     // How the work of a head group is handed out (see the kernel):

@@ -43,6 +43,11 @@ CHOICES = [
     # 4 or 8 slots
     (40, 40, 0, [(512, 6144)], "eight"), (24, 8, 0, [(512, 4000)], "four"), (16, 16, 0, [(1024, 2560)], "short"), (16, 16, 0, [(1024, 4200)], "eight"),
     (32, 8, 0, [(2048, 300)], "eight"),
+    # more short tiles than compute units: nothing to balance; one long context; one that is long beside few
+    (32, 8, 0, [(102, 0)] * 40, "self"), (32, 8, 1, [(102, 512)] + [(102, 0)] * 39, "self"), (32, 8, 0, [(102, 641)] + [(102, 0)] * 39, "self"),
+    (32, 8, 0, [(102, 1000)] + [(102, 0)] * 39, "four"), (32, 8, 0, [(102, 641)] + [(102, 0)] * 30, "four"), (16, 16, 0, [(103, 0)] * 40, "self"),
+    # 35 tiles of 8 slots, all long, for 32 workgroups
+    (40, 40, 1, [(609, 11542), (752, 63), (210, 251), (75, 4326), (779, 11722), (134, 241), (477, 143)], "four"),
 ]
 
 
