@@ -536,17 +536,18 @@ static bool plan_short(const tetri_ctx *h, const int32_t *cu, const int32_t *ctx
     //    some compute units half empty, also up to 27 (14) steps on a wavefront times the part of the two (256 rows of 40 heads:
     //    1.05 (1.18) at 14 steps, 1.14 (1.3) at 22, 1.26 (1.4) at 32; 512 rows of 24/8 heads: 0.98 (1.07) at 16, 1.03 (1.14) at 24);
     //  - more: what a launch takes is the chain of steps of its longest row blocks, which the total does not show: up to 30000 (15000)
-    //    steps in all with 22 (11) on a wavefront, at two to a row block.  Where the work is even over the row blocks of several segments,
+    //    steps in all with 22 (11) on a wavefront, at two to a row block, and 22 as laid out (1.08 at 24, 1.07 to 1.16 at 29).  Where the work is even over the row blocks of several segments,
     //    the shared-tile kernel's tiles are ragged and teams keep the chains short: up to 30000 whatever the chain, over codes 20000
     //    unless every query head has K and V of its own (40 heads, 300 rows at 1000 and 212 at 200 cached tokens: 0.75 (0.75); 200 at 2000
     //    and 312 at 600: 0.87 (0.94); 32/8 heads, the same: 1.0 (1.1), 345 at 1353 and 167 at 0: 0.85 (0.95)).
     // head_dim 64: always (1.3 % over 224 chunks of 40x64 and 12/4x64, up to 24 % on single ones; a limit on the chain gains nothing).
     const int Hkv = h->cfg.num_kv_heads;
     const int64_t chain = (most + wavefronts - 1) / wavefronts;
+    const bool even = num_segs > 1 && (int64_t)most * n <= 2 * steps;
     if (h->cfg.head_dim == 64) shape.preferred = true;
     else if (wgs <= cus) shape.preferred = chain <= (wgs == cus || p.splits > 2 ? 128 : (p.splits == 2 ? 2 * (fp8 ? 15 : 20) : (fp8 ? 12 : 16)));
     else if (wgs <= 2 * cus) shape.preferred = total <= (fp8 ? 20000 : 65000);        // (the steps on a wavefront: below)
-    else if (num_segs > 1 && (int64_t)most * n <= 2 * steps) shape.preferred = total <= (fp8 && Hq != Hkv ? 20000 : 30000);
+    else if (even) shape.preferred = total <= (fp8 && Hq != Hkv ? 20000 : 30000);
     else shape.preferred = total <= (fp8 ? 15000 : 30000) && chain <= (fp8 ? 11 : 22);
     if (!shape.preferred && h->attn_variant != 3) return true;      // (not to be laid out)
     std::sort(units, units + n, [](const Unit &a, const Unit &b) { return a.steps > b.steps; });
@@ -579,10 +580,15 @@ static bool plan_short(const tetri_ctx *h, const int32_t *cu, const int32_t *ctx
         }
         return first_wg;
     };
-    // the least cap for which all workgroups are on the chip at once, and the steps on a wavefront
+    // the least cap for which all workgroups are on the chip at once (searched for in steps of a quarter, it was up to a fifth more: 1024
+    // rows of 40 heads 32.4 us, now 30.7; 735 and 810 of 24/8 33.3, now 31.3), and the steps on a wavefront
     auto search = [&](int nwl, int32_t &longest) -> int32_t {
         int32_t cap = 1;
-        while (cap < most && lay_out(nwl, cap) > 8 * room >> nwl) cap += std::max(1, cap / 4);
+        for (int32_t above = most; cap < above;) {
+            const int32_t mid = cap + (above - cap) / 2;
+            if (lay_out(nwl, mid) > 8 * room >> nwl) cap = mid + 1;
+            else above = mid;
+        }
         longest = 0;
         for (int i = 0; i < n; ++i) {
             const int t = team(units[i].steps, cap, nwl);
@@ -606,6 +612,7 @@ static bool plan_short(const tetri_ctx *h, const int32_t *cu, const int32_t *ctx
     p.attn_wgs = lay_out(nwl, cap);
     shape.nwl = nwl;
     if (h->cfg.head_dim != 64 && wgs > cus && wgs < 2 * cus) shape.preferred = shape.preferred && 2 * cus * longest <= (fp8 ? 14 : 27) * wgs;
+    else if (h->cfg.head_dim != 64 && wgs > 2 * cus && !even && !fp8) shape.preferred = shape.preferred && longest <= 22;
     return (uint64_t)(wgs * p.splits + p.zero_wgs + 8) * (uint64_t)std::max<int64_t>(Hq, p.splits) < 0x100000000ull;   // (the divisions by multiplication)
 }
 

@@ -4,6 +4,7 @@
 // without a GPU, also where the real thing would be a race.  argv[1] names the check.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -43,6 +44,7 @@ int g_parts = 0, g_ranges = 0;                // how the last decode was cut
 std::string g_kernel;                         // the attention kernel launched last
 const char *g_partials = nullptr;             // where the last attention or decode launch keeps partial results
 int g_out_past_l2 = -1;                       // how the last launch of the short kernel stores its output
+int g_longest = 0, g_short_wgs = 0;           // the steps of its longest wavefront, and its workgroups (of the attention)
 int g_places = 0;                             // of the last division made by the host: tiles' pieces there
 
 struct Event { bool pending = false; };       // pending: work in front of it that nobody has waited for
@@ -128,6 +130,13 @@ hipError_t tetri_launch_short(int, bool, const ShortParams &p, int, hipStream_t)
 {
     g_kernel = "short";
     g_out_past_l2 = p.out_past_l2;
+    g_longest = 0;
+    g_short_wgs = p.attn_wgs;
+    for (int tl = 0; tl < 4; ++tl)
+        for (int u = p.first_unit[tl]; u < (tl == 0 ? p.units : p.first_unit[tl - 1]); ++u) {
+            const int steps = (int)((p.unit[u][1] & 0x3ffffff) + 31) / 32 + (int)(p.unit[u][0] >> 6 & 127) + 1;
+            g_longest = std::max(g_longest, (steps + (1 << tl) - 1) >> tl);
+        }
     if (p.splits > 1) g_counters.push_back({p.counters, p.counters_next, p.n_counters});
     return hipSuccess;
 }
@@ -428,6 +437,20 @@ void short_output_stores()
     tetri_destroy(h);
 }
 
+// Teams are as small as leaves all workgroups on the chip at once and no smaller: 32 row blocks of 1 to 32 steps and 40 heads, 512 places
+// for workgroups of four wavefronts, take 480 with up to 16 steps to a wavefront (15 would take 530).
+void short_teams()
+{
+    const tetri_config c = {40, 40, 128, 16, 1024, 8192, 512, 40, TETRI_BF16};
+    tetri_ctx *h = nullptr;
+    CHECK(tetri_create(&c, &h) == TETRI_OK);
+    const int32_t *meta = reinterpret_cast<const int32_t *>(g_any);
+    const int32_t cu[2] = {0, 1024}, ctx = 0;
+    CHECK(tetri_chunk_prefill_planned(h, g_any, g_any, g_any, g_any, meta, meta, meta, 1, 0.1f, 1, 0, 1.f, 1.f, cu, &ctx, g_any, nullptr) == TETRI_OK);
+    CHECK(g_kernel == "short" && g_longest == 16 && g_short_wgs == 480);
+    tetri_destroy(h);
+}
+
 // How the host cuts a decode batch: equal ranges where there is much to read and fewer than two pairs per compute unit
 // (the batches of test_gpu_decode_ranges.py's default rule are among these), equal parts or whole pairs otherwise.
 void decode_division()
@@ -466,6 +489,7 @@ int main(int argc, char **argv)
     else if (name == "uploads_name_no_stream_later") uploads_name_no_stream_later();
     else if (name == "choice_of_kernel") choice_of_kernel();
     else if (name == "short_output_stores") short_output_stores();
+    else if (name == "short_teams") short_teams();
     else if (name == "decode_division") decode_division();
     else return 2;
     std::printf("%s: ok\n", name.c_str());

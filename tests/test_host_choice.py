@@ -38,6 +38,9 @@ CHOICES = [
     # even work over several segments; uneven work
     (32, 8, 1, [(300, 1000), (212, 200)], "short"), (32, 8, 1, [(36, 1191), (476, 0)], "four"), (40, 40, 1, [(200, 2000), (312, 600)], "short"),
     (32, 8, 1, [(200, 2000), (312, 600)], "four"),
+    # the longest wavefront as laid out: 16 steps, 24, 29
+    (40, 40, 0, [(1024, 0)], "short"), (16, 16, 0, [(1235, 0), (139, 0), (1196, 0), (258, 657), (17, 90)], "four"),
+    (32, 8, 0, [(538, 0), (591, 32), (45, 158), (505, 729)], "four"),
     # row tiles and helpers that fill the chip; not even, not filling, too long
     (40, 40, 1, [(512, 1000)], "self"), (40, 40, 0, [(100, 3000), (412, 0)], "four"), (40, 40, 0, [(384, 3000)], "four"), (40, 40, 0, [(512, 2560)], "eight"),
     # 4 or 8 slots
