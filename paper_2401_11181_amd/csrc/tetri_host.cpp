@@ -802,10 +802,11 @@ static int32_t plan_tiles(const tetri_ctx *h, const int32_t *cu, const int32_t *
 // 32 keys x 32 rows, 8 from 75000 on; in between both divisions are laid out and their longest workgroups compared: 4 where it has
 // fewer stages than 1.7 times those of 8 and half a stage for each piece that the tiles of 8 are cut into (the merge).  Timed on 33 such
 // chunks of the 16-bit and the FP8 cache (40x128, 32/8 and 8/2 heads, 256 to 2048 rows, 0 to 13000 cached tokens): 0.4 % on average
-// against the better shape each time, 6 % at most (without the merge 2.5 % and 26 %, by the number of steps alone 1.3 % and 21 %).  None: where the launch that divides itself fills the chip with row tiles and their helpers, whose
-// wavefronts walk a head's keys side by side (an odd number of query heads to a kv head, evenly spread work, under 50000 steps: 512 rows of
-// 40 heads at 1000 cached tokens 34.3 us (FP8 37.8) against 38.2 (44.2); at 2560, 56000 steps, 48.2 against 46.8; 384 rows,
-// which fill 200 compute units: 41.0 against 37.3).
+// against the better shape each time, 6 % at most (without the merge 2.5 % and 26 %, by the number of steps alone 1.3 % and 21 %).  None: over
+// codes, where the launch that divides itself fills the chip with up to four row tiles to a head and their helpers, whose wavefronts walk a head's
+// keys side by side (an odd number of query heads to a kv head, evenly spread work, under 50000 steps: the chunks of 512 rows of 40 heads at 1024 and
+// 1536 cached tokens 1.3 us less of 83; over 16-bit rows 2.6 us more of 76; with more tiles to a head, 24/8, 20, 16 and 12 heads, prompts of 1500 to
+// 3900 tokens take 1.04 to 1.41 times as long).
 struct SlotChoice { bool four, eight; };
 
 // Does a full chunk of the handle have five row tiles of 4 slots or more for every four compute units?  Then the launch that divides
@@ -837,7 +838,7 @@ static bool short_even_tiles(const tetri_ctx *h, const int32_t *cu, const int32_
     return 4 * tiles * groups >= 5 * cus && (longest <= 5 || 20 * longest * cus <= 27 * stages * groups);
 }
 
-static SlotChoice planned_slots(const tetri_ctx *h, const int32_t *cu, const int32_t *ctx_lens, int32_t num_segs)
+static SlotChoice planned_slots(const tetri_ctx *h, const int32_t *cu, const int32_t *ctx_lens, int32_t num_segs, bool fp8)
 {
     if (h->cfg.head_dim != 128) return {false, false};
     if (h->attn_variant == 4) return {false, true};
@@ -853,7 +854,7 @@ static SlotChoice planned_slots(const tetri_ctx *h, const int32_t *cu, const int
         most = std::max(most, ctx_steps + blocks);
     }
     const int64_t Hq = h->cfg.num_q_heads, self = (tiles + tiles / 2) * Hq;
-    if (Hq / h->cfg.num_kv_heads % 2 != 0 && steps * Hq < 50000 && most * all <= 2 * steps && self <= h->num_cus && 8 * self > 7 * h->num_cus)
+    if (fp8 && tiles <= 4 && Hq / h->cfg.num_kv_heads % 2 != 0 && steps * Hq < 50000 && most * all <= 2 * steps && self <= h->num_cus && 8 * self > 7 * h->num_cus)
         return {false, false};
     return {steps * Hq < 75000, steps * Hq >= 30000};
 }
@@ -926,7 +927,7 @@ static tetri_status attn_common(const char *fn, tetri_ctx *h, const void *q, con
         TilePlan plans[2];
         AttnParams shapes[2];                          // 4 and 8 slots
         int32_t load[2] = {0, 0}, average[2] = {0, 0};
-        const SlotChoice may = planned_slots(h, host_cu, host_ctx, num_segs);
+        const SlotChoice may = planned_slots(h, host_cu, host_ctx, num_segs, fp8);
         const int mem = may.four || may.eight ? plan_memory(h, hs) : -1;
         for (int i = 1; i >= 0; --i) {
             // (a few more tiles of 8 than workgroups, too long to be cut: one workgroup has two, most have one.  40 heads, 609 and 779 rows at

@@ -43,6 +43,8 @@ CHOICES = [
     (32, 8, 0, [(538, 0), (591, 32), (45, 158), (505, 729)], "four"),
     # row tiles and helpers that fill the chip; not even, not filling, too long
     (40, 40, 1, [(512, 1000)], "self"), (40, 40, 0, [(100, 3000), (412, 0)], "four"), (40, 40, 0, [(384, 3000)], "four"), (40, 40, 0, [(512, 2560)], "eight"),
+    # ... over 16-bit rows, or with more than four tiles to a head
+    (40, 40, 0, [(512, 1000)], "four"), (24, 8, 1, [(896, 1000)], "four"), (20, 20, 0, [(1024, 1000)], "four"), (12, 12, 1, [(1792, 600)], "four"),
     # 4 or 8 slots
     (40, 40, 0, [(512, 6144)], "eight"), (24, 8, 0, [(512, 4000)], "four"), (16, 16, 0, [(1024, 2560)], "short"), (16, 16, 0, [(1024, 4200)], "eight"),
     (32, 8, 0, [(2048, 300)], "eight"),
