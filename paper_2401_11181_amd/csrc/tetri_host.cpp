@@ -898,7 +898,7 @@ static tetri_status attn_common(const char *fn, tetri_ctx *h, const void *q, con
     // ---- a chunk with little work, its segments known on the host.  (What is captured into a graph is replayed for other
     // metadata in the same device arrays: a launch that carries the segments along is not the one to capture.)
     ShortParams sp;
-    ShortShape shape;
+    ShortShape shape = {0, false};
     // A caller who has set one of the shared-tile kernel's ways of dividing its work gets that kernel.
     if (host_cu && (h->attn_variant == 3 || (h->attn_variant == 0 && !h->division_set)) && !stream_captures(hs) &&
         plan_short(h, host_cu, host_ctx, num_segs, fp8, sp, shape) && (shape.preferred || h->attn_variant == 3)) {

@@ -1,8 +1,9 @@
 // Driver of tests/test_host_plan.py: the host layer (tetri_host.cpp, tetri_plan.cpp) with launchers that check the division of
-// a launch of the shared-tile kernel instead of running it.  Draws chunks (argv: seed, number of draws, heads, kv heads, chunk size) and fails
-// if a stage of a row tile is missing or done twice, a partial result or an arrival counter lies outside the handle's
-// memory or belongs to two tiles, or a workgroup's chain of jobs does not end.  With "time" as a further argument: chunks of packed
-// short prompts, some behind a carried-over one, by the library's own choice of kernel; prints what a call takes of the host.
+// a launch of the shared-tile kernel instead of running it.  Draws chunks (argv: seed, number of draws, heads, kv heads, chunk size,
+// "attn_variant" (4), "split_keys" (1)) and fails if a stage of a row tile is missing or done twice, a partial result or an arrival counter lies outside the handle's
+// memory or belongs to two tiles, a workgroup's chain of jobs does not end, or a tile is shared in spite of split_keys = 0.  With "time" in
+// place of the last two: chunks of packed short prompts, some behind a carried-over one, by the library's own choice of kernel;
+// prints what a call takes of the host.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -60,16 +61,18 @@ hipError_t tetri_launch_upload_inline(const int32_t *, int32_t *, int64_t, hipSt
 namespace {
 
 std::vector<int32_t> g_cu, g_ctx;
-int g_planned = 0, g_shared = 0;
+int g_planned = 0, g_shared = 0, g_eight = 0, g_variant = 0;
 bool g_timed = false;
 
 void check_plan(const tetri_ctx *h, const AttnParams &p)
 {
     const TilePlan &plan = *p.plan;
-    const int pools = 8 >> p.span_shift, rows = 32 * p.rb;
-    CHECK(p.hpw * p.rb == 8 && p.groups * p.hpw == p.Hq && p.g % p.hpw == 0 && (1 << p.hpw_shift) == p.hpw && (1 << p.rb_shift) == p.rb);
+    const int pools = 8 >> p.span_shift, rows = 32 * p.rb, slots = p.hpw * p.rb;
+    CHECK((g_variant == 0 ? slots == 4 || slots == 8 : slots == (g_variant == 4 ? 8 : 4)) && p.groups * p.hpw == p.Hq && p.g % p.hpw == 0 && (1 << p.hpw_shift) == p.hpw && (1 << p.rb_shift) == p.rb);
     CHECK(pools * p.gpx >= p.groups && p.attn_grid % 8 == 0 && (p.attn_grid / 8) << p.span_shift >= plan.wgs && plan.wgs <= kPlanJobs);
-    CHECK((int64_t)pools * plan.places * 8 <= (int64_t)(2 * h->scratch_units) && (int64_t)pools * plan.places * 8 <= p.n_counters);
+    CHECK((int64_t)pools * plan.places * slots <= (int64_t)(2 * h->scratch_units) && (int64_t)pools * plan.places * slots <= p.n_counters);
+    CHECK(plan.places == 0 || h->split_keys != 0);
+    g_eight += slots == 8;
     CHECK(plan.rows == g_cu.back());
     struct Piece { int begin, end, piece, npieces, place; };
     std::map<std::tuple<int, int, int>, std::vector<Piece>> tiles;       // (group, segment, first row)
@@ -126,7 +129,8 @@ hipError_t tetri_launch_attn(const tetri_ctx *h, const AttnParams &p, int, bool,
 int main(int argc, char **argv)
 {
     g_timed = argc == 7 && std::strcmp(argv[6], "time") == 0;
-    CHECK(argc == 6 || g_timed);
+    CHECK(argc == 6 || argc == 8 || g_timed);
+    g_variant = g_timed ? 0 : (argc == 8 ? std::atoi(argv[6]) : 4);
     std::mt19937 rng((unsigned)std::atoi(argv[1]));
     const int draws = std::atoi(argv[2]), hq = std::atoi(argv[3]), hkv = std::atoi(argv[4]), chunk = std::atoi(argv[5]);
     alignas(16) static char any[64];
@@ -134,7 +138,8 @@ int main(int argc, char **argv)
     const tetri_config c = {hq, hkv, 128, 16, chunk, 1 << 20, 4096, std::min(chunk, 64), TETRI_BF16};
     tetri_ctx *h = nullptr;
     CHECK(tetri_create(&c, &h) == TETRI_OK);
-    CHECK(tetri_set_option(h, "attn_variant", g_timed ? 0 : 4) == TETRI_OK);
+    CHECK(tetri_set_option(h, "attn_variant", g_variant) == TETRI_OK);
+    if (argc == 8 && std::atoi(argv[7]) == 0) CHECK(tetri_set_option(h, "split_keys", 0) == TETRI_OK);
     auto upto = [&](int n) { return (int)(rng() % (unsigned)n); };
     std::vector<double> us;
     for (int d = 0; d < draws && g_timed; ++d) {
@@ -176,5 +181,6 @@ int main(int argc, char **argv)
     }
     tetri_destroy(h);
     std::printf("%d launches, %d on a division of the host\n", g_shared, g_planned);
+    if (argc == 8) std::printf("with eight slots: %d\n", g_eight);
     return 0;
 }

@@ -43,6 +43,27 @@ def test_division(driver, heads, chunk):
     assert launches == 300 and planned >= 100, res.stdout
 
 
+# the same with row tiles of 4 slots, and with no tile shared
+@pytest.mark.parametrize("heads, chunk", [((40, 40), 512), ((40, 40), 2048), ((32, 8), 2048), ((24, 8), 500), ((12, 12), 1000),
+                                          ((8, 2), 4096), ((6, 2), 77), ((4, 4), 4096), ((32, 8), 1), ((40, 8), 8192)])
+@pytest.mark.parametrize("variant, split_keys", [(5, 1), (4, 0), (5, 0)])
+def test_division_by_options(driver, heads, chunk, variant, split_keys):
+    res = subprocess.run([driver, "17", "300", str(heads[0]), str(heads[1]), str(chunk), str(variant), str(split_keys)],
+                         capture_output=True, text=True, timeout=120)
+    assert res.returncode == 0, res.stdout + res.stderr
+    launches, planned, eight = (int(x) for x in res.stdout.split() if x.isdigit())
+    assert launches == 300 and planned >= 25 and eight == (planned if variant == 4 else 0), res.stdout
+
+
+# by the library's choice, which lays both shapes out in between and takes one of them
+@pytest.mark.parametrize("heads, chunk", [((40, 40), 1024), ((40, 40), 2048), ((32, 8), 2048), ((24, 8), 1500), ((8, 2), 4096), ((40, 8), 8192)])
+def test_chosen_division(driver, heads, chunk):
+    res = subprocess.run([driver, "18", "300", str(heads[0]), str(heads[1]), str(chunk), "0", "1"], capture_output=True, text=True, timeout=120)
+    assert res.returncode == 0, res.stdout + res.stderr
+    _launches, planned, eight = (int(x) for x in res.stdout.split() if x.isdigit())
+    assert 0 < eight < planned, res.stdout
+
+
 @pytest.mark.parametrize("heads, chunk", [((8, 2), 4096), ((40, 40), 2048), ((32, 8), 2048)])
 def test_host_time_of_a_call(optimised_driver, heads, chunk):
     """A call lays its launch out in line with launches of 20 us and more.  With a search that tried every length of the pieces in turn,
