@@ -567,7 +567,17 @@ static bool plan_short(const tetri_ctx *h, const int32_t *cu, const int32_t *ctx
     p.hkx = Hkv >> p.rshift;
     p.spread = wgs <= cus;
     // (of a row block of n steps, at most `cap` to a wavefront)
-    auto team = [](int32_t st, int32_t cap, int nwl) { int t = 0; while (t < nwl && (cap << t) < st) ++t; return t; };
+    // head_dim 64, more row blocks than the chip takes with teams of three on average, the work evenly spread or more than one round in any case:
+    // teams of two at least, the shortest row blocks in a further round.  (In one round, with single wavefronts for the shorter half: 4096 rows of 16 heads, nothing cached, 81 us
+    // (FP8 95), now 66 (84); 4096 of 12/4 62 (79), now 58 (65); 2048 of 32/8 at 2200 113, now 92; 1280 row blocks 0.98 to 1.04.  Uneven work over
+    // codes, 1984 row blocks of 15 segments: 78 in one round, 142.)
+    const bool twos = h->cfg.head_dim == 64 && 2 * wgs > 5 * room && (2 * wgs <= 9 * room || total > 16 * wgs)
+                      && ((int64_t)most * n <= 2 * steps || wgs > 8 * room);
+    auto team = [&](int32_t st, int32_t cap, int nwl) {
+        int t = 0;
+        while (t < nwl && (cap << t) < st) ++t;
+        return twos ? std::max(t, 1) : t;
+    };
     auto lay_out = [&](int nwl, int32_t cap) -> int32_t {
         int32_t first_wg = 0;
         for (int tl = 3, i = 0; tl >= 0; --tl) {

@@ -449,6 +449,16 @@ void short_teams()
     CHECK(tetri_chunk_prefill_planned(h, g_any, g_any, g_any, g_any, meta, meta, meta, 1, 0.1f, 1, 0, 1.f, 1.f, cu, &ctx, g_any, nullptr) == TETRI_OK);
     CHECK(g_kernel == "short" && g_longest == 16 && g_short_wgs == 480);
     tetri_destroy(h);
+    // head_dim 64, 128 row blocks of 1 to 128 steps and 16 heads: two wavefronts to each in two rounds, not one round with up to 52 steps to
+    // single ones; a long context beside them: one round
+    const tetri_config c64 = {16, 16, 64, 16, 4096, 8192, 1024, 40, TETRI_BF16};
+    CHECK(tetri_create(&c64, &h) == TETRI_OK);
+    const int32_t cu64[2] = {0, 4096}, ragged[3] = {0, 96, 4096}, contexts[2] = {9000, 0};
+    CHECK(tetri_chunk_prefill_planned(h, g_any, g_any, g_any, g_any, meta, meta, meta, 1, 0.1f, 1, 0, 1.f, 1.f, cu64, &ctx, g_any, nullptr) == TETRI_OK);
+    CHECK(g_longest == 64 && g_short_wgs == 128 * 16 / 2);
+    CHECK(tetri_chunk_prefill_planned(h, g_any, g_any, g_any, g_any, meta, meta, meta, 2, 0.1f, 1, 0, 1.f, 1.f, ragged, contexts, g_any, nullptr) == TETRI_OK);
+    CHECK(g_longest >= 71 && g_short_wgs <= 1024);
+    tetri_destroy(h);
 }
 
 // How the host cuts a decode batch: equal ranges where there is much to read and fewer than two pairs per compute unit

@@ -21,6 +21,7 @@ CASES = {
     "long": (24, 8, 128, [(500, 3003)]),
     "head-dim-64": (12, 4, 64, [(33, 1203), (64, 129), (90, 0), (301, 17), (2, 600)]),
     "head-dim-64-many": (40, 40, 64, [(50, 1100), (400, 30), (128, 0)]),
+    "twos": (40, 40, 64, [(1031, 17)]),                        # more than one round of workgroups, no row block with one wavefront
 }
 
 
