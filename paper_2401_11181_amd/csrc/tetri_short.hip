@@ -9,7 +9,7 @@
 //     decode kernel).  The host, which knows the segments of the chunk, gives each row block the team that leaves its
 //     wavefronts about as many steps as those of the others and fills the chip's places for wavefronts (plan_short): with one
 //     size of team for all row blocks a launch lasted as long as its longest one (512 rows of 40 heads: 18.3 us, now 14.0; 286 short
-//     prompts of 40 heads in 64 chunks: 1154 us, now 1012);
+//     prompts of 40 heads in 64 chunks: 1154 us, now 1006);
 //   * the row blocks, longest first, travel in the kernel arguments: a workgroup's first memory access after those is its page
 //     ids, the second Q, K and V;
 //   * few row blocks with long key ranges: the keys of a row block are split over several workgroups, so that every compute
