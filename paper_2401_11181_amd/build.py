@@ -12,8 +12,10 @@ NATIVE = os.path.join(HERE, "_native.so")
 SOURCES = ["tetri_host.cpp", "tetri_plan.cpp", "tetri_append.hip", "tetri_kv_transfer.hip", "tetri_decode.hip", "tetri_attn.hip", "tetri_planned.hip", "tetri_short.hip"]
 HEADERS = [os.path.join(CSRC, "tetri_internal.h"), os.path.join(CSRC, "tetri_plan.h"), os.path.join(CSRC, "attn_common.h"), os.path.join(CSRC, "attn_tile.h"), os.path.join(ROOT, "include", "tetri.h")]
 
-# packed-fp32 instructions are switched off for all device code
+# packed-fp32 instructions are switched off for all device code; a kernel's leading scalar arguments (up to 14 words in front of
+# its first structure) are in registers when a wavefront starts, instead of a first memory read away
 HIP_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fvisibility=hidden",
+             "-mllvm", "-amdgpu-kernarg-preload-count=16",
              "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
              "-Wno-unused-command-line-argument", "-Wno-ignored-attributes"]
 
