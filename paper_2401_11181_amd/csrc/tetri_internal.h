@@ -130,8 +130,8 @@ struct AttnParams {
 
 // Launch parameters of the attention kernel for chunks with little work (tetri_short.hip): the chunk's row blocks travel in them.
 constexpr int kShortSegs = 40, kShortUnits = 128;
-struct ShortParams {
-    // (read together at the kernel's start, 64 bytes)
+struct __attribute__((aligned(64))) ShortParams {
+    // (what finds a wavefront's row block: the kernel gets these packed, as arguments in front of the structure)
     int32_t first_wg[4];          // of the row blocks of 1, 2, 4 and 8 wavefronts: the classes follow each other from 8 down ...
     int32_t first_unit[4];        // ... and their first row blocks
     int32_t attn_wgs;             // workgroups but for those that write the padding rows
@@ -142,12 +142,12 @@ struct ShortParams {
     int32_t hkx;                  // ... and such kv heads
     uint32_t hkx_magic;
     int32_t rshift;
-    // (64 more)
+    // (read together at the kernel's start, 64 bytes ...)
     const uint16_t *q, *k_new, *v_new, *pages;
     const int32_t *bt;
     uint16_t *out, *pages_w;      // pages_w: pool for the fused append (null: none)
     const void *zero;             // a row of zeros
-    // (64 more)
+    // (... and 64 more)
     int32_t C, rows;              // chunk rows, and those that belong to a request
     int32_t Hq, Hkv, g, max_blocks;
     int32_t units;                // row blocks of 32 rows

@@ -79,8 +79,16 @@ template <int D> struct CodeTile {
     static __device__ __forceinline__ constexpr int swizzle(int row) { return D == 128 ? row & 7 : (row >> 2) & 3; }
 };
 
+// Bytes of the kernel's arguments in front of its structure (which starts on a cache line).  What a wavefront's row block is found with
+// comes first and by itself: those words are in scalar registers when a wavefront starts, and the row block, with the pointers that
+// go with it, is one read of the arguments away instead of two.
+constexpr int kShortLead = 64;
+static_assert(alignof(ShortParams) == kShortLead, "52 bytes of arguments, then the structure");
+
 template <int D, bool F8, int NW>
-__global__ __launch_bounds__(NW * 64, D == 64 ? (F8 ? 3 : 4) : 2) void attn_short_kernel(ShortParams)
+__global__ __launch_bounds__(NW * 64, D == 64 ? (F8 ? 3 : 4) : 2) void attn_short_kernel(
+    const int32_t *block_tables, int max_blocks, int first_wg0, int first_wg1, int first_wg2, uint32_t first_units, int attn_wgs, uint32_t shape,
+    uint32_t splits_magic, uint32_t hpx_magic, uint32_t hkx_magic, uint32_t per_x, ShortParams)
 {
     typedef CodeTile<D> CT;
     constexpr int KSTEPS = D / 16, DBLK = D / 32, NI = D / 16, CH = D / 8, RPI = 64 / CH;
@@ -88,17 +96,58 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? (F8 ? 3 : 4) : 2) void attn_shor
     constexpr int ESZ = F8 ? 1 : 2, NWL = NW == 8 ? 3 : 2;
     static_assert(2 * CT::NI == NI && 2 * CT::BYTES == TILE_BYTES, "a step of codes takes a region");
     __shared__ __attribute__((aligned(1024))) char smem[NW * 2 * TILE_BYTES];
+    __shared__ __attribute__((aligned(1024))) char q_rows[NW / 4 * TILE_BYTES];      // of teams of 4 and 8
     __shared__ float stat[NW][2][32];
     __shared__ int last;
-    const const_params *p = (const const_params *)__builtin_amdgcn_kernarg_segment_ptr();
+    // (the structure lies behind the leading arguments)
+    const const_params *p = (const const_params *)((__attribute__((address_space(4))) const char *)__builtin_amdgcn_kernarg_segment_ptr() + kShortLead);
 
-    // the launch's shape and pointers, in one round trip: read where they are used, they are four or five
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int half = lane >> 5, l32 = lane & 31;
+    const int bid = blockIdx.x;
+    if (bid >= attn_wgs) {
+        // ---- padding rows [rows, C) are written as +0, 16 bytes per lane and pass
+        const size_t first = (size_t)p->rows * p->Hq * CH, n = (size_t)p->C * p->Hq * CH;
+        const size_t stride = (size_t)(gridDim.x - attn_wgs) * (NW * 64);
+        for (size_t i = first + (size_t)(bid - attn_wgs) * (NW * 64) + tid; i < n; i += stride)
+            reinterpret_cast<global_u32x4_w *>((uintptr_t)p->out)[i] = u32x4{0u, 0u, 0u, 0u};
+        return;
+    }
+    // ---- the wavefront's row block, head and place in its team.  Row blocks come in classes of 8, 4, 2 or 1 wavefronts (1 <<
+    // tl), the longest first.  The heads whose kv head is x modulo R (R = 1 << rshift) sit in workgroups x modulo R: those
+    // that share a kv head run on one XCD (R = 8).
+    const int fu0 = first_units & 255, fu1 = (first_units >> 8) & 255, fu2 = (first_units >> 16) & 255, units = first_units >> 24;
+    const int splits = shape & 255, rshift = (shape >> 8) & 3, hpx = per_x & 0xffff, hkx = per_x >> 16;
+    const int tl = bid >= first_wg0 ? 0 : (bid >= first_wg1 ? 1 : (bid >= first_wg2 ? 2 : 3));
+    const int T = 1 << tl;
+    int j = bid - (tl == 0 ? first_wg0 : (tl == 1 ? first_wg1 : (tl == 2 ? first_wg2 : 0)));
+    const int u_first = tl == 0 ? fu0 : (tl == 1 ? fu1 : (tl == 2 ? fu2 : 0));
+    const int u_end = tl == 0 ? units : (tl == 1 ? fu0 : (tl == 2 ? fu1 : fu2));
+    int part = 0;
+    if (splits > 1) {
+        const int q = magic_div(j, splits_magic);
+        part = j - q * splits;
+        j = q;
+    }
+    const int x = j & ((1 << rshift) - 1);
+    const int pack = (shape >> 10) != 0 ? 0 : NWL - tl;      // log2 of a workgroup's teams (few row blocks: one, on a compute unit of its own)
+    const int team_ = wave >> tl, item_ = ((j >> rshift) << pack) + team_, rank = wave & (T - 1), team0 = wave - rank;
+    const int ul = magic_div(item_, hpx_magic), hh = item_ - ul * hpx;
+    const int hgrp = magic_div(hh, hkx_magic), kh = x + ((hh - hgrp * hkx) << rshift);
+    const bool valid = u_first + ul < u_end && (team_ >> pack) == 0;
+    const int u = valid ? u_first + ul : u_first;
+
+    // the row block, and the launch's shape and pointers, in one round trip: read where they are used, they are four or five
     typedef __attribute__((ext_vector_type(16))) int i32x16;
+    typedef __attribute__((ext_vector_type(2))) int i32x2s;
     typedef __attribute__((address_space(4))) const i32x16 const_i32x16;
-    static_assert(offsetof(ShortParams, q) == 64 && offsetof(ShortParams, C) == 128, "read as three vectors");
-    i32x16 hd = ((const const_i32x16 *)p)[0], hp = ((const const_i32x16 *)p)[1], hc = ((const const_i32x16 *)p)[2];
+    typedef __attribute__((address_space(4))) const i32x2s const_i32x2s;
+    static_assert(offsetof(ShortParams, q) == 64 && offsetof(ShortParams, C) == 128, "read as vectors");
+    i32x16 hp = ((const const_i32x16 *)p)[1], hc = ((const const_i32x16 *)p)[2];
+    i32x2s unit = *(const const_i32x2s *)&p->unit[u];
     int out_past_l2 = p->out_past_l2;
-    asm volatile("" : "+s"(hd), "+s"(hp), "+s"(hc), "+s"(out_past_l2));
+    asm volatile("" : "+s"(hp), "+s"(hc), "+s"(unit), "+s"(out_past_l2));
     auto pointer = [&](auto i) __attribute__((always_inline)) -> char * {
         constexpr int I = decltype(i)::value;
         return reinterpret_cast<char *>((uintptr_t)((uint64_t)(uint32_t)hp[2 * I] | (uint64_t)(uint32_t)hp[2 * I + 1] << 32));
@@ -106,45 +155,10 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? (F8 ? 3 : 4) : 2) void attn_shor
     typedef std::integral_constant<int, 0> R0;
     typedef std::integral_constant<int, 1> R1;
     char *const p_q = pointer(R0()), *const p_k_new = pointer(R1()), *const p_v_new = pointer(std::integral_constant<int, 2>()),
-         *const p_pages = pointer(std::integral_constant<int, 3>()), *const p_bt = pointer(std::integral_constant<int, 4>()),
-         *const p_out = pointer(std::integral_constant<int, 5>()), *const p_pages_w = pointer(std::integral_constant<int, 6>()),
-         *const p_zero = pointer(std::integral_constant<int, 7>());
-    const int C = hc[0], rows = hc[1], Hq = hc[2], Hkv = hc[3], heads_per_kv = hc[4], max_blocks = hc[5], units = hc[6];
-    const int attn_wgs = hd[8], splits = hd[9], hpx = hd[11], hkx = hd[13], rshift = hd[15];
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int half = lane >> 5, l32 = lane & 31;
-    const int bid = blockIdx.x;
-    if (bid >= attn_wgs) {
-        // ---- padding rows [rows, C) are written as +0, 16 bytes per lane and pass
-        const size_t first = (size_t)rows * Hq * CH, n = (size_t)C * Hq * CH;
-        const size_t stride = (size_t)(gridDim.x - attn_wgs) * (NW * 64);
-        for (size_t i = first + (size_t)(bid - attn_wgs) * (NW * 64) + tid; i < n; i += stride)
-            reinterpret_cast<global_u32x4_w *>((uintptr_t)p_out)[i] = u32x4{0u, 0u, 0u, 0u};
-        return;
-    }
-    // ---- the wavefront's row block, head and place in its team.  Row blocks come in classes of 8, 4, 2 or 1 wavefronts (1 <<
-    // tl), the longest first.  The heads whose kv head is x modulo R (R = 1 << rshift) sit in workgroups x modulo R: those
-    // that share a kv head run on one XCD (R = 8).
-    const int tl = bid >= hd[0] ? 0 : (bid >= hd[1] ? 1 : (bid >= hd[2] ? 2 : 3));
-    const int T = 1 << tl;
-    int j = bid - (tl == 0 ? hd[0] : (tl == 1 ? hd[1] : (tl == 2 ? hd[2] : hd[3])));
-    const int u_first = tl == 0 ? hd[4] : (tl == 1 ? hd[5] : (tl == 2 ? hd[6] : hd[7]));
-    const int u_end = tl == 0 ? units : (tl == 1 ? hd[4] : (tl == 2 ? hd[5] : hd[6]));
-    int part = 0;
-    if (splits > 1) {
-        const int q = magic_div(j, hd[10]);
-        part = j - q * splits;
-        j = q;
-    }
-    const int x = j & ((1 << rshift) - 1);
-    const int pack = hc[15] != 0 ? 0 : NWL - tl;             // log2 of a workgroup's teams (few row blocks: one, on a compute unit of its own)
-    const int team_ = wave >> tl, item_ = ((j >> rshift) << pack) + team_, rank = wave & (T - 1), team0 = wave - rank;
-    const int ul = magic_div(item_, hd[12]), hh = item_ - ul * hpx;
-    const int hgrp = magic_div(hh, hd[14]), kh = x + ((hh - hgrp * hkx) << rshift);
-    const bool valid = u_first + ul < u_end && (team_ >> pack) == 0;
-    const int u = valid ? u_first + ul : u_first;
-    const uint32_t unit_lo = p->unit[u][0], unit_hi = p->unit[u][1];
+         *const p_pages = pointer(std::integral_constant<int, 3>()), *const p_out = pointer(std::integral_constant<int, 5>()),
+         *const p_pages_w = pointer(std::integral_constant<int, 6>()), *const p_zero = pointer(std::integral_constant<int, 7>());
+    const int Hq = hc[2], Hkv = hc[3], heads_per_kv = hc[4];
+    const uint32_t unit_lo = unit[0], unit_hi = unit[1];
     const int seg = unit_lo & 63, t0 = ((unit_lo >> 6) & 127) * 32, n_s = (unit_lo >> 13) & 8191, L = unit_hi & 0x3ffffff;
     const int row0 = (int)(unit_lo >> 26) | (int)(unit_hi >> 26) << 6;
     const int head = kh * heads_per_kv + hgrp;
@@ -162,7 +176,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? (F8 ? 3 : 4) : 2) void attn_shor
         return;
     }
 
-    const const_i32 *bt = (const const_i32 *)(uintptr_t)(p_bt + (size_t)seg * max_blocks * 4);
+    const const_i32 *bt = (const const_i32 *)(uintptr_t)(block_tables + (size_t)seg * max_blocks);
     const int last_entry = max_blocks - 1;
     const size_t head_bytes = (size_t)kPage * D * ESZ, page_bytes = 2 * (size_t)Hkv * head_bytes;
     const char *pool_k = p_pages + (size_t)kh * head_bytes;
@@ -299,35 +313,57 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? (F8 ? 3 : 4) : 2) void attn_shor
         }
     }
     // Q fragments (B operand of S^T = K Q^T): column l32 is row t0 + l32; rows past the segment's end are its row t0.  The rows
-    // come by way of the region that the stream needs second, whole rows of 256 bytes per instruction: as fragments, 32 bytes of
-    // 32 rows each, they took 1.6 us more of a launch with 1920 wavefronts.  (Fragments loaded from inline assembly with the
-    // wait further down are not safe: where the compiler spills, it spills registers that the load has yet to write.)
+    // come by way of LDS, whole rows per instruction: as fragments, 32 bytes of 32 rows each, they took 1.6 us more of a launch with
+    // 1920 wavefronts.  (Fragments loaded from inline assembly with the wait further down are not safe: where the compiler spills, it
+    // spills registers that the load has yet to write.)
     const int n_here = min(32, n_s - t0);
     bf16x8 qf[KSTEPS];
     int region = F8 ? (code_steps & 1) : 0;                   // of the step about to run (a 16-bit step: 0, and 1 for V)
-    if (left > 0) {
-        const uint32_t q_row = Hq * ROW, q_lds = my_lds + (region ^ 1) * TILE_BYTES;
-        const char *qb = p_q + ((size_t)(row0 + t0) * Hq + head) * ROW;
-        if (n_here == 32) {
-            const uint32_t off = r0 * q_row + (((lane % CH) ^ k_swizzle<D>(r0)) << 4), step = RPI * q_row - 1024;
-            issue_half<D>(qb, off, false, step, q_lds);
-            issue_half<D>(qb + (size_t)16 * q_row, off, false, step, q_lds + 16 * ROW);
-        } else {
-#pragma unroll
-            for (int i = 0; i < NI; ++i) {
-                const int r = RPI * i + r0;
-                dma16(qb + (size_t)(r < n_here ? r : 0) * q_row + (((lane % CH) ^ k_swizzle<D>(r)) << 4), q_lds + 1024 * i);
-            }
-        }
-        if (F8 && region != 0) feed(R1());
-        else feed(R0());
-        wait_vm<NI>();                                   // behind Q only the first load of the stream
-        const char *qt = my + (region ^ 1) * TILE_BYTES;
+    const uint32_t q_row = Hq * ROW;
+    const char *qb = p_q + ((size_t)(row0 + t0) * Hq + head) * ROW;
+    auto q_source = [&](int i) __attribute__((always_inline)) -> const char * {     // of instruction i of the block's rows
+        const int r = RPI * i + r0;
+        return qb + (size_t)(r < n_here ? r : 0) * q_row + (((lane % CH) ^ k_swizzle<D>(r)) << 4);
+    };
+    auto read_q = [&](const char *qt) __attribute__((always_inline)) {
 #pragma unroll
         for (int s = 0; s < KSTEPS; ++s) qf[s] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(qt + (kbase0 ^ (s << 5))));
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    };
+    // A team of 4 or 8 loads them once, a share each wavefront, into a place of their own: nothing of the stream waits for them.  The
+    // others take the region that the stream needs second (places of their own would not fit).
+    const bool shared_q = tl >= 2;
+    char *qt = shared_q ? q_rows + (valid ? team_ : 0) * TILE_BYTES : my + (region ^ 1) * TILE_BYTES;
+    if (shared_q) {
+        if (valid)
+            for (int i = rank; i < NI; i += T) dma16(q_source(i), lds_address(qt) + 1024 * i);
+    } else if (left > 0) {
+        if (n_here == 32) {
+            const uint32_t off = r0 * q_row + (((lane % CH) ^ k_swizzle<D>(r0)) << 4), step = RPI * q_row - 1024;
+            issue_half<D>(qb, off, false, step, lds_address(qt));
+            issue_half<D>(qb + (size_t)16 * q_row, off, false, step, lds_address(qt) + 16 * ROW);
+        } else {
+#pragma unroll
+            for (int i = 0; i < NI; ++i) dma16(q_source(i), lds_address(qt) + 1024 * i);
+        }
+    }
+    if (left > 0) {
+        if (F8 && region != 0) feed(R1());
+        else feed(R0());
+        if (!shared_q) {
+            wait_vm<NI>();                                   // behind Q only the first load of the stream
+            read_q(qt);
+        }
         if (F8 && region != 0) feed(R0());
         else feed(R1());
+    }
+    if (shared_q) {
+        // (the wavefront's share; behind it the stream's first two loads, or one where its only step is one of codes)
+        if (left <= 0) wait_vm<0>();
+        else if (F8 && left == 1 && code_steps != 0) wait_vm<NI>();
+        else wait_vm<2 * NI>();
+        lds_barrier();
+        read_q(qt);
     }
     // pages of the block's own rows, for the append: positions L + t0 .. L + t0 + 31 touch up to three
     const int ap = (L + t0) / kPage;
@@ -480,27 +516,36 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? (F8 ? 3 : 4) : 2) void attn_shor
                 for (int v = 0; v < 16; ++v) o[i][v] *= vs;
         }
     }
-    // ---- fused append: the wavefront of the last step has rows t0 .. t0 + 31 of K and V in its regions
+    // ---- fused append: the wavefront of the last step has rows t0 .. t0 + 31 of K and V in its regions.  (The rows of a matrix are read
+    // together: row by row, each behind the condition of its store, its LDS round trips held the whole team up before the merge)
     if (appends) {
+        const int slot0 = (L + t0) % kPage, ch = lane % CH;
 #pragma unroll
-        for (int mat = 0; mat < 2; ++mat)
+        for (int mat = 0; mat < 2; ++mat) {
+            char *const slab = p_pages_w + (size_t)(mat * Hkv + kh) * head_bytes;
+            char *const to0 = slab + (size_t)ap0 * page_bytes, *const to1 = slab + (size_t)ap1 * page_bytes, *const to2 = slab + (size_t)ap2 * page_bytes;
+            u32x4 rows[NI];
 #pragma unroll
             for (int i = 0; i < NI; ++i) {
-                const int r = RPI * i + r0, ch = lane % CH;
+                const int r = RPI * i + r0;
+                rows[i] = *reinterpret_cast<const u32x4 *>(my + mat * TILE_BYTES + r * ROW + ((ch ^ (mat ? v_swizzle<D>(r) : k_swizzle<D>(r))) << 4));
+            }
+#pragma unroll
+            for (int i = 0; i < NI; ++i) asm volatile("" : "+v"(rows[i]));
+#pragma unroll
+            for (int i = 0; i < NI; ++i) {
+                const int r = RPI * i + r0, e = (slot0 + r) / kPage;
+                char *dst = (e == 0 ? to0 : (e == 1 ? to1 : to2)) + (uint32_t)(((slot0 + r) % kPage) * CH + ch) * (8 * ESZ);
                 if (r < n_here) {
-                    const int pos = L + t0 + r, e = pos / kPage - ap;
-                    const int page = e == 0 ? ap0 : (e == 1 ? ap1 : ap2);
-                    const u32x4 v = *reinterpret_cast<const u32x4 *>(my + mat * TILE_BYTES + r * ROW + ((ch ^ (mat ? v_swizzle<D>(r) : k_swizzle<D>(r))) << 4));
-                    char *dst = p_pages_w + (size_t)page * page_bytes + (size_t)(mat * Hkv + kh) * head_bytes
-                                + (size_t)((pos % kPage) * CH + ch) * (8 * ESZ);
                     if constexpr (F8) {
-                        const uint2 y = bf16_to_codes(v, mat ? p->v_inv : p->k_inv);
+                        const uint2 y = bf16_to_codes(rows[i], mat ? p->v_inv : p->k_inv);
                         *reinterpret_cast<global_u32x2_w *>((uintptr_t)dst) = u32x2{y.x, y.y};
                     } else {
-                        *reinterpret_cast<global_u32x4_w *>((uintptr_t)dst) = v;
+                        *reinterpret_cast<global_u32x4_w *>((uintptr_t)dst) = rows[i];
                     }
                 }
             }
+        }
     }
 
     const int t = t0 + l32;
@@ -560,24 +605,58 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? (F8 ? 3 : 4) : 2) void attn_shor
         if (half == 0) { stat[wave][0][l32] = m; stat[wave][1][l32] = ltot; }
     }
     lds_barrier();
-    float ms = stat[team0][0][l32];
-    for (int w = 1; w < parts; ++w) ms = fmaxf(ms, stat[team0 + w][0][l32]);
+    // (whatever lies in LDS is read together, places past the last wavefront as the last one's: read one by one as it is used, it cost
+    // teams of eight a round trip each, three times over.  With the append's rows read together and Q in a place of its own, 286 short
+    // prompts of 40 heads: 1006 us, now 976)
+    float wgt[NW], sum[NW];
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        const int from = team0 + min(w, parts - 1);
+        wgt[w] = stat[from][0][l32];
+        sum[w] = stat[from][1][l32];
+    }
+    float ms = wgt[0], l = 0.f;
+#pragma unroll
+    for (int w = 1; w < NW; ++w) ms = fmaxf(ms, wgt[w]);
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        wgt[w] = __builtin_amdgcn_exp2f(wgt[w] - ms);
+        if (w < parts) l = __builtin_fmaf(sum[w], wgt[w], l);
+    }
     auto partial = [&](int i) -> float * { return p->scratch + ((size_t)(u * Hq + head) * splits + i) * (32 * D + 64); };
     // an item is 16 of the columns, two neighbouring vectors: 2 * DBLK of them
     for (int item = rank; item < 2 * DBLK; item += T) {
         const int vec = item * 2;                        // = db * 4 + q4 with q4 in {0, 2}
         f32x4 a = {0.f, 0.f, 0.f, 0.f}, b = a;
-        float l = 0.f;
-        for (int w = 0; w < parts; ++w) {
-            const float wgt = __builtin_amdgcn_exp2f(stat[team0 + w][0][l32] - ms);
-            l = __builtin_fmaf(stat[team0 + w][1][l32], wgt, l);
-            const f32x4 *src = reinterpret_cast<const f32x4 *>(smem + (team0 + w) * (2 * TILE_BYTES)) + lane;
-            const f32x4 xa = src[vec * 64], xb = src[(vec + 1) * 64];
+        auto add = [&](auto first_, auto count_) __attribute__((always_inline)) {
+            constexpr int W0 = decltype(first_)::value, N = decltype(count_)::value;
+            f32x4 xa[N], xb[N];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                a[e] = __builtin_fmaf(xa[e], wgt, a[e]);
-                b[e] = __builtin_fmaf(xb[e], wgt, b[e]);
+            for (int w = 0; w < N; ++w) {
+                const f32x4 *src = reinterpret_cast<const f32x4 *>(smem + (team0 + min(W0 + w, parts - 1)) * (2 * TILE_BYTES)) + lane;
+                xa[w] = src[vec * 64];
+                xb[w] = src[(vec + 1) * 64];
             }
+#pragma unroll
+            for (int w = 0; w < N; ++w) asm volatile("" : "+v"(xa[w]), "+v"(xb[w]));
+#pragma unroll
+            for (int w = 0; w < N; ++w)
+                if (W0 + w < parts) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        a[e] = __builtin_fmaf(xa[w][e], wgt[W0 + w], a[e]);
+                        b[e] = __builtin_fmaf(xb[w][e], wgt[W0 + w], b[e]);
+                    }
+                }
+        };
+        typedef std::integral_constant<int, 2> N2;
+        typedef std::integral_constant<int, 4> N4;
+        if (T == 2) {
+            add(R0(), N2());
+        } else {
+            add(R0(), N4());
+            if constexpr (NW == 8)
+                if (parts > 4) add(N4(), N4());
         }
         if (splits == 1) {
             finish(vec, a, b, l);
@@ -639,8 +718,13 @@ template <int D, bool F8>
 hipError_t launch(const ShortParams &p, int wavefronts, hipStream_t stream)
 {
     const dim3 grid(p.attn_wgs + p.zero_wgs);
-    if (wavefronts == 8) hipLaunchKernelGGL((attn_short_kernel<D, F8, 8>), grid, dim3(512), 0, stream, p);
-    else hipLaunchKernelGGL((attn_short_kernel<D, F8, 4>), grid, dim3(256), 0, stream, p);
+    auto kernel = wavefronts == 8 ? attn_short_kernel<D, F8, 8> : attn_short_kernel<D, F8, 4>;
+    // (the class of the largest teams starts at workgroup 0 and row block 0)
+    static_assert(kShortUnits <= 255, "row blocks in a byte");
+    hipLaunchKernelGGL(kernel, grid, dim3(64 * wavefronts), 0, stream, p.bt, p.max_blocks, p.first_wg[0], p.first_wg[1], p.first_wg[2],
+                       (uint32_t)(p.first_unit[0] | p.first_unit[1] << 8 | p.first_unit[2] << 16) | (uint32_t)p.units << 24, p.attn_wgs,
+                       (uint32_t)(p.splits | p.rshift << 8 | p.spread << 10), p.splits_magic, p.hpx_magic, p.hkx_magic,
+                       (uint32_t)p.hpx | (uint32_t)p.hkx << 16, p);
     return hipGetLastError();
 }
 
