@@ -95,6 +95,17 @@ def test_more_requests_than_one_lookup_step():
     check_both_ways(lens, firsts, 2, 64, seed=232)
 
 
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 5, 63, 64, 65, 127, 128, 129])
+@pytest.mark.parametrize("pass_first", [True, False])
+def test_requests_at_the_edges_of_the_lookup(n, pass_first):
+    """The prefix sum runs over as many lanes as a lookup step has requests: powers of two and their neighbours, one step
+    and several, the last request (whose lane is the last that counts) never empty."""
+    rng = np.random.default_rng(240 + n)
+    lens = [int(x) for x in rng.choice([0, 1, 15, 16, 17, 40], size=n - 1)] + [33]
+    firsts = [int(x) for x in rng.integers(0, 20, size=n)] if pass_first else [0] * n
+    check_both_ways(lens, firsts, 2, 128, seed=260 + n, pass_first=pass_first)
+
+
 def test_many_tokens_several_slabs_per_workgroup():
     """Enough tiles that a workgroup takes more than one (K / V, head) slab."""
     check_both_ways([5000, 3000, 4097, 2500, 3333], [0, 16, 5, 0, 1], 3, 64, seed=233)
