@@ -9,7 +9,7 @@
 //     decode kernel).  The host, which knows the segments of the chunk, gives each row block the team that leaves its
 //     wavefronts about as many steps as those of the others and fills the chip's places for wavefronts (plan_short): with one
 //     size of team for all row blocks a launch lasted as long as its longest one (512 rows of 40 heads: 18.3 us, now 14.0; 286 short
-//     prompts of 40 heads in 64 chunks: 1154 us, now 1006);
+//     prompts of 40 heads in 64 chunks: 1154 us, with teams 1006, now 976);
 //   * the row blocks, longest first, travel in the kernel arguments: a workgroup's first memory access after those is its page
 //     ids, the second Q, K and V;
 //   * few row blocks with long key ranges: the keys of a row block are split over several workgroups, so that every compute
@@ -21,8 +21,8 @@
 //     page slots from there (fused append), so there are no workgroups for that.
 // What bounds it in turn: the chain of steps of the wavefront with the most of them, 1.0 to 1.3 us a step, because a wavefront
 // has one step of loads in flight (codes two) and the keys of a step serve 32 rows instead of 256.  Long chains go to the shared-tile
-// kernel: the host chooses.  Of a launch of 64 packed chunks (15.6 us each) 3.5 us lie between two launches, 9 are loads (16 MB that no
-// launch before has touched), 2.3 the merge and the output, 2 to 3 the append.
+// kernel: the host chooses.  Of a launch of 64 packed chunks (15.2 us each) 3.5 us lie between two launches, most of the others are
+// loads (16 MB that no launch before has touched); the append, the merge and the output follow.
 // Arithmetic is that of the shared-tile kernel: bf16 operands, fp32 accumulation, weights rounded to bf16 before the PV
 // product and summed as rounded, parts of the keys merged in a fixed order.
 #include <type_traits>
@@ -721,6 +721,7 @@ hipError_t launch(const ShortParams &p, int wavefronts, hipStream_t stream)
     auto kernel = wavefronts == 8 ? attn_short_kernel<D, F8, 8> : attn_short_kernel<D, F8, 4>;
     // (the class of the largest teams starts at workgroup 0 and row block 0)
     static_assert(kShortUnits <= 255, "row blocks in a byte");
+    // (hpx and hkx in 16 bits: plan_short refuses what is not below 2^32 as row blocks x heads x heads)
     hipLaunchKernelGGL(kernel, grid, dim3(64 * wavefronts), 0, stream, p.bt, p.max_blocks, p.first_wg[0], p.first_wg[1], p.first_wg[2],
                        (uint32_t)(p.first_unit[0] | p.first_unit[1] << 8 | p.first_unit[2] << 16) | (uint32_t)p.units << 24, p.attn_wgs,
                        (uint32_t)(p.splits | p.rshift << 8 | p.spread << 10), p.splits_magic, p.hpx_magic, p.hkx_magic,
