@@ -1,9 +1,9 @@
-"""GPU parity of tetri_kv_export / tetri_kv_import (through the C ABI) against the numpy oracle: bit-exact."""
+"""GPU parity of tetri_kv_export / tetri_kv_import and of their FP8 forms (through the C ABI) against the numpy oracle: bit-exact."""
 import numpy as np
 import pytest
 import torch
 
-from oracle import kv_transfer
+from oracle import fp8 as ofp8, kv_transfer
 from paper_2401_11181_amd import synth, tetri
 import gpu_common as gc
 
@@ -104,6 +104,44 @@ def test_requests_at_the_edges_of_the_lookup(n, pass_first):
     lens = [int(x) for x in rng.choice([0, 1, 15, 16, 17, 40], size=n - 1)] + [33]
     firsts = [int(x) for x in rng.integers(0, 20, size=n)] if pass_first else [0] * n
     check_both_ways(lens, firsts, 2, 128, seed=260 + n, pass_first=pass_first)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("n", [1, 2, 5, 63, 64, 65, 129])
+def test_fp8_requests_at_the_edges_of_the_lookup(n, d):
+    """The quantising export and the import of its codes, one lookup step and several, first tokens inside a page, empty
+    requests, and three kv heads, so that K ends inside a run of slabs.  Codes and the receiver's pool bit for bit."""
+    hkv, k_scale, v_scale = 3, 0.0137, 0.31
+    rng = np.random.default_rng(270 + n)
+    lens = [int(x) for x in rng.choice([0, 1, 15, 16, 17, 33], size=n - 1)] + [40]
+    firsts = [int(x) for x in rng.integers(1, 16, size=n)]
+    pool, bt, cu, first = make_case(lens, firsts, hkv, d, seed=280 + n)
+    values = (np.arange(65536, dtype=np.uint32) << 16).view(np.float32)
+    pool[np.isnan(values)[pool]] = 0x3F80                    # (a NaN has no defined code)
+    values[np.isnan(values)] = 1.0
+    codes = np.empty(pool.shape, dtype=np.uint8)             # the code of every bf16 value, once for K's scale and once for V's
+    for half, scale in enumerate((k_scale, v_scale)):
+        codes[:, half] = ofp8.quantize(values, scale)[pool[:, half]]
+    want = kv_transfer.kv_export(codes, bt, cu, first)
+    if n <= 2:
+        assert np.array_equal(want, kv_transfer.kv_export_fp8(values[pool], bt, cu, first, k_scale, v_scale))
+    h = handle_for(hkv, d, pool.shape[0], bt.shape[1])
+    total = int(cu[-1])
+    d_pool, d_cu, d_first = dev(pool), dev(cu), dev(first)
+    buf = torch.full((want.size + 64,), 0x5a, dtype=torch.uint8, device=DEV)
+    h.tetri_kv_export_fp8(d_pool, dev(bt), d_cu, d_first, n, total, k_scale, v_scale, buf)
+    torch.cuda.synchronize()
+    got = buf.cpu().numpy()
+    assert np.array_equal(got[:want.size], want) and (got[want.size:] == 0x5a).all()
+    assert np.array_equal(bits(d_pool), pool), "export must not write the pool"
+    bt2 = (pool.shape[0] - 1 - bt).astype(np.int32)
+    ref = np.full(pool.shape, 0x12, dtype=np.uint8)
+    d_dst = dev(ref.copy())
+    h.tetri_kv_import_fp8(buf, dev(bt2), d_cu, d_first, n, total, d_dst)
+    torch.cuda.synchronize()
+    kv_transfer.kv_import(want, ref, bt2, cu, first)
+    assert np.array_equal(d_dst.cpu().numpy(), ref)
+    h.close()
 
 
 def test_many_tokens_several_slabs_per_workgroup():
