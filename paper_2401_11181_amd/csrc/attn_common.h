@@ -32,6 +32,17 @@ constexpr int kXcd = 8;       // XCDs (L2 domains) workgroups are dealt to round
 #define TETRI_MARK(i_) do { } while (0)
 #endif
 
+// The argument memory of a kernel: every argument lies behind the one before it, at its own alignment.
+template <class F> struct KernelArgs;
+template <class... A> struct KernelArgs<void (*)(A...)> {
+    static constexpr size_t last_offset()        // where the last argument starts
+    {
+        size_t at = 0, end = 0;
+        ((at = (end + alignof(A) - 1) / alignof(A) * alignof(A), end = at + sizeof(A)), ...);
+        return at;
+    }
+};
+
 // A row of zeros: out-of-range key rows of a partial tile are loaded from here.
 static __device__ __attribute__((aligned(256))) uint4 g_zero_row[16];
 

@@ -121,7 +121,6 @@ struct Job {
 // words are in scalar registers when a wavefront starts, the structure is a memory read of 0.4 us away (one request of 1000
 // tokens, 40 heads: 9.32 us before, 8.96 now).
 constexpr int kDecodeLead = 56;
-static_assert(alignof(DecodeParams) == 8, "52 bytes of arguments, then the structure");
 
 // RANGES: `ranges` equal ranges of the batch's steps, a workgroup each per kv head; otherwise every (request, kv head) in
 // `parts` equal parts, a workgroup each.  Grid: kv head fastest.
@@ -675,6 +674,7 @@ static hipError_t launch_decode(const DecodeParams &p, hipStream_t stream)
 {
     const dim3 grid((p.parts > 0 ? p.B * p.parts : p.ranges) * p.Hkv);
     auto kernel = p.parts > 0 ? decode_attn_kernel<D, FP8, 4, false> : decode_attn_kernel<D, FP8, 4, true>;
+    static_assert(KernelArgs<decltype(kernel)>::last_offset() == kDecodeLead, "where the kernel reads its structure");
     hipLaunchKernelGGL(kernel, grid, dim3(256), 0, stream, p.ctx, p.bt, p.pages, p.max_blocks, p.Hkv, p.hkv_magic, p.parts, p.q, p.B, p);
     return hipGetLastError();
 }

@@ -83,7 +83,6 @@ template <int D> struct CodeTile {
 // comes first and by itself: those words are in scalar registers when a wavefront starts, and the row block, with the pointers that
 // go with it, is one read of the arguments away instead of two.
 constexpr int kShortLead = 64;
-static_assert(alignof(ShortParams) == kShortLead, "52 bytes of arguments, then the structure");
 
 template <int D, bool F8, int NW>
 __global__ __launch_bounds__(NW * 64, D == 64 ? (F8 ? 3 : 4) : 2) void attn_short_kernel(
@@ -719,6 +718,7 @@ hipError_t launch(const ShortParams &p, int wavefronts, hipStream_t stream)
 {
     const dim3 grid(p.attn_wgs + p.zero_wgs);
     auto kernel = wavefronts == 8 ? attn_short_kernel<D, F8, 8> : attn_short_kernel<D, F8, 4>;
+    static_assert(KernelArgs<decltype(kernel)>::last_offset() == kShortLead, "where the kernel reads its structure");
     // (the class of the largest teams starts at workgroup 0 and row block 0)
     static_assert(kShortUnits <= 255, "row blocks in a byte");
     // (hpx and hkx in 16 bits: plan_short refuses what is not below 2^32 as row blocks x heads x heads)
