@@ -107,7 +107,7 @@ __device__ __forceinline__ void issue_last(const char *page_lo, const char *page
     }
 }
 
-typedef __attribute__((address_space(4))) const DecodeParams const_decode_params;
+typedef __attribute__((address_space(4))) const DecodeArgs const_decode_args;
 
 // A stretch of steps of one request; wave-uniform.
 struct Job {
@@ -126,7 +126,7 @@ constexpr int kDecodeLead = 56;
 // `parts` equal parts, a workgroup each.  Grid: kv head fastest.
 template <int D, bool FP8, int NW, bool RANGES>
 __global__ __launch_bounds__(NW * 64, 2) void decode_attn_kernel(const int32_t *ctx_lens, const int32_t *bt, const uint16_t *pages, int max_blocks, int Hkv,
-                                                                  uint32_t hkv_magic, int parts, const uint16_t *q, int B, DecodeParams)
+                                                                  uint32_t hkv_magic, int parts, const uint16_t *q, int B, DecodeArgs)
 {
     typedef Tile<D, FP8> T;
     constexpr int KSTEPS = D / 16, DBLK = D / 32, NI = T::NI, NT = NW * 64, ROW = 2 * D;
@@ -136,7 +136,7 @@ __global__ __launch_bounds__(NW * 64, 2) void decode_attn_kernel(const int32_t *
     __shared__ float stat[NW][2][32];
     __shared__ int arrived;
     // (the structure lies behind the leading arguments)
-    const const_decode_params *p = (const const_decode_params *)((__attribute__((address_space(4))) const char *)__builtin_amdgcn_kernarg_segment_ptr() + kDecodeLead);
+    const const_decode_args *p = (const const_decode_args *)((__attribute__((address_space(4))) const char *)__builtin_amdgcn_kernarg_segment_ptr() + kDecodeLead);
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -210,7 +210,7 @@ __global__ __launch_bounds__(NW * 64, 2) void decode_attn_kernel(const int32_t *
     // the job after `j`, with `rest` steps of the range behind j: rest goes down by the new job's steps
     auto next_job = [&](Job &j, int &rest) {
         ++j.b;
-        j.L = ctx_of(min(j.b, p->B - 1));
+        j.L = ctx_of(min(j.b, B - 1));
         j.begin = 0;
         j.end = min(j.steps(), rest);
         rest -= j.end;
@@ -467,7 +467,7 @@ __global__ __launch_bounds__(NW * 64, 2) void decode_attn_kernel(const int32_t *
 
     // ---- the job is done: the wavefronts merge.  (The tiles may be receiving the next job's first steps: the merge has an
     // area of its own in LDS, for kMergeCols query heads at a time.)
-    const const_decode_params *e = p;
+    const const_decode_args *e = p;
     int te = tid;
     asm volatile("" : "+v"(te), "+s"(e));                // (values worked out and read here, not kept across the loop)
     const int half_e = (te >> 5) & 1, col_e = te & 31, g = e->g;
@@ -675,7 +675,7 @@ static hipError_t launch_decode(const DecodeParams &p, hipStream_t stream)
     const dim3 grid((p.parts > 0 ? p.B * p.parts : p.ranges) * p.Hkv);
     auto kernel = p.parts > 0 ? decode_attn_kernel<D, FP8, 4, false> : decode_attn_kernel<D, FP8, 4, true>;
     static_assert(KernelArgs<decltype(kernel)>::last_offset() == kDecodeLead, "where the kernel reads its structure");
-    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, stream, p.ctx, p.bt, p.pages, p.max_blocks, p.Hkv, p.hkv_magic, p.parts, p.q, p.B, p);
+    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, stream, p.ctx, p.bt, p.pages, p.max_blocks, p.Hkv, p.hkv_magic, p.parts, p.q, p.B, static_cast<const DecodeArgs &>(p));
     return hipGetLastError();
 }
 

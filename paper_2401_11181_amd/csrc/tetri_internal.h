@@ -128,13 +128,41 @@ struct AttnParams {
     const TilePlan *plan; // host memory: the host's division of the launch (null: none)
 };
 
-// Launch parameters of the attention kernel for chunks with little work (tetri_short.hip): the chunk's row blocks travel in them.
+// The attention kernel for chunks with little work (tetri_short.hip).  What it reads of its arguments, behind the words that find a
+// wavefront's row block: the chunk's row blocks travel in it.
 constexpr int kShortSegs = 40, kShortUnits = 128;
-struct __attribute__((aligned(64))) ShortParams {
-    // (what finds a wavefront's row block: the kernel gets these packed, as arguments in front of the structure)
+struct __attribute__((aligned(64))) ShortArgs {
+    // (read together with the row block at the kernel's start: a cache line ...)
+    const uint16_t *q, *k_new, *v_new, *pages;
+    uint16_t *out, *pages_w;      // pages_w: pool for the fused append (null: none)
+    const void *zero;             // a row of zeros
+    int32_t Hq, Hkv;
+    // (... and two words)
+    int32_t g;
+    int32_t out_past_l2;          // 1: the output rows are stored past the caches
+    // (read where they are used)
+    float c;                      // |scale| * log2(e)
+    int32_t neg;                  // 1 if scale < 0
+    float k_scale, v_scale, k_inv, v_inv;
+    int32_t C, rows;              // chunk rows, and those that belong to a request
+    float *scratch;               // splits > 1: partial results, [(unit * Hq + head) * splits + part][32 * D + 64] floats
+    int32_t *counters;            // ... and arrival counters, one per (unit, head), zero before and after the launch
+    int32_t *counters_next;       // the set of a later launch: zeroed by this one
+    int32_t n_counters;           // size of a set
+    int32_t pad;
+    // most work first, 64 bits each: segment (6), row block in it (7), the segment's rows (13) and first row (12), cached tokens (26)
+    uint32_t unit[kShortUnits][2];
+};
+
+// The launch as the host lays it out; what it adds goes to the kernel as leading scalars, some of them packed.
+struct ShortParams : ShortArgs {
+    const int32_t *bt;
+    int32_t max_blocks;
     int32_t first_wg[4];          // of the row blocks of 1, 2, 4 and 8 wavefronts: the classes follow each other from 8 down ...
     int32_t first_unit[4];        // ... and their first row blocks
+    int32_t units;                // row blocks of 32 rows
     int32_t attn_wgs;             // workgroups but for those that write the padding rows
+    int32_t zero_wgs;             // ... and those
     int32_t splits;               // workgroups that share the keys of a row block of one head (> 1: one class, the whole workgroup)
     uint32_t splits_magic;        // ceil(2^32 / d), 0 for 1
     int32_t hpx;                  // query heads whose kv head is x modulo 1 << rshift: as many for every x
@@ -142,29 +170,29 @@ struct __attribute__((aligned(64))) ShortParams {
     int32_t hkx;                  // ... and such kv heads
     uint32_t hkx_magic;
     int32_t rshift;
-    // (read together at the kernel's start, 64 bytes ...)
-    const uint16_t *q, *k_new, *v_new, *pages;
-    const int32_t *bt;
-    uint16_t *out, *pages_w;      // pages_w: pool for the fused append (null: none)
-    const void *zero;             // a row of zeros
-    // (... and 64 more)
-    int32_t C, rows;              // chunk rows, and those that belong to a request
-    int32_t Hq, Hkv, g, max_blocks;
-    int32_t units;                // row blocks of 32 rows
-    int32_t zero_wgs;             // workgroups that write the padding rows
-    float c;                      // |scale| * log2(e)
-    int32_t neg;                  // 1 if scale < 0
-    float k_scale, v_scale, k_inv, v_inv;
-    int32_t n_counters;           // size of a set
     int32_t spread;               // 1: one team to a workgroup
-    float *scratch;               // splits > 1: partial results, [(unit * Hq + head) * splits + part][32 * D + 64] floats
-    int32_t *counters;            // ... and arrival counters, one per (unit, head), zero before and after the launch
-    int32_t *counters_next;       // the set of a later launch: zeroed by this one
-    int32_t out_past_l2;          // 1: the output rows are stored past the caches
-    int32_t pad2;
-    // most work first, 64 bits each: segment (6), row block in it (7), the segment's rows (13) and first row (12), cached tokens (26)
-    uint32_t unit[kShortUnits][2];
 };
+
+// Row blocks of the classes and the shape of the launch, in three words.  (The class of the largest teams starts at workgroup 0 and row
+// block 0: neither travels.)  Row blocks <= kShortUnits, splits <= 16, rshift <= 3, heads below 65536: plan_short refuses what is
+// not below 2^32 as row blocks x heads x heads.
+struct ShortWords {
+    uint32_t first_units, shape, per_x;
+};
+struct ShortShapeWords {
+    int32_t first_unit[3], units, splits, rshift, spread, hpx, hkx;
+};
+__host__ __device__ inline ShortWords short_pack(const ShortParams &p)
+{
+    static_assert(kShortUnits <= 255, "row blocks in a byte");
+    return {(uint32_t)p.first_unit[0] | (uint32_t)p.first_unit[1] << 8 | (uint32_t)p.first_unit[2] << 16 | (uint32_t)p.units << 24,
+            (uint32_t)p.splits | (uint32_t)p.rshift << 8 | (uint32_t)p.spread << 10, (uint32_t)p.hpx | (uint32_t)p.hkx << 16};
+}
+__host__ __device__ inline ShortShapeWords short_unpack(const ShortWords &w)
+{
+    return {{(int32_t)(w.first_units & 255), (int32_t)(w.first_units >> 8 & 255), (int32_t)(w.first_units >> 16 & 255)}, (int32_t)(w.first_units >> 24),
+            (int32_t)(w.shape & 255), (int32_t)(w.shape >> 8 & 3), (int32_t)(w.shape >> 10), (int32_t)(w.per_x & 0xffff), (int32_t)(w.per_x >> 16)};
+}
 
 struct AppendParams {
     const uint16_t *k_new, *v_new;
@@ -188,26 +216,33 @@ struct TransferParams {
 // Most requests of a decode batch whose steps are divided evenly (a lane of a wavefront looks at up to 16 of them).
 constexpr int kDecodeLookup = 1024;
 
-// Launch parameters of the decode-iteration kernel.
-struct DecodeParams {
-    const uint16_t *q, *k_new, *v_new, *pages;
-    const int32_t *bt, *ctx;
+// What the decode-iteration kernel reads of its arguments behind the leading scalars.
+struct DecodeArgs {
+    const uint16_t *k_new, *v_new;
     uint16_t *out;
     uint16_t *pages_w;    // pool for the fused append of the new token (null: no append)
     float *partial;       // scratch: partial results of (request, kv head)s shared by workgroups
     int32_t *counters;    // ... and their arrival counters, zero before and after the launch
     int32_t *counters_next;   // the set of a later launch: zeroed by this one
     int32_t n_counters;   // size of a set; 0: no (request, kv head) is shared, the launch touches no counters
-    int32_t B, Hq, Hkv, g, max_blocks;
-    uint32_t hkv_magic;   // ceil(2^32 / Hkv), 0 for 1
-    int32_t parts;        // > 0: each (request, kv head)'s keys in that many equal parts, a workgroup each;
+    int32_t Hq, g;
     int32_t ranges;       // parts == 0: the steps of the batch in that many equal ranges, a workgroup each per kv head
     int32_t min_steps;    // ... of at least this many steps
     float c;              // |scale| * log2(e)
     int32_t neg;          // 1 if scale < 0
-    int32_t fp8;          // 1: the pool holds E4M3 codes (one byte per element) with per-tensor scales
-    float k_scale, v_scale, k_inv, v_inv;   // the scales and fl32(1 / scale)
+    float k_scale, v_scale, k_inv, v_inv;   // FP8 pool: the scales and fl32(1 / scale)
     float out_scale;      // factor on the finished output: v_scale for an FP8 pool, else 1
+};
+
+// The launch as the host lays it out: what it adds goes to the kernel as leading scalars, but for the choice of the kernel.
+struct DecodeParams : DecodeArgs {
+    const int32_t *ctx, *bt;
+    const uint16_t *pages, *q;
+    int32_t max_blocks, Hkv;
+    uint32_t hkv_magic;   // ceil(2^32 / Hkv), 0 for 1
+    int32_t parts;        // > 0: each (request, kv head)'s keys in that many equal parts, a workgroup each
+    int32_t B;
+    int32_t fp8;          // 1: the pool holds E4M3 codes (one byte per element) with per-tensor scales
 };
 
 hipError_t tetri_launch_attn(const tetri_ctx *h, const AttnParams &p, int key_parts, bool fp8_pool, hipStream_t stream);

@@ -33,7 +33,7 @@ namespace {
 
 using namespace tetri_dev;
 
-typedef __attribute__((address_space(4))) const ShortParams const_params;
+typedef __attribute__((address_space(4))) const ShortArgs const_params;
 
 // 32 rows of K or V, as two halves of 16 rows with a scalar base each, into a wavefront's tile (swizzled like
 // everywhere); rows of a half are row_bytes apart.
@@ -87,7 +87,7 @@ constexpr int kShortLead = 64;
 template <int D, bool F8, int NW>
 __global__ __launch_bounds__(NW * 64, D == 64 ? (F8 ? 3 : 4) : 2) void attn_short_kernel(
     const int32_t *block_tables, int max_blocks, int first_wg0, int first_wg1, int first_wg2, uint32_t first_units, int attn_wgs, uint32_t shape,
-    uint32_t splits_magic, uint32_t hpx_magic, uint32_t hkx_magic, uint32_t per_x, ShortParams)
+    uint32_t splits_magic, uint32_t hpx_magic, uint32_t hkx_magic, uint32_t per_x, ShortArgs)
 {
     typedef CodeTile<D> CT;
     constexpr int KSTEPS = D / 16, DBLK = D / 32, NI = D / 16, CH = D / 8, RPI = 64 / CH;
@@ -116,8 +116,9 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? (F8 ? 3 : 4) : 2) void attn_shor
     // ---- the wavefront's row block, head and place in its team.  Row blocks come in classes of 8, 4, 2 or 1 wavefronts (1 <<
     // tl), the longest first.  The heads whose kv head is x modulo R (R = 1 << rshift) sit in workgroups x modulo R: those
     // that share a kv head run on one XCD (R = 8).
-    const int fu0 = first_units & 255, fu1 = (first_units >> 8) & 255, fu2 = (first_units >> 16) & 255, units = first_units >> 24;
-    const int splits = shape & 255, rshift = (shape >> 8) & 3, hpx = per_x & 0xffff, hkx = per_x >> 16;
+    const ShortShapeWords sw = short_unpack({first_units, shape, per_x});
+    const int fu0 = sw.first_unit[0], fu1 = sw.first_unit[1], fu2 = sw.first_unit[2], units = sw.units;
+    const int splits = sw.splits, rshift = sw.rshift, hpx = sw.hpx, hkx = sw.hkx;
     const int tl = bid >= first_wg0 ? 0 : (bid >= first_wg1 ? 1 : (bid >= first_wg2 ? 2 : 3));
     const int T = 1 << tl;
     int j = bid - (tl == 0 ? first_wg0 : (tl == 1 ? first_wg1 : (tl == 2 ? first_wg2 : 0)));
@@ -130,7 +131,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? (F8 ? 3 : 4) : 2) void attn_shor
         j = q;
     }
     const int x = j & ((1 << rshift) - 1);
-    const int pack = (shape >> 10) != 0 ? 0 : NWL - tl;      // log2 of a workgroup's teams (few row blocks: one, on a compute unit of its own)
+    const int pack = sw.spread != 0 ? 0 : NWL - tl;      // log2 of a workgroup's teams (few row blocks: one, on a compute unit of its own)
     const int team_ = wave >> tl, item_ = ((j >> rshift) << pack) + team_, rank = wave & (T - 1), team0 = wave - rank;
     const int ul = magic_div(item_, hpx_magic), hh = item_ - ul * hpx;
     const int hgrp = magic_div(hh, hkx_magic), kh = x + ((hh - hgrp * hkx) << rshift);
@@ -142,11 +143,10 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? (F8 ? 3 : 4) : 2) void attn_shor
     typedef __attribute__((ext_vector_type(2))) int i32x2s;
     typedef __attribute__((address_space(4))) const i32x16 const_i32x16;
     typedef __attribute__((address_space(4))) const i32x2s const_i32x2s;
-    static_assert(offsetof(ShortParams, q) == 64 && offsetof(ShortParams, C) == 128, "read as vectors");
-    i32x16 hp = ((const const_i32x16 *)p)[1], hc = ((const const_i32x16 *)p)[2];
-    i32x2s unit = *(const const_i32x2s *)&p->unit[u];
-    int out_past_l2 = p->out_past_l2;
-    asm volatile("" : "+s"(hp), "+s"(hc), "+s"(unit), "+s"(out_past_l2));
+    static_assert(offsetof(ShortArgs, q) == 0 && offsetof(ShortArgs, Hq) == 56 && offsetof(ShortArgs, g) == 64, "read as vectors");
+    i32x16 hp = *(const const_i32x16 *)p;
+    i32x2s hg = *(const const_i32x2s *)&p->g, unit = *(const const_i32x2s *)&p->unit[u];
+    asm volatile("" : "+s"(hp), "+s"(hg), "+s"(unit));
     auto pointer = [&](auto i) __attribute__((always_inline)) -> char * {
         constexpr int I = decltype(i)::value;
         return reinterpret_cast<char *>((uintptr_t)((uint64_t)(uint32_t)hp[2 * I] | (uint64_t)(uint32_t)hp[2 * I + 1] << 32));
@@ -154,9 +154,9 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? (F8 ? 3 : 4) : 2) void attn_shor
     typedef std::integral_constant<int, 0> R0;
     typedef std::integral_constant<int, 1> R1;
     char *const p_q = pointer(R0()), *const p_k_new = pointer(R1()), *const p_v_new = pointer(std::integral_constant<int, 2>()),
-         *const p_pages = pointer(std::integral_constant<int, 3>()), *const p_out = pointer(std::integral_constant<int, 5>()),
-         *const p_pages_w = pointer(std::integral_constant<int, 6>()), *const p_zero = pointer(std::integral_constant<int, 7>());
-    const int Hq = hc[2], Hkv = hc[3], heads_per_kv = hc[4];
+         *const p_pages = pointer(std::integral_constant<int, 3>()), *const p_out = pointer(std::integral_constant<int, 4>()),
+         *const p_pages_w = pointer(std::integral_constant<int, 5>()), *const p_zero = pointer(std::integral_constant<int, 6>());
+    const int Hq = hp[14], Hkv = hp[15], heads_per_kv = hg[0], out_past_l2 = hg[1];
     const uint32_t unit_lo = unit[0], unit_hi = unit[1];
     const int seg = unit_lo & 63, t0 = ((unit_lo >> 6) & 127) * 32, n_s = (unit_lo >> 13) & 8191, L = unit_hi & 0x3ffffff;
     const int row0 = (int)(unit_lo >> 26) | (int)(unit_hi >> 26) << 6;
@@ -719,13 +719,9 @@ hipError_t launch(const ShortParams &p, int wavefronts, hipStream_t stream)
     const dim3 grid(p.attn_wgs + p.zero_wgs);
     auto kernel = wavefronts == 8 ? attn_short_kernel<D, F8, 8> : attn_short_kernel<D, F8, 4>;
     static_assert(KernelArgs<decltype(kernel)>::last_offset() == kShortLead, "where the kernel reads its structure");
-    // (the class of the largest teams starts at workgroup 0 and row block 0)
-    static_assert(kShortUnits <= 255, "row blocks in a byte");
-    // (hpx and hkx in 16 bits: plan_short refuses what is not below 2^32 as row blocks x heads x heads)
+    const ShortWords w = short_pack(p);
     hipLaunchKernelGGL(kernel, grid, dim3(64 * wavefronts), 0, stream, p.bt, p.max_blocks, p.first_wg[0], p.first_wg[1], p.first_wg[2],
-                       (uint32_t)(p.first_unit[0] | p.first_unit[1] << 8 | p.first_unit[2] << 16) | (uint32_t)p.units << 24, p.attn_wgs,
-                       (uint32_t)(p.splits | p.rshift << 8 | p.spread << 10), p.splits_magic, p.hpx_magic, p.hkx_magic,
-                       (uint32_t)p.hpx | (uint32_t)p.hkx << 16, p);
+                       w.first_units, p.attn_wgs, w.shape, p.splits_magic, p.hpx_magic, p.hkx_magic, w.per_x, static_cast<const ShortArgs &>(p));
     return hipGetLastError();
 }
 

@@ -3,7 +3,8 @@
 // heads, head dim, chunk size) and fails if a 32-key step of a row block is missing or done twice, a row block is not the
 // chunk's, or a partial result lies outside the handle's memory.  Prints how many row blocks had teams of 1, 2, 4 and 8 wavefronts
 // and how many had their keys split over workgroups.  With the heads alone (argv: heads, kv heads) it reads chunks from the standard input (FP8
-// or not, number of segments, rows and cached tokens of each) and prints the kernel the library's own rule gives each of them.
+// or not, number of segments, rows and cached tokens of each) and prints the kernel the library's own rule gives each of them.  Without arguments: the
+// packed words of a launch at the edges of their fields.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -58,9 +59,41 @@ namespace {
 std::vector<int32_t> g_cu, g_ctx;
 const char *g_taken = "";
 const tetri_ctx *g_h = nullptr;
-int g_launches = 0, g_teams[4] = {0, 0, 0, 0}, g_split = 0;
+int g_launches = 0, g_teams[4] = {0, 0, 0, 0}, g_split = 0, g_most_units = 0, g_most_splits = 0;
 
 uint32_t div_by(uint32_t n, uint32_t magic) { return magic == 0 ? n : (uint32_t)(((uint64_t)n * magic) >> 32); }
+
+// The words that the kernel gets of a launch say what the host laid out.
+void check_words(const ShortParams &p)
+{
+    const ShortShapeWords s = short_unpack(short_pack(p));
+    CHECK(p.first_wg[3] == 0 && p.first_unit[3] == 0);                 // (neither travels)
+    for (int tl = 0; tl < 3; ++tl) CHECK(s.first_unit[tl] == p.first_unit[tl]);
+    CHECK(s.units == p.units && s.splits == p.splits && s.rshift == p.rshift && s.spread == p.spread && s.hpx == p.hpx && s.hkx == p.hkx);
+}
+
+// ... at the edges of what plan_short lays out, every field at its largest and smallest beside the others
+int words()
+{
+    int n = 0;
+    for (int units : {1, 2, 127, kShortUnits})
+        for (int f0 : {0, 1, units - 1, units})
+            for (int f1 : {0, f0 / 2, f0})
+                for (int f2 : {0, f1 / 2, f1})
+                    for (int splits : {1, 2, 15, 16})
+                        for (int rshift : {0, 1, 2, 3})
+                            for (int spread : {0, 1})
+                                for (int hpx : {1, 40, 0xffff})
+                                    for (int hkx : {1, 5, hpx}) {
+                                        ShortParams p = {};
+                                        p.units = units; p.first_unit[0] = f0; p.first_unit[1] = f1; p.first_unit[2] = f2;
+                                        p.splits = splits; p.rshift = rshift; p.spread = spread; p.hpx = hpx; p.hkx = hkx;
+                                        check_words(p);
+                                        ++n;
+                                    }
+    std::printf("%d launches\n", n);
+    return 0;
+}
 
 int choices(int hq, int hkv)
 {
@@ -101,6 +134,9 @@ hipError_t tetri_launch_short(int D, bool, const ShortParams &p, int wavefronts,
     g_taken = "short";
     if (g_h == nullptr) return hipSuccess;
     CHECK(wavefronts == 4 || wavefronts == 8);
+    check_words(p);
+    g_most_units = std::max(g_most_units, p.units);
+    g_most_splits = std::max(g_most_splits, p.splits);
     const int nwl = wavefronts == 8 ? 3 : 2;
     CHECK(p.units >= 1 && p.units <= kShortUnits && p.rows == g_cu.back() && p.hpx << p.rshift == p.Hq && p.hkx << p.rshift == p.Hkv);
     std::vector<std::vector<int>> done((size_t)p.units * p.Hq);          // how often each step ran
@@ -153,6 +189,7 @@ hipError_t tetri_launch_short(int D, bool, const ShortParams &p, int wavefronts,
 
 int main(int argc, char **argv)
 {
+    if (argc == 1) return words();
     if (argc == 3) return choices(std::atoi(argv[1]), std::atoi(argv[2]));
     CHECK(argc == 7);
     std::mt19937 rng((unsigned)std::atoi(argv[1]));
@@ -177,6 +214,7 @@ int main(int argc, char **argv)
                                           g_cu.data(), g_ctx.data(), any, nullptr) == TETRI_OK);
     }
     tetri_destroy(h);
-    std::printf("%d launches, row blocks by team %d %d %d %d, split %d\n", g_launches, g_teams[0], g_teams[1], g_teams[2], g_teams[3], g_split);
+    std::printf("%d launches, row blocks by team %d %d %d %d, split %d, at most %d row blocks, %d parts\n", g_launches, g_teams[0], g_teams[1], g_teams[2], g_teams[3],
+                g_split, g_most_units, g_most_splits);
     return 0;
 }

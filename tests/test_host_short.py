@@ -24,6 +24,12 @@ def driver(tmp_path_factory):
     return exe
 
 
+def test_packed_words(driver):
+    """The words that a launch's shape travels in, at the smallest and largest of every field (those of a drawn launch: test_teams)."""
+    res = subprocess.run([driver], capture_output=True, text=True, timeout=60)
+    assert res.returncode == 0 and int(res.stdout.split()[0]) > 10000, res.stdout + res.stderr
+
+
 # teams: log2 of the team sizes that the drawn launches have to show
 @pytest.mark.parametrize("heads, dim, chunk, teams", [((40, 40), 128, 512, (0, 1, 2, 3)), ((40, 40), 64, 2048, (0, 1, 2)), ((32, 8), 128, 512, (0, 1, 2, 3)),
                                                       ((24, 8), 128, 500, (0, 1, 2)), ((6, 3), 64, 500, (0, 1, 3)), ((4, 4), 128, 4096, (0, 1, 2)),
@@ -34,3 +40,5 @@ def test_teams(driver, heads, dim, chunk, teams):
     nums = [int(x.rstrip(",")) for x in res.stdout.split() if x.rstrip(",").isdigit()]
     assert nums[0] >= 200 and all(nums[1 + t] > 0 for t in teams), res.stdout
     assert nums[5] > 0 or heads[0] * -(-chunk // 32) > 128, res.stdout
+    assert chunk < 4096 or nums[6] > 120, res.stdout                   # (row blocks: up to 128 of them)
+    assert heads != (2, 1) or nums[7] == 16, res.stdout                # (parts of a row block's keys: up to 16)
