@@ -95,7 +95,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? (F8 ? 3 : 4) : 2) void attn_shor
     constexpr int ESZ = F8 ? 1 : 2, NWL = NW == 8 ? 3 : 2;
     static_assert(2 * CT::NI == NI && 2 * CT::BYTES == TILE_BYTES, "a step of codes takes a region");
     __shared__ __attribute__((aligned(1024))) char smem[NW * 2 * TILE_BYTES];
-    __shared__ __attribute__((aligned(1024))) char q_rows[NW / 4 * TILE_BYTES];      // of teams of 4 and 8
+    __shared__ __attribute__((aligned(1024))) char q_rows[F8 ? 16 : NW / 4 * TILE_BYTES];      // of teams of 4 and 8, 16-bit cache
     __shared__ float stat[NW][2][32];
     __shared__ int last;
     // (the structure lies behind the leading arguments)
@@ -329,9 +329,11 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? (F8 ? 3 : 4) : 2) void attn_shor
         for (int s = 0; s < KSTEPS; ++s) qf[s] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(qt + (kbase0 ^ (s << 5))));
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     };
-    // A team of 4 or 8 loads them once, a share each wavefront, into a place of their own: nothing of the stream waits for them.  The
-    // others take the region that the stream needs second (places of their own would not fit).
-    const bool shared_q = tl >= 2;
+    // A team of 4 or 8 loads them once, a share each wavefront, into a place of their own: nothing of the stream waits for them (286
+    // short prompts of 40 heads: 981.0 us, this way 977.7).  The others take the region that the stream needs second (places of their
+    // own would not fit); so do all teams over codes, whose regions hold whole steps (ragged prompts of 32/8 heads: 642.5 us
+    // with a place of their own, 640.6 without).
+    const bool shared_q = !F8 && tl >= 2;
     char *qt = shared_q ? q_rows + (valid ? team_ : 0) * TILE_BYTES : my + (region ^ 1) * TILE_BYTES;
     if (shared_q) {
         if (valid)
@@ -357,9 +359,8 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? (F8 ? 3 : 4) : 2) void attn_shor
         else feed(R1());
     }
     if (shared_q) {
-        // (the wavefront's share; behind it the stream's first two loads, or one where its only step is one of codes)
+        // (the wavefront's share; behind it the stream's first two loads)
         if (left <= 0) wait_vm<0>();
-        else if (F8 && left == 1 && code_steps != 0) wait_vm<NI>();
         else wait_vm<2 * NI>();
         lds_barrier();
         read_q(qt);
