@@ -121,6 +121,7 @@ struct Job {
 // words are in scalar registers when a wavefront starts, the structure is a memory read of 0.4 us away (one request of 1000
 // tokens, 40 heads: 9.32 us before, 8.96 now).
 constexpr int kDecodeLead = 56;
+static_assert((kDecodeLead + offsetof(DecodeArgs, k_new)) % 64 == 0 && offsetof(DecodeArgs, pages_w) == offsetof(DecodeArgs, k_new) + 64, "a cache line");
 
 // RANGES: `ranges` equal ranges of the batch's steps, a workgroup each per kv head; otherwise every (request, kv head) in
 // `parts` equal parts, a workgroup each.  Grid: kv head fastest.

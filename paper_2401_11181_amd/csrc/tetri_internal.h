@@ -216,22 +216,25 @@ struct TransferParams {
 // Most requests of a decode batch whose steps are divided evenly (a lane of a wavefront looks at up to 16 of them).
 constexpr int kDecodeLookup = 1024;
 
-// What the decode-iteration kernel reads of its arguments behind the leading scalars.
+// What the decode-iteration kernel reads of its arguments behind the leading scalars: what it needs up to the end of its loop in
+// one cache line (the structure starts 8 bytes before one), the others behind.  (Heads of 4 x 64, 6 requests of up to 184 tokens
+// over codes: 6.14 us with Hq and g in the line before c and k_scale, this way 6.07.)
 struct DecodeArgs {
-    const uint16_t *k_new, *v_new;
     uint16_t *out;
+    const uint16_t *k_new, *v_new;
+    int32_t Hq, g;
+    float c;              // |scale| * log2(e)
+    int32_t neg;          // 1 if scale < 0
+    float k_scale, v_inv; // FP8 pool: the scales and fl32(1 / scale)
+    int32_t ranges;       // parts == 0: the steps of the batch in that many equal ranges, a workgroup each per kv head
+    int32_t min_steps;    // ... of at least this many steps
+    int32_t *counters_next;   // the set of a later launch: zeroed by this one
+    int32_t n_counters;   // size of a set; 0: no (request, kv head) is shared, the launch touches no counters
+    float out_scale;      // factor on the finished output: v_scale for an FP8 pool, else 1
     uint16_t *pages_w;    // pool for the fused append of the new token (null: no append)
     float *partial;       // scratch: partial results of (request, kv head)s shared by workgroups
     int32_t *counters;    // ... and their arrival counters, zero before and after the launch
-    int32_t *counters_next;   // the set of a later launch: zeroed by this one
-    int32_t n_counters;   // size of a set; 0: no (request, kv head) is shared, the launch touches no counters
-    int32_t Hq, g;
-    int32_t ranges;       // parts == 0: the steps of the batch in that many equal ranges, a workgroup each per kv head
-    int32_t min_steps;    // ... of at least this many steps
-    float c;              // |scale| * log2(e)
-    int32_t neg;          // 1 if scale < 0
-    float k_scale, v_scale, k_inv, v_inv;   // FP8 pool: the scales and fl32(1 / scale)
-    float out_scale;      // factor on the finished output: v_scale for an FP8 pool, else 1
+    float v_scale, k_inv;
 };
 
 // The launch as the host lays it out: what it adds goes to the kernel as leading scalars, but for the choice of the kernel.
