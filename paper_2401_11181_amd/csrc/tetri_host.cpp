@@ -559,9 +559,9 @@ static bool plan_short(const tetri_ctx *h, const int32_t *cu, const int32_t *ctx
     }
     // ---- the shape of the launch.  A row block of one head is the work of a team of 1, 2, 4 or 8 wavefronts: as many as leave at
     // most `cap` steps to each, cap the least for which all workgroups of the launch are on the chip at once.  (Teams of one
-    // size made the launch as long as its longest row block: 64 packed chunks of 40 heads 18.0 us each, now 15.8.  Counted in
-    // wavefronts instead of workgroups, a launch could need a few workgroups more than there is room for: 512 rows of 40 heads at 100
-    // cached tokens 20.3 us (FP8 25.3), now 17.2 (20.3).)
+    // size made the launch as long as its longest row block: the 71 packed chunks of 286 short prompts of 40 heads 16.2 us
+    // each, then 14.2.  Counted in wavefronts instead of workgroups, a launch could need a few workgroups more than there is room
+    // for: 512 rows of 40 heads at 100 cached tokens 20.3 us (FP8 25.3), now 17.2 (20.3).)
     p.rshift = Hkv % 8 == 0 ? 3 : (Hkv % 4 == 0 ? 2 : (Hkv % 2 == 0 ? 1 : 0));
     p.hpx = (int32_t)Hq >> p.rshift;
     p.hkx = Hkv >> p.rshift;

@@ -9,7 +9,7 @@
 //     decode kernel).  The host, which knows the segments of the chunk, gives each row block the team that leaves its
 //     wavefronts about as many steps as those of the others and fills the chip's places for wavefronts (plan_short): with one
 //     size of team for all row blocks a launch lasted as long as its longest one (512 rows of 40 heads: 18.3 us, now 14.0; 286 short
-//     prompts of 40 heads in 64 chunks: 1154 us, with teams 1006, now 976);
+//     prompts of 40 heads, 71 chunks: 1154 us, with teams 1006);
 //   * the row blocks, longest first, travel in the kernel arguments: a workgroup's first memory access after those is its page
 //     ids, the second Q, K and V;
 //   * few row blocks with long key ranges: the keys of a row block are split over several workgroups, so that every compute
@@ -21,8 +21,10 @@
 //     page slots from there (fused append), so there are no workgroups for that.
 // What bounds it in turn: the chain of steps of the wavefront with the most of them, 1.0 to 1.3 us a step, because a wavefront
 // has one step of loads in flight (codes two) and the keys of a step serve 32 rows instead of 256.  Long chains go to the shared-tile
-// kernel: the host chooses.  Of a launch of 64 packed chunks (15.2 us each) 3.5 us lie between two launches, most of the others are
-// loads (16 MB that no launch before has touched); the append, the merge and the output follow.
+// kernel: the host chooses.  The 71 packed chunks of 286 short prompts take 13.7 us each, by clock values stored at points of the kernel
+// (which cost 2 %): 2.4 us from the last wavefront's end to the next launch's first instruction, then for the wavefront that
+// ends last 0.8 to its row block, 0.4 to its page ids, 4.2 to Q and the first K (up to 16 MB that no launch before has touched, all
+// asked for at once; 2.3 in the median wavefront), 2.9 the steps, 1.9 the append and the team's barrier, 1.3 merge and output.
 // Arithmetic is that of the shared-tile kernel: bf16 operands, fp32 accumulation, weights rounded to bf16 before the PV
 // product and summed as rounded, parts of the keys merged in a fixed order.
 #include <type_traits>
@@ -82,6 +84,7 @@ template <int D> struct CodeTile {
 // Bytes of the kernel's arguments in front of its structure (which starts on a cache line).  What a wavefront's row block is found with
 // comes first and by itself: those words are in scalar registers when a wavefront starts, and the row block, with the pointers that
 // go with it, is one read of the arguments away instead of two.
+// (Ragged prompts over codes 649.9 us with the words read from memory, 642.8 so; the packed chunks above 998.7, so 977.0.)
 constexpr int kShortLead = 64;
 
 template <int D, bool F8, int NW>
@@ -517,7 +520,8 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? (F8 ? 3 : 4) : 2) void attn_shor
         }
     }
     // ---- fused append: the wavefront of the last step has rows t0 .. t0 + 31 of K and V in its regions.  (The rows of a matrix are read
-    // together: row by row, each behind the condition of its store, its LDS round trips held the whole team up before the merge)
+    // together: row by row, each behind the condition of its store, its LDS round trips held the whole team up before the merge: 286
+    // short prompts of 40 heads 987.1 us, this way 977.9; ragged prompts over codes 648.9, this way 642.3)
     if (appends) {
         const int slot0 = (L + t0) % kPage, ch = lane % CH;
 #pragma unroll
@@ -606,8 +610,8 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? (F8 ? 3 : 4) : 2) void attn_shor
     }
     lds_barrier();
     // (whatever lies in LDS is read together, places past the last wavefront as the last one's: read one by one as it is used, it cost
-    // teams of eight a round trip each, three times over.  With the append's rows read together and Q in a place of its own, 286 short
-    // prompts of 40 heads: 1006 us, now 976)
+    // teams of eight a round trip each, three times over: 286 short prompts of 40 heads 981.1 us, this way 977.3; ragged prompts over
+    // codes 644.7, this way 642.6)
     float wgt[NW], sum[NW];
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
