@@ -269,6 +269,8 @@ TETRI_API tetri_status tetri_chunk_prefill_planned(tetri_ctx *ctx, const void *q
  *   the plan that staging buffer 0 holds and the caller has copied to meta_dev), in order, each as tetri_chunk_prefill_planned
  *   does it: mode 1 with append = 1, mode 2 attention only, mode 0 attention followed by tetri_kv_append.
  *   q, k_new, v_new, out: host arrays of a device pointer per chunk.
+ *   tetri_batch_step: tetri_batch_upload, then tetri_batch_launch of all n_chunks chunks, in one call; what meta_dev holds when it is
+ *   done is the same.  A small plan needs no launch of its own here: the first chunk's takes it along where it can.
  */
 typedef struct tetri_batch tetri_batch;
 TETRI_API tetri_status tetri_batch_create(tetri_ctx *ctx, int64_t meta_len, int32_t *staging, int32_t *meta_dev,
@@ -281,6 +283,10 @@ TETRI_API tetri_status tetri_batch_upload(tetri_batch *batch, const int32_t *pro
 TETRI_API tetri_status tetri_batch_launch(tetri_batch *batch, const int32_t *layout, int32_t first_chunk, int32_t n,
                                           const void *const *q, const void *const *k_new, const void *const *v_new,
                                           void *kv_pages, void *const *out, float scale, int32_t mode, void *stream);
+TETRI_API tetri_status tetri_batch_step(tetri_batch *batch, const int32_t *prompt_lens, int32_t n_prompts, const int32_t *order,
+                                        int32_t n_order, const int32_t *req_block_tables, int32_t *layout_out, int32_t n_chunks,
+                                        const void *const *q, const void *const *k_new, const void *const *v_new, void *kv_pages,
+                                        void *const *out, float scale, int32_t mode, void *stream);
 
 /*
  * KV export and import: the data plane of the dispatcher (Sec. 3.3.4 "Dispatcher": a prefilled

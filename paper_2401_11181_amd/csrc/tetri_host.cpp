@@ -869,11 +869,20 @@ static SlotChoice planned_slots(const tetri_ctx *h, const int32_t *cu, const int
     return {steps * Hq < 75000, steps * Hq >= 30000};
 }
 
+// A batch's metadata that has not been sent yet, in the arguments of a kernel of its own.
+static tetri_status send_metadata(tetri_ctx *h, const char *fn, MetaUpload &m, hipStream_t hs)
+{
+    if (!m.host) return TETRI_OK;
+    const hipError_t e = tetri_launch_upload_inline(m.host, m.dev, m.len, hs);
+    m.host = nullptr;
+    return e == hipSuccess ? TETRI_OK : fail(h, TETRI_ERR_HIP, "%s: launch failed: %s", fn, hipGetErrorString(e));
+}
+
 static tetri_status attn_common(const char *fn, tetri_ctx *h, const void *q, const void *k_new, const void *v_new,
                                 const void *kv_pages, void *kv_pages_w, const int32_t *block_table, const int32_t *cu,
                                 const int32_t *ctx_lens, int32_t num_segs, float scale, void *out, void *stream,
                                 bool fp8 = false, float k_scale = 1.f, float v_scale = 1.f,
-                                const int32_t *host_cu = nullptr, const int32_t *host_ctx = nullptr)
+                                const int32_t *host_cu = nullptr, const int32_t *host_ctx = nullptr, MetaUpload *carry = nullptr)
 {
     const void *ptrs[] = {q, k_new, v_new, kv_pages, out};
     const char *names[] = {"q", "k_new", "v_new", "kv_pages", "out"};
@@ -923,14 +932,20 @@ static tetri_status attn_common(const char *fn, tetri_ctx *h, const void *q, con
         sp.counters_next = cs.clear;
         sp.n_counters = h->n_counters;
         if (sp.splits > 1 && (st = claim_scratch(h, fn, hs, false)) != TETRI_OK) return st;
+        // (metadata that has not been sent yet goes with this launch, if it fits)
+        const bool takes = carry && carry->host && !fp8 && carry->len <= kShortCarry;
+        if (carry && !takes && (st = send_metadata(h, fn, *carry, hs)) != TETRI_OK) return st;
+        sp.carry = takes ? carry : nullptr;
         hipError_t e = tetri_launch_short(h->cfg.head_dim, fp8, sp, 1 << shape.nwl, hs);
         if (e != hipSuccess) return fail(h, TETRI_ERR_HIP, "%s: launch failed: %s", fn, hipGetErrorString(e));
+        if (takes) carry->host = nullptr;
         if (sp.splits > 1) {
             ++h->counter_turn;
             scratch_claimed(h, hs);
         }
         return TETRI_OK;
     }
+    if (carry && (st = send_metadata(h, fn, *carry, hs)) != TETRI_OK) return st;
     auto log2i = [](int v) { int s = 0; while ((1 << s) < v) ++s; return s; };
     // ---- the other chunks whose segments the host knows: the shared-tile kernel on a division made here
     if (host_cu && !stream_captures(hs)) {
@@ -1183,10 +1198,13 @@ tetri_status tetri_batch_create(tetri_ctx *h, int64_t meta_len, int32_t *staging
     return TETRI_OK;
 }
 
-tetri_status tetri_batch_upload(tetri_batch *b, const int32_t *prompt_lens, int32_t n_prompts, const int32_t *order, int32_t n_order,
-                                const int32_t *req_block_tables, int32_t *layout_out, int32_t n_chunks, void *stream)
+}  // extern "C"
+
+// The plan of a batch in the next staging buffer and on its way to the device.  later (null: now): a plan that fits a kernel's arguments is
+// left to be sent by the caller's next launch.
+static tetri_status batch_plan(const char *fn, tetri_batch *b, const int32_t *prompt_lens, int32_t n_prompts, const int32_t *order, int32_t n_order,
+                               const int32_t *req_block_tables, int32_t *layout_out, int32_t n_chunks, void *stream, MetaUpload *later)
 {
-    const char *fn = "tetri_batch_upload";
     if (!b) return fail(nullptr, TETRI_ERR_INVALID_ARG, "%s: null batch", fn);
     tetri_ctx *h = b->h;
     if (!layout_out || n_chunks < 0) return fail(h, TETRI_ERR_INVALID_ARG, "%s: null layout_out or negative n_chunks", fn);
@@ -1209,9 +1227,13 @@ tetri_status tetri_batch_upload(tetri_batch *b, const int32_t *prompt_lens, int3
         // Small plans travel in the kernel's arguments.  (Captured into a graph, the upload runs in replays: they read the staging
         // buffer, whatever it holds by then, and no event tells of them.)
         const bool capturing = stream_captures(hs), inside = len <= kUploadInline && !capturing;
-        e = inside ? tetri_launch_upload_inline(host, b->dev, len, hs)
-                   : tetri_launch_upload(host, b->dev, len, hs, capturing ? nullptr : b->done[slot]);
-        if (e != hipSuccess) return fail(h, TETRI_ERR_HIP, "%s: launch failed: %s", fn, hipGetErrorString(e));
+        if (inside && later) {
+            *later = {host, b->dev, len};
+        } else {
+            e = inside ? tetri_launch_upload_inline(host, b->dev, len, hs)
+                       : tetri_launch_upload(host, b->dev, len, hs, capturing ? nullptr : b->done[slot]);
+            if (e != hipSuccess) return fail(h, TETRI_ERR_HIP, "%s: launch failed: %s", fn, hipGetErrorString(e));
+        }
         b->pending[slot] = !capturing && !inside;
     }
     b->slot = slot;
@@ -1219,11 +1241,10 @@ tetri_status tetri_batch_upload(tetri_batch *b, const int32_t *prompt_lens, int3
     return TETRI_OK;
 }
 
-tetri_status tetri_batch_launch(tetri_batch *b, const int32_t *layout, int32_t first_chunk, int32_t n, const void *const *q,
-                                const void *const *k_new, const void *const *v_new, void *kv_pages, void *const *out, float scale,
-                                int32_t mode, void *stream)
+static tetri_status batch_launch(const char *fn, tetri_batch *b, const int32_t *layout, int32_t first_chunk, int32_t n, const void *const *q,
+                                 const void *const *k_new, const void *const *v_new, void *kv_pages, void *const *out, float scale,
+                                 int32_t mode, void *stream, MetaUpload *carry)
 {
-    const char *fn = "tetri_batch_launch";
     if (!b) return fail(nullptr, TETRI_ERR_INVALID_ARG, "%s: null batch", fn);
     tetri_ctx *h = b->h;
     if (mode < 0 || mode > 2) return fail(h, TETRI_ERR_INVALID_ARG, "%s: mode=%d (0, 1 or 2)", fn, mode);
@@ -1238,12 +1259,42 @@ tetri_status tetri_batch_launch(tetri_batch *b, const int32_t *layout, int32_t f
         tetri_status st = check_host_chunk(h, fn, host + o_cu, host + o_ctx, S);
         if (st != TETRI_OK) return st;
         st = attn_common(fn, h, q[c], k_new[c], v_new[c], kv_pages, mode == 1 ? kv_pages : nullptr, b->dev + o_bt, b->dev + o_cu,
-                         b->dev + o_ctx, S, scale, out[c], stream, false, 1.f, 1.f, host + o_cu, host + o_ctx);
+                         b->dev + o_ctx, S, scale, out[c], stream, false, 1.f, 1.f, host + o_cu, host + o_ctx, carry);
         if (st == TETRI_OK && mode == 0)
             st = tetri_kv_append(h, k_new[c], v_new[c], kv_pages, b->dev + o_bt, b->dev + o_cu, b->dev + o_ctx, S, stream);
         if (st != TETRI_OK) return st;
     }
     return TETRI_OK;
+}
+
+extern "C" {
+
+tetri_status tetri_batch_upload(tetri_batch *b, const int32_t *prompt_lens, int32_t n_prompts, const int32_t *order, int32_t n_order,
+                                const int32_t *req_block_tables, int32_t *layout_out, int32_t n_chunks, void *stream)
+{
+    return batch_plan("tetri_batch_upload", b, prompt_lens, n_prompts, order, n_order, req_block_tables, layout_out, n_chunks, stream, nullptr);
+}
+
+tetri_status tetri_batch_launch(tetri_batch *b, const int32_t *layout, int32_t first_chunk, int32_t n, const void *const *q,
+                                const void *const *k_new, const void *const *v_new, void *kv_pages, void *const *out, float scale,
+                                int32_t mode, void *stream)
+{
+    return batch_launch("tetri_batch_launch", b, layout, first_chunk, n, q, k_new, v_new, kv_pages, out, scale, mode, stream, nullptr);
+}
+
+tetri_status tetri_batch_step(tetri_batch *b, const int32_t *prompt_lens, int32_t n_prompts, const int32_t *order, int32_t n_order,
+                              const int32_t *req_block_tables, int32_t *layout_out, int32_t n_chunks, const void *const *q,
+                              const void *const *k_new, const void *const *v_new, void *kv_pages, void *const *out, float scale, int32_t mode,
+                              void *stream)
+{
+    const char *fn = "tetri_batch_step";
+    MetaUpload meta = {nullptr, nullptr, 0};
+    tetri_status st = batch_plan(fn, b, prompt_lens, n_prompts, order, n_order, req_block_tables, layout_out, n_chunks, stream, &meta);
+    if (st != TETRI_OK) return st;
+    st = batch_launch(fn, b, layout_out, 0, n_chunks, q, k_new, v_new, kv_pages, out, scale, mode, stream, &meta);
+    // (no chunk, or an error before the first launch: the metadata is sent all the same, as by tetri_batch_upload; the first error counts)
+    const hipError_t e = meta.host ? tetri_launch_upload_inline(meta.host, meta.dev, meta.len, static_cast<hipStream_t>(stream)) : hipSuccess;
+    return st != TETRI_OK || e == hipSuccess ? st : fail(b->h, TETRI_ERR_HIP, "%s: launch failed: %s", fn, hipGetErrorString(e));
 }
 
 tetri_status tetri_validate_chunk(tetri_ctx *h, const int32_t *block_table, const int32_t *cu, const int32_t *ctx_lens,

@@ -154,8 +154,26 @@ struct __attribute__((aligned(64))) ShortArgs {
     uint32_t unit[kShortUnits][2];
 };
 
+// A batch's metadata on its way to the device: len int32 of host memory for dev (16-byte aligned); host is null once it has been sent.
+struct MetaUpload {
+    const int32_t *host;
+    int32_t *dev;
+    int64_t len;
+};
+
+// The same with the metadata of the whole batch: the launch finds its page ids there and copies it to the device, for the launches
+// behind it.  At most kShortCarry int32.
+constexpr int64_t kShortCarry = 672;
+struct __attribute__((aligned(64))) ShortCarry : ShortArgs {
+    int32_t *meta_dev;
+    int32_t meta_vectors;         // of 16 bytes
+    int32_t pad2;
+    uint32_t meta[kShortCarry];
+};
+
 // The launch as the host lays it out; what it adds goes to the kernel as leading scalars, some of them packed.
 struct ShortParams : ShortArgs {
+    const MetaUpload *carry;      // metadata that this launch takes along (null: none); bt lies in its dev then
     const int32_t *bt;
     int32_t max_blocks;
     int32_t first_wg[4];          // of the row blocks of 1, 2, 4 and 8 wavefronts: the classes follow each other from 8 down ...

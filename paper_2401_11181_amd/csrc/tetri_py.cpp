@@ -165,7 +165,7 @@ template <typename... A> struct Entry<tetri_status(A...)> {
     X(tetri_kv_append) X(tetri_chunk_prefill_attn) X(tetri_chunk_prefill_attn_append) X(tetri_chunk_prefill_attn_fp8) \
     X(tetri_decode_attn) X(tetri_decode_attn_static) X(tetri_decode_attn_append) X(tetri_decode_attn_fp8) \
     X(tetri_kv_export) X(tetri_kv_import) X(tetri_kv_export_fp8) X(tetri_kv_import_fp8) \
-    X(tetri_chunk_prefill_planned) X(tetri_batch_upload) X(tetri_batch_launch)
+    X(tetri_chunk_prefill_planned) X(tetri_batch_upload) X(tetri_batch_launch) X(tetri_batch_step)
 
 #define X(f) \
     decltype(&f) g_##f = nullptr; \

@@ -27,6 +27,8 @@
 // asked for at once; 2.3 in the median wavefront), 2.9 the steps, 1.9 the append and the team's barrier, 1.3 merge and output.
 // Arithmetic is that of the shared-tile kernel: bf16 operands, fp32 accumulation, weights rounded to bf16 before the PV
 // product and summed as rounded, parts of the keys merged in a fixed order.
+#include <string.h>
+
 #include <type_traits>
 
 #include "attn_common.h"
@@ -34,8 +36,6 @@
 namespace {
 
 using namespace tetri_dev;
-
-typedef __attribute__((address_space(4))) const ShortArgs const_params;
 
 // 32 rows of K or V, as two halves of 16 rows with a scalar base each, into a wavefront's tile (swizzled like
 // everywhere); rows of a half are row_bytes apart.
@@ -87,11 +87,16 @@ template <int D> struct CodeTile {
 // (Ragged prompts over codes 649.9 us with the words read from memory, 642.8 so; the packed chunks above 998.7, so 977.0.)
 constexpr int kShortLead = 64;
 
-template <int D, bool F8, int NW>
+// Args: ShortArgs, or ShortCarry for the first launch of a batch's step, which brings the metadata of all its launches (block_tables is then
+// the offset of the chunk's in it, in int32): one launch less in front of the first result.  (Four chunks of 64 rows of 4 heads of 64: 23.5 us with
+// the upload in front, 20.1 so; four of 512 of 40 heads 116.3, 115.3.)
+template <int D, bool F8, int NW, typename Args>
 __global__ __launch_bounds__(NW * 64, D == 64 ? (F8 ? 3 : 4) : 2) void attn_short_kernel(
     const int32_t *block_tables, int max_blocks, int first_wg0, int first_wg1, int first_wg2, uint32_t first_units, int attn_wgs, uint32_t shape,
-    uint32_t splits_magic, uint32_t hpx_magic, uint32_t hkx_magic, uint32_t per_x, ShortArgs)
+    uint32_t splits_magic, uint32_t hpx_magic, uint32_t hkx_magic, uint32_t per_x, Args)
 {
+    constexpr bool CARRY = std::is_same<Args, ShortCarry>::value;
+    typedef __attribute__((address_space(4))) const Args const_params;
     typedef CodeTile<D> CT;
     constexpr int KSTEPS = D / 16, DBLK = D / 32, NI = D / 16, CH = D / 8, RPI = 64 / CH;
     constexpr int ROW = D * 2, TILE_BYTES = 32 * ROW;
@@ -109,9 +114,17 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? (F8 ? 3 : 4) : 2) void attn_shor
     const int half = lane >> 5, l32 = lane & 31;
     const int bid = blockIdx.x;
     if (bid >= attn_wgs) {
+        if constexpr (CARRY) {
+            if (bid == (int)gridDim.x - 1) {             // ---- the metadata, for the launches behind this one
+                const int n = p->meta_vectors;
+                const auto *v = (__attribute__((address_space(4))) const u32x4 *)p->meta;
+                for (int i = tid; i < n; i += NW * 64) reinterpret_cast<global_u32x4_w *>((uintptr_t)p->meta_dev)[i] = v[i];
+                return;
+            }
+        }
         // ---- padding rows [rows, C) are written as +0, 16 bytes per lane and pass
         const size_t first = (size_t)p->rows * p->Hq * CH, n = (size_t)p->C * p->Hq * CH;
-        const size_t stride = (size_t)(gridDim.x - attn_wgs) * (NW * 64);
+        const size_t stride = (size_t)(gridDim.x - attn_wgs - (int)CARRY) * (NW * 64);
         for (size_t i = first + (size_t)(bid - attn_wgs) * (NW * 64) + tid; i < n; i += stride)
             reinterpret_cast<global_u32x4_w *>((uintptr_t)p->out)[i] = u32x4{0u, 0u, 0u, 0u};
         return;
@@ -178,7 +191,9 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? (F8 ? 3 : 4) : 2) void attn_shor
         return;
     }
 
-    const const_i32 *bt = (const const_i32 *)(uintptr_t)(block_tables + (size_t)seg * max_blocks);
+    const const_i32 *bt;
+    if constexpr (CARRY) bt = (const const_i32 *)p->meta + ((uintptr_t)block_tables + (size_t)seg * max_blocks);
+    else bt = (const const_i32 *)(uintptr_t)(block_tables + (size_t)seg * max_blocks);
     const int last_entry = max_blocks - 1;
     const size_t head_bytes = (size_t)kPage * D * ESZ, page_bytes = 2 * (size_t)Hkv * head_bytes;
     const char *pool_k = p_pages + (size_t)kh * head_bytes;
@@ -740,9 +755,24 @@ template <int D, bool F8>
 hipError_t launch(const ShortParams &p, int wavefronts, hipStream_t stream)
 {
     const dim3 grid(p.attn_wgs + p.zero_wgs);
-    auto kernel = wavefronts == 8 ? attn_short_kernel<D, F8, 8> : attn_short_kernel<D, F8, 4>;
-    static_assert(KernelArgs<decltype(kernel)>::last_offset() == kShortLead, "where the kernel reads its structure");
     const ShortWords w = short_pack(p);
+    if constexpr (!F8) {
+        if (p.carry != nullptr) {
+            auto kernel = wavefronts == 8 ? attn_short_kernel<D, F8, 8, ShortCarry> : attn_short_kernel<D, F8, 4, ShortCarry>;
+            static_assert(KernelArgs<decltype(kernel)>::last_offset() == kShortLead && kShortLead + sizeof(ShortCarry) <= 4096, "the kernel's arguments");
+            ShortCarry a;
+            static_cast<ShortArgs &>(a) = p;
+            a.meta_dev = p.carry->dev;
+            a.meta_vectors = (int32_t)((p.carry->len + 3) / 4);
+            memcpy(a.meta, p.carry->host, (size_t)a.meta_vectors * 16);
+            hipLaunchKernelGGL(kernel, dim3(grid.x + 1), dim3(64 * wavefronts), 0, stream, reinterpret_cast<const int32_t *>((uintptr_t)(p.bt - p.carry->dev)),
+                               p.max_blocks, p.first_wg[0], p.first_wg[1], p.first_wg[2], w.first_units, p.attn_wgs, w.shape, p.splits_magic, p.hpx_magic,
+                               p.hkx_magic, w.per_x, a);
+            return hipGetLastError();
+        }
+    }
+    auto kernel = wavefronts == 8 ? attn_short_kernel<D, F8, 8, ShortArgs> : attn_short_kernel<D, F8, 4, ShortArgs>;
+    static_assert(KernelArgs<decltype(kernel)>::last_offset() == kShortLead, "where the kernel reads its structure");
     hipLaunchKernelGGL(kernel, grid, dim3(64 * wavefronts), 0, stream, p.bt, p.max_blocks, p.first_wg[0], p.first_wg[1], p.first_wg[2],
                        w.first_units, p.attn_wgs, w.shape, p.splits_magic, p.hpx_magic, p.hkx_magic, w.per_x, static_cast<const ShortArgs &>(p));
     return hipGetLastError();

@@ -261,8 +261,12 @@ class PrefillPipeline:
         if rc != tetri.TETRI_OK:
             raise tetri.TetriError(rc, tetri.tetri_last_error(self.handle))
 
+    @property
+    def _mode(self):
+        return tetri.BATCH_FUSED if self.fused else tetri.BATCH_TWO_LAUNCHES
+
     def _launch_all(self):
-        mode = tetri.BATCH_FUSED if self.fused else tetri.BATCH_TWO_LAUNCHES
+        mode = self._mode
         if self.export != "chunk":
             self.batch.launch(self.layout_np, 0, self.n_chunks, *self._batch_args, mode, None)
         else:
@@ -274,10 +278,18 @@ class PrefillPipeline:
                 self._check(self._lib.tetri_kv_export(*self._chunk_export_args[c]))
             self.side_done.record(self.side)
             torch.cuda.current_stream().wait_event(self.side_done)
+        self._export_requests()
+
+    def _export_requests(self):
         if self.export == "request":
             self._check(self._lib.tetri_kv_export(*self._request_export_args, tetri._stream(None)))
 
     def step(self):
+        # (a staging ring need not have the two in one call)
+        if not self.use_graph and self.export != "chunk" and hasattr(self.batch, "step"):
+            self.batch.step(*self._plan_args, *self._batch_args, self._mode, None)
+            self._export_requests()
+            return
         self.batch.upload(*self._plan_args, None)
         if self.use_graph:
             if self.graph is None:                  # one graph: the launches read meta_dev, whose address is fixed

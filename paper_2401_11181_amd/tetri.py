@@ -376,6 +376,11 @@ class Batch:
         if rc:
             self.handle._check(rc)
 
+    def step(self, *args):
+        rc = self._n.tetri_batch_step(self._p, *args)
+        if rc:
+            self.handle._check(rc)
+
     def close(self):
         if self.b is not None:
             lib().tetri_batch_destroy(self.b)

@@ -1,0 +1,78 @@
+"""A batch's step in one call (tetri_batch_step), whose first launch brings the metadata of all of them where it can: bit for bit what
+tetri_batch_upload followed by tetri_batch_launch leaves in the output, the pool and the metadata, for plans on both sides of the
+sizes at which they stop fitting the first launch's arguments (672 int32) and the upload's (896), for first chunks that go to other kernels, with padding rows."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2401_11181_amd import synth, tetri
+from paper_2401_11181_amd.prefill import PrefillPipeline
+import gpu_common as gc
+
+pytestmark = pytest.mark.gpu
+
+# prompts, chunk size, heads, kv heads, head dim, entries added to every block-table row, "attn_variant"
+CASES = {
+    "one-chunk": ([60], 64, 4, 4, 64, 0, 0),                          # 12 int32
+    "small": ([70, 33, 150], 64, 4, 4, 64, 0, 0),
+    "split": ([300], 64, 2, 1, 128, 0, 0),                            # keys split over workgroups in later chunks
+    "eight-wavefronts": ([300, 90], 256, 32, 8, 128, 0, 3),
+    "first-launch-full": ([512], 128, 8, 2, 128, 128, 0),             # 4 chunks x (8 + 160) = 672 int32
+    "one-more": ([512], 128, 8, 2, 128, 129, 0),
+    "own-launch-full": ([512], 128, 8, 2, 128, 184, 0),               # 4 x (8 + 216) = 896
+    "staged": ([512], 128, 8, 2, 128, 188, 0),
+    "shared-tiles": ([260, 70], 128, 4, 4, 128, 0, 2),                # no launch of the short kernel
+}
+
+
+@pytest.mark.parametrize("fused", [True, False], ids=["fused", "two-launches"])
+@pytest.mark.parametrize("name", sorted(CASES))
+def test_step_is_upload_and_launch(name, fused):
+    lens, chunk, hq, hkv, d, spare, variant = CASES[name]
+    w = synth.small("step-" + name, lens, chunk, hq, hkv, d, seed=960)
+    tables = [[int(p) for p in t] + [0] * spare for t in synth.place_pages(w)]
+    pipe = PrefillPipeline(lens, None, chunk, hq, hkv, d, w.num_pages, tables, w.scale, device=gc.DEV, fused=fused)
+    if variant:
+        pipe.handle.tetri_set_option("attn_variant", variant)
+    if name in ("first-launch-full", "own-launch-full"):
+        assert pipe.meta_len == (672 if name == "first-launch-full" else 896)
+    g = torch.Generator(device=gc.DEV).manual_seed(961)
+    rnd = lambda *s: torch.randn(s, device=gc.DEV, generator=g).to(torch.bfloat16)
+    n = pipe.n_chunks
+    q, k, v = rnd(n, chunk, hq, d), rnd(n, chunk, hkv, d), rnd(n, chunk, hkv, d)
+    pool, out = torch.zeros((w.num_pages, 2, hkv, 16, d), dtype=torch.bfloat16, device=gc.DEV), torch.empty_like(q)
+    pipe.bind(q, k, v, pool, out)
+    got = []
+    for step in (pipe.step, lambda: (pipe.batch.upload(*pipe._plan_args, None), pipe._launch_all()), pipe.step):
+        pool.zero_()
+        out.fill_(7.0)
+        pipe.meta_dev.fill_(-9)
+        step()
+        torch.cuda.synchronize()
+        got.append((pool.clone(), out.clone(), pipe.meta_dev.clone()))
+    for pool_, out_, meta in (got[0], got[2]):
+        assert torch.equal(pool_.view(torch.int16), got[1][0].view(torch.int16))
+        assert torch.equal(out_.view(torch.int16), got[1][1].view(torch.int16))
+        want = np.zeros(pipe.meta_len, np.int32), np.zeros((n, 4), np.int32)
+        tetri.tetri_plan_metadata(pipe.lens, None, chunk, pipe.req_bt, *want)
+        for at, x in ((meta.cpu().numpy(), want[0]), (got[1][2].cpu().numpy(), want[0])):
+            for o_cu, o_ctx, o_bt, S in want[1]:
+                for first, count in ((o_cu, S + 1), (o_ctx, S), (o_bt, S * pipe.max_blocks)):
+                    assert np.array_equal(at[first:first + count], x[first:first + count])
+
+
+def test_metadata_is_sent_where_the_launch_is_refused():
+    """An error before the first launch leaves the plan on the device, as the two calls do."""
+    w = synth.small("step-refused", [70, 33], 64, 4, 4, 64, seed=962)
+    pipe = PrefillPipeline(w.prompt_lens, None, 64, 4, 4, 64, w.num_pages, synth.place_pages(w), w.scale, device=gc.DEV)
+    t = torch.zeros((pipe.n_chunks, 64, 4, 64), dtype=torch.bfloat16, device=gc.DEV)
+    pool = torch.zeros((w.num_pages, 2, 4, 16, 64), dtype=torch.bfloat16, device=gc.DEV)
+    pipe.bind(t, t, t, pool, torch.zeros_like(t))
+    pipe.meta_dev.fill_(-9)
+    args = list(pipe._batch_args)
+    args[5] = float("nan")
+    with pytest.raises(tetri.TetriError) as e:
+        pipe.batch.step(*pipe._plan_args, *args, tetri.BATCH_FUSED, None)
+    assert "scale" in str(e.value)
+    torch.cuda.synchronize()
+    assert (pipe.meta_dev != -9).any()
