@@ -878,11 +878,36 @@ static tetri_status send_metadata(tetri_ctx *h, const char *fn, MetaUpload &m, h
     return e == hipSuccess ? TETRI_OK : fail(h, TETRI_ERR_HIP, "%s: launch failed: %s", fn, hipGetErrorString(e));
 }
 
+// What a launch of the short kernel asks for of the next chunk's rows: K first, then V and Q, by workgroups in the places that its row blocks
+// leave free.  Not for rows of less than 4 MB (head_dim 64: never): such launches are over before the reads are, and would wait for them.  Nor with
+// places for less: a prompt of 2048 tokens, 16 places in the first chunk's launch, gains nothing.
+static void fetch_ahead(const tetri_ctx *h, const NextRows *next, int wavefronts, ShortParams &p)
+{
+    p.fetch_wgs = 0;
+    if (!next || next->rows == 0 || h->cfg.head_dim != 128) return;
+    const int64_t row = 2 * (int64_t)h->cfg.head_dim, kv = next->rows * row * h->cfg.num_kv_heads, q = next->rows * row * h->cfg.num_q_heads;
+    const int64_t places = (int64_t)std::max(h->num_cus, 1) * 8 / wavefronts - p.attn_wgs;
+    const int64_t each = (int64_t)wavefronts * kFetchKB, sizes[3] = {kv, kv, q};
+    if (places * each < 4096 || 2 * kv + q < 4 << 20 || 2 * kv + q > INT32_MAX) return;
+    const void *from[3] = {next->k_new, next->v_new, next->q};
+    int64_t left = places * each;
+    for (int i = 0; i < 3; ++i) {
+        const int64_t kb = std::min((sizes[i] + 1023) / 1024, left);
+        p.next[i] = static_cast<const uint16_t *>(from[i]);
+        p.next_kb[i] = (uint32_t)kb;
+        left -= kb;
+    }
+    p.next_bytes[0] = (uint32_t)kv;
+    p.next_bytes[1] = (uint32_t)q;
+    p.fetch_wgs = (int32_t)(places - left / each);
+}
+
 static tetri_status attn_common(const char *fn, tetri_ctx *h, const void *q, const void *k_new, const void *v_new,
                                 const void *kv_pages, void *kv_pages_w, const int32_t *block_table, const int32_t *cu,
                                 const int32_t *ctx_lens, int32_t num_segs, float scale, void *out, void *stream,
                                 bool fp8 = false, float k_scale = 1.f, float v_scale = 1.f,
-                                const int32_t *host_cu = nullptr, const int32_t *host_ctx = nullptr, MetaUpload *carry = nullptr)
+                                const int32_t *host_cu = nullptr, const int32_t *host_ctx = nullptr, MetaUpload *carry = nullptr,
+                                const NextRows *next = nullptr)
 {
     const void *ptrs[] = {q, k_new, v_new, kv_pages, out};
     const char *names[] = {"q", "k_new", "v_new", "kv_pages", "out"};
@@ -936,6 +961,7 @@ static tetri_status attn_common(const char *fn, tetri_ctx *h, const void *q, con
         const bool takes = carry && carry->host && !fp8 && carry->len <= kShortCarry;
         if (carry && !takes && (st = send_metadata(h, fn, *carry, hs)) != TETRI_OK) return st;
         sp.carry = takes ? carry : nullptr;
+        fetch_ahead(h, next, 1 << shape.nwl, sp);
         hipError_t e = tetri_launch_short(h->cfg.head_dim, fp8, sp, 1 << shape.nwl, hs);
         if (e != hipSuccess) return fail(h, TETRI_ERR_HIP, "%s: launch failed: %s", fn, hipGetErrorString(e));
         if (takes) carry->host = nullptr;
@@ -1258,8 +1284,16 @@ static tetri_status batch_launch(const char *fn, tetri_batch *b, const int32_t *
             return fail(h, TETRI_ERR_INVALID_ARG, "%s: the layout of chunk %d does not fit the batch", fn, c);
         tetri_status st = check_host_chunk(h, fn, host + o_cu, host + o_ctx, S);
         if (st != TETRI_OK) return st;
+        // the next chunk's rows, where its launch follows this one here
+        NextRows next = {nullptr, nullptr, nullptr, 0};
+        if (c + 1 < first_chunk + n) {
+            const int64_t at = layout[4 * c + 4], segs = layout[4 * c + 7];
+            if (segs >= 1 && at >= 0 && at + segs < b->len && q[c + 1] && k_new[c + 1] && v_new[c + 1] && aligned16(q[c + 1]) &&
+                aligned16(k_new[c + 1]) && aligned16(v_new[c + 1]) && host[at + segs] >= 1 && host[at + segs] <= h->cfg.chunk_size)
+                next = {q[c + 1], k_new[c + 1], v_new[c + 1], host[at + segs]};
+        }
         st = attn_common(fn, h, q[c], k_new[c], v_new[c], kv_pages, mode == 1 ? kv_pages : nullptr, b->dev + o_bt, b->dev + o_cu,
-                         b->dev + o_ctx, S, scale, out[c], stream, false, 1.f, 1.f, host + o_cu, host + o_ctx, carry);
+                         b->dev + o_ctx, S, scale, out[c], stream, false, 1.f, 1.f, host + o_cu, host + o_ctx, carry, &next);
         if (st == TETRI_OK && mode == 0)
             st = tetri_kv_append(h, k_new[c], v_new[c], kv_pages, b->dev + o_bt, b->dev + o_cu, b->dev + o_ctx, S, stream);
         if (st != TETRI_OK) return st;

@@ -149,6 +149,10 @@ struct __attribute__((aligned(64))) ShortArgs {
     int32_t *counters;            // ... and arrival counters, one per (unit, head), zero before and after the launch
     int32_t *counters_next;       // the set of a later launch: zeroed by this one
     int32_t n_counters;           // size of a set
+    int32_t fetch_wgs;            // workgroups that ask for rows of the next chunk (0: none)
+    const uint16_t *next[3];      // ... of K, V and Q, and how many instructions of 1 KB go to each
+    uint32_t next_kb[3];
+    uint32_t next_bytes[2];       // what the rows take: K or V, and Q
     int32_t pad;
     // most work first, 64 bits each: segment (6), row block in it (7), the segment's rows (13) and first row (12), cached tokens (26)
     uint32_t unit[kShortUnits][2];
@@ -160,6 +164,13 @@ struct MetaUpload {
     int32_t *dev;
     int64_t len;
 };
+
+// The rows of the chunk that the caller's next launch is for (rows 0: not known), and how much of them a wavefront of a launch asks for.
+struct NextRows {
+    const void *q, *k_new, *v_new;
+    int32_t rows;
+};
+constexpr int kFetchKB = 32;
 
 // The same with the metadata of the whole batch: the launch finds its page ids there and copies it to the device, for the launches
 // behind it.  At most kShortCarry int32.

@@ -122,10 +122,30 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? (F8 ? 3 : 4) : 2) void attn_shor
                 return;
             }
         }
+        const int fetch_wgs = F8 ? 0 : p->fetch_wgs;
+        if (bid - attn_wgs < fetch_wgs) {
+            // ---- rows of the next chunk, 1 KB to an instruction, into a place that nobody reads: they are in the cache in front of the memory
+            // when its launch asks for them.  What bounds a launch is that all of its first reads are made at once and none after that: 512 rows of
+            // 40 heads are 16 MB, 4.2 us, of 13.  (286 short prompts of 40 heads, 71 chunks, 928 us without this; 4 us of sleep before: 893, none 897, 8 us 919.  With
+            // 16 KB to a wavefront 920, 40 905, 64 974: a compute unit takes 25 GB/s of such reads.  Asked for by the wavefronts with row blocks, behind their
+            // loop, 945, behind their first step 990.  With Q, K and V in the cache from the start, 748.)
+            const uint32_t nk = p->next_kb[0], nv = nk + p->next_kb[1], n = nv + p->next_kb[2], kv_bytes = p->next_bytes[0], q_bytes = p->next_bytes[1];
+            const char *const nx[3] = {reinterpret_cast<const char *>(p->next[0]), reinterpret_cast<const char *>(p->next[1]),
+                                       reinterpret_cast<const char *>(p->next[2])};
+            const uint32_t to = lds_address(smem + wave * 1024);
+            __builtin_amdgcn_s_sleep(64);                // (2 us: behind the launch's own first reads)
+            for (uint32_t i = (bid - attn_wgs) * NW + wave; i < n; i += fetch_wgs * NW) {
+                const char *from = i < nk ? nx[0] : (i < nv ? nx[1] : nx[2]);
+                const uint32_t at = (i < nk ? i : (i < nv ? i - nk : i - nv)) * 1024 + lane * 16;
+                dma16(from + min(at, (i < nv ? kv_bytes : q_bytes) - 16), to);
+            }
+            wait_vm<0>();                                // (nothing may be on its way to LDS when a wavefront ends)
+            return;
+        }
         // ---- padding rows [rows, C) are written as +0, 16 bytes per lane and pass
         const size_t first = (size_t)p->rows * p->Hq * CH, n = (size_t)p->C * p->Hq * CH;
-        const size_t stride = (size_t)(gridDim.x - attn_wgs - (int)CARRY) * (NW * 64);
-        for (size_t i = first + (size_t)(bid - attn_wgs) * (NW * 64) + tid; i < n; i += stride)
+        const size_t stride = (size_t)(gridDim.x - attn_wgs - fetch_wgs - (int)CARRY) * (NW * 64);
+        for (size_t i = first + (size_t)(bid - attn_wgs - fetch_wgs) * (NW * 64) + tid; i < n; i += stride)
             reinterpret_cast<global_u32x4_w *>((uintptr_t)p->out)[i] = u32x4{0u, 0u, 0u, 0u};
         return;
     }
@@ -754,7 +774,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? (F8 ? 3 : 4) : 2) void attn_shor
 template <int D, bool F8>
 hipError_t launch(const ShortParams &p, int wavefronts, hipStream_t stream)
 {
-    const dim3 grid(p.attn_wgs + p.zero_wgs);
+    const dim3 grid(p.attn_wgs + p.fetch_wgs + p.zero_wgs);
     const ShortWords w = short_pack(p);
     if constexpr (!F8) {
         if (p.carry != nullptr) {

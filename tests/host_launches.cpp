@@ -43,6 +43,8 @@ std::vector<Counters> g_counters;
 int g_parts = 0, g_ranges = 0;                // how the last decode was cut
 std::string g_kernel;                         // the attention kernel launched last
 const char *g_partials = nullptr;             // where the last attention or decode launch keeps partial results
+ShortParams g_short;                          // the last launch of the short kernel
+int g_short_wavefronts = 0;
 int g_out_past_l2 = -1;                       // how the last launch of the short kernel stores its output
 int g_longest = 0, g_short_wgs = 0;           // the steps of its longest wavefront, and its workgroups (of the attention)
 int g_places = 0;                             // of the last division made by the host: tiles' pieces there
@@ -126,9 +128,11 @@ hipError_t tetri_launch_attn(const tetri_ctx *, const AttnParams &p, int, bool, 
     } else if (p.stream_wgs > 0 || p.helpers > 0) g_counters.push_back({p.counters, p.counters_next, p.n_counters});
     return hipSuccess;
 }
-hipError_t tetri_launch_short(int, bool, const ShortParams &p, int, hipStream_t)
+hipError_t tetri_launch_short(int, bool, const ShortParams &p, int wavefronts, hipStream_t)
 {
     g_kernel = "short";
+    g_short = p;
+    g_short_wavefronts = wavefronts;
     g_out_past_l2 = p.out_past_l2;
     g_longest = 0;
     g_short_wgs = p.attn_wgs;
@@ -437,6 +441,83 @@ void short_output_stores()
     tetri_destroy(h);
 }
 
+// A launch of the short kernel that the next chunk's follows asks for rows of that chunk and for nothing outside them, with the places
+// that its row blocks leave free; the last chunk's launch, one with no place left, one for small rows and head_dim 64 do not.
+void next_chunk_rows()
+{
+    auto batch = [&](int hq, int hkv, int d, int chunk, std::vector<int32_t> lens, int32_t first, int32_t n) {
+        const int max_blocks = 128, prompts = (int)lens.size();
+        const tetri_config c = {hq, hkv, d, 16, chunk, 8192, max_blocks, 40, TETRI_BF16};
+        tetri_ctx *h = nullptr;
+        CHECK(tetri_create(&c, &h) == TETRI_OK && tetri_set_option(h, "attn_variant", 3) == TETRI_OK);
+        std::vector<int32_t> pages((size_t)prompts * max_blocks), layout(4 * 64);
+        const int64_t len = 1 << 14;
+        int32_t *staging = static_cast<int32_t *>(std::aligned_alloc(16, tetri_batch_slots() * len * 4));
+        alignas(16) static int32_t dev[4];
+        tetri_batch *b = nullptr;
+        CHECK(tetri_batch_create(h, len, staging, dev, &b) == TETRI_OK);
+        int32_t rows = 0;
+        for (int32_t x : lens) rows += x;
+        const int32_t chunks = (rows + chunk - 1) / chunk;
+        CHECK(tetri_batch_upload(b, lens.data(), prompts, nullptr, prompts, pages.data(), layout.data(), chunks, nullptr) == TETRI_OK);
+        std::vector<const void *> q, k, v;
+        std::vector<void *> out;
+        for (uintptr_t i = 0; i < (uintptr_t)chunks; ++i) {
+            q.push_back(reinterpret_cast<void *>((4 * i + 1) << 32));
+            k.push_back(reinterpret_cast<void *>((4 * i + 2) << 32));
+            v.push_back(reinterpret_cast<void *>((4 * i + 3) << 32));
+            out.push_back(reinterpret_cast<void *>((4 * i + 4) << 32));
+        }
+        CHECK(tetri_batch_launch(b, layout.data(), first, n, q.data(), k.data(), v.data(), g_any, out.data(), 0.1f, 1, nullptr) == TETRI_OK);
+        CHECK(g_kernel == "short");
+        const ShortParams &p = g_short;
+        uint64_t asked = 0;
+        CHECK(p.fetch_wgs == 0);                     // (of the last chunk)
+        // the launch before it: the last chunk is refused
+        if (n > 1) {
+            std::vector<const void *> none(q);
+            none[first + n - 1] = nullptr;
+            CHECK(tetri_batch_launch(b, layout.data(), first, n, none.data(), k.data(), v.data(), g_any, out.data(), 0.1f, 1, nullptr) != TETRI_OK);
+            CHECK(p.fetch_wgs == 0);                 // (and its rows are not known)
+            int32_t wider[4 * 64];
+            std::copy(layout.begin(), layout.end(), wider);
+            wider[4 * (first + n - 1) + 3] = 0;      // no segments: refused too
+            CHECK(tetri_batch_launch(b, wider, first, n, q.data(), k.data(), v.data(), g_any, out.data(), 0.1f, 1, nullptr) != TETRI_OK);
+            CHECK(p.fetch_wgs == 0);
+            std::vector<void *> bad(out);
+            bad[first + n - 1] = nullptr;            // refused, its rows known
+            CHECK(tetri_batch_launch(b, layout.data(), first, n, q.data(), k.data(), v.data(), g_any, bad.data(), 0.1f, 1, nullptr) != TETRI_OK);
+            const int32_t next = first + n - 1;
+            const uint64_t have = (uint64_t)std::min(chunk, rows - next * chunk), row = 2 * (uint64_t)d;
+            if (p.fetch_wgs != 0) {
+                const void *from[3] = {k[next], v[next], q[next]};
+                CHECK(p.attn_wgs + p.fetch_wgs <= 256 * 8 / g_short_wavefronts);
+                CHECK(p.next_bytes[0] == have * row * hkv && p.next_bytes[1] == have * row * hq);
+                for (int i = 0; i < 3; ++i) {
+                    CHECK(p.next[i] == from[i] && 1024 * (uint64_t)p.next_kb[i] < p.next_bytes[i == 2] + 1024);
+                    asked += p.next_kb[i];
+                }
+                CHECK(asked <= (uint64_t)p.fetch_wgs * g_short_wavefronts * kFetchKB && asked > (uint64_t)(p.fetch_wgs - 1) * g_short_wavefronts * kFetchKB);
+            }
+        }
+        tetri_batch_destroy(b);
+        tetri_destroy(h);
+        std::free(staging);
+        return asked;
+    };
+    CHECK(batch(40, 40, 128, 512, {1024}, 0, 1) == 0);
+    CHECK(batch(40, 40, 128, 512, {1024}, 0, 2) == 0);                                // 496 places taken
+    CHECK(batch(40, 40, 128, 512, {512, 512, 512}, 1, 2) == 0);
+    CHECK(batch(40, 40, 128, 512, {1536}, 1, 2) == 32 * 4 * kFetchKB);                // 480
+    CHECK(batch(40, 40, 128, 512, {200, 312, 139}, 0, 2) != 0);                       // 139 rows: 4.27 MB, not a multiple of 1 KB per head
+    CHECK(batch(40, 40, 128, 512, {200, 312, 136}, 0, 2) == 0);                       // 4.18 MB: below 4 MiB
+    CHECK(batch(32, 8, 128, 512, {100, 412, 511}, 0, 2) != 0);
+    CHECK(batch(8, 2, 128, 512, {1024}, 0, 2) == 0);
+    CHECK(batch(40, 40, 64, 512, {1024}, 0, 2) == 0);
+    CHECK(batch(40, 40, 128, 1024, {2048}, 0, 2) != 0);
+    CHECK(batch(40, 40, 128, 512, {200, 312, 300, 500, 77}, 1, 2) != 0);
+}
+
 // Teams are as small as leaves all workgroups on the chip at once and no smaller: 32 row blocks of 1 to 32 steps and 40 heads, 512 places
 // for workgroups of four wavefronts, take 480 with up to 16 steps to a wavefront (15 would take 530).
 void short_teams()
@@ -499,6 +580,7 @@ int main(int argc, char **argv)
     else if (name == "uploads_name_no_stream_later") uploads_name_no_stream_later();
     else if (name == "choice_of_kernel") choice_of_kernel();
     else if (name == "short_output_stores") short_output_stores();
+    else if (name == "next_chunk_rows") next_chunk_rows();
     else if (name == "short_teams") short_teams();
     else if (name == "decode_division") decode_division();
     else return 2;
