@@ -74,6 +74,18 @@ __device__ __forceinline__ void load_four_partials(const char *const (&po)[4], c
                  : "v"(po[0]), "v"(po[1]), "v"(po[2]), "v"(po[3]), "v"(ps[0]), "v"(ps[1]), "v"(ps[2]), "v"(ps[3]) : "memory");
 }
 
+// O times x where it is, one instruction a register.  The compiler does not see what wait states this needs: those of a transcendental
+// result in x and of a matrix product that has just written O stand in front of it, one for the product behind it.
+template <int N> __device__ __forceinline__ void scale_in_place(f32x16 (&o)[N], float x)
+{
+    asm volatile("s_nop 15\n\ts_nop 7" : "+v"(x));
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) asm volatile("v_mul_f32 %0, %1, %0" : "+v"(o[i][v]) : "v"(x));
+    asm volatile("s_nop 1");
+}
+
 // 16 codes per lane and instruction: how the 32 rows of a step of cached keys lie in a region, K codes then V codes (rows of D
 // bytes, 16-byte chunks XOR-ed by the row).
 template <int D> struct CodeTile {
@@ -415,25 +427,13 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? (F8 ? 3 : 4) : 2) void attn_shor
     const float c_new = p->neg ? -p->c : p->c;
     float m = -1e30f, lsum = 0.f;                        // reference exponent of the row (not its exact maximum), this lane's row sum
     bool first = true;
-    [[maybe_unused]] bool o_scaled = code_steps == 0;    // FP8: O is in units of code values until the first new keys
 
-    for (; left > 0; --left, st += T) {
-        const bool more = left > 1, ctx = st < ctx_steps, codes = F8 && ctx;
-        float c = c_new;
-        if constexpr (F8) {
-            // the K scale rides on the score factor of cached keys, the V scale is applied to O once, before the first
-            // new keys add to it (or behind the loop)
-            if (ctx) {
-                c = c_new * p->k_scale;
-            } else if (!o_scaled) {
-                const float vs = p->v_scale;
-#pragma unroll
-                for (int i = 0; i < DBLK; ++i)
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) o[i][v] *= vs;
-                o_scaled = true;
-            }
-        }
+    // (Steps of codes and of rows are two loops.  In one loop the ways through it that multiply O and those that do not met in registers of their own: O
+    // was copied twice a step of codes, 64 instructions, and 254 registers were in use, now 199.  Ragged prompts of 32/8 heads over codes 636 us, now 599.)
+    auto step = [&](auto codes_) __attribute__((always_inline)) {
+        constexpr bool codes = decltype(codes_)::value;
+        const bool more = left > 1, ctx = codes || st < ctx_steps;
+        const float c = codes ? c_new * p->k_scale : c_new;
         // K has landed when only what was issued after it is outstanding: the other region's load (behind a step of codes, if there
         // is one; the V rows of a 16-bit step) and the second half of a step of codes
         if (codes) {
@@ -482,7 +482,23 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? (F8 ? 3 : 4) : 2) void attn_shor
                 pf[v / 8][v % 8 + 1] = (__bf16)__builtin_amdgcn_exp2f(__builtin_fmaf(sc[v + 1], c, -m));
             }
         };
-        if (first) {
+        if constexpr (F8) {
+            // (one branch that writes to O, in place: the first step's multiplies nothing by nothing)
+            bool raise = first;
+            if (!first) {
+                weights();
+                raise = weights_reach_two(pf);
+            }
+            first = false;
+            if (raise) {
+                const float m_new = fmaxf(m, step_max(sc, c));
+                const float alpha = __builtin_amdgcn_exp2f(m - m_new);
+                m = m_new;
+                lsum *= alpha;
+                scale_in_place(o, alpha);
+                weights();
+            }
+        } else if (first) {
             m = fmaxf(m, step_max(sc, c));
             first = false;
             weights();
@@ -544,16 +560,15 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? (F8 ? 3 : 4) : 2) void attn_shor
 #pragma unroll
             for (int db = 0; db < DBLK; ++db)
                 o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[jj * DBLK + db], pf[jj], o[db], 0, 0, 0);
-    }
+    };
     if constexpr (F8) {
-        if (!o_scaled) {
-            const float vs = p->v_scale;
-#pragma unroll
-            for (int i = 0; i < DBLK; ++i)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) o[i][v] *= vs;
+        // the K scale rides on the score factor of cached keys, the V scale is applied to O once, before the first new keys add to it
+        if (code_steps > 0) {
+            for (int i = 0; i < code_steps; ++i, --left, st += T) step(std::true_type());
+            scale_in_place(o, p->v_scale);
         }
     }
+    for (; left > 0; --left, st += T) step(std::false_type());
     // ---- fused append: the wavefront of the last step has rows t0 .. t0 + 31 of K and V in its regions.  (The rows of a matrix are read
     // together: row by row, each behind the condition of its store, its LDS round trips held the whole team up before the merge: 286
     // short prompts of 40 heads 987.1 us, this way 977.9; ragged prompts over codes 648.9, this way 642.3.)
