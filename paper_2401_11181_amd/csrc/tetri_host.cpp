@@ -532,11 +532,13 @@ static bool plan_short(const tetri_ctx *h, const int32_t *cu, const int32_t *ctx
     //  - fewer: three or more workgroups to a row block, up to 128 steps too (0.5 to 0.99 (1.07) at 31); two, up to 20 (15) steps
     //    (0.93 to 0.98 (0.96 to 1.02) at 16, 1.05 (1.1) at 24, 1.2 (1.3) at 63); one, which leaves compute units without work, up to 16
     //    (12) (0.8 to 0.9 at 9, 1.0 (1.1 to 1.2) at 16, 1.15 (1.3) at 24, 1.4 to 1.9 at 95);
-    //  - exactly two workgroups per compute unit: up to 65000 (20000) steps of 32 keys x 32 rows in all; between one and two, which leaves
-    //    some compute units half empty, also up to 27 (14) steps on a wavefront times the part of the two (256 rows of 40 heads:
-    //    1.05 (1.18) at 14 steps, 1.14 (1.3) at 22, 1.26 (1.4) at 32; 512 rows of 24/8 heads: 0.98 (1.07) at 16, 1.03 (1.14) at 24);
-    //  - more: what a launch takes is the chain of steps of its longest row blocks, which the total does not show: up to 30000 (15000)
-    //    steps in all with 22 (11) on a wavefront, at two to a row block, and 22 as laid out (1.08 at 24, 1.07 to 1.16 at 29).  Where the work is even over the row blocks of several segments,
+    //  - exactly two workgroups per compute unit: up to 65000 (20000) steps of 32 keys x 32 rows in all (over codes the line is from when a step
+    //    of codes took longer: 512 rows of 32/8 heads now 0.78 at 20700, 0.84 at 28400, 0.94 at 52500); between one and two, which leaves
+    //    some compute units half empty, also up to 27 (17) steps on a wavefront times the part of the two (256 rows of 40 heads:
+    //    1.05 (0.87) at 10 and 14 steps, 1.14 at 22, 1.26 at 32; 512 rows of 24/8 heads: 0.98 at 16, 1.03 at 24; 384 of 40 (0.78) at 11 and 14);
+    //  - more: what a launch takes is the chain of steps of its longest row blocks, which the total does not show: up to 30000
+    //    steps in all with 22 on a wavefront, at two to a row block, and 22 as laid out (1.08 at 24, 1.07 to 1.16 at 29; one segment over codes 0.66 to 0.98
+    //    below these lines, 0.84 to 0.97 right behind them); over codes, several segments, 15000 and 11.  Where the work is even over the row blocks of several segments,
     //    the shared-tile kernel's tiles are ragged and teams keep the chains short: up to 30000 whatever the chain, over codes 20000
     //    unless every query head has K and V of its own (40 heads, 300 rows at 1000 and 212 at 200 cached tokens: 0.75 (0.75); 200 at 2000
     //    and 312 at 600: 0.87 (0.94); 32/8 heads, the same: 1.0 (1.1), 345 at 1353 and 167 at 0: 0.85 (0.95)).
@@ -546,9 +548,9 @@ static bool plan_short(const tetri_ctx *h, const int32_t *cu, const int32_t *ctx
     const bool even = num_segs > 1 && (int64_t)most * n <= 2 * steps;
     if (h->cfg.head_dim == 64) shape.preferred = true;
     else if (wgs <= cus) shape.preferred = chain <= (wgs == cus || p.splits > 2 ? 128 : (p.splits == 2 ? 2 * (fp8 ? 15 : 20) : (fp8 ? 12 : 16)));
-    else if (wgs <= 2 * cus) shape.preferred = total <= (fp8 ? 20000 : 65000);        // (the steps on a wavefront: below)
+    else if (wgs <= 2 * cus) shape.preferred = total <= (fp8 && wgs == 2 * cus ? 20000 : 65000);        // (the steps on a wavefront: below)
     else if (even) shape.preferred = total <= (fp8 && Hq != Hkv ? 20000 : 30000);
-    else shape.preferred = total <= (fp8 ? 15000 : 30000) && chain <= (fp8 ? 11 : 22);
+    else shape.preferred = total <= (fp8 && num_segs > 1 ? 15000 : 30000) && chain <= (fp8 && num_segs > 1 ? 11 : 22);
     if (!shape.preferred && h->attn_variant != 3) return true;      // (not to be laid out)
     std::sort(units, units + n, [](const Unit &a, const Unit &b) { return a.steps > b.steps; });
     for (int i = 0; i < n; ++i) {
@@ -621,7 +623,7 @@ static bool plan_short(const tetri_ctx *h, const int32_t *cu, const int32_t *ctx
     }
     p.attn_wgs = lay_out(nwl, cap);
     shape.nwl = nwl;
-    if (h->cfg.head_dim != 64 && wgs > cus && wgs < 2 * cus) shape.preferred = shape.preferred && 2 * cus * longest <= (fp8 ? 14 : 27) * wgs;
+    if (h->cfg.head_dim != 64 && wgs > cus && wgs < 2 * cus) shape.preferred = shape.preferred && 2 * cus * longest <= (fp8 ? 17 : 27) * wgs;
     else if (h->cfg.head_dim != 64 && wgs > 2 * cus && !even && !fp8) shape.preferred = shape.preferred && longest <= 22;
     return (uint64_t)(wgs * p.splits + p.zero_wgs + 8) * (uint64_t)std::max<int64_t>(Hq, p.splits) < 0x100000000ull;   // (the divisions by multiplication)
 }

@@ -56,7 +56,24 @@ CHOICES = [
 ]
 
 
+# Over codes: one segment with more than two row blocks to a compute unit (30000 steps in all, 22 on a wavefront); between one and two (17 steps
+# times the part of the two)
+CODES = [
+    (40, 40, 1, [(512, 896)], "short"), (40, 40, 1, [(512, 897)], "self"), (32, 8, 1, [(1024, 384)], "short"), (32, 8, 1, [(1024, 385)], "eight"),
+    (40, 40, 1, [(1024, 192)], "short"), (40, 40, 1, [(1024, 193)], "four"), (40, 40, 1, [(412, 0), (100, 1500)], "four"),
+    (40, 40, 1, [(256, 1024)], "short"), (40, 40, 1, [(384, 1200)], "short"), (40, 40, 1, [(384, 1700)], "four"), (32, 8, 1, [(480, 1300)], "short"),
+]
+
+
+def test_choice_over_codes(driver):
+    check(driver, CODES)
+
+
 def test_choice(driver):
+    check(driver, CHOICES)
+
+
+def check(driver, CHOICES):
     for heads in sorted({c[:2] for c in CHOICES}):
         cases = [c for c in CHOICES if c[:2] == heads]
         text = "".join("%d %d %s\n" % (c[2], len(c[3]), " ".join("%d %d" % s for s in c[3])) for c in cases)
