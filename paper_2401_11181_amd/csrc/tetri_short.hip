@@ -21,8 +21,8 @@
 //     page slots from there (fused append), so there are no workgroups for that.
 // What bounds it in turn: the chain of steps of the wavefront with the most of them, 1.0 to 1.3 us a step, because a wavefront
 // has one step of loads in flight (codes two) and the keys of a step serve 32 rows instead of 256.  Long chains go to the shared-tile
-// kernel: the host chooses.  The 71 packed chunks of 286 short prompts take 13.7 us each, by clock values stored at points of the kernel
-// (which cost 2 %): 2.4 us from the last wavefront's end to the next launch's first instruction, then for the wavefront that
+// kernel: the host chooses.  The 71 packed chunks of 286 short prompts take 12.6 us each.  At 13.7, by clock values stored at points of the kernel
+// (which cost 2 %), they were 2.4 us from the last wavefront's end to the next launch's first instruction, then for the wavefront that
 // ends last 0.8 to its row block, 0.4 to its page ids, 4.2 to Q and the first K (up to 16 MB that no launch before has touched, all
 // asked for at once; 2.3 in the median wavefront), 2.9 the steps, 1.9 the append and the team's barrier, 1.3 merge and output.
 // Arithmetic is that of the shared-tile kernel: bf16 operands, fp32 accumulation, weights rounded to bf16 before the PV
