@@ -185,11 +185,11 @@ template <int N> __device__ __forceinline__ void dma16_stream(const void *sbase,
 // served by the memory side, not by an XCD's L2), for data handed from one workgroup to another
 // inside a launch.  No cache write-back or invalidation is needed around them, only order:
 // coherent_stores_done() returns when this wavefront's stores have been performed.
-// (A store of 16 bytes reads its registers one wait state after it is issued; the compiler keeps the next instruction from writing to them for
-// its own stores, not for those in inline assembly: hence the s_nop.)
+// (A store of more than 8 bytes still reads its registers two wait states after it is issued on gfx950.  The compiler keeps the next
+// instructions from writing to them for its own stores, not for those in inline assembly: hence the s_nop 1, the same that it puts behind its own.)
 __device__ __forceinline__ void store_coherent(f32x4 *p, f32x4 v)
 {
-    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 0" ::"v"(p), "v"(v) : "memory");
+    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(p), "v"(v) : "memory");
 }
 __device__ __forceinline__ void store_coherent(float *p, float v)
 {
@@ -197,11 +197,17 @@ __device__ __forceinline__ void store_coherent(float *p, float v)
 }
 __device__ __forceinline__ void store_coherent(global_u32x4_w *p, u32x4 v)
 {
-    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 0" ::"v"(p), "v"(v) : "memory");
+    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(p), "v"(v) : "memory");
 }
 __device__ __forceinline__ void store_coherent(global_u32x2_w *p, u32x2 v)
 {
     asm volatile("global_store_dwordx2 %0, %1, off sc1" ::"v"(p), "v"(v) : "memory");
+}
+// A store past the caches (cache policy nt) where an ordinary one of the same value stands beside it: of two stores that differ in a
+// hint the compiler makes one without.
+__device__ __forceinline__ void store_past_caches(global_u32x4_w *p, u32x4 v)
+{
+    asm volatile("global_store_dwordx4 %0, %1, off nt\n\ts_nop 1" ::"v"(p), "v"(v) : "memory");
 }
 __device__ __forceinline__ void coherent_stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 // A coherent read of one word that is not needed yet: every lane's copy of it goes to 256 bytes

@@ -637,8 +637,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? (F8 ? 3 : 4) : 2) void attn_shor
             uint16_t *orow = reinterpret_cast<uint16_t *>(p_out) + ((size_t)(row0 + t) * Hq + head) * D;
             global_u32x4_w *at = reinterpret_cast<global_u32x4_w *>((uintptr_t)(orow + (vec + half) * 8));
             const u32x4 row = {y.x, y.y, z.x, z.y};
-            // (written out: of two stores that differ in a hint the compiler makes one without)
-            if (out_past_l2 != 0) asm volatile("global_store_dwordx4 %0, %1, off nt\n\ts_nop 0" :: "v"(at), "v"(row) : "memory");
+            if (out_past_l2 != 0) store_past_caches(at, row);
             else *at = row;
         }
     };
