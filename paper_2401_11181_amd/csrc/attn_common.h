@@ -120,6 +120,23 @@ __device__ __forceinline__ void add_weights(const bf16x8 (&pf)[2], float &lsum)
     }
 }
 
+// O times x where it is, one instruction a register (left to the compiler, O is copied on ways that meet).  What wait states this needs the
+// compiler does not see: those of a transcendental result in x and of a matrix product that has just written O stand in front of it, those of a
+// product that reads O behind it.  O is an operand of both waits, so that no product on it can come to stand between them and the
+// multiplications.
+template <int N> __device__ __forceinline__ void scale_in_place(f32x16 (&o)[N], float x)
+{
+    static_assert(N == 2 || N == 4, "blocks of O");
+    if constexpr (N == 4) asm volatile("s_nop 15\n\ts_nop 7" : "+v"(x), "+v"(o[0]), "+v"(o[1]), "+v"(o[2]), "+v"(o[3]));
+    else asm volatile("s_nop 15\n\ts_nop 7" : "+v"(x), "+v"(o[0]), "+v"(o[1]));
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) asm volatile("v_mul_f32 %0, %1, %0" : "+v"(o[i][v]) : "v"(x));
+    if constexpr (N == 4) asm volatile("s_nop 1" : "+v"(o[0]), "+v"(o[1]), "+v"(o[2]), "+v"(o[3]));
+    else asm volatile("s_nop 1" : "+v"(o[0]), "+v"(o[1]));
+}
+
 // Direct global -> LDS load of 16 bytes per lane, issued from inline assembly: lane l's 16 bytes
 // land at LDS byte address lds_base + 16*l (lds_base is wave-uniform and goes to M0).  The
 // compiler does not see this as a memory access, so it inserts no waits for it: the caller

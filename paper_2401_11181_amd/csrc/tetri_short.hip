@@ -74,18 +74,6 @@ __device__ __forceinline__ void load_four_partials(const char *const (&po)[4], c
                  : "v"(po[0]), "v"(po[1]), "v"(po[2]), "v"(po[3]), "v"(ps[0]), "v"(ps[1]), "v"(ps[2]), "v"(ps[3]) : "memory");
 }
 
-// O times x where it is, one instruction a register.  The compiler does not see what wait states this needs: those of a transcendental
-// result in x and of a matrix product that has just written O stand in front of it, one for the product behind it.
-template <int N> __device__ __forceinline__ void scale_in_place(f32x16 (&o)[N], float x)
-{
-    asm volatile("s_nop 15\n\ts_nop 7" : "+v"(x));
-#pragma unroll
-    for (int i = 0; i < N; ++i)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) asm volatile("v_mul_f32 %0, %1, %0" : "+v"(o[i][v]) : "v"(x));
-    asm volatile("s_nop 1");
-}
-
 // 16 codes per lane and instruction: how the 32 rows of a step of cached keys lie in a region, K codes then V codes (rows of D
 // bytes, 16-byte chunks XOR-ed by the row).
 template <int D> struct CodeTile {

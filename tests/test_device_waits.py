@@ -76,3 +76,67 @@ def test_no_store_is_written_out_elsewhere():
         if name.endswith((".hip", ".h")) and name != "attn_common.h":
             with open(os.path.join(build.CSRC, name)) as f:
                 assert not re.search(r'"[^"]*\b(global|flat|buffer)_store', f.read()), name
+
+
+# O between two matrix products, multiplied by a transcendental result: with nothing else in the way that keeps them apart.
+SCALE = """
+extern "C" __global__ void probe(float *out, const bf16x8 *a, const bf16x8 *b, float x)
+{
+    f32x16 o[%(blocks)d];
+    bf16x8 va[%(blocks)d];
+    const bf16x8 vb = b[threadIdx.x];
+    const float y = __builtin_amdgcn_exp2f(x + threadIdx.x);
+    for (int i = 0; i < %(blocks)d; ++i) {
+        for (int v = 0; v < 16; ++v) o[i][v] = 0.f;
+        va[i] = a[i * 64 + threadIdx.x];
+        o[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[i], vb, o[i], 0, 0, 0);
+    }
+    %(scale)s;
+    for (int i = 0; i < %(blocks)d; ++i) o[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vb, va[i], o[i], 0, 0, 0);
+    for (int i = 0; i < %(blocks)d; ++i)
+        for (int v = 0; v < 16; ++v) out[(i * 16 + v) * 64 + threadIdx.x] = o[i][v];
+}
+"""
+
+
+def waits_around_scaling(code):
+    """The fewest wait states from a product to a multiplication of its result, from a multiplication to a product that adds to its
+    result, and from the exponential to a multiplication by it."""
+    states, product, scaled, exponential = 0, {}, {}, {}
+    least = {}
+
+    def note(what, since, reg):
+        if reg in since:
+            least[what] = min(least.get(what, 1 << 30), states - since[reg] - 1)
+
+    for op, text in code:
+        operands = text.split(",")
+        states += int(text) + 1 if op == "s_nop" else 1
+        if op.startswith("v_mfma"):
+            for reg in registers(operands[3]):
+                note("multiplied, product", scaled, reg)
+            for reg in registers(operands[0]):
+                product[reg] = states
+                scaled.pop(reg, None)
+        elif op.startswith("v_mul_f32"):
+            to, = registers(operands[0])
+            for source in operands[1:]:
+                for reg in registers(source):
+                    note("product, multiplied", product, reg)
+                    note("exponential, multiplied", exponential, reg)
+            scaled[to] = states
+            product.pop(to, None)
+        elif op.startswith("v_exp_f32"):
+            exponential[next(iter(registers(operands[0])))] = states
+    return least
+
+
+@pytest.mark.parametrize("blocks", [2, 4])
+def test_scaling_in_place_waits_as_long_as_the_compiler_does(tmp_path, blocks):
+    own = "for (int i = 0; i < %d; ++i) for (int v = 0; v < 16; ++v) o[i][v] *= y" % blocks
+    want, got = (waits_around_scaling(instructions(tmp_path, SCALE % {"blocks": blocks, "scale": scale}, "probe"))
+                 for scale in (own, "scale_in_place(o, y)"))
+    assert set(want) == set(got) == {"product, multiplied", "multiplied, product", "exponential, multiplied"}
+    assert want["product, multiplied"] > 0               # (the hazard is there)
+    assert got["product, multiplied"] >= want["product, multiplied"] and got["multiplied, product"] >= want["multiplied, product"], (want, got)
+    assert got["exponential, multiplied"] >= 1           # (one wait state; the compiler's own code has the products in between)
