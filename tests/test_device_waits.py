@@ -2,6 +2,7 @@
 itself is kept apart there by hand.  Small kernels are compiled for gfx950 and their instructions read; no GPU is used."""
 import os
 import re
+import shutil
 import subprocess
 
 import pytest
@@ -140,3 +141,34 @@ def test_scaling_in_place_waits_as_long_as_the_compiler_does(tmp_path, blocks):
     assert want["product, multiplied"] > 0               # (the hazard is there)
     assert got["product, multiplied"] >= want["product, multiplied"] and got["multiplied, product"] >= want["multiplied, product"], (want, got)
     assert got["exponential, multiplied"] >= 1           # (one wait state; the compiler's own code has the products in between)
+
+
+def test_built_kernels_keep_them_apart(tmp_path):
+    """The same in the library as built, all kernels (the shared-tile kernels multiply O in place in a block of its own, by instructions of
+    their own): 11 wait states from a product to a multiplication of its result, one from there to a product that adds to it, two from
+    a store of more than 8 bytes to a write to its data; the compiler's own are the same."""
+    if not os.path.exists(build.LIB):
+        build.build()
+    lib = tmp_path / "lib.so"
+    shutil.copyfile(build.LIB, lib)
+    objdump = os.path.join(os.path.dirname(os.path.realpath(build.hipcc())), "..", "lib", "llvm", "bin", "llvm-objdump")
+    subprocess.run([objdump, "--offloading", str(lib)], check=True, capture_output=True)
+    kernels = multiplied = 0
+    for part in sorted(tmp_path.glob("lib.so.*gfx950")):
+        text = subprocess.run([objdump, "-d", "--mcpu=gfx950", str(part)], check=True, capture_output=True, text=True).stdout
+        for body in re.split(r"^[0-9a-f]+ <", text, flags=re.M)[1:]:
+            name, lines = body.split(">:", 1)
+            code = [l.split("//")[0].split(None, 1) for l in lines.split("\n") if l.startswith("\t")]
+            code = [(x[0], x[1].strip() if len(x) > 1 else "") for x in code]
+            least = waits_around_scaling(code)
+            kernels += 1
+            multiplied += "product, multiplied" in least
+            assert least.get("product, multiplied", 11) >= 11 and least.get("multiplied, product", 1) >= 1, (name, least)
+            for i, (op, operands) in enumerate(code):
+                if re.match(r"(global|flat|buffer)_store_dwordx[34]", op):
+                    data, waits = registers(operands.split(",")[1 if op[0] != "b" else 0]), 0
+                    for other, text_ in code[i + 1:i + 3]:
+                        if waits < 2 and other.startswith("v_"):
+                            assert not registers(text_.split(",")[0]) & data, (name, op, operands, other, text_)
+                        waits += int(text_, 0) + 1 if other == "s_nop" else 1
+    assert kernels > 20 and multiplied > 10
