@@ -1279,21 +1279,23 @@ static tetri_status batch_launch(const char *fn, tetri_batch *b, const int32_t *
     if (!layout || !q || !k_new || !v_new || !out || first_chunk < 0 || n < 0)
         return fail(h, TETRI_ERR_INVALID_ARG, "%s: null argument or negative count", fn);
     const int32_t *host = b->host + (size_t)b->slot * b->len;
-    for (int32_t c = first_chunk; c < first_chunk + n; ++c) {
+    // chunk c of the layout: does it fit the batch, and is its metadata a chunk of the handle?
+    auto check = [&](int32_t c) -> tetri_status {
         const int32_t o_cu = layout[4 * c], o_ctx = layout[4 * c + 1], o_bt = layout[4 * c + 2], S = layout[4 * c + 3];
         if (S < 1 || S > h->cfg.max_segs_per_chunk || o_cu < 0 || o_ctx < o_cu + S + 1 || o_bt < o_ctx + S ||
             o_bt + (int64_t)S * h->cfg.max_blocks_per_seq > b->len)
             return fail(h, TETRI_ERR_INVALID_ARG, "%s: the layout of chunk %d does not fit the batch", fn, c);
-        tetri_status st = check_host_chunk(h, fn, host + o_cu, host + o_ctx, S);
+        return check_host_chunk(h, fn, host + o_cu, host + o_ctx, S);
+    };
+    for (int32_t c = first_chunk; c < first_chunk + n; ++c) {
+        const int32_t o_cu = layout[4 * c], o_ctx = layout[4 * c + 1], o_bt = layout[4 * c + 2], S = layout[4 * c + 3];
+        tetri_status st = check(c);
         if (st != TETRI_OK) return st;
-        // the next chunk's rows, where its launch follows this one here
+        // the next chunk's rows, where its launch follows this one here and will not be refused for what it says of them
         NextRows next = {nullptr, nullptr, nullptr, 0};
-        if (c + 1 < first_chunk + n) {
-            const int64_t at = layout[4 * c + 4], segs = layout[4 * c + 7];
-            if (segs >= 1 && at >= 0 && at + segs < b->len && q[c + 1] && k_new[c + 1] && v_new[c + 1] && aligned16(q[c + 1]) &&
-                aligned16(k_new[c + 1]) && aligned16(v_new[c + 1]) && host[at + segs] >= 1 && host[at + segs] <= h->cfg.chunk_size)
-                next = {q[c + 1], k_new[c + 1], v_new[c + 1], host[at + segs]};
-        }
+        if (c + 1 < first_chunk + n && q[c + 1] && k_new[c + 1] && v_new[c + 1] && aligned16(q[c + 1]) && aligned16(k_new[c + 1]) &&
+            aligned16(v_new[c + 1]) && check(c + 1) == TETRI_OK)
+            next = {q[c + 1], k_new[c + 1], v_new[c + 1], host[layout[4 * c + 4] + layout[4 * c + 7]]};
         st = attn_common(fn, h, q[c], k_new[c], v_new[c], kv_pages, mode == 1 ? kv_pages : nullptr, b->dev + o_bt, b->dev + o_cu,
                          b->dev + o_ctx, S, scale, out[c], stream, false, 1.f, 1.f, host + o_cu, host + o_ctx, carry, &next);
         if (st == TETRI_OK && mode == 0)

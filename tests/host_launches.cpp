@@ -484,6 +484,11 @@ void next_chunk_rows()
             wider[4 * (first + n - 1) + 3] = 0;      // no segments: refused too
             CHECK(tetri_batch_launch(b, wider, first, n, q.data(), k.data(), v.data(), g_any, out.data(), 0.1f, 1, nullptr) != TETRI_OK);
             CHECK(p.fetch_wgs == 0);
+            std::copy(layout.begin(), layout.end(), wider);
+            int32_t *const l = wider + 4 * (first + n - 1);
+            l[0] = l[1] - l[3];                      // refused; where its number of rows would be stands that of its cached tokens
+            CHECK(tetri_batch_launch(b, wider, first, n, q.data(), k.data(), v.data(), g_any, out.data(), 0.1f, 1, nullptr) != TETRI_OK);
+            CHECK(p.fetch_wgs == 0);
             std::vector<void *> bad(out);
             bad[first + n - 1] = nullptr;            // refused, its rows known
             CHECK(tetri_batch_launch(b, layout.data(), first, n, q.data(), k.data(), v.data(), g_any, bad.data(), 0.1f, 1, nullptr) != TETRI_OK);
@@ -513,6 +518,7 @@ void next_chunk_rows()
     CHECK(batch(40, 40, 128, 512, {200, 312, 136}, 0, 2) == 0);                       // 4.18 MB: below 4 MiB
     CHECK(batch(32, 8, 128, 512, {100, 412, 511}, 0, 2) != 0);
     CHECK(batch(8, 2, 128, 512, {1024}, 0, 2) == 0);
+    CHECK(batch(32, 8, 128, 512, {100, 611}, 0, 2) == 0);                             // 199 rows at 412 cached tokens
     CHECK(batch(40, 40, 64, 512, {1024}, 0, 2) == 0);
     CHECK(batch(40, 40, 128, 1024, {2048}, 0, 2) != 0);
     CHECK(batch(40, 40, 128, 512, {200, 312, 300, 500, 77}, 1, 2) != 0);
