@@ -888,7 +888,7 @@ static void fetch_ahead(const tetri_ctx *h, const NextRows *next, int wavefronts
     p.fetch_wgs = 0;
     if (!next || next->rows == 0 || h->cfg.head_dim != 128) return;
     const int64_t row = 2 * (int64_t)h->cfg.head_dim, kv = next->rows * row * h->cfg.num_kv_heads, q = next->rows * row * h->cfg.num_q_heads;
-    const int64_t places = (int64_t)std::max(h->num_cus, 1) * 8 / wavefronts - p.attn_wgs;
+    const int64_t places = (int64_t)std::max(h->num_cus, 1) * 8 / wavefronts - p.attn_wgs - (p.carry ? 1 : 0);     // (one copies the metadata)
     const int64_t each = (int64_t)wavefronts * kFetchKB, sizes[3] = {kv, kv, q};
     if (places * each < 4096 || 2 * kv + q < 4 << 20 || 2 * kv + q > INT32_MAX) return;
     const void *from[3] = {next->k_new, next->v_new, next->q};

@@ -114,8 +114,9 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? (F8 ? 3 : 4) : 2) void attn_shor
     const int half = lane >> 5, l32 = lane & 31;
     const int bid = blockIdx.x;
     if (bid >= attn_wgs) {
+        const int extra = bid - attn_wgs - (int)CARRY;
         if constexpr (CARRY) {
-            if (bid == (int)gridDim.x - 1) {             // ---- the metadata, for the launches behind this one
+            if (extra < 0) {                             // ---- the metadata, first: the launches behind this one wait for it
                 const int n = p->meta_vectors;
                 const auto *v = (__attribute__((address_space(4))) const u32x4 *)p->meta;
                 for (int i = tid; i < n; i += NW * 64) reinterpret_cast<global_u32x4_w *>((uintptr_t)p->meta_dev)[i] = v[i];
@@ -123,7 +124,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? (F8 ? 3 : 4) : 2) void attn_shor
             }
         }
         const int fetch_wgs = F8 ? 0 : p->fetch_wgs;
-        if (bid - attn_wgs < fetch_wgs) {
+        if (extra < fetch_wgs) {
             // ---- rows of the next chunk, 1 KB to an instruction, into a place that nobody reads: they are in the cache in front of the memory
             // when its launch asks for them.  What bounds a launch is that all of its first reads are made at once and none after that: 512 rows of
             // 40 heads are 16 MB, 4.2 us, of 13.  (286 short prompts of 40 heads, 71 chunks, 928 us without this; 4 us of sleep before: 893, none 897, 8 us 919.  With
@@ -134,7 +135,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? (F8 ? 3 : 4) : 2) void attn_shor
                                        reinterpret_cast<const char *>(p->next[2])};
             const uint32_t to = lds_address(smem + wave * 1024);
             __builtin_amdgcn_s_sleep(64);                // (2 us: behind the launch's own first reads)
-            for (uint32_t i = (bid - attn_wgs) * NW + wave; i < n; i += fetch_wgs * NW) {
+            for (uint32_t i = extra * NW + wave; i < n; i += fetch_wgs * NW) {
                 const char *from = i < nk ? nx[0] : (i < nv ? nx[1] : nx[2]);
                 const uint32_t at = (i < nk ? i : (i < nv ? i - nk : i - nv)) * 1024 + lane * 16;
                 dma16(from + min(at, (i < nv ? kv_bytes : q_bytes) - 16), to);
@@ -145,7 +146,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? (F8 ? 3 : 4) : 2) void attn_shor
         // ---- padding rows [rows, C) are written as +0, 16 bytes per lane and pass
         const size_t first = (size_t)p->rows * p->Hq * CH, n = (size_t)p->C * p->Hq * CH;
         const size_t stride = (size_t)(gridDim.x - attn_wgs - fetch_wgs - (int)CARRY) * (NW * 64);
-        for (size_t i = first + (size_t)(bid - attn_wgs - fetch_wgs) * (NW * 64) + tid; i < n; i += stride)
+        for (size_t i = first + (size_t)(extra - fetch_wgs) * (NW * 64) + tid; i < n; i += stride)
             reinterpret_cast<global_u32x4_w *>((uintptr_t)p->out)[i] = u32x4{0u, 0u, 0u, 0u};
         return;
     }

@@ -505,6 +505,16 @@ void next_chunk_rows()
                 CHECK(asked <= (uint64_t)p.fetch_wgs * g_short_wavefronts * kFetchKB && asked > (uint64_t)(p.fetch_wgs - 1) * g_short_wavefronts * kFetchKB);
             }
         }
+        // the same with the metadata in the first launch: it leaves a place for the workgroup that copies it (the second chunk's launch refused)
+        if (first == 0 && n > 1) {
+            const int32_t fetched = p.fetch_wgs;
+            CHECK(fetched == 0 || p.carry == nullptr);
+            std::vector<void *> bad(out);
+            bad[1] = nullptr;
+            CHECK(tetri_batch_step(b, lens.data(), prompts, nullptr, prompts, pages.data(), layout.data(), chunks, q.data(), k.data(), v.data(), g_any,
+                                   bad.data(), 0.1f, 1, nullptr) != TETRI_OK);
+            CHECK(p.fetch_wgs <= fetched && (p.fetch_wgs == 0 || (p.carry != nullptr && p.attn_wgs + p.fetch_wgs < 256 * 8 / g_short_wavefronts)));
+        }
         tetri_batch_destroy(b);
         tetri_destroy(h);
         std::free(staging);
