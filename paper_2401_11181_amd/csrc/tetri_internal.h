@@ -171,6 +171,18 @@ struct NextRows {
     int32_t rows;
 };
 constexpr int kFetchKB = 32;
+// What a lane of instruction i of those asks for: 16 bytes of K (0), V (1) or Q (2), lanes past the end of the rows the last ones.
+struct FetchAt {
+    int32_t matrix;
+    uint32_t byte;
+};
+__host__ __device__ inline FetchAt fetch_at(uint32_t i, uint32_t lane, uint32_t k_kb, uint32_t v_kb, uint32_t kv_bytes, uint32_t q_bytes)
+{
+    const int32_t matrix = i < k_kb ? 0 : (i < k_kb + v_kb ? 1 : 2);
+    const uint32_t at = (i - (matrix == 0 ? 0 : (matrix == 1 ? k_kb : k_kb + v_kb))) * 1024 + lane * 16;
+    const uint32_t last = (matrix == 2 ? q_bytes : kv_bytes) - 16;
+    return {matrix, at < last ? at : last};
+}
 
 // The same with the metadata of the whole batch: the launch finds its page ids there and copies it to the device, for the launches
 // behind it.  At most kShortCarry int32.

@@ -130,15 +130,14 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? (F8 ? 3 : 4) : 2) void attn_shor
             // 40 heads are 16 MB, 4.2 us, of 13.  (286 short prompts of 40 heads, 71 chunks, 928 us without this; 4 us of sleep before: 893, none 897, 8 us 919.  With
             // 16 KB to a wavefront 920, 40 905, 64 974: a compute unit takes 25 GB/s of such reads.  Asked for by the wavefronts with row blocks, behind their
             // loop, 945, behind their first step 990.  With Q, K and V in the cache from the start, 748.)
-            const uint32_t nk = p->next_kb[0], nv = nk + p->next_kb[1], n = nv + p->next_kb[2], kv_bytes = p->next_bytes[0], q_bytes = p->next_bytes[1];
+            const uint32_t k_kb = p->next_kb[0], v_kb = p->next_kb[1], n = k_kb + v_kb + p->next_kb[2], kv_bytes = p->next_bytes[0], q_bytes = p->next_bytes[1];
             const char *const nx[3] = {reinterpret_cast<const char *>(p->next[0]), reinterpret_cast<const char *>(p->next[1]),
                                        reinterpret_cast<const char *>(p->next[2])};
             const uint32_t to = lds_address(smem + wave * 1024);
             __builtin_amdgcn_s_sleep(64);                // (2 us: behind the launch's own first reads)
             for (uint32_t i = extra * NW + wave; i < n; i += fetch_wgs * NW) {
-                const char *from = i < nk ? nx[0] : (i < nv ? nx[1] : nx[2]);
-                const uint32_t at = (i < nk ? i : (i < nv ? i - nk : i - nv)) * 1024 + lane * 16;
-                dma16(from + min(at, (i < nv ? kv_bytes : q_bytes) - 16), to);
+                const FetchAt f = fetch_at(i, lane, k_kb, v_kb, kv_bytes, q_bytes);
+                dma16((f.matrix == 0 ? nx[0] : (f.matrix == 1 ? nx[1] : nx[2])) + f.byte, to);
             }
             wait_vm<0>();                                // (nothing may be on its way to LDS when a wavefront ends)
             return;

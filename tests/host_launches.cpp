@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -45,6 +46,7 @@ std::string g_kernel;                         // the attention kernel launched l
 const char *g_partials = nullptr;             // where the last attention or decode launch keeps partial results
 ShortParams g_short;                          // the last launch of the short kernel
 int g_short_wavefronts = 0;
+std::vector<int64_t> g_carried;               // of each: int32 of metadata that it takes along
 int g_out_past_l2 = -1;                       // how the last launch of the short kernel stores its output
 int g_longest = 0, g_short_wgs = 0;           // the steps of its longest wavefront, and its workgroups (of the attention)
 int g_places = 0;                             // of the last division made by the host: tiles' pieces there
@@ -133,6 +135,7 @@ hipError_t tetri_launch_short(int, bool, const ShortParams &p, int wavefronts, h
     g_kernel = "short";
     g_short = p;
     g_short_wavefronts = wavefronts;
+    g_carried.push_back(p.carry ? p.carry->len : 0);
     g_out_past_l2 = p.out_past_l2;
     g_longest = 0;
     g_short_wgs = p.attn_wgs;
@@ -503,6 +506,18 @@ void next_chunk_rows()
                     asked += p.next_kb[i];
                 }
                 CHECK(asked <= (uint64_t)p.fetch_wgs * g_short_wavefronts * kFetchKB && asked > (uint64_t)(p.fetch_wgs - 1) * g_short_wavefronts * kFetchKB);
+                // what the kernel's lanes make of that: every 16 bytes of that much of a matrix, none outside its rows
+                for (int m = 0; m < 3; ++m) {
+                    std::vector<char> seen(p.next_bytes[m == 2] / 16, 0);
+                    for (uint32_t i = 0; i < (uint32_t)asked; ++i)
+                        for (uint32_t lane = 0; lane < 64; ++lane) {
+                            const FetchAt f = fetch_at(i, lane, p.next_kb[0], p.next_kb[1], p.next_bytes[0], p.next_bytes[1]);
+                            CHECK(f.byte % 16 == 0 && f.byte + 16 <= p.next_bytes[f.matrix == 2]);
+                            if (f.matrix == m) seen[f.byte / 16] = 1;
+                        }
+                    const size_t want = std::min<size_t>(seen.size(), (size_t)p.next_kb[m] * 64);
+                    CHECK(std::count(seen.begin(), seen.begin() + want, 1) == (ptrdiff_t)want);
+                }
             }
         }
         // the same with the metadata in the first launch: it leaves a place for the workgroup that copies it (the second chunk's launch refused)
@@ -513,7 +528,7 @@ void next_chunk_rows()
             bad[1] = nullptr;
             CHECK(tetri_batch_step(b, lens.data(), prompts, nullptr, prompts, pages.data(), layout.data(), chunks, q.data(), k.data(), v.data(), g_any,
                                    bad.data(), 0.1f, 1, nullptr) != TETRI_OK);
-            CHECK(p.fetch_wgs <= fetched && (p.fetch_wgs == 0 || (p.carry != nullptr && p.attn_wgs + p.fetch_wgs < 256 * 8 / g_short_wavefronts)));
+            CHECK(p.fetch_wgs <= fetched && (p.fetch_wgs == 0 || p.attn_wgs + p.fetch_wgs + (p.carry != nullptr) <= 256 * 8 / g_short_wavefronts));
         }
         tetri_batch_destroy(b);
         tetri_destroy(h);
@@ -531,7 +546,60 @@ void next_chunk_rows()
     CHECK(batch(32, 8, 128, 512, {100, 611}, 0, 2) == 0);                             // 199 rows at 412 cached tokens
     CHECK(batch(40, 40, 64, 512, {1024}, 0, 2) == 0);
     CHECK(batch(40, 40, 128, 1024, {2048}, 0, 2) != 0);
+    // (those that tests/test_gpu_batch_step.py runs)
+    CHECK(batch(36, 9, 128, 512, {150, 362, 301, 211, 333}, 0, 2) != 0 && batch(36, 9, 128, 512, {150, 362, 301, 211, 333}, 1, 2) != 0);
+    CHECK(batch(40, 40, 128, 512, {60, 60, 60, 60, 60, 60, 60, 60, 32, 200, 200, 200, 200, 200}, 0, 2) != 0);
+    CHECK(batch(40, 40, 128, 160, {480}, 0, 2) != 0 && g_short_wavefronts == 8);
     CHECK(batch(40, 40, 128, 512, {200, 312, 300, 500, 77}, 1, 2) != 0);
+}
+
+// Where a step's metadata travels: with the first launch up to kShortCarry int32 if that is one of the short kernel; else in one upload in front
+// of it; once, whatever the launch comes to.
+void carried_metadata()
+{
+    auto step = [&](int max_blocks, int variant, float scale, int32_t chunks_expected, int64_t expected_len, bool refused_later = false) {
+        const tetri_config c = {8, 2, 128, 16, 128, 8192, max_blocks, 40, TETRI_BF16};
+        tetri_ctx *h = nullptr;
+        CHECK(tetri_create(&c, &h) == TETRI_OK && tetri_set_option(h, "attn_variant", variant) == TETRI_OK);
+        const int32_t lens[1] = {chunks_expected * 128};
+        const int64_t len = 1 << 12;
+        int32_t *staging = static_cast<int32_t *>(std::aligned_alloc(16, tetri_batch_slots() * len * 4));
+        std::vector<int32_t> pages(max_blocks), layout(4 * chunks_expected + 4);
+        alignas(16) static int32_t dev[4];
+        tetri_batch *b = nullptr;
+        CHECK(tetri_batch_create(h, len, staging, dev, &b) == TETRI_OK);
+        std::vector<const void *> in(chunks_expected, g_any);
+        std::vector<void *> out(chunks_expected, g_any);
+        if (refused_later) out.back() = nullptr;
+        g_uploads.clear();
+        g_carried.clear();
+        const tetri_status st = tetri_batch_step(b, lens, 1, nullptr, 1, pages.data(), layout.data(), chunks_expected, in.data(), in.data(), in.data(), g_any,
+                                                 out.data(), scale, 1, nullptr);
+        CHECK((st == TETRI_OK) == (std::isfinite(scale) && !refused_later));
+        int64_t carried = 0;
+        for (size_t i = 0; i < g_carried.size(); ++i) {
+            CHECK(i == 0 || g_carried[i] == 0);          // (the first launch, no other)
+            carried += g_carried[i];
+        }
+        if (carried != 0) CHECK(carried == expected_len && g_short.bt >= dev);
+        CHECK(g_uploads.size() == (carried == 0));
+        const bool inside = !g_uploads.empty() && g_uploads[0].pinned == nullptr;
+        if (!g_uploads.empty() && !inside) event(g_uploads[0].done).pending = false;
+        tetri_batch_destroy(b);
+        tetri_destroy(h);
+        std::free(staging);
+        return carried != 0 ? "carried" : (inside ? "inline" : "staged");
+    };
+    // 4 chunks of a segment: 8 int32 and a table of 160 to 224 (a multiple of 4) each
+    CHECK(step(160, 3, 0.1f, 4, 672) == std::string("carried"));
+    CHECK(step(164, 3, 0.1f, 4, 688) == std::string("inline"));
+    CHECK(step(216, 3, 0.1f, 4, 896) == std::string("inline"));
+    CHECK(step(220, 3, 0.1f, 4, 912) == std::string("staged"));
+    CHECK(step(32, 3, 0.1f, 1, 40) == std::string("carried") && step(664, 3, 0.1f, 1, 672) == std::string("carried"));
+    CHECK(step(668, 3, 0.1f, 1, 676) == std::string("inline"));
+    CHECK(step(160, 2, 0.1f, 4, 672) == std::string("inline"));                      // no launch of the short kernel
+    CHECK(step(160, 3, NAN, 4, 672) == std::string("inline"));                       // refused before the first launch
+    CHECK(step(160, 3, 0.1f, 4, 672, true) == std::string("carried"));               // ... and behind it
 }
 
 // Teams are as small as leaves all workgroups on the chip at once and no smaller: 32 row blocks of 1 to 32 steps and 40 heads, 512 places
@@ -597,6 +665,7 @@ int main(int argc, char **argv)
     else if (name == "choice_of_kernel") choice_of_kernel();
     else if (name == "short_output_stores") short_output_stores();
     else if (name == "next_chunk_rows") next_chunk_rows();
+    else if (name == "carried_metadata") carried_metadata();
     else if (name == "short_teams") short_teams();
     else if (name == "decode_division") decode_division();
     else return 2;

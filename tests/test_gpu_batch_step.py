@@ -61,6 +61,58 @@ def test_step_is_upload_and_launch(name, fused):
                     assert np.array_equal(at[first:first + count], x[first:first + count])
 
 
+# 16-bit rows of head_dim 128, 4 MB or more of them in a next chunk, and places for as much beside a chunk's row blocks: that launch asks for
+# rows of the next chunk.  prompts, chunk size, heads, kv heads
+AHEAD = {
+    "ragged": ([200, 312, 139], 512, 40, 40),                         # the first launch brings the metadata; 139 rows of 10 KB: whole KBs
+    "gqa": ([100, 412, 511], 512, 32, 8),
+    "odd-kb": ([150, 362, 301, 211, 333], 512, 36, 9),                # 301 + 211 and 333 rows of 2304 bytes of K: 333 rows end inside a KB
+    "staged": ([60] * 8 + [32] + [200] * 5, 512, 40, 40),             # a plan that the first launch cannot bring
+    "eight-wavefronts": ([480], 160, 40, 40),
+}
+
+
+@pytest.mark.parametrize("fused", [True, False], ids=["fused", "two-launches"])
+@pytest.mark.parametrize("name", sorted(AHEAD))
+def test_rows_asked_for_ahead_change_nothing(name, fused):
+    """Against the same chunks launched one to a call, which know of no next chunk."""
+    lens, chunk, hq, hkv = AHEAD[name]
+    d = 128
+    w = synth.small("ahead-" + name, lens, chunk, hq, hkv, d, seed=970)
+    spare = 64 if name == "staged" else 0
+    tables = [[int(p) for p in t] + [0] * spare for t in synth.place_pages(w)]
+    pipe = PrefillPipeline(lens, None, chunk, hq, hkv, d, w.num_pages, tables, w.scale, device=gc.DEV, fused=fused)
+    pipe.handle.tetri_set_option("attn_variant", 3)
+    rows = [sum(n for _r, _s, n in pipe.chunk_segments(c)) for c in range(pipe.n_chunks)]
+    assert max(rows[1:]) * (hq + 2 * hkv) * d * 2 >= 4 << 20
+    assert (pipe.meta_len > 672) == (name == "staged")
+    if name == "odd-kb":
+        assert any(r * hkv * d * 2 % 1024 for r in rows[1:])
+    g = torch.Generator(device=gc.DEV).manual_seed(971)
+    rnd = lambda *s: torch.randn(s, device=gc.DEV, generator=g).to(torch.bfloat16)
+    n = pipe.n_chunks
+    q, k, v = rnd(n, chunk, hq, d), rnd(n, chunk, hkv, d), rnd(n, chunk, hkv, d)
+    out = torch.empty_like(q)
+    pool = torch.zeros((w.num_pages, 2, hkv, 16, d), dtype=torch.bfloat16, device=gc.DEV)
+    pipe.bind(q, k, v, pool, out)
+
+    def one_by_one():
+        pipe.batch.upload(*pipe._plan_args, None)
+        for c in range(pipe.n_chunks):
+            pipe.batch.launch(pipe.layout_np, c, 1, *pipe._batch_args, pipe._mode, None)
+
+    got = []
+    for step in (one_by_one, pipe.step, lambda: (pipe.batch.upload(*pipe._plan_args, None), pipe._launch_all()), pipe.step):
+        pool.zero_()
+        out.fill_(7.0)
+        pipe.meta_dev.fill_(-9)
+        step()
+        torch.cuda.synchronize()
+        got.append((pool.clone().view(torch.int16), out.clone().view(torch.int16)))
+    for other in got[1:]:
+        assert torch.equal(got[0][0], other[0]) and torch.equal(got[0][1], other[1])
+
+
 def test_metadata_is_sent_where_the_launch_is_refused():
     """An error before the first launch leaves the plan on the device, as the two calls do."""
     w = synth.small("step-refused", [70, 33], 64, 4, 4, 64, seed=962)
