@@ -285,8 +285,7 @@ class PrefillPipeline:
             self._check(self._lib.tetri_kv_export(*self._request_export_args, tetri._stream(None)))
 
     def step(self):
-        # (a staging ring need not have the two in one call)
-        if not self.use_graph and self.export != "chunk" and hasattr(self.batch, "step"):
+        if not self.use_graph and self.export != "chunk":
             self.batch.step(*self._plan_args, *self._batch_args, self._mode, None)
             self._export_requests()
             return

@@ -21,7 +21,7 @@ class Recorder:
 
 
 class Ring:
-    """A staging ring: upload plans into a buffer as tetri_batch_upload does, from the arguments' addresses."""
+    """A staging ring: upload and step plan into a buffer as tetri_batch_upload and tetri_batch_step do, from the arguments' addresses."""
     def __init__(self, handle, meta_len, _meta_dev):
         self.meta = np.zeros(meta_len, np.int32)
         self.slots = [self.meta]
@@ -36,9 +36,12 @@ class Ring:
     def launch(self, *_args):
         pass
 
+    def step(self, lens, n, order, n_order, req_bt, layout, n_chunks, *_launch_args):
+        self.upload(lens, n, order, n_order, req_bt, layout, n_chunks, None)
 
-@pytest.fixture
-def pipe(monkeypatch):
+
+@pytest.fixture(params=["one call", "upload and launch"])
+def pipe(request, monkeypatch):
     monkeypatch.setattr(tetri, "Batch", Ring)
     w = synth.small("host-step", [70, 33, 150], 64, 4, 4, 64, seed=5)
     handle = Recorder()
@@ -47,6 +50,8 @@ def pipe(monkeypatch):
                                 handle=handle)
     t = torch.zeros((p.n_chunks, 1))
     p.bind(t, t, t, t, t)
+    if request.param != "one call":                      # (what a step with a graph or with chunks exported inside does)
+        p.step = lambda: (p.batch.upload(*p._plan_args, None), p._launch_all())
     return p
 
 
