@@ -882,15 +882,22 @@ static tetri_status send_metadata(tetri_ctx *h, const char *fn, MetaUpload &m, h
 
 // What a launch of the short kernel asks for of the next chunk's rows: K first, then V and Q, by workgroups in the places that its row blocks
 // leave free.  Not for rows of less than 4 MB (head_dim 64: never): such launches are over before the reads are, and would wait for them.  Nor with
-// places for less: a prompt of 2048 tokens, 16 places in the first chunk's launch, gains nothing.
+// places for less: a prompt of 2048 tokens, 16 places in the first chunk's launch, gains nothing.  All free places share what there is to read:
+// with up to kFetchKB a wavefront wherever there is as much, launches of few row blocks, short and with many places, ended later than without
+// (chunks of short prompts of 16 heads, 384 rows: 112 us without, 120 so, 115 shared; 40 heads, 160 rows: 110, 115, 111; 32 heads, 192 rows: 107, 113,
+// 105; prompts of 600 tokens, 16 heads, 384 rows: 144, 137, 138).  Nor with more than 4 row blocks of a head to a compute unit, whose own first reads go
+// on for longer than the others wait (without and with: 40 heads, 896 rows, 204 and 214, 640 rows, 3.7 row blocks, 170 and 165; 32 heads, 1024 rows, 191 and
+// 197, 768 rows, 3.5, 167 and 154; 24/8 heads, 1536 rows, 161 and 165; 20 heads, 1536 rows, 190 and 193).
 static void fetch_ahead(const tetri_ctx *h, const NextRows *next, int wavefronts, ShortParams &p)
 {
     p.fetch_wgs = 0;
-    if (!next || next->rows == 0 || h->cfg.head_dim != 128) return;
+    const int64_t cus = std::max(h->num_cus, 1);
+    if (!next || next->rows == 0 || h->cfg.head_dim != 128 || (int64_t)p.units * h->cfg.num_q_heads > 4 * cus) return;
     const int64_t row = 2 * (int64_t)h->cfg.head_dim, kv = next->rows * row * h->cfg.num_kv_heads, q = next->rows * row * h->cfg.num_q_heads;
-    const int64_t places = (int64_t)std::max(h->num_cus, 1) * 8 / wavefronts - p.attn_wgs - (p.carry ? 1 : 0);     // (one copies the metadata)
-    const int64_t each = (int64_t)wavefronts * kFetchKB, sizes[3] = {kv, kv, q};
-    if (places * each < 4096 || 2 * kv + q < 4 << 20 || 2 * kv + q > INT32_MAX) return;
+    const int64_t places = cus * 8 / wavefronts - p.attn_wgs - (p.carry ? 1 : 0);     // (one copies the metadata)
+    const int64_t sizes[3] = {kv, kv, q};
+    if (places * wavefronts * kFetchKB < 4096 || 2 * kv + q < 4 << 20 || 2 * kv + q > INT32_MAX) return;
+    const int64_t share = (2 * kv + q + 1024 * places * wavefronts - 1) / (1024 * places * wavefronts), each = wavefronts * std::min<int64_t>(share, kFetchKB);
     const void *from[3] = {next->k_new, next->v_new, next->q};
     int64_t left = places * each;
     for (int i = 0; i < 3; ++i) {

@@ -458,6 +458,7 @@ void next_chunk_rows()
         int32_t *staging = static_cast<int32_t *>(std::aligned_alloc(16, tetri_batch_slots() * len * 4));
         alignas(16) static int32_t dev[4];
         tetri_batch *b = nullptr;
+        g_uploads.clear();
         CHECK(tetri_batch_create(h, len, staging, dev, &b) == TETRI_OK);
         int32_t rows = 0;
         for (int32_t x : lens) rows += x;
@@ -505,7 +506,10 @@ void next_chunk_rows()
                     CHECK(p.next[i] == from[i] && 1024 * (uint64_t)p.next_kb[i] < p.next_bytes[i == 2] + 1024);
                     asked += p.next_kb[i];
                 }
-                CHECK(asked <= (uint64_t)p.fetch_wgs * g_short_wavefronts * kFetchKB && asked > (uint64_t)(p.fetch_wgs - 1) * g_short_wavefronts * kFetchKB);
+                // (all free places share what there is, up to kFetchKB to a wavefront)
+                const uint64_t all = (2 * p.next_bytes[0] + p.next_bytes[1] + 1023) / 1024, waves = (uint64_t)(256 * 8 / g_short_wavefronts - p.attn_wgs) * g_short_wavefronts;
+                const uint64_t each = std::min<uint64_t>(kFetchKB, (all + waves - 1) / waves) * g_short_wavefronts;
+                CHECK(asked <= p.fetch_wgs * each && asked > (p.fetch_wgs - 1) * each);
                 // what the kernel's lanes make of that: every 16 bytes of that much of a matrix, none outside its rows
                 for (int m = 0; m < 3; ++m) {
                     std::vector<char> seen(p.next_bytes[m == 2] / 16, 0);
@@ -545,7 +549,11 @@ void next_chunk_rows()
     CHECK(batch(8, 2, 128, 512, {1024}, 0, 2) == 0);
     CHECK(batch(32, 8, 128, 512, {100, 611}, 0, 2) == 0);                             // 199 rows at 412 cached tokens
     CHECK(batch(40, 40, 64, 512, {1024}, 0, 2) == 0);
-    CHECK(batch(40, 40, 128, 1024, {2048}, 0, 2) != 0);
+    // up to four row blocks of a head to a compute unit: 1024 of them, not 1280 or 1056
+    CHECK(batch(40, 40, 128, 1024, {2048}, 0, 2) == 0);
+    CHECK(batch(32, 32, 128, 1020, {64, 64, 64, 64, 64, 64, 64, 64, 64, 64, 380, 1020}, 0, 2) != 0);
+    CHECK(batch(32, 32, 128, 1052, {64, 64, 64, 64, 64, 64, 64, 64, 64, 64, 412, 1052}, 0, 2) == 0);
+    CHECK(batch(16, 16, 128, 384, {200, 184, 384}, 0, 2) == 3 * 384 * 4);             // 1300 places for wavefronts: 4 KB each
     // (those that tests/test_gpu_batch_step.py runs)
     CHECK(batch(36, 9, 128, 512, {150, 362, 301, 211, 333}, 0, 2) != 0 && batch(36, 9, 128, 512, {150, 362, 301, 211, 333}, 1, 2) != 0);
     CHECK(batch(40, 40, 128, 512, {60, 60, 60, 60, 60, 60, 60, 60, 32, 200, 200, 200, 200, 200}, 0, 2) != 0);
