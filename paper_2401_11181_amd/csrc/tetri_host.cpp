@@ -911,6 +911,22 @@ static void fetch_ahead(const tetri_ctx *h, const NextRows *next, int wavefronts
     p.fetch_wgs = (int32_t)(places - left / each);
 }
 
+// How a launch of the short kernel stores its new rows of K and V (head_dim 64: ordinarily, nothing gained otherwise).  Ordinary stores leave them in the
+// L2s, which are written back when the launch ends.  Written through they are in the cache in front of the memory by then, where the transfer or decode
+// iteration that reads them next finds them; past the caches, costs least where none of them will be there any more: in calls whose rows do not fit that
+// cache, 256 MB.  In launches that the caches do not hold (out_past_l2), and where the one prompt of a chunk goes on in the next, ordinary
+// stores are the best or as good.  Prompts of 16 to 512 tokens, stored ordinarily, through and past, the step alone, with the export of its requests and
+// with a decode iteration behind it, us: 40 heads, chunks of 512, 4175 tokens 118, 114, 109; 138, 136, 139; 133, 131, 134; 36320 tokens 954, 908, 894; 1229,
+// 1184, 1178; 1110, 1067, 1044 (16485 tokens, 338 MB: through and past 415, 410; 524, 522; 486, 481); 32/8 heads, chunks of 1024, 12496 tokens 173, 170,
+// 171; 188, 186, 192; 187, 184, 189; 40 heads, 1024, 4175 tokens (launches of 42 MB) 102, 99, 100; 123, 120, 131; 120, 117, 125; 24/8 heads, 2048 (34 MB)
+// 236, 239, 238; 269, 272, 277; 261, 264, 267.  One prompt to a chunk (16 heads, chunks of 1024) 396, 399 and 401.
+static int32_t new_row_stores(const tetri_ctx *h, int32_t num_segs, bool fp8, bool fits, int64_t call_rows)
+{
+    if (h->cfg.head_dim != 128 || num_segs < 2) return kRowsCached;
+    if (!fp8 && call_rows * 4 * h->cfg.num_kv_heads * h->cfg.head_dim > 256 << 20) return kRowsPast;
+    return fits ? kRowsThrough : kRowsCached;
+}
+
 static tetri_status attn_common(const char *fn, tetri_ctx *h, const void *q, const void *k_new, const void *v_new,
                                 const void *kv_pages, void *kv_pages_w, const int32_t *block_table, const int32_t *cu,
                                 const int32_t *ctx_lens, int32_t num_segs, float scale, void *out, void *stream,
@@ -970,6 +986,7 @@ static tetri_status attn_common(const char *fn, tetri_ctx *h, const void *q, con
         const bool takes = carry && carry->host && !fp8 && carry->len <= kShortCarry;
         if (carry && !takes && (st = send_metadata(h, fn, *carry, hs)) != TETRI_OK) return st;
         sp.carry = takes ? carry : nullptr;
+        sp.new_rows = new_row_stores(h, num_segs, fp8, sp.out_past_l2 != 0, next ? next->call_rows : 0);
         fetch_ahead(h, next, 1 << shape.nwl, sp);
         hipError_t e = tetri_launch_short(h->cfg.head_dim, fp8, sp, 1 << shape.nwl, hs);
         if (e != hipSuccess) return fail(h, TETRI_ERR_HIP, "%s: launch failed: %s", fn, hipGetErrorString(e));
@@ -1294,15 +1311,17 @@ static tetri_status batch_launch(const char *fn, tetri_batch *b, const int32_t *
             return fail(h, TETRI_ERR_INVALID_ARG, "%s: the layout of chunk %d does not fit the batch", fn, c);
         return check_host_chunk(h, fn, host + o_cu, host + o_ctx, S);
     };
+    int32_t known = first_chunk;      // chunks in front of this one will not be refused for their layout or metadata
+    int64_t call_rows = 0;
+    for (; known < first_chunk + n && check(known) == TETRI_OK; ++known) call_rows += host[layout[4 * known] + layout[4 * known + 3]];
     for (int32_t c = first_chunk; c < first_chunk + n; ++c) {
         const int32_t o_cu = layout[4 * c], o_ctx = layout[4 * c + 1], o_bt = layout[4 * c + 2], S = layout[4 * c + 3];
-        tetri_status st = check(c);
+        tetri_status st = c < known ? TETRI_OK : check(c);
         if (st != TETRI_OK) return st;
-        // the next chunk's rows, where its launch follows this one here and will not be refused for what it says of them
-        NextRows next = {nullptr, nullptr, nullptr, 0};
-        if (c + 1 < first_chunk + n && q[c + 1] && k_new[c + 1] && v_new[c + 1] && aligned16(q[c + 1]) && aligned16(k_new[c + 1]) &&
-            aligned16(v_new[c + 1]) && check(c + 1) == TETRI_OK)
-            next = {q[c + 1], k_new[c + 1], v_new[c + 1], host[layout[4 * c + 4] + layout[4 * c + 7]]};
+        // the next chunk's rows, where its launch follows this one here
+        NextRows next = {nullptr, nullptr, nullptr, 0, call_rows};
+        if (c + 1 < known && q[c + 1] && k_new[c + 1] && v_new[c + 1] && aligned16(q[c + 1]) && aligned16(k_new[c + 1]) && aligned16(v_new[c + 1]))
+            next = {q[c + 1], k_new[c + 1], v_new[c + 1], host[layout[4 * c + 4] + layout[4 * c + 7]], call_rows};
         st = attn_common(fn, h, q[c], k_new[c], v_new[c], kv_pages, mode == 1 ? kv_pages : nullptr, b->dev + o_bt, b->dev + o_cu,
                          b->dev + o_ctx, S, scale, out[c], stream, false, 1.f, 1.f, host + o_cu, host + o_ctx, carry, &next);
         if (st == TETRI_OK && mode == 0)

@@ -131,6 +131,9 @@ struct AttnParams {
 // The attention kernel for chunks with little work (tetri_short.hip).  What it reads of its arguments, behind the words that find a
 // wavefront's row block: the chunk's row blocks travel in it.
 constexpr int kShortSegs = 40, kShortUnits = 128;
+// How the fused append stores new rows: by ordinary stores; written through the L2; past the caches, but for the last segment's, which may go on
+// in the next chunk.
+enum { kRowsCached, kRowsThrough, kRowsPast };
 struct __attribute__((aligned(64))) ShortArgs {
     // (read together with the row block at the kernel's start: a cache line ...)
     const uint16_t *q, *k_new, *v_new, *pages;
@@ -153,7 +156,7 @@ struct __attribute__((aligned(64))) ShortArgs {
     const uint16_t *next[3];      // ... of K, V and Q, and how many instructions of 1 KB go to each
     uint32_t next_kb[3];
     uint32_t next_bytes[2];       // what the rows take: K or V, and Q
-    int32_t pad;
+    int32_t new_rows;             // how the fused append stores the chunk's K and V: kRowsCached ...
     // most work first, 64 bits each: segment (6), row block in it (7), the segment's rows (13) and first row (12), cached tokens (26)
     uint32_t unit[kShortUnits][2];
 };
@@ -165,10 +168,12 @@ struct MetaUpload {
     int64_t len;
 };
 
-// The rows of the chunk that the caller's next launch is for (rows 0: not known), and how much of them a wavefront of a launch asks for.
+// The rows of the chunk that the caller's next launch is for (rows 0: not known), those of all chunks of the call, and how many KB of the
+// former a wavefront of a launch asks for at most.
 struct NextRows {
     const void *q, *k_new, *v_new;
     int32_t rows;
+    int64_t call_rows;
 };
 constexpr int kFetchKB = 32;
 // What a lane of instruction i of those asks for: 16 bytes of K (0), V (1) or Q (2), lanes past the end of the rows the last ones.

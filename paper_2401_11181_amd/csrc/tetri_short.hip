@@ -560,16 +560,11 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? (F8 ? 3 : 4) : 2) void attn_shor
     // ---- fused append: the wavefront of the last step has rows t0 .. t0 + 31 of K and V in its regions.  (The rows of a matrix are read
     // together: row by row, each behind the condition of its store, its LDS round trips held the whole team up before the merge: 286
     // short prompts of 40 heads 987.1 us, this way 977.9; ragged prompts over codes 648.9, this way 642.3.)
-    // head_dim 128: rows of a prompt that ends in this chunk are not read again before its transfer or its first decode iteration: they are
-    // stored past the caches.  Only the chunk's last segment can go on in the next chunk, which reads its rows: those are written
-    // through, none is left to write back when the launch ends.  Packed short prompts, ordinary stores and this way: chunks of 384 rows of 40
-    // heads 211.1 and 196.5 us, 512 968.9 and 931, 2048 443.1 and 430.6, the worst of 14 chunk sizes 768, 268.4 and 271.0; 384 of 32/8 170.9 and
-    // 163.6; 640 rows over codes 304.4 and 289.5.  (All rows past the caches: six prompts of 1562 tokens, chunks of 384 of 8/2 heads, 4 %
-    // more.  head_dim 64: nothing gained.)
+    // How they are stored the host says (new_row_stores), in ways of their own: decided store by store, a chunk of 128 rows of 8/2 heads took 0.6 us more.
     if (appends) {
         const int slot0 = (L + t0) % kPage, ch = lane % CH;
-        auto append_rows = [&](auto past_) __attribute__((always_inline)) {
-            constexpr bool PAST = decltype(past_)::value;
+        auto append_rows = [&](auto how_) __attribute__((always_inline)) {
+            constexpr int HOW = decltype(how_)::value;
 #pragma unroll
             for (int mat = 0; mat < 2; ++mat) {
                 char *const slab = p_pages_w + (size_t)(mat * Hkv + kh) * head_bytes;
@@ -590,22 +585,22 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? (F8 ? 3 : 4) : 2) void attn_shor
                         if constexpr (F8) {
                             const uint2 y = bf16_to_codes(rows[i], mat ? p->v_inv : p->k_inv);
                             global_u32x2_w *at = reinterpret_cast<global_u32x2_w *>((uintptr_t)dst);
-                            if constexpr (PAST) __builtin_nontemporal_store(u32x2{y.x, y.y}, at);
-                            else if constexpr (D == 128) store_coherent(at, u32x2{y.x, y.y});
+                            if constexpr (HOW == kRowsThrough) store_coherent(at, u32x2{y.x, y.y});
                             else *at = u32x2{y.x, y.y};
                         } else {
                             global_u32x4_w *at = reinterpret_cast<global_u32x4_w *>((uintptr_t)dst);
-                            if constexpr (PAST) __builtin_nontemporal_store(rows[i], at);
-                            else if constexpr (D == 128) store_coherent(at, rows[i]);
+                            if constexpr (HOW == kRowsPast) store_past_caches(at, rows[i]);
+                            else if constexpr (HOW == kRowsThrough) store_coherent(at, rows[i]);
                             else *at = rows[i];
                         }
                     }
                 }
             }
-            if constexpr (PAST) asm volatile("; past the caches");     // (of two stores that differ in a hint the compiler makes one without)
         };
-        if (D == 64 || row0 + n_s == p->rows) append_rows(std::false_type());
-        else append_rows(std::true_type());
+        const int how = D == 64 ? kRowsCached : p->new_rows;
+        if (how == kRowsCached) append_rows(std::integral_constant<int, kRowsCached>());
+        else if (F8 || how == kRowsThrough || row0 + n_s == p->rows) append_rows(std::integral_constant<int, kRowsThrough>());
+        else append_rows(std::integral_constant<int, kRowsPast>());
     }
 
     const int t = t0 + l32;

@@ -561,6 +561,56 @@ void next_chunk_rows()
     CHECK(batch(40, 40, 128, 512, {200, 312, 300, 500, 77}, 1, 2) != 0);
 }
 
+// How new rows are stored: through the L2 in launches of several segments that the caches hold, past the caches in calls of more than 256 MB
+// of them.
+void new_row_stores()
+{
+    auto launch = [&](int hq, int hkv, int d, std::vector<int32_t> rows, int fp8) {
+        const tetri_config c = {hq, hkv, d, 16, 2048, 8192, 512, 40, TETRI_BF16};
+        tetri_ctx *h = nullptr;
+        CHECK(tetri_create(&c, &h) == TETRI_OK && tetri_set_option(h, "attn_variant", 3) == TETRI_OK);
+        const int32_t *meta = reinterpret_cast<const int32_t *>(g_any);
+        std::vector<int32_t> cu{0}, ctx(rows.size());
+        for (int32_t n : rows) cu.push_back(cu.back() + n);
+        CHECK(tetri_chunk_prefill_planned(h, g_any, g_any, g_any, g_any, meta, meta, meta, (int32_t)ctx.size(), 0.1f, 1, fp8, 1.f, 1.f, cu.data(), ctx.data(), g_any,
+                                          nullptr) == TETRI_OK);
+        CHECK(g_kernel == "short");
+        tetri_destroy(h);
+        return g_short.new_rows;
+    };
+    CHECK(launch(40, 40, 128, {512}, 0) == kRowsCached && launch(40, 40, 128, {200, 312}, 0) == kRowsThrough && launch(40, 40, 128, {200, 312}, 1) == kRowsThrough);
+    CHECK(launch(40, 40, 128, {200, 483}, 0) == kRowsThrough && launch(40, 40, 128, {200, 484}, 0) == kRowsCached);      // (28 MB)
+    CHECK(launch(40, 40, 64, {200, 312}, 0) == kRowsCached);
+    // 40 heads: 20 KB a token, 13107 tokens are not quite 256 MB
+    auto batch = [&](int32_t tokens, int32_t first, int32_t n) {
+        const int max_blocks = 32;
+        const tetri_config c = {40, 40, 128, 16, 512, 8192, max_blocks, 40, TETRI_BF16};
+        tetri_ctx *h = nullptr;
+        CHECK(tetri_create(&c, &h) == TETRI_OK && tetri_set_option(h, "attn_variant", 3) == TETRI_OK);
+        std::vector<int32_t> lens(51, 256);
+        lens.push_back(tokens - 51 * 256);
+        const int64_t len = 1 << 14;
+        std::vector<int32_t> pages(52 * max_blocks), layout(4 * 26);
+        int32_t *staging = static_cast<int32_t *>(std::aligned_alloc(16, tetri_batch_slots() * len * 4));
+        alignas(16) static int32_t dev[4];
+        tetri_batch *b = nullptr;
+        g_uploads.clear();
+        CHECK(tetri_batch_create(h, len, staging, dev, &b) == TETRI_OK);
+        CHECK(tetri_batch_upload(b, lens.data(), 52, nullptr, 52, pages.data(), layout.data(), 26, nullptr) == TETRI_OK);
+        std::vector<const void *> in(26, g_any);
+        std::vector<void *> out(26, g_any);
+        CHECK(tetri_batch_launch(b, layout.data(), first, n, in.data(), in.data(), in.data(), g_any, out.data(), 0.1f, 1, nullptr) == TETRI_OK);
+        CHECK(g_kernel == "short");
+        if (!g_uploads.empty() && g_uploads[0].done) event(g_uploads[0].done).pending = false;
+        tetri_batch_destroy(b);
+        tetri_destroy(h);
+        std::free(staging);
+        return g_short.new_rows;
+    };
+    CHECK(batch(13107, 0, 26) == kRowsThrough && batch(13108, 0, 26) == kRowsPast);
+    CHECK(batch(13108, 1, 25) == kRowsThrough && batch(13108, 25, 1) == kRowsThrough);
+}
+
 // Where a step's metadata travels: with the first launch up to kShortCarry int32 if that is one of the short kernel; else in one upload in front
 // of it; once, whatever the launch comes to.
 void carried_metadata()
@@ -673,6 +723,7 @@ int main(int argc, char **argv)
     else if (name == "choice_of_kernel") choice_of_kernel();
     else if (name == "short_output_stores") short_output_stores();
     else if (name == "next_chunk_rows") next_chunk_rows();
+    else if (name == "new_row_stores") new_row_stores();
     else if (name == "carried_metadata") carried_metadata();
     else if (name == "short_teams") short_teams();
     else if (name == "decode_division") decode_division();

@@ -69,6 +69,7 @@ AHEAD = {
     "odd-kb": ([150, 362, 301, 211, 333], 512, 36, 9),                # 301 + 211 and 333 rows of 2304 bytes of K: 333 rows end inside a KB
     "staged": ([60] * 8 + [32] + [200] * 5, 512, 40, 40),             # a plan that the first launch cannot bring
     "eight-wavefronts": ([480], 160, 40, 40),
+    "past-the-caches": ([250] * 53, 512, 40, 40),                     # more than 256 MB of new K and V in a call: stored otherwise than in calls of one chunk
 }
 
 
@@ -85,7 +86,7 @@ def test_rows_asked_for_ahead_change_nothing(name, fused):
     pipe.handle.tetri_set_option("attn_variant", 3)
     rows = [sum(n for _r, _s, n in pipe.chunk_segments(c)) for c in range(pipe.n_chunks)]
     assert max(rows[1:]) * (hq + 2 * hkv) * d * 2 >= 4 << 20
-    assert (pipe.meta_len > 672) == (name == "staged")
+    assert (pipe.meta_len > 672) == (name in ("staged", "past-the-caches"))
     if name == "odd-kb":
         assert any(r * hkv * d * 2 % 1024 for r in rows[1:])
     g = torch.Generator(device=gc.DEV).manual_seed(971)

@@ -26,7 +26,7 @@ def driver(tmp_path_factory):
 
 
 @pytest.mark.parametrize("check", ["static_decode_counters", "counters_are_cleared", "planned_launches_overlap", "upload_checks_the_device",
-                                   "uploads_name_no_stream_later", "choice_of_kernel", "short_output_stores", "next_chunk_rows", "carried_metadata",
+                                   "uploads_name_no_stream_later", "choice_of_kernel", "short_output_stores", "next_chunk_rows", "new_row_stores", "carried_metadata",
                                    "short_teams", "decode_division"])
 def test_host_layer(driver, check):
     res = subprocess.run([driver, check], capture_output=True, text=True, timeout=120)
