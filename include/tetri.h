@@ -268,7 +268,8 @@ TETRI_API tetri_status tetri_chunk_prefill_planned(tetri_ctx *ctx, const void *q
  *   tetri_batch_launch: chunks first_chunk .. first_chunk + n - 1 of the plan uploaded last (before the first upload: of
  *   the plan that staging buffer 0 holds and the caller has copied to meta_dev), in order, each as tetri_chunk_prefill_planned
  *   does it: mode 1 with append = 1, mode 2 attention only, mode 0 attention followed by tetri_kv_append.
- *   q, k_new, v_new, out: host arrays of a device pointer per chunk.
+ *   q, k_new, v_new, out: host arrays of a device pointer per chunk.  The launch of a chunk may read q, k_new and v_new of the chunk
+ *   behind it in the same call, to have them in a cache when that chunk's launch needs them; no result depends on it.
  *   tetri_batch_step: tetri_batch_upload, then tetri_batch_launch of all n_chunks chunks, in one call; what meta_dev holds when it is
  *   done is the same.  A small plan needs no launch of its own here: the first chunk's takes it along where it can.
  */

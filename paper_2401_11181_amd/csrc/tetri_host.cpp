@@ -881,7 +881,8 @@ static tetri_status send_metadata(tetri_ctx *h, const char *fn, MetaUpload &m, h
 }
 
 // What a launch of the short kernel asks for of the next chunk's rows: K first, then V and Q, by workgroups in the places that its row blocks
-// leave free.  Not for rows of less than 4 MB (head_dim 64: never): such launches are over before the reads are, and would wait for them.  Nor with
+// leave free.  Not for rows of less than 4 MB, nor for head_dim 64, which gain little (chunks of 256 rows of 16 and 24/8 heads, 3.1 and 2.6 MB, 2 to 3 %, 512 of
+// 8/2 heads, 1.5 MB, nothing; head_dim 64, 512 rows of 40 heads 3 % more to 1 % less).  Nor with
 // places for less: a prompt of 2048 tokens, 16 places in the first chunk's launch, gains nothing.  All free places share what there is to read:
 // with up to kFetchKB a wavefront wherever there is as much, launches of few row blocks, short and with many places, ended later than without
 // (chunks of short prompts of 16 heads, 384 rows: 112 us without, 120 so, 115 shared; 40 heads, 160 rows: 110, 115, 111; 32 heads, 192 rows: 107, 113,
