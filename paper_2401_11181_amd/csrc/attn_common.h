@@ -158,12 +158,14 @@ __device__ __forceinline__ void dma16(const void *gptr, uint32_t lds_base)
 // A group of such loads that share one scalar base and one LDS base: instruction i moves
 // 16 bytes per lane from sbase + voff_i + 1024*i to LDS byte lds_base + 1024*i + 16*lane.  The
 // instruction's immediate offset advances the global and the LDS address alike, so M0 is written
-// once per group.
+// once per group.  A vector instruction that writes scalar registers (uniform_ptr, or a spilled register that comes back) may
+// stand right in front: five wait states from there to a load that reads them, which the compiler keeps in front of
+// its own loads only, are the write to M0 and the s_nop 3.
 __device__ __forceinline__ void dma16_group4(const void *sbase, uint32_t v0, uint32_t v1, uint32_t v2, uint32_t v3, uint32_t lds_base)
 {
     sbase = uniform_ptr(sbase);
     lds_base = __builtin_amdgcn_readfirstlane(lds_base);
-    asm volatile("s_mov_b32 m0, %5\n\ts_nop 0\n\t"
+    asm volatile("s_mov_b32 m0, %5\n\ts_nop 3\n\t"
                  "global_load_lds_dwordx4 %0, %4\n\t"
                  "global_load_lds_dwordx4 %1, %4 offset:1024\n\t"
                  "global_load_lds_dwordx4 %2, %4 offset:2048\n\t"
@@ -173,7 +175,7 @@ __device__ __forceinline__ void dma16_group2(const void *sbase, uint32_t v0, uin
 {
     sbase = uniform_ptr(sbase);
     lds_base = __builtin_amdgcn_readfirstlane(lds_base);
-    asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\t"
+    asm volatile("s_mov_b32 m0, %3\n\ts_nop 3\n\t"
                  "global_load_lds_dwordx4 %0, %2\n\t"
                  "global_load_lds_dwordx4 %1, %2 offset:1024" ::"v"(v0), "v"(v1), "s"(sbase), "s"(lds_base) : "memory", "m0");
 }
@@ -185,17 +187,17 @@ template <int N> __device__ __forceinline__ void dma16_stream(const void *sbase,
     sbase = uniform_ptr(sbase);
     lds_base = __builtin_amdgcn_readfirstlane(lds_base);
     if constexpr (N == 4)
-        asm volatile("s_mov_b32 m0, %5\n\ts_nop 0\n\t"
+        asm volatile("s_mov_b32 m0, %5\n\ts_nop 3\n\t"
                      "global_load_lds_dwordx4 %0, %4 nt\n\t"
                      "global_load_lds_dwordx4 %1, %4 offset:1024 nt\n\t"
                      "global_load_lds_dwordx4 %2, %4 offset:2048 nt\n\t"
                      "global_load_lds_dwordx4 %3, %4 offset:3072 nt" ::"v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]), "s"(sbase), "s"(lds_base) : "memory", "m0");
     else if constexpr (N == 2)
-        asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\t"
+        asm volatile("s_mov_b32 m0, %3\n\ts_nop 3\n\t"
                      "global_load_lds_dwordx4 %0, %2 nt\n\t"
                      "global_load_lds_dwordx4 %1, %2 offset:1024 nt" ::"v"(v[0]), "v"(v[1]), "s"(sbase), "s"(lds_base) : "memory", "m0");
     else
-        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\t"
+        asm volatile("s_mov_b32 m0, %2\n\ts_nop 3\n\t"
                      "global_load_lds_dwordx4 %0, %1 nt" ::"v"(v[0]), "s"(sbase), "s"(lds_base) : "memory", "m0");
 }
 // Accesses that are coherent across the whole device by themselves (cache policy sc1: they are
