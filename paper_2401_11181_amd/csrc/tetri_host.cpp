@@ -913,19 +913,22 @@ static void fetch_ahead(const tetri_ctx *h, const NextRows *next, int wavefronts
 }
 
 // How a launch of the short kernel stores its new rows of K and V (head_dim 64: ordinarily, nothing gained otherwise).  Ordinary stores leave them in the
-// L2s, which are written back when the launch ends.  Written through they are in the cache in front of the memory by then, where the transfer or decode
-// iteration that reads them next finds them; past the caches, costs least where none of them will be there any more: in calls whose rows do not fit that
-// cache, 256 MB.  In launches that the caches do not hold (out_past_l2), and where the one prompt of a chunk goes on in the next, ordinary
-// stores are the best or as good.  Prompts of 16 to 512 tokens, stored ordinarily, through and past, the step alone, with the export of its requests and
-// with a decode iteration behind it, us: 40 heads, chunks of 512, 4175 tokens 118, 114, 109; 138, 136, 139; 133, 131, 134; 36320 tokens 954, 908, 894; 1229,
-// 1184, 1178; 1110, 1067, 1044 (16485 tokens, 338 MB: through and past 415, 410; 524, 522; 486, 481); 32/8 heads, chunks of 1024, 12496 tokens 173, 170,
-// 171; 188, 186, 192; 187, 184, 189; 40 heads, 1024, 4175 tokens (launches of 42 MB) 102, 99, 100; 123, 120, 131; 120, 117, 125; 24/8 heads, 2048 (34 MB)
-// 236, 239, 238; 269, 272, 277; 261, 264, 267.  One prompt to a chunk (16 heads, chunks of 1024) 396, 399 and 401.
-static int32_t new_row_stores(const tetri_ctx *h, int32_t num_segs, bool fp8, bool fits, int64_t call_rows)
+// L2s, which are written back when the launch ends.  Written through they are in the cache in front of the memory by then, where the next chunk, the
+// transfer or the decode iteration that reads them finds them; past the caches, costs least where none of them will be there any more: in calls whose rows
+// do not fit that cache, 256 MB.  In launches of more than 28 MB of Q, K, V and output ordinary stores are the best or as good.  Prompts of 16 to 512
+// tokens, stored ordinarily, through and past, the step alone, with the export of its requests and with a decode iteration behind it, us: 40 heads, chunks
+// of 512, 4175 tokens 118, 114, 109; 138, 136, 139; 133, 131, 134; 36320 tokens 954, 908, 894; 1229, 1184, 1178; 1110, 1067, 1044 (16485 tokens, 338 MB:
+// through and past 415, 410; 524, 522; 486, 481); 32/8 heads, chunks of 1024, 12496 tokens 173, 170, 171; 188, 186, 192; 187, 184, 189; 40 heads, 1024, 4175
+// tokens (42 MB) 102, 99, 100; 123, 120, 131; 120, 117, 125; 24/8 heads, 2048 (34 MB) 236, 239, 238; 269, 272, 277; 261, 264, 267.  Through against
+// ordinarily, over 8 head shapes and the step alone, repeated over the same buffers, with export and with decode: 0.92 to 1.02 up to 25 MB, 0.93 to 1.05 at 31 to
+// 34, 0.98 to 1.04 beyond.  One prompt: 40 heads, chunks of 256, 512 tokens 23.5, 22.6; 16 heads, chunks of 512, 1024 tokens 25.0, 24.1; 8/2 heads, chunks of
+// 1024, 2048 tokens 33.9, 33.2 (prompts of 700 to 4000 tokens, chunks of 1024 of 16 heads: 396, 399).
+static int32_t new_row_stores(const tetri_ctx *h, int32_t num_segs, bool fp8, int64_t rows, int64_t call_rows)
 {
-    if (h->cfg.head_dim != 128 || num_segs < 2) return kRowsCached;
-    if (!fp8 && call_rows * 4 * h->cfg.num_kv_heads * h->cfg.head_dim > 256 << 20) return kRowsPast;
-    return fits ? kRowsThrough : kRowsCached;
+    if (h->cfg.head_dim != 128) return kRowsCached;
+    const int64_t row = 4 * h->cfg.head_dim;
+    if (!fp8 && num_segs > 1 && call_rows * row * h->cfg.num_kv_heads > 256 << 20) return kRowsPast;
+    return rows * row * (h->cfg.num_q_heads + h->cfg.num_kv_heads) <= 28 << 20 ? kRowsThrough : kRowsCached;
 }
 
 static tetri_status attn_common(const char *fn, tetri_ctx *h, const void *q, const void *k_new, const void *v_new,
@@ -987,7 +990,7 @@ static tetri_status attn_common(const char *fn, tetri_ctx *h, const void *q, con
         const bool takes = carry && carry->host && !fp8 && carry->len <= kShortCarry;
         if (carry && !takes && (st = send_metadata(h, fn, *carry, hs)) != TETRI_OK) return st;
         sp.carry = takes ? carry : nullptr;
-        sp.new_rows = new_row_stores(h, num_segs, fp8, sp.out_past_l2 != 0, next ? next->call_rows : 0);
+        sp.new_rows = new_row_stores(h, num_segs, fp8, host_cu[num_segs], next ? next->call_rows : 0);
         fetch_ahead(h, next, 1 << shape.nwl, sp);
         hipError_t e = tetri_launch_short(h->cfg.head_dim, fp8, sp, 1 << shape.nwl, hs);
         if (e != hipSuccess) return fail(h, TETRI_ERR_HIP, "%s: launch failed: %s", fn, hipGetErrorString(e));

@@ -561,8 +561,7 @@ void next_chunk_rows()
     CHECK(batch(40, 40, 128, 512, {200, 312, 300, 500, 77}, 1, 2) != 0);
 }
 
-// How new rows are stored: through the L2 in launches of several segments that the caches hold, past the caches in calls of more than 256 MB
-// of them.
+// How new rows are stored: through the L2 in launches of up to 28 MB of rows, past the caches in calls of more than 256 MB of new ones.
 void new_row_stores()
 {
     auto launch = [&](int hq, int hkv, int d, std::vector<int32_t> rows, int fp8) {
@@ -578,8 +577,8 @@ void new_row_stores()
         tetri_destroy(h);
         return g_short.new_rows;
     };
-    CHECK(launch(40, 40, 128, {512}, 0) == kRowsCached && launch(40, 40, 128, {200, 312}, 0) == kRowsThrough && launch(40, 40, 128, {200, 312}, 1) == kRowsThrough);
-    CHECK(launch(40, 40, 128, {200, 483}, 0) == kRowsThrough && launch(40, 40, 128, {200, 484}, 0) == kRowsCached);      // (28 MB)
+    CHECK(launch(40, 40, 128, {716}, 0) == kRowsThrough && launch(40, 40, 128, {717}, 0) == kRowsCached && launch(40, 40, 128, {200, 312}, 0) == kRowsThrough && launch(40, 40, 128, {200, 312}, 1) == kRowsThrough);
+    CHECK(launch(40, 40, 128, {200, 516}, 0) == kRowsThrough && launch(40, 40, 128, {200, 517}, 1) == kRowsCached);      // (40 KB a row)
     CHECK(launch(40, 40, 64, {200, 312}, 0) == kRowsCached);
     // 40 heads: 20 KB a token, 13107 tokens are not quite 256 MB
     auto batch = [&](int32_t tokens, int32_t first, int32_t n) {
